@@ -6,7 +6,6 @@
 
 constexpr int kB16MaxWidth = 1024;   // widest layer and observation
 constexpr int kB16MaxOut = 32;       // head outputs: one block of 32 features
-constexpr int kB16MaxSlices = 16;    // slices of the batch in the weight gradient
 
 // A matrix operand is stored as the matrix instruction takes it: fragments of 16 rows x 32 contraction elements, 1 KB,
 // lane (q, n) = row n, elements 8 q .. 8 q + 7; four of them (two row tiles x two steps) make a contiguous 4 KB group
@@ -46,7 +45,7 @@ int tj_b16_rows(const TjB16Rows &a, int mode, hipStream_t st);
 struct TjB16Update : TjUpdateCall {
     TjB16Layer lay[TJ_MAX_LAYERS];
 };
-int tj_b16_slices(int L, const TjB16Layer *lay, int B);
+int tj_b16_slices(int L, const TjB16Layer *lay, int B);   // most that an update of B rows or fewer writes
 int tj_b16_update(const TjB16Update &a, hipStream_t st);
 // Fragments and padded biases of one network from its master parameters.
 int tj_b16_cast(int L, const TjB16Layer *lay, bool online, hipStream_t st);

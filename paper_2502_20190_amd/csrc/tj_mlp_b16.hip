@@ -15,6 +15,7 @@
 // v_mfma_f32_16x16x32_bf16: the weights are the first operand (rows = features), the transitions the second, so that a
 // lane ends up with four neighbouring features of one transition: 8-byte LDS stores.
 #include "tj_mlp_b16.h"
+#include "tj_mlp_plan.h"
 #include <algorithm>
 #include <cmath>
 
@@ -445,11 +446,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
 //   64 x 64 tiles, eight waves: half the operand traffic per weight, which bounds long batches; the batch is cut into
 //     slices so that the tiles fill the chip, and b16_adam adds them.
 // The bias gradient is one more product, with a fragment of ones.
-struct UpdatePlan {
-    int begin[TJ_MAX_LAYERS + 1];   // first tile of every layer
-    int nk[TJ_MAX_LAYERS];          // tiles along k
-    int S, steps, per;              // slices; 32-row steps of the batch, of a slice
-};
+using UpdatePlan = tjplan::B16Update;
 
 __device__ __forceinline__ u32x4 frag(const tj_bf16 *F, int fp, int ms, int step, int t, int lane)
 {
@@ -685,39 +682,6 @@ __global__ __launch_bounds__(256) void b16_cast(const TjB16Layer y, const int on
     if (e < (size_t)y.out) (online ? y.BP : y.BP_tg)[e] = b[e];
 }
 
-int plan_tiles(int L, const TjB16Layer *lay, int tile, UpdatePlan &p)
-{
-    int n = 0;
-    for (int l = 0; l < L; ++l) {
-        p.begin[l] = n;
-        p.nk[l] = (lay[l].in + tile - 1) / tile;
-        n += p.nk[l] * ((lay[l].out + tile - 1) / tile);
-    }
-    p.begin[L] = n;
-    return n;
-}
-
-// 32 x 32 tiles while their operand traffic (128 bytes per tile and row) stays below what a second launch costs; then
-// 64-wide tiles and the number of slices with the least estimated time: rounds of 256 blocks (one per CU) of 5 us and
-// 94 ns per 32-row step, and a pass over the slices at 5 TB/s (128-512-512-512-18, 32768 rows: 96 us with one
-// slice on 152 blocks).  Returns the tile side.
-int update_plan(int L, const TjB16Layer *lay, int B, UpdatePlan &p)
-{
-    p.steps = (B + 31) / 32;
-    p.S = 1;
-    p.per = p.steps;
-    int n = plan_tiles(L, lay, 32, p);
-    if ((size_t)n * B <= 400000) return 32;
-    n = plan_tiles(L, lay, 64, p);
-    float best = 0.f;
-    for (int S = 1; S <= std::min(kB16MaxSlices, std::max(1, p.steps / 8)); ++S) {
-        const int per = (p.steps + S - 1) / S;
-        const float ns = (float)((n * S + 255) / 256) * (5000.f + 94.f * per) + (float)n * 4096 * 8 / 5000 * S;
-        if (S == 1 || ns < best) { best = ns; p.S = S; p.per = per; }
-    }
-    return 64;
-}
-
 RowsLds lds_of(const TjB16Rows &a, int nr, bool dqn, bool back)
 {
     int in[TJ_MAX_LAYERS], out[TJ_MAX_LAYERS];
@@ -802,15 +766,7 @@ int tj_b16_rows(const TjB16Rows &a, int mode, hipStream_t st)
                    : nr == 2 ? launch_rows<TJ_ROWS_ACT, 2>(a, mode, st) : launch_rows<TJ_ROWS_ACT, 4>(a, mode, st);
 }
 
-int tj_b16_slices(int L, const TjB16Layer *lay, int B)   // of a batch of B rows or fewer
-{
-    int most = 0;
-    for (int b = B; b > 0; b = b > 32 ? b - 32 : 0) {
-        UpdatePlan p;
-        if (update_plan(L, lay, b, p) == 64) most = std::max(most, p.S);
-    }
-    return most;
-}
+int tj_b16_slices(int L, const TjB16Layer *lay, int B) { return tjplan::b16_slices(L, lay, B); }
 
 int tj_b16_update(const TjB16Update &a, hipStream_t st)
 {
@@ -822,12 +778,12 @@ int tj_b16_update(const TjB16Update &a, hipStream_t st)
         attr_set = true;
     }
     UpdatePlan p;
-    const int tile = update_plan(a.L, a.lay, a.B, p), n = p.begin[a.L];
+    const int tile = tjplan::b16_update(a.L, a.lay, a.B, p), n = p.begin[a.L];
     if (tile == 32) {
         b16_update<32><<<n + 1, 1024, 16 * 32 * 32 * 4 + 16 * 32 * 4, st>>>(a, p);
     } else {
         b16_update<64><<<up(n * p.S, 8), 512, 8 * 64 * 64 * 4 + 8 * 64 * 4, st>>>(a, p);
-        b16_adam<<<plan_tiles(a.L, a.lay, 32, p) + 1, 512, 0, st>>>(a, p);
+        b16_adam<<<tjplan::b16_tiles(a.L, a.lay, 32, p) + 1, 512, 0, st>>>(a, p);
     }
     return hipGetLastError() == hipSuccess ? TJ_OK : TJ_ERR_DEVICE;
 }

@@ -1,0 +1,63 @@
+// How the whole-network kernels (tj_mlp_f32.hip, tj_mlp_b16.hip) divide an update: plain host arithmetic without HIP, so
+// that it can be compiled and checked on its own.  `Layer` is anything with the members in and out.
+#pragma once
+#include "../../include/tianji.h"
+#include <stddef.h>
+#include <algorithm>
+
+namespace tjplan {
+
+constexpr int kB16MaxSlices = 16;    // slices of the batch in the bf16 weight gradient
+
+struct B16Update {
+    int begin[TJ_MAX_LAYERS + 1];   // first tile of every layer
+    int nk[TJ_MAX_LAYERS];          // tiles along k
+    int S, steps, per;              // slices; 32-row steps of the batch, of a slice
+};
+
+template <typename Layer> int b16_tiles(int L, const Layer *lay, int tile, B16Update &p)
+{
+    int n = 0;
+    for (int l = 0; l < L; ++l) {
+        p.begin[l] = n;
+        p.nk[l] = (lay[l].in + tile - 1) / tile;
+        n += p.nk[l] * ((lay[l].out + tile - 1) / tile);
+    }
+    p.begin[L] = n;
+    return n;
+}
+
+// 32 x 32 tiles while their operand traffic (128 bytes per tile and row) stays below what a second launch costs; then
+// 64-wide tiles and the number of slices with the least estimated time: rounds of 256 blocks (one per CU) of 5 us and
+// 94 ns per 32-row step, and a pass over the slices at 5 TB/s (128-512-512-512-18, 32768 rows: 96 us with one
+// slice on 152 blocks).  Returns the tile side.
+template <typename Layer> int b16_update(int L, const Layer *lay, int B, B16Update &p)
+{
+    p.steps = (B + 31) / 32;
+    p.S = 1;
+    p.per = p.steps;
+    int n = b16_tiles(L, lay, 32, p);
+    if ((size_t)n * B <= 400000) return 32;
+    n = b16_tiles(L, lay, 64, p);
+    float best = 0.f;
+    for (int S = 1; S <= std::min(kB16MaxSlices, std::max(1, p.steps / 8)); ++S) {
+        const int per = (p.steps + S - 1) / S;
+        const float ns = (float)((n * S + 255) / 256) * (5000.f + 94.f * per) + (float)n * 4096 * 8 / 5000 * S;
+        if (S == 1 || ns < best) { best = ns; p.S = S; p.per = per; }
+    }
+    return 64;
+}
+
+// Most gradient slices that an update of B rows or fewer writes.  The count follows the steps but not evenly, and only 64-wide
+// tiles have any; of the batches with the same steps the longest one is the first to take them, so it speaks for all.
+template <typename Layer> int b16_slices(int L, const Layer *lay, int B)
+{
+    int most = 0;
+    for (int steps = (B + 31) / 32; steps > 0; --steps) {
+        B16Update p;
+        if (b16_update(L, lay, std::min(32 * steps, B), p) == 64) most = std::max(most, p.S);
+    }
+    return most;
+}
+
+}  // namespace tjplan

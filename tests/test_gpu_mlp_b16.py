@@ -8,6 +8,7 @@ Tolerance 2e-2 of each tensor's largest entry, as for every bf16 update: both si
 (2^-8 of one operand) wherever their fp32 and fp64 sums differ."""
 from dataclasses import replace
 
+import numpy as np
 import pytest
 
 from paper_2502_20190_amd import synth
@@ -54,3 +55,47 @@ def test_on_policy_learner(tj, orc, D, widths, A, B):
     for step in range(2):
         rows = P._batch(orc, o, D, A, 1 + B // 8, 8, 70 + step, "bf16", n=B)
         P._step_both(tj, orc, g, o, rows, TOL, sync=step > 0, precision="bf16")
+
+
+@pytest.mark.parametrize("D,widths,A,max_batch,batches", [
+    (180, (215, 215), 3, 4177, (4090, 4177, 4082, 4080)), (187, (207,), 6, 8323, (8164, 8323, 40))])
+@pytest.mark.parametrize("on_policy", [False, True])
+def test_smaller_batches_of_a_larger_learner(tj, D, widths, A, max_batch, batches, on_policy):
+    """Across the switch between the tilings, where a smaller batch may be cut into more slices than the largest one: the
+    kernels see the batch only, so a learner made for it gives the same bits."""
+    import torch
+
+    if on_policy:
+        layers = synth.ppo_layers(widths, A)
+        theta = synth.xavier_init(layers, (D, 1, 1), 1)
+        make = lambda n: tj.PpoLearner(D, widths, A, "bf16", n, theta)
+    else:
+        layers = tuple((LIN, w, 0, 0) for w in widths) + ((LIN, A, 0, 0),)
+        wl = replace(synth.WORKLOADS["c2"], obs_shape=(D,), n_actions=A, batch=max_batch, layers=layers, precision="bf16")
+        theta, target = T._init_state(wl, 1)
+        make = lambda n: tj.learner_for_workload(wl, theta, target, max_batch=n)
+    large = make(max_batch)
+    g = torch.Generator(device="cuda").manual_seed(2)
+    randn = lambda *s: torch.randn(s, generator=g, device="cuda")
+    for t, B in enumerate(batches):
+        small = make(B)
+        action = torch.randint(0, A, (B,), generator=g, device="cuda", dtype=torch.int32)
+        if on_policy:
+            rows = (randn(B, D), action, -1.0 + 0.1 * randn(B), randn(B), randn(B))
+            step = lambda lrn: lrn.step(*rows)
+        else:
+            mb = tj.Minibatch(B, D, "f32")
+            for f, v in (("obs", randn(B, D)), ("next_obs", randn(B, D)), ("action", action), ("reward", randn(B)),
+                         ("done", (randn(B) > 1.5).to(torch.uint8))):
+                getattr(mb, f).copy_(v.view(getattr(mb, f).shape))
+            step = lambda lrn: lrn.step(mb)
+        for which in (tj.TJ_STATE_PARAMS, tj.TJ_STATE_ADAM_M, tj.TJ_STATE_ADAM_V):
+            small.set_state(which, large.get_state(which))
+        assert tj.lib().tj_learner_set_step(small.h, t) == tj.TJ_OK
+        if not on_policy:
+            small.set_state(tj.TJ_STATE_TARGET, large.get_state(tj.TJ_STATE_TARGET))
+        assert step(large) == step(small) == tj.TJ_OK
+        torch.cuda.synchronize()
+        assert torch.equal(large.stats, small.stats)
+        for which in (tj.TJ_STATE_PARAMS, tj.TJ_STATE_ADAM_M, tj.TJ_STATE_ADAM_V, tj.TJ_STATE_GRADS):
+            assert np.array_equal(large.get_state(which), small.get_state(which)), (B, which)

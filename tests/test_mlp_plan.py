@@ -1,0 +1,39 @@
+"""The plan of the whole-network kernels, compiled for the CPU: what an update writes fits what its learner holds."""
+import ctypes
+import os
+import subprocess
+
+import numpy as np
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+
+
+@pytest.fixture(scope="module")
+def plan(tmp_path_factory):
+    out = str(tmp_path_factory.mktemp("plan") / "mlp_plan.so")
+    subprocess.run(["g++", "-O2", "-std=c++17", "-Wall", "-shared", "-fPIC", os.path.join(HERE, "mlp_plan.cpp"), "-o", out],
+                   check=True)
+    return ctypes.CDLL(out)
+
+
+def _layers(*widths):
+    flat = [v for pair in zip(widths, widths[1:]) for v in pair]
+    return len(widths) - 1, (ctypes.c_int * len(flat))(*flat)
+
+
+def _random_nets():
+    g = np.random.default_rng(0)
+    nets = []
+    for _ in range(60):
+        depth = g.integers(1, 4)
+        widths = [int(v) for v in np.exp(g.uniform(np.log(8), np.log(700), depth + 1))] + [int(g.integers(2, 33))]
+        nets.append((widths, int(np.exp(g.uniform(np.log(64), np.log(20000))))))
+    return nets
+
+
+@pytest.mark.parametrize("widths,max_batch", [((180, 215, 215, 3), 4177), ((187, 207, 6), 8323)] + _random_nets())
+def test_bf16_gradient_slices_of_every_smaller_batch_fit(plan, widths, max_batch):
+    held, written = ctypes.c_int(), ctypes.c_int()
+    plan.b16_slices(*_layers(*widths), max_batch, ctypes.byref(held), ctypes.byref(written))
+    assert written.value == held.value, (widths, max_batch)

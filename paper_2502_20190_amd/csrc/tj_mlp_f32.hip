@@ -23,6 +23,7 @@
 // features x slices of k; the slices are added through LDS in slice order.  Weight loads do not depend on activations, so a wave has its first loads of the next
 // layer in flight across the barriers between two layers.
 #include "tj_mlp_f32.h"
+#include "tj_mlp_plan.h"
 #include <math.h>
 #include <algorithm>
 
@@ -32,7 +33,7 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef const __attribute__((address_space(1))) uint8_t *gbytes;
 typedef const __attribute__((address_space(1))) __attribute__((aligned(4))) f32x4 *gf32x4;
 
-constexpr int kThreads = 512, kWaves = kThreads / 64;      // f32_rows: two waves per SIMD, 256 registers each
+constexpr int kWaves = tjplan::kF32Waves, kThreads = 64 * kWaves;   // f32_rows: two waves per SIMD, 256 registers each
 constexpr size_t kLdsMax = 160 * 1024;
 
 __host__ __device__ inline int up(int x, int a) { return (x + a - 1) / a * a; }
@@ -67,11 +68,8 @@ RowsLds rows_lds(int L, const TjF32Layer *lay, int nr, bool dqn, bool backward)
     return o;
 }
 
-// One contraction of the block's rows with a weight matrix [k][features]: F groups of 64 features x KS slices of the
-// nk chunks of 16 k, one per wave.
-struct Phase {
+struct Phase : tjplan::F32Phase {
     const float *w0, *w1;     // w1: the target network's (forward of the Q-learner; elsewhere never used)
-    int pitch, nk, F, KS;
     uint32_t rF;              // u / F = u * rF >> 16 (u < 4096, F <= 16)
 };
 
@@ -85,8 +83,8 @@ struct RowsArgs {
 Phase make_phase(const float *w0, const float *w1, int pitch, int rows, int cols)
 {
     Phase p;
-    p.w0 = w0; p.w1 = w1; p.pitch = pitch; p.nk = (rows + 15) / 16;
-    p.F = (cols + 63) / 64; p.rF = 65535u / (uint32_t)p.F + 1u; p.KS = kWaves / p.F;
+    static_cast<tjplan::F32Phase &>(p) = tjplan::f32_phase(pitch, rows, cols);
+    p.w0 = w0; p.w1 = w1; p.rF = 65535u / (uint32_t)p.F + 1u;
     return p;
 }
 
@@ -127,19 +125,19 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
         int pitch, nk, F, KS, f, ks;
         uint32_t rF, off[4];
     };
-    const uint32_t quarter = lane >> 4, fcol = 4 * (lane & 15);
+    const uint32_t quarter = lane >> 4;
     auto mine = [&](const Phase &p) {
         Mine m;
         m.w0 = p.w0; m.w1 = p.w1; m.pitch = p.pitch; m.nk = p.nk; m.F = p.F; m.KS = p.KS; m.rF = p.rF;
         m.ks = (int)((uint32_t)wave * p.rF >> 16);
         m.f = wave - m.ks * p.F;
 #pragma unroll
-        for (int b = 0; b < 4; ++b) m.off[b] = 4u * (__umul24(quarter + 4 * b, (uint32_t)p.pitch) + (uint32_t)m.f * 64 + fcol);
+        for (int b = 0; b < 4; ++b) m.off[b] = 4u * tjplan::f32_lane_at(lane, b, p.pitch, m.f);
         return m;
     };
     auto active = [](const Mine &p) { return p.ks < p.KS && p.ks < p.nk; };
     auto load = [&](f32x4 (&w)[4], const float *base, const Mine &p, int c) {
-        gbytes rows = (gbytes)(uintptr_t)(base + (uint32_t)(16 * c * p.pitch));
+        gbytes rows = (gbytes)(uintptr_t)(base + tjplan::f32_chunk_at(c, p.pitch));
         asm("" : "+s"(rows));                // wave-uniform: the scalar base of the loads, off[] their lane offset
 #pragma unroll
         for (int b = 0; b < 4; ++b) w[b] = *(gf32x4)(rows + p.off[b]);
@@ -147,8 +145,9 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
     };
     f32x4 wa[2][4], wb[2][4];
     auto load_first = [&](const Mine &p, auto two) {
-        load(wa[0], p.w0, p, p.ks);
-        if constexpr (decltype(two)::value) load(wb[0], p.w1, p, p.ks);
+        const int c = tjplan::f32_first_chunk(p.ks, p.nk);
+        load(wa[0], p.w0, p, c);
+        if constexpr (decltype(two)::value) load(wb[0], p.w1, p, c);
     };
     // this wave's chunks of a phase; mul(set, chunk) multiplies a set.  The last round is apart: a loop that loads in
     // every round has no wait that covers more than it must.

@@ -5,7 +5,38 @@
 #include <stddef.h>
 #include <algorithm>
 
+#ifdef __HIPCC__
+#define TJ_HD __host__ __device__
+#else
+#define TJ_HD
+#endif
+
 namespace tjplan {
+
+// ---- the row kernel of fp32 networks: one contraction of a block's rows with a weight matrix [k][features], as F groups of
+// 64 features x KS slices of the nk chunks of 16 k, one per wave.
+constexpr int kF32Waves = 8;
+
+struct F32Phase {
+    int pitch, nk, F, KS;     // pitch: elements between rows of the matrix
+};
+inline F32Phase f32_phase(int pitch, int rows, int cols)
+{
+    F32Phase p;
+    p.pitch = pitch; p.nk = (rows + 15) / 16; p.F = (cols + 63) / 64; p.KS = kF32Waves / p.F;
+    return p;
+}
+// A wave whose slice is ks multiplies chunks ks, ks + KS, ... < nk, or none (ks >= KS or ks >= nk).  Its first load goes out
+// before that is decided, so it is of a chunk that exists.
+TJ_HD inline int f32_first_chunk(int ks, int nk) { return ks < nk ? ks : nk - 1; }
+// Element of the matrix at which load b of a chunk starts, four features wide: the chunk's part and the lane's.
+TJ_HD inline unsigned f32_chunk_at(int chunk, int pitch) { return 16u * chunk * pitch; }
+TJ_HD inline unsigned f32_lane_at(int lane, int b, int pitch, int f)
+{
+    return (unsigned)(lane >> 4) * pitch + 4u * b * pitch + 64u * f + 4u * (lane & 15);
+}
+
+// ---- the weight kernel of bf16 networks
 
 constexpr int kB16MaxSlices = 16;    // slices of the batch in the bf16 weight gradient
 

@@ -13,3 +13,23 @@ extern "C" void b16_slices(int L, const Layer *lay, int max_batch, int *held, in
         if (tjplan::b16_update(L, lay, B, p) == 64 && p.S > *written) *written = p.S;
     }
 }
+
+// Elements from the start of a weight matrix to the end of what the row kernel of fp32 networks loads of it: every wave's first
+// chunk, whether it is used or not, and the chunks it multiplies.
+extern "C" long f32_reach(int pitch, int rows, int cols)
+{
+    const tjplan::F32Phase p = tjplan::f32_phase(pitch, rows, cols);
+    long most = 0;
+    auto load = [&](int chunk, int f) {
+        for (int lane = 0; lane < 64; ++lane)
+            for (int b = 0; b < 4; ++b)
+                most = std::max(most, (long)tjplan::f32_chunk_at(chunk, pitch) + tjplan::f32_lane_at(lane, b, pitch, f) + 4);
+    };
+    for (int wave = 0; wave < tjplan::kF32Waves; ++wave) {
+        const int ks = wave / p.F, f = wave % p.F;
+        load(tjplan::f32_first_chunk(ks, p.nk), f);
+        if (ks < p.KS)
+            for (int c = ks; c < p.nk; c += p.KS) load(c, f);
+    }
+    return most;
+}

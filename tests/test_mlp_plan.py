@@ -37,3 +37,15 @@ def test_bf16_gradient_slices_of_every_smaller_batch_fit(plan, widths, max_batch
     held, written = ctypes.c_int(), ctypes.c_int()
     plan.b16_slices(*_layers(*widths), max_batch, ctypes.byref(held), ctypes.byref(written))
     assert written.value == held.value, (widths, max_batch)
+
+
+SIDES = list(range(1, 70)) + [127, 128, 129, 255, 257, 511, 512]
+
+
+def test_fp32_row_kernel_loads_stay_inside_the_weight_copies(plan):
+    """The transposed copy of a layer has its inputs rounded up to 16 as rows and its outputs rounded up to 64 as columns."""
+    plan.f32_reach.restype = ctypes.c_long
+    for fin in SIDES + [1000, 1024]:
+        for fout in SIDES:
+            kp, ldn = (fin + 15) // 16 * 16, (fout + 63) // 64 * 64
+            assert plan.f32_reach(ldn, kp, ldn) == kp * ldn, (fin, fout)

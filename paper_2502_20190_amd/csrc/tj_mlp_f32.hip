@@ -118,29 +118,29 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
 
     // A chunk is 16 k; load b of it takes k = 4 b + q in lane quarter q, features 4 n .. 4 n + 3 (n = lane % 16) of the
     // wave's 64.  Weights come in two sets of one chunk, set 0 loaded ahead of the phase that uses it.  In the backward
-    // pass the last chunk's rows and the last group's columns may run past the matrix into the parameters
-    // behind it: such rows meet zeros of the other operand, such columns are features that nobody reads.
+    // pass the last group's columns may run past the matrix into the parameters behind it: features that nobody reads.
     struct Mine {             // this wave's part of a phase
         const float *w0, *w1;
-        int pitch, nk, F, KS, f, ks;
-        uint32_t rF, off[4];
+        int pitch, rows, nk, F, KS, f, ks;
+        uint32_t rF, row[4];
     };
     const uint32_t quarter = lane >> 4;
     auto mine = [&](const Phase &p) {
         Mine m;
-        m.w0 = p.w0; m.w1 = p.w1; m.pitch = p.pitch; m.nk = p.nk; m.F = p.F; m.KS = p.KS; m.rF = p.rF;
+        m.w0 = p.w0; m.w1 = p.w1; m.pitch = p.pitch; m.rows = p.rows; m.nk = p.nk; m.F = p.F; m.KS = p.KS; m.rF = p.rF;
         m.ks = (int)((uint32_t)wave * p.rF >> 16);
         m.f = wave - m.ks * p.F;
 #pragma unroll
-        for (int b = 0; b < 4; ++b) m.off[b] = 4u * tjplan::f32_lane_at(lane, b, p.pitch, m.f);
+        for (int b = 0; b < 4; ++b) m.row[b] = tjplan::f32_row_at(lane, b, p.pitch);
         return m;
     };
     auto active = [](const Mine &p) { return p.ks < p.KS && p.ks < p.nk; };
     auto load = [&](f32x4 (&w)[4], const float *base, const Mine &p, int c) {
         gbytes rows = (gbytes)(uintptr_t)(base + tjplan::f32_chunk_at(c, p.pitch));
-        asm("" : "+s"(rows));                // wave-uniform: the scalar base of the loads, off[] their lane offset
+        asm("" : "+s"(rows));                // wave-uniform: the scalar base of the loads
+        const uint32_t last_row = tjplan::f32_last_row_at(c, p.rows, p.pitch);
 #pragma unroll
-        for (int b = 0; b < 4; ++b) w[b] = *(gf32x4)(rows + p.off[b]);
+        for (int b = 0; b < 4; ++b) w[b] = *(gf32x4)(rows + 4u * tjplan::f32_lane_at(p.row[b], last_row, lane, p.f));
         __builtin_amdgcn_sched_barrier(0);   // issued here, not where the registers run short
     };
     f32x4 wa[2][4], wb[2][4];

@@ -18,22 +18,26 @@ namespace tjplan {
 constexpr int kF32Waves = 8;
 
 struct F32Phase {
-    int pitch, nk, F, KS;     // pitch: elements between rows of the matrix
+    int pitch, rows, nk, F, KS;     // pitch: elements between rows of the matrix
 };
 inline F32Phase f32_phase(int pitch, int rows, int cols)
 {
     F32Phase p;
-    p.pitch = pitch; p.nk = (rows + 15) / 16; p.F = (cols + 63) / 64; p.KS = kF32Waves / p.F;
+    p.pitch = pitch; p.rows = rows; p.nk = (rows + 15) / 16; p.F = (cols + 63) / 64; p.KS = kF32Waves / p.F;
     return p;
 }
 // A wave whose slice is ks multiplies chunks ks, ks + KS, ... < nk, or none (ks >= KS or ks >= nk).  Its first load goes out
 // before that is decided, so it is of a chunk that exists.
 TJ_HD inline int f32_first_chunk(int ks, int nk) { return ks < nk ? ks : nk - 1; }
-// Element of the matrix at which load b of a chunk starts, four features wide: the chunk's part and the lane's.
+// Element of the matrix at which load b of a chunk starts, four features wide: the chunk's part, and the lane's from the start of
+// row 4 b + lane / 16 of the chunk.  Rows past the matrix meet zeros of the other operand and are its last row instead: what
+// lies behind the matrix need not be finite.
 TJ_HD inline unsigned f32_chunk_at(int chunk, int pitch) { return 16u * chunk * pitch; }
-TJ_HD inline unsigned f32_lane_at(int lane, int b, int pitch, int f)
+TJ_HD inline unsigned f32_row_at(int lane, int b, int pitch) { return (unsigned)(lane >> 4) * pitch + 4u * b * pitch; }
+TJ_HD inline unsigned f32_last_row_at(int chunk, int rows, int pitch) { return (unsigned)(rows - 1 - 16 * chunk) * pitch; }
+TJ_HD inline unsigned f32_lane_at(unsigned row_at, unsigned last_row_at, int lane, int f)
 {
-    return (unsigned)(lane >> 4) * pitch + 4u * b * pitch + 64u * f + 4u * (lane & 15);
+    return (row_at < last_row_at ? row_at : last_row_at) + 64u * f + 4u * (lane & 15);
 }
 
 // ---- the weight kernel of bf16 networks

@@ -23,7 +23,8 @@ extern "C" long f32_reach(int pitch, int rows, int cols)
     auto load = [&](int chunk, int f) {
         for (int lane = 0; lane < 64; ++lane)
             for (int b = 0; b < 4; ++b)
-                most = std::max(most, (long)tjplan::f32_chunk_at(chunk, pitch) + tjplan::f32_lane_at(lane, b, pitch, f) + 4);
+                most = std::max(most, (long)tjplan::f32_chunk_at(chunk, pitch) + 4 +
+                                          tjplan::f32_lane_at(tjplan::f32_row_at(lane, b, pitch), tjplan::f32_last_row_at(chunk, rows, pitch), lane, f));
     };
     for (int wave = 0; wave < tjplan::kF32Waves; ++wave) {
         const int ks = wave / p.F, f = wave % p.F;

@@ -8,6 +8,7 @@ most 1500) in fp32, whose rounding is bounded by terms * 2^-24 of the sum of mag
 1e-6 when the roundings are independent; the batches are drawn clear of the ReLU kinks."""
 from dataclasses import replace
 
+import numpy as np
 import pytest
 
 from paper_2502_20190_amd import synth
@@ -57,3 +58,39 @@ def test_on_policy_learner(tj, orc, D, widths, A, B):
         rows = P._batch(orc, o, D, A, 1 + B // 8, 8, 70 + step, "fp32", n=B)
         P._step_both(tj, orc, g, o, rows, TOL, sync=step > 0)
         P._check_compute_copies(tj, g, "fp32")
+
+
+@pytest.mark.parametrize("on_policy", [False, True])
+@pytest.mark.parametrize("D,widths,B", [(4, (16, 17), 8), (20, (33, 40, 29), 33), (5, (1, 3, 2), 3)])
+def test_a_unit_switched_off_by_an_infinite_bias_leaves_the_rest_finite(tj, D, widths, B, on_policy):
+    """Biases lie behind their weight matrix, where the last chunk of a contraction over 17, 29 .. units ends: minus infinity is a
+    unit that never fires, the same as a very large negative bias, bit for bit."""
+    import torch
+
+    A = 3
+    layers = synth.ppo_layers(widths, A) if on_policy else tuple((LIN, w, 0, 0) for w in widths) + ((LIN, A, 0, 0),)
+    g = torch.Generator(device="cuda").manual_seed(4)
+    randn = lambda *s: torch.randn(s, generator=g, device="cuda")
+    obs, next_obs, a, b, c = randn(B, D), randn(B, D), -1.0 + 0.1 * randn(B), randn(B), randn(B)
+    action = torch.zeros(B, dtype=torch.int32, device="cuda")
+    got = []
+    for off in (-np.inf, -1e30):
+        theta = synth.xavier_init(layers, (D, 1, 1), 1)
+        at = 0
+        for i, (_, w, _, _, _) in enumerate(synth.layer_shapes(layers, (D, 1, 1))):
+            at += int(np.prod(w))
+            if i + 1 < len(layers):
+                theta[at + w[0] // 2] = off
+            at += w[0]
+        if on_policy:
+            lrn = tj.PpoLearner(D, widths, A, "fp32", B, theta)
+            assert lrn.step(obs, action, a, b, c) == tj.TJ_OK
+        else:
+            wl = replace(synth.WORKLOADS["c2"], obs_shape=(D,), n_actions=A, batch=B, layers=layers, precision="fp32")
+            lrn = tj.learner_for_workload(wl, theta, synth.xavier_init(layers, (D, 1, 1), 2))
+            mb = tj.Minibatch(B, D, "f32")
+            mb.obs.copy_(obs), mb.next_obs.copy_(next_obs), mb.action.copy_(action), mb.reward.copy_(b), mb.done.zero_()
+            assert lrn.step(mb) == tj.TJ_OK
+        torch.cuda.synchronize()
+        got.append(lrn.get_state(tj.TJ_STATE_GRADS))
+    assert np.isfinite(got[0]).all() and np.array_equal(*got)

@@ -49,3 +49,11 @@ def test_fp32_row_kernel_loads_stay_inside_the_weight_copies(plan):
         for fout in SIDES:
             kp, ldn = (fin + 15) // 16 * 16, (fout + 63) // 64 * 64
             assert plan.f32_reach(ldn, kp, ldn) == kp * ldn, (fin, fout)
+
+
+def test_fp32_row_kernel_loads_of_the_parameters_end_with_their_matrix(plan):
+    """The backward pass reads W [out][in] itself, whole groups of 64 inputs: at most 63 floats behind it."""
+    plan.f32_reach.restype = ctypes.c_long
+    for fin in SIDES:
+        for fout in SIDES:
+            assert plan.f32_reach(fin, fout, fin) == (fout - 1) * fin + (fin + 63) // 64 * 64, (fin, fout)

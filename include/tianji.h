@@ -140,7 +140,10 @@ int tj_buffer_insert(tj_buffer *buf, uint32_t n, const void *d_obs, const void *
  *    slot s is skipped iff (s - begin) mod capacity < len for the arc
  *    [begin, begin+len) those inserts cover, which holds the oldest
  *    transitions of the ring.  The arc the last tj_sample used is reported by
- *    tj_buffer_status.
+ *    tj_buffer_status.  The inserts meant are those of this call and ordinary
+ *    ones; of the ordinary ones made before the first concurrent insert, those
+ *    on the stream of the latest tj_sample (before any: of tj_buffer_create)
+ *    are not left out, the first sample on another stream waits for them.
  * head and count advance at the call, as for tj_buffer_insert.  All concurrent
  * inserts of one buffer go to the same insert_stream; tj_sample calls of one
  * buffer go to one stream at a time (they share the sampler's scratch).  The

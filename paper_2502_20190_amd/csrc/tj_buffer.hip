@@ -532,13 +532,14 @@ __global__ void publish_rows(uint32_t *state, unsigned long long total)
 // Before a sample that may overlap concurrent inserts: the arc of slots whose insert had been
 // issued (rows_issued, host count at the call) but had not finished when this kernel ran.  One
 // snapshot serves all blocks of the mask kernel, and tj_buffer_status reports it.
-__global__ void snapshot_arc(uint32_t *state, unsigned long long rows_floor, unsigned long long rows_issued,
+// The first home_rows of them precede every sample in stream order.
+__global__ void snapshot_arc(uint32_t *state, unsigned long long home_rows, unsigned long long rows_issued,
                              unsigned long long cap)
 {
     if (threadIdx.x != 0 || blockIdx.x != 0) return;
     const unsigned long long published =
         __hip_atomic_load((unsigned long long *)(state + 4), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    const unsigned long long done = published > rows_floor ? published : rows_floor;
+    const unsigned long long done = published > home_rows ? published : home_rows;
     unsigned long long len = rows_issued > done ? rows_issued - done : 0;
     if (len > cap) len = cap;
     state[2] = (uint32_t)(done % cap);
@@ -785,15 +786,18 @@ struct tj_buffer {
     hipEvent_t ev[3];
     bool timed;
     // Concurrent inserts: rows_issued counts every row ever passed to an insert call (host side, at
-    // the call); its device twin in state[4..5] advances when an insert's kernels have run (inserts before the first
-    // concurrent one are not published one by one: rows_floor and that insert see to them).  The
+    // the call); its device twin in state[4..5] advances when an insert's kernels have run (but see home).  The
     // difference, taken on the device just before a sample's mask kernel, is the arc that sample
     // leaves out.  sample_done marks the end of the latest tj_sample.
     uint64_t rows_issued = 0;
-    // Before the first concurrent insert: stream of the last plain insert, and rows_issued when they moved to it.
-    hipStream_t plain_stream = nullptr;
-    uint64_t plain_begin = 0;
-    uint64_t rows_floor = 0;    // rows known to precede every sample, published or not
+    // While there has been no concurrent insert, ordinary ones on the home stream (that of the latest tj_sample; before any,
+    // the one the ring was created on) do not advance the device's count: samples follow them in stream order.  home_rows
+    // is the total behind the last of them, home_rows_stream a stream that has them in its order.  The first concurrent
+    // insert marks that point with home_done, and the first sample after it, if it is on another stream, waits there.
+    hipStream_t home = nullptr, home_rows_stream = nullptr;
+    uint64_t home_rows = 0;
+    hipEvent_t home_done = nullptr;
+    bool wait_home = false;
     bool concurrent_used = false;
     hipEvent_t sample_done = nullptr;
     hipStream_t last_sample_stream = nullptr;
@@ -824,6 +828,7 @@ int tj_buffer_create(const tj_buffer_desc *desc, void *dev_arena, size_t arena_b
     b->n_tiles = (uint32_t)((desc->capacity + kTile - 1) / kTile);
     b->head = b->count = 0;
     b->timed = false;
+    b->home = (hipStream_t)hip_stream;
     zero_words<<<1, 64, 0, (hipStream_t)hip_stream>>>(b->state, 8);
     if (hipGetLastError() != hipSuccess) {
         delete b;
@@ -837,6 +842,7 @@ int tj_buffer_destroy(tj_buffer *buf)
 {
     if (!buf) return TJ_ERR_INVALID_ARG;
     if (buf->sample_done) (void)hipEventDestroy(buf->sample_done);
+    if (buf->home_done) (void)hipEventDestroy(buf->home_done);
     delete buf;
     return TJ_OK;
 }
@@ -858,12 +864,12 @@ static int insert_rows(tj_buffer *buf, uint32_t n, const void *d_obs, const void
                             d_version + done_rows});
         if (rc != TJ_OK) return rc;
     }
-    if (buf->concurrent_used) {
+    if (!buf->concurrent_used && st == buf->home) {
+        buf->home_rows = buf->rows_issued + n;
+        buf->home_rows_stream = st;
+    } else {
         publish_rows<<<1, 64, 0, st>>>(buf->state, (unsigned long long)(buf->rows_issued + n));
         if (hipGetLastError() != hipSuccess) return TJ_ERR_DEVICE;
-    } else if (buf->rows_issued == 0 || buf->plain_stream != st) {
-        buf->plain_stream = st;
-        buf->plain_begin = buf->rows_issued;
     }
     buf->rows_issued += n;
     buf->head = (buf->head + n) % cap;
@@ -899,12 +905,13 @@ int tj_buffer_insert_concurrent(tj_buffer *buf, uint32_t n, const void *d_obs, c
         TJ_HIP_TRY(hipEventRecord(buf->sample_done, buf->last_sample_stream));
     }
     if (buf->sample_done) TJ_HIP_TRY(hipStreamWaitEvent(st, buf->sample_done, 0));
-    if (!buf->concurrent_used && buf->rows_issued > 0) {
-        // Plain inserts do not publish.  Those of this stream are published on it; those before them went through
-        // the caller's other streams, in whose order the samples are.
-        buf->rows_floor = buf->plain_stream == st ? buf->plain_begin : buf->rows_issued;
-        publish_rows<<<1, 64, 0, st>>>(buf->state, (unsigned long long)buf->rows_issued);
-        if (hipGetLastError() != hipSuccess) return TJ_ERR_DEVICE;
+    if (!buf->concurrent_used && buf->home_rows > 0) {
+        if (!buf->home_done) TJ_HIP_TRY(hipEventCreateWithFlags(&buf->home_done, hipEventDisableTiming));
+        buf->wait_home = hipEventRecord(buf->home_done, buf->home_rows_stream) == hipSuccess;
+        if (!buf->wait_home) {   // a stream that is gone
+            (void)hipGetLastError();
+            TJ_HIP_TRY(hipDeviceSynchronize());
+        }
     }
     buf->concurrent_used = true;
     return insert_rows(buf, n, d_obs, d_next_obs, d_action, d_reward, d_done, d_version, st);
@@ -933,9 +940,13 @@ static int sample_into(tj_buffer *buf, uint32_t batch, int64_t current_version, 
     // With concurrent inserts in play, the arc to leave out is taken on the device, in stream order
     // just before the mask kernel; otherwise it stays empty (state[2..3] = 0).
     if (buf->concurrent_used) {
-        snapshot_arc<<<1, 64, 0, st>>>(buf->state, (unsigned long long)buf->rows_floor, (unsigned long long)buf->rows_issued,
+        if (buf->wait_home && st != buf->home_rows_stream) TJ_HIP_TRY(hipStreamWaitEvent(st, buf->home_done, 0));
+        buf->wait_home = false;   // later samples are in the order of this one
+        snapshot_arc<<<1, 64, 0, st>>>(buf->state, (unsigned long long)buf->home_rows, (unsigned long long)buf->rows_issued,
                                        (unsigned long long)buf->desc.capacity);
         if (hipGetLastError() != hipSuccess) return TJ_ERR_DEVICE;
+    } else {
+        buf->home = buf->home_rows_stream = st;   // the caller has put this sample behind every ordinary insert so far
     }
     if (buf->timed) TJ_HIP_TRY(hipEventRecord(buf->ev[0], st));
     launch_sampler<false>(make_eligible(buf->ring.version, nullptr, count, 0u, (uint32_t)buf->desc.capacity,

@@ -463,6 +463,77 @@ def test_ordinary_inserts_before_the_first_concurrent_one_on_its_stream(tj, orc)
     assert gbuf.status()[1].last_excluded_len == 0
 
 
+@pytest.mark.parametrize("created_there", [False, True])
+def test_finished_ordinary_inserts_on_the_insert_stream_stay_eligible(tj, orc, created_there):
+    """A ring filled through the insert stream, other work of the caller's behind that, then the first concurrent insert: at
+    most its own rows are left out (they may have arrived by then)."""
+    import torch
+
+    wl = synth.small_variant(synth.WORKLOADS["c2"], capacity=3000, batch=64)
+    side = torch.cuda.Stream()
+    gbuf = tj.Buffer(wl.capacity, wl.obs_elems, wl.obs_dtype, stream=side if created_there else None)
+    obuf = orc.Buffer(wl.capacity, wl.obs_elems, wl.obs_dtype)
+    rows, new = synth.make_chunk(wl, 43, 0, 3000), synth.make_chunk(wl, 44, 0, 200)
+    dev = [[torch.from_numpy(np.ascontiguousarray(r[f])).cuda()
+            for f in ("obs", "next_obs", "action", "reward", "done", "version")] for r in (rows, new)]
+    assert obuf.insert(**rows) == 0
+    _sync()
+    gbuf.insert(*dev[0], stream=side)
+    side.synchronize()
+    keep = _busy(side)
+    gbuf.insert_concurrent(*dev[1], side)
+    mb = tj.Minibatch(wl.batch, gbuf.obs_elems, gbuf.obs_dtype)
+    for seed in (5, 6):
+        assert gbuf.sample(mb, wl.current_version, 40, seed) == tj.TJ_OK
+        st, info = gbuf.status()
+        begin, left_out = int(info.last_excluded_begin), int(info.last_excluded_len)
+        assert st == tj.TJ_OK and begin == 0 and left_out in ([0, 200] if seed == 5 else [0])
+        if left_out == 0 and obuf.head == 0:
+            assert obuf.insert(**new) == 0
+        ost, oidx, oK = orc.sample_excluding(obuf.versions(), obuf.count, wl.capacity, begin, left_out, wl.current_version, 40,
+                                             seed, wl.batch)
+        assert ost == 0 and info.last_n_eligible == oK
+        np.testing.assert_array_equal(mb.host()["idx"], oidx)
+        side.synchronize()
+    del keep
+
+
+def test_ordinary_inserts_on_the_sampling_stream_precede_every_sample(tj, orc):
+    """The sampling loop moves on to another stream after ordinary inserts that its old stream has not come to yet."""
+    import torch
+
+    wl = synth.small_variant(synth.WORKLOADS["c2"], capacity=3000, batch=64)
+    gbuf, obuf = _fill_both(tj, orc, wl, 45, 3000, 3000)
+    old, side = torch.cuda.Stream(), torch.cuda.Stream()
+    rows, new = synth.make_chunk(wl, 46, 0, 300), synth.make_chunk(wl, 47, 0, 200)
+    dev = [[torch.from_numpy(np.ascontiguousarray(r[f])).cuda()
+            for f in ("obs", "next_obs", "action", "reward", "done", "version")] for r in (rows, new)]
+    mb = tj.Minibatch(wl.batch, gbuf.obs_elems, gbuf.obs_dtype)
+    _sync()
+    assert gbuf.sample(mb, wl.current_version, 40, 4, stream=old) == tj.TJ_OK
+    old.synchronize()
+    keep = _busy(old)
+    gbuf.insert(*dev[0], stream=old)
+    also = _busy(side)
+    gbuf.insert_concurrent(*dev[1], side)
+    assert gbuf.sample(mb, wl.current_version, 40, 5) == tj.TJ_OK
+    st, info = gbuf.status()
+    assert obuf.insert(**rows) == 0
+    begin, left_out = int(info.last_excluded_begin), int(info.last_excluded_len)
+    assert st == tj.TJ_OK and (begin, left_out) in [(300, 200), (0, 0)]   # the last insert alone, unless it is there already
+    if left_out == 0:
+        assert obuf.insert(**new) == 0
+    ost, oidx, oK = orc.sample_excluding(obuf.versions(), obuf.count, wl.capacity, begin, left_out, wl.current_version, 40, 5,
+                                         wl.batch)
+    assert ost == 0 and info.last_n_eligible == oK
+    got, want = mb.host(), obuf.gather(oidx)
+    np.testing.assert_array_equal(got["idx"], oidx)
+    for f in FIELDS:
+        np.testing.assert_array_equal(got[f], want[f], err_msg=f)
+    side.synchronize()
+    del keep, also
+
+
 @pytest.mark.parametrize("elems,dtype", [(1, "f32"), (37, "u8"), (1020, "f32"), (1024, "f32"), (2056, "f32"), (28224, "u8")])
 @pytest.mark.parametrize("n", [1, 255, 257, 600])
 def test_insert_copies_rows_and_scalars_in_one_launch(tj, elems, dtype, n):

@@ -18,6 +18,7 @@
 //   3 copy_rows    : gathers obs / next_obs rows with 16-byte lanes
 //                    (HBM bound, 2*B*row_bytes read + written)
 // Rings of more than 8192 tiles (8.4 M slots) scan in a kernel of their own (tile_scan, select_slots).
+// For small rings and moderate batches 1 and 2 are one kernel (sample_small).
 #include "tj_common.h"
 #include <mutex>
 
@@ -263,13 +264,20 @@ __device__ __forceinline__ uint32_t pick_slot(const unsigned long long *words, u
     return (t * kWordsPerTile + w) * 64 + (uint32_t)(__ffsll((long long)mm) - 1);
 }
 
-// Mask, scan and select in one kernel, for rings of at most kSmallTiles tiles, 64 draws per block: every block
+// Mask, scan and select in one kernel, for rings of at most kSmallTiles tiles and moderate batches, 64 draws per block: every block
 // finds the eligible rows of the whole ring itself and keeps the mask in LDS.  Two dependent launches with the mask
 // through memory between them are bound by their latency, not by the tags.  The counts fit the lanes of one wave: a
 // shuffle scan, and a binary search by shuffles.  Per sample, back to back: 2000 .. 20000 slots 9.2 -> 7.1 us; each round of
 // sixteen tiles costs a block 2 us, so that 32768 slots break even (9.0) and 65536 lose (14.5), hence the limit.  With the
-// 4-64-64-2 update behind it, a ring of 10000: 24.7 -> 21.7 us.
-constexpr int kSmallTiles = 24;
+// 4-64-64-2 update behind it, a ring of 10000: 24.7 -> 21.7 us.  Blocks beyond two per CU wait for a place and repeat
+// the whole ring's mask once more: past kSmallRounds rounds of sixteen tiles in all blocks together the separate launches are
+// faster (us against theirs: 24 tiles 10.6 : 14.0 at 16384 draws, 14.9 : 13.9 at 20000, 80 : 32 at 262144; 16 tiles 13.1 : 13.9
+// at 32768, 20.5 : 14.6 at 65536).
+constexpr int kSmallTiles = 24, kSmallRounds = 512;
+inline bool sample_is_small(uint32_t n_tiles, uint32_t batch)
+{
+    return n_tiles <= (uint32_t)kSmallTiles && ((uint64_t)batch + 63) / 64 * ((n_tiles + 15) / 16) <= (uint64_t)kSmallRounds;
+}
 
 template <bool FRAME>
 __global__ __launch_bounds__(1024) void sample_small(const Eligible a, uint32_t n_tiles, uint32_t *__restrict__ state,
@@ -394,14 +402,14 @@ __global__ __launch_bounds__(256) void select_rows(
     idx[j] = slot;
 }
 
-// Eligibility, K, and the draws with their scalar fields: one launch for small rings, two up to kScanTiles tiles, else
+// Eligibility, K, and the draws with their scalar fields: one launch for small samples, two up to kScanTiles tiles, else
 // three.
 template <bool FRAME>
 void launch_sampler(const Eligible &a, unsigned long long *mask, uint32_t *tile_count, uint32_t *tile_off, uint32_t *state,
                     uint32_t n_tiles, uint64_t seed, uint32_t batch, const RingPtrs &ring, const tj_minibatch *out,
                     hipStream_t st)
 {
-    if (n_tiles <= (uint32_t)kSmallTiles) {
+    if (sample_is_small(n_tiles, batch)) {
         sample_small<FRAME><<<(batch + 63) / 64, 1024, 0, st>>>(a, n_tiles, state, seed, batch, ring, out->idx, out->action,
                                                                 out->reward, out->done);
         return;

@@ -590,3 +590,18 @@ def test_rings_around_the_one_launch_sampler(tj, orc, rows):
         st, info = frames.status()
         assert st == ost and info.last_n_eligible == oK
         np.testing.assert_array_equal(mb.host()["idx"], oidx)
+
+
+@pytest.mark.parametrize("rows,batch", [(24 * 1024, 16384), (24 * 1024, 16385), (16 * 1024 + 1, 16385), (16 * 1024, 32768),
+                                        (16 * 1024, 32769)])
+def test_batches_around_the_one_launch_sampler(tj, orc, rows, batch):
+    """Both sides of the number of blocks that the one-launch sampler takes, with one and with two rounds of sixteen tiles."""
+    rng = np.random.default_rng(batch)
+    data = dict(obs=rng.standard_normal((rows, 1)).astype(np.float32), next_obs=rng.standard_normal((rows, 1)).astype(np.float32),
+                action=rng.integers(0, 9, rows).astype(np.int32), reward=rng.standard_normal(rows).astype(np.float32),
+                done=rng.integers(0, 2, rows).astype(np.uint8), version=(np.arange(rows) // 700).astype(np.int32))
+    gbuf, obuf = tj.Buffer(rows, 1, "f32"), orc.Buffer(rows, 1, "f32")
+    gbuf.insert_host(data)
+    assert obuf.insert(**data) == 0
+    for max_st in (3, 1 << 40):
+        _compare_sample(tj, gbuf, obuf, batch, (rows - 1) // 700, max_st, 7)

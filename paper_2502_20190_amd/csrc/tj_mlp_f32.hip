@@ -452,6 +452,7 @@ struct UpdatePlan {
 };
 
 constexpr int kUThreads = 1024, kUWaves = 16;
+constexpr int kLongBatch = 2048;   // rows
 
 template <int TN, int TK>
 __device__ __forceinline__ void update_tile(const TjF32Update &a, const UpdatePlan &plan, const int l, const int t,
@@ -762,13 +763,15 @@ int plan_tiles(int L, const TjF32Layer *lay, UpdatePlan &p)
 
 // 16 x 16 tiles while their operand traffic (128 bytes per tile and row, at the 24 bytes per clock and CU that 4-byte
 // loads reach) stays below what a second launch costs; then 64-wide tiles and as many slices of the batch as
-// one round of blocks holds.
+// one round of blocks holds.  A network of few tiles never has that traffic, but its few blocks are a chain as long as
+// the batch: past kLongBatch rows the slices are worth the launch for every network (on-policy updates, us with whole columns :
+// sliced; 4-64-64-2 at 2048 rows 33 : 33, 4096 49 : 40, 8192 85 : 60; 4-16-2 at 2048 28 : 28, 4096 42 : 30, 32768 254 : 101).
 int update_plan(int L, const TjF32Layer *lay, int B, UpdatePlan &p)
 {
     for (int l = 0; l < L; ++l) p.tn[l] = p.tk[l] = 16;
     int n = plan_tiles(L, lay, p);
     p.S = 1;
-    p.wide = (size_t)n * B > 400000;
+    p.wide = (size_t)n * B > 400000 || B > kLongBatch;
     if (p.wide) {
         for (int l = 0; l < L; ++l) {
             p.tn[l] = lay[l].out > 32 ? 64 : 16;

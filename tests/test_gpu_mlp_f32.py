@@ -94,3 +94,15 @@ def test_a_unit_switched_off_by_an_infinite_bias_leaves_the_rest_finite(tj, D, w
         torch.cuda.synchronize()
         got.append(lrn.get_state(tj.TJ_STATE_GRADS))
     assert np.isfinite(got[0]).all() and np.array_equal(*got)
+
+
+@pytest.mark.parametrize("D,widths,A,batches", [(4, (16,), 2, (2049, 2048, 2063, 2064, 2100)), (20, (33, 70), 3, (4100, 2049, 2048, 2500))])
+def test_small_networks_on_long_batches(tj, orc, D, widths, A, batches):
+    """Both sides of the batch from which the gradient of every network comes in slices, the last of them empty or of a few rows, on
+    one learner that has held longer batches before."""
+    layers = tuple((LIN, w, 0, 0) for w in widths) + ((LIN, A, 0, 0),)
+    wl = replace(synth.WORKLOADS["c2"], obs_shape=(D,), n_actions=A, batch=max(batches), layers=layers, precision="fp32", lr=1e-3)
+    g, o = T._pair(tj, orc, wl, seed=6)
+    for step, B in enumerate(batches):
+        T._step_both(tj, orc, g, o, wl, T._batch_clear_of_kinks(o, wl, 90 + step, B), TOL, check_state=False, sync=step > 0)
+        T._check_compute_copies(tj, g, wl)

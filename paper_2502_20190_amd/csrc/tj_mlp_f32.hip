@@ -56,7 +56,7 @@ RowsLds rows_lds(int L, const TjF32Layer *lay, int nr, bool dqn, bool backward)
     o.pitch = up(w, 64) + 16;
     const int R = 4 * nr, NG = dqn ? 3 * nr : nr;
     int at = 0;
-    o.keep = at; at += L * R * o.pitch;                 // input rows of every layer, s
+    o.keep = at; at += (backward ? L : std::min(L, 2)) * R * o.pitch;   // input rows of every layer, s; acting: two layers in turn
     o.pp = at; at += dqn ? 2 * 2 * R * o.pitch : 0;     // s' (online), s' (target), two layers in turn
     o.part = at; at += kWaves * 2 * NG * 256;           // the k slices of one layer
     o.dz = at; at += backward ? 2 * R * o.pitch : 0;    // output gradients, two layers in turn
@@ -93,7 +93,7 @@ template <bool V> struct Two { static constexpr bool value = V; };   // both net
 // KIND: TJ_ROWS_DQN (three passes, backward), TJ_ROWS_PPO (one pass, backward), TJ_ROWS_ACT (forward only; `mode`
 // says what is done with the head outputs)
 template <int KIND, int NR>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void f32_rows(const RowsArgs args, const int mode)
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, KIND == TJ_ROWS_ACT && NR == 2 ? 4 : 2))) void f32_rows(const RowsArgs args, const int mode)
 {
     constexpr bool DQN = KIND == TJ_ROWS_DQN, BACK = KIND != TJ_ROWS_ACT;
     constexpr int R = 4 * NR;                       // transitions per block
@@ -113,6 +113,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
     const RowsLds &o = args.o;
     const int P = o.pitch;
     float *const keep = lds + o.keep, *const pp = lds + o.pp, *const part = lds + o.part, *const dzb = lds + o.dz;
+    auto kept = [&](int l) { return keep + (BACK ? l : l & 1) * R * P; };
     float *const qs = lds + o.qs, *const bs = lds + o.bias, *const sm = lds + o.small;
     const int last = L - 1, A = a.lay[last].out;
 
@@ -263,7 +264,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
     int boff = 0;
     for (int l = 0; l < L; ++l) {
         // rows of this layer's input, group g
-        const float *xs = keep + l * R * P, *xn = pp + (l & 1) * 2 * R * P, *xt = l == 0 ? xn : xn + R * P;
+        const float *xs = kept(l), *xn = pp + (l & 1) * 2 * R * P, *xt = l == 0 ? xn : xn + R * P;
         Mine nx = ph;
         if (l + 1 < L) nx = mine(args.fwd[l + 1]);
         else if (BACK && (DQN ? L - 2 : L - 1) >= 1) nx = mine(args.bwd[DQN ? L - 2 : L - 1]);   // the Q-learner's head gradient is no contraction
@@ -298,7 +299,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
             const float b = bs[(g < NON ? boff : args.n_bias + boff) + col];
             f32x4 s = get_part(ph, g, NG, f) + b;
             if (l < last) {
-                float *dst = g < NR ? keep + ((l + 1) * R + 4 * g) * P + col : pp + (((l + 1) & 1) * 2 * R + 4 * (g - NR)) * P + col;
+                float *dst = g < NR ? kept(l + 1) + 4 * g * P + col : pp + (((l + 1) & 1) * 2 * R + 4 * (g - NR)) * P + col;
 #pragma unroll
                 for (int i = 0; i < 4; ++i) { s[i] = fmaxf(s[i], 0.f); dst[i * P] = s[i]; }
                 if (BACK && g < NR) {
@@ -784,11 +785,18 @@ int update_plan(int L, const TjF32Layer *lay, int B, UpdatePlan &p)
     return n;
 }
 
+// Groups of four rows per block: the fewest that need no second round of blocks on the chip, or the most that LDS holds.
+// Acting on rows of at most kActPaired floats stays at two groups, whose blocks find place in pairs on a CU: one hides the other's
+// latency.  On wider rows the weights, read once per block, weigh more (us for 32768 rows, two groups : four; 4-64-64-3 51 : 61,
+// 128-256-256-19 121 : 134, 64-384-384-7 187 : 206, 128-512-512-19 294 : 286, 256-512-512-512-33 547 : 499).
+constexpr int kActPaired = 384 + 16;
+
 int rows_nr(const TjF32Rows &a, int mode)
 {
     const bool dqn = mode == TJ_ROWS_DQN, back = dqn || mode == TJ_ROWS_PPO;
+    const int most = dqn ? 1 : !back && rows_lds(a.L, a.lay, 2, dqn, back).pitch <= kActPaired ? 2 : 4;
     int best = 1;
-    for (int nr = 1; nr <= (dqn ? 1 : 4); nr *= 2) {
+    for (int nr = 1; nr <= most; nr *= 2) {
         if (rows_lds(a.L, a.lay, nr, dqn, back).total * sizeof(float) > kLdsMax) break;
         best = nr;
         if ((a.B + 4 * nr - 1) / (4 * nr) <= 256) break;   // one round of blocks on the chip

@@ -106,3 +106,14 @@ def test_small_networks_on_long_batches(tj, orc, D, widths, A, batches):
     for step, B in enumerate(batches):
         T._step_both(tj, orc, g, o, wl, T._batch_clear_of_kinks(o, wl, 90 + step, B), TOL, check_state=False, sync=step > 0)
         T._check_compute_copies(tj, g, wl)
+
+
+@pytest.mark.parametrize("D,widths,A", [(4, (16,), 2), (20, (33, 70, 29, 64, 5), 3), (70, (385,), 18), (17, (512, 40, 512, 400), 6),
+                                        (1000, (512, 512), 33)])
+def test_acting_on_many_observations(tj, orc, D, widths, A):
+    """One, two and four groups of rows per block, whole and partial; deeper networks than the two layers that are kept."""
+    layers = tuple((LIN, w, 0, 0) for w in widths) + ((LIN, A, 0, 0),)
+    wl = replace(synth.WORKLOADS["c2"], obs_shape=(D,), n_actions=A, batch=2500, layers=layers, precision="fp32")
+    g, o = T._pair(tj, orc, wl, seed=7)
+    for n in (1024, 1025, 2048, 2053, 4999):
+        T._check_act(tj, orc, g, o, wl, T._batch(wl, 61, n)["obs"], 0.1, n, TOL)

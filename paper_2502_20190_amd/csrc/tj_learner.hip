@@ -1557,7 +1557,7 @@ template <typename T> struct MlpLearner : tj_learner {
         v = (float *)a.take(P * 4);
         int fin[TJ_MAX_LAYERS], fout[TJ_MAX_LAYERS];
         for (int l = 0; l < L; ++l) { fin[l] = lay[l].in; fout[l] = lay[l].out; }
-        whole = sizeof(T) == 4 ? tj_f32_fits(L, fin, fout, n_pass) : tj_b16_fits(L, fin, fout, n_pass, Bmax);
+        whole = sizeof(T) == 4 ? tj_f32_fits(L, fin, fout, n_pass, Bmax) : tj_b16_fits(L, fin, fout, n_pass, Bmax);
         if (whole) return plan_whole(a);
         // The first layer's and the head's weight gradients share one launch of few 256 x 128 tiles; on a
         // large batch more slices than S let that launch reach every CU (bf16 nets of three layers or more,

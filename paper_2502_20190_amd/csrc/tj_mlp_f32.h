@@ -27,8 +27,8 @@ struct TjF32Rows : TjRowsCall {
     const float *bias, *bias_tg;     // lay[0].BP, lay[0].BP_tg
 };
 
-// True if the networks of this shape run in these kernels (LDS, lanes); decides the learner's layout.
-bool tj_f32_fits(int L, const int *in, const int *out, int passes);
+// True if the networks of this shape, in updates of up to max_batch rows, run in these kernels; decides the learner's layout.
+bool tj_f32_fits(int L, const int *in, const int *out, int passes, int max_batch);
 // Blocks (and with them loss_part entries) of a launch for B rows.
 int tj_f32_blocks(const TjF32Rows &a, int mode);
 int tj_f32_rows(const TjF32Rows &a, int mode, hipStream_t st);

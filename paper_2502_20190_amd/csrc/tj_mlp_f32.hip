@@ -47,8 +47,10 @@ struct RowsLds {
 RowsLds rows_lds(int L, const TjF32Layer *lay, int nr, bool dqn, bool backward)
 {
     RowsLds o;
-    int w = 0, nb = 0;
+    int w = 0, nb = 0, waves = 0;   // waves: those with a part of some phase
     for (int l = 0; l < L; ++l) {
+        waves = std::max(waves, tjplan::f32_part_waves(tjplan::f32_phase(lay[l].ldn, lay[l].kp, lay[l].ldn)));
+        if (backward && l) waves = std::max(waves, tjplan::f32_part_waves(tjplan::f32_phase(lay[l].in, lay[l].out, lay[l].in)));
         w = lay[l].kp > w ? lay[l].kp : w;
         if (l + 1 < L) w = lay[l].ldn > w ? lay[l].ldn : w;
         nb += lay[l].ldn;
@@ -58,7 +60,7 @@ RowsLds rows_lds(int L, const TjF32Layer *lay, int nr, bool dqn, bool backward)
     int at = 0;
     o.keep = at; at += (backward ? L : std::min(L, 2)) * R * o.pitch;   // input rows of every layer, s; acting: two layers in turn
     o.pp = at; at += dqn ? 2 * 2 * R * o.pitch : 0;     // s' (online), s' (target), two layers in turn
-    o.part = at; at += kWaves * 2 * NG * 256;           // the k slices of one layer
+    o.part = at; at += waves * 2 * NG * 256;            // the k slices of one layer
     o.dz = at; at += backward ? 2 * R * o.pitch : 0;    // output gradients, two layers in turn
     o.wa = at; at += dqn ? R * o.pitch : 0;             // head weights of the actions taken
     o.qs = at; at += 4 * NG * 64;                       // head outputs
@@ -785,7 +787,9 @@ int update_plan(int L, const TjF32Layer *lay, int B, UpdatePlan &p)
     return n;
 }
 
-// Groups of four rows per block: the fewest that need no second round of blocks on the chip, or the most that LDS holds.
+// Groups of four rows per block: the fewest that need no second round of blocks on the chip, or the most that LDS holds.  The
+// Q-learner's second group fits where rows are narrow or the layers short enough that not all waves have partial sums
+// (us with one group : two; 4-64-64-2 at 2048 rows 37 : 31, 8192 101 : 76; 16-32-5 8192 66 : 50).
 // Acting on rows of at most kActPaired floats stays at two groups, whose blocks find place in pairs on a CU: one hides the other's
 // latency.  On wider rows the weights, read once per block, weigh more (us for 32768 rows, two groups : four; 4-64-64-3 51 : 61,
 // 128-256-256-19 121 : 134, 64-384-384-7 187 : 206, 128-512-512-19 294 : 286, 256-512-512-512-33 547 : 499).
@@ -794,7 +798,7 @@ constexpr int kActPaired = 384 + 16;
 int rows_nr(const TjF32Rows &a, int mode)
 {
     const bool dqn = mode == TJ_ROWS_DQN, back = dqn || mode == TJ_ROWS_PPO;
-    const int most = dqn ? 1 : !back && rows_lds(a.L, a.lay, 2, dqn, back).pitch <= kActPaired ? 2 : 4;
+    const int most = dqn ? 2 : !back && rows_lds(a.L, a.lay, 2, dqn, back).pitch <= kActPaired ? 2 : 4;
     int best = 1;
     for (int nr = 1; nr <= most; nr *= 2) {
         if (rows_lds(a.L, a.lay, nr, dqn, back).total * sizeof(float) > kLdsMax) break;
@@ -831,7 +835,13 @@ template <int KIND, int NR> int launch_rows(const TjF32Rows &a, int mode, hipStr
 
 }  // namespace
 
-bool tj_f32_fits(int L, const int *in, const int *out, int passes)
+// Largest batch of a Q-learner that is updated here.  One group of four rows per block reads the weights of both networks for
+// every four transitions, and past some batch the layered kernels, whose tiles share them, are faster (us here : there;
+// 128-512-512-512-18 at 8192 rows 769 : 844, 16384 1559 : 1394; 300-500-384-500-33 757 : 773, 1515 : 1315; 128-256-256-18 at 16384
+// 358 : 370, 32768 701 : 637; seven layers of 64-128 513 : 581, 1000 : 969; with two groups 16-32-5 84 : 96, 157 : 150).
+constexpr int kQRows = 16384, kQRowsWide = 8192, kQWide = 256 + 16;   // the latter past rows of kQWide floats
+
+bool tj_f32_fits(int L, const int *in, const int *out, int passes, int max_batch)
 {
     if (L < 1 || L > TJ_MAX_LAYERS || in[0] > kF32MaxInput || out[L - 1] > kF32MaxOut) return false;
     TjF32Layer lay[TJ_MAX_LAYERS] = {};
@@ -840,7 +850,9 @@ bool tj_f32_fits(int L, const int *in, const int *out, int passes)
         lay[l].in = in[l]; lay[l].out = out[l];
         lay[l].kp = up(in[l], 16); lay[l].ldn = up(out[l], 64);
     }
-    return rows_lds(L, lay, 1, passes == 3, true).total * sizeof(float) <= kLdsMax;
+    const RowsLds o = rows_lds(L, lay, 1, passes == 3, true);
+    if (passes == 3 && max_batch > (o.pitch > kQWide ? kQRowsWide : kQRows)) return false;
+    return o.total * sizeof(float) <= kLdsMax;
 }
 
 int tj_f32_blocks(const TjF32Rows &a, int mode)
@@ -853,7 +865,7 @@ int tj_f32_rows(const TjF32Rows &a, int mode, hipStream_t st)
 {
     if (a.B < 1 || a.L < 1 || a.L > TJ_MAX_LAYERS) return TJ_ERR_SHAPE;
     const int nr = rows_nr(a, mode);
-    if (mode == TJ_ROWS_DQN) return launch_rows<TJ_ROWS_DQN, 1>(a, mode, st);
+    if (mode == TJ_ROWS_DQN) return nr == 1 ? launch_rows<TJ_ROWS_DQN, 1>(a, mode, st) : launch_rows<TJ_ROWS_DQN, 2>(a, mode, st);
     if (mode == TJ_ROWS_PPO)
         return nr == 1 ? launch_rows<TJ_ROWS_PPO, 1>(a, mode, st)
                        : nr == 2 ? launch_rows<TJ_ROWS_PPO, 2>(a, mode, st) : launch_rows<TJ_ROWS_PPO, 4>(a, mode, st);

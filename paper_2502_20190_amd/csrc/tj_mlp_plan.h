@@ -26,6 +26,8 @@ inline F32Phase f32_phase(int pitch, int rows, int cols)
     p.pitch = pitch; p.rows = rows; p.nk = (rows + 15) / 16; p.F = (cols + 63) / 64; p.KS = kF32Waves / p.F;
     return p;
 }
+// Waves 0 .. n - 1 have a part of the phase (wave = ks F + f).
+inline int f32_part_waves(const F32Phase &p) { return p.F * std::min(p.KS, p.nk); }
 // A wave whose slice is ks multiplies chunks ks, ks + KS, ... < nk, or none (ks >= KS or ks >= nk).  Its first load goes out
 // before that is decided, so it is of a chunk that exists.
 TJ_HD inline int f32_first_chunk(int ks, int nk) { return ks < nk ? ks : nk - 1; }

@@ -34,3 +34,14 @@ extern "C" long f32_reach(int pitch, int rows, int cols)
     }
     return most;
 }
+
+// Waves that multiply in a phase (a mask), and how many of them the memory for their partial sums is laid out for.
+extern "C" unsigned f32_active(int pitch, int rows, int cols, int *held)
+{
+    const tjplan::F32Phase p = tjplan::f32_phase(pitch, rows, cols);
+    unsigned mask = 0;
+    for (int wave = 0; wave < tjplan::kF32Waves; ++wave)
+        if (wave / p.F < p.KS && wave / p.F < p.nk) mask |= 1u << wave;
+    *held = tjplan::f32_part_waves(p);
+    return mask;
+}

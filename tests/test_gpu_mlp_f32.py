@@ -108,6 +108,20 @@ def test_small_networks_on_long_batches(tj, orc, D, widths, A, batches):
         T._check_compute_copies(tj, g, wl)
 
 
+@pytest.mark.parametrize("D,widths,A,batches", [
+    (4, (16,), 2, (1025, 1031, 1024)), (20, (33, 64, 5), 18, (1032, 1029)), (100, (128,), 7, (1027,)), (4, (16,), 2, (16384, 16381)),
+    (4, (16,), 2, (16385, 1030))])
+def test_q_learner_with_two_groups_of_rows_per_block(tj, orc, D, widths, A, batches):
+    """From 1025 rows on, narrow networks; partial groups, and both sides of the largest batch that these kernels take.  Roundings of a
+    sum over 16 k rows: 16385 * 2^-24 = 1e-3 at the worst, some 128 * 2^-24 = 8e-6 where they are independent."""
+    layers = tuple((LIN, w, 0, 0) for w in widths) + ((LIN, A, 0, 0),)
+    wl = replace(synth.WORKLOADS["c2"], obs_shape=(D,), n_actions=A, batch=max(batches), layers=layers, precision="fp32", lr=1e-3)
+    g, o = T._pair(tj, orc, wl, seed=8)
+    for step, B in enumerate(batches):
+        T._step_both(tj, orc, g, o, wl, T._batch_clear_of_kinks(o, wl, 95 + step, B), TOL, check_state=False, sync=step > 0)
+        T._check_compute_copies(tj, g, wl)
+
+
 @pytest.mark.parametrize("D,widths,A", [(4, (16,), 2), (20, (33, 70, 29, 64, 5), 3), (70, (385,), 18), (17, (512, 40, 512, 400), 6),
                                         (1000, (512, 512), 33)])
 def test_acting_on_many_observations(tj, orc, D, widths, A):

@@ -57,3 +57,11 @@ def test_fp32_row_kernel_loads_of_the_parameters_end_with_their_matrix(plan):
     for fin in SIDES:
         for fout in SIDES:
             assert plan.f32_reach(fin, fout, fin) == (fout - 1) * fin + (fin + 63) // 64 * 64, (fin, fout)
+
+
+def test_fp32_row_kernel_partial_sums_have_room_for_every_wave_that_multiplies(plan):
+    plan.f32_active.restype = ctypes.c_uint
+    held = ctypes.c_int()
+    for rows in SIDES:
+        for cols in SIDES:
+            assert plan.f32_active(cols, rows, cols, ctypes.byref(held)) == (1 << held.value) - 1, (rows, cols)

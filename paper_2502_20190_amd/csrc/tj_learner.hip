@@ -675,7 +675,7 @@ __global__ __launch_bounds__(256) void adam_update(float *__restrict__ theta, fl
                                                    float *__restrict__ v, float *__restrict__ gpart,
                                                    int S, size_t gstride, size_t P, float lr, float b1,
                                                    float b2, float eps, float c1, float c2,
-                                                   const EmitTable<T> tab, const LossFinal lf, const DgradEmit dg,
+                                                   const EmitTable<T> tab, const LossFinal lf,
                                                    const size_t mid_begin, const size_t mid_end, const int S_mid)
 {
     if (blockIdx.x == 0 && threadIdx.x < 64 && lf.ppo_part) {
@@ -741,10 +741,6 @@ __global__ __launch_bounds__(256) void adam_update(float *__restrict__ theta, fl
 #pragma unroll
             for (int e = 0; e < 4; ++e) emit_transposed<T>(tab, k, i + e, ta[e]);
         }
-        if (dg.n > 0) {
-#pragma unroll
-            for (int e = 0; e < 4; ++e) emit_dgrad(dg, i + e, ta[e]);
-        }
     } else {
         for (size_t e = i; e < P; ++e) {
             float g = gpart[e];
@@ -761,7 +757,6 @@ __global__ __launch_bounds__(256) void adam_update(float *__restrict__ theta, fl
                 if (e >= tab.begin[k] && e < tab.end[k]) tab.dst[k][e - tab.begin[k]] = TjElem<T>::from_f32(th);
                 emit_transposed<T>(tab, k, e, th);
             }
-            emit_dgrad(dg, e, th);
         }
     }
 }
@@ -1973,13 +1968,11 @@ template <typename T> struct MlpLearner : tj_learner {
             lf.c_v = ppo_fin.c_v; lf.c_e = ppo_fin.c_e;
             lf.ppo_out = ppo_fin.out; lf.ppo_internal = ppo_fin.internal;
         }
-        DgradEmit no_dgrad;
-        no_dgrad.n = 0;
         // hidden layers: S slices, or one where the last launch has summed them; first and last layer: S_ends
         const bool mid = L >= 3 && (slices_summed || S_ends != S);
         const size_t mid_begin = mid ? lay[1].w_off : 0, mid_end = mid ? lay[L - 1].w_off : 0;
         adam_update<T><<<(unsigned)((P + 1023) / 1024), 256, 0, st>>>(theta_on, m, v, gpart, S_ends, Ppad, P, d.lr,
-                                                                      d.beta1, d.beta2, d.eps, c1, c2, tab, lf, no_dgrad,
+                                                                      d.beta1, d.beta2, d.eps, c1, c2, tab, lf,
                                                                       mid_begin, mid_end, slices_summed ? 1 : S);
         if (hipGetLastError() != hipSuccess) return TJ_ERR_DEVICE;
         if ((rc = mark(4, st)) != TJ_OK) return rc;

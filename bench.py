@@ -35,7 +35,19 @@ GEMM_SOURCES = ("tj_gemm.h", "tj_gemm.hip", "tj_conv_first.hip", "tj_conv_wgrad.
 GEMM_TRAFFIC = {"c3": {"bytes_per_step": 738.6e6, "gemm_source_sha256_16": "db2a35045902baea"},
                 "c5": {"bytes_per_step": 1354.0e6, "gemm_source_sha256_16": "db2a35045902baea"}}
 PEAK_HBM_GBS = 8000.0
+FP32_KERNELS = {2: "f32_rows + f32_update", 3: "f32_rows + f32_update + f32_adam"}   # by launches of an update
 PEAK_TFLOPS = {"bf16": 2500.0, "fp32": 157.3}
+
+
+def fp32_launches(dims, B):
+    """Launches of an fp32 vector network's update (the library's rule; dims: (in, out) per layer): all per-row
+    work, all per-weight work, and past some size of the batch the sum of the latter's slices with Adam."""
+    ceil = lambda x, t: (x + t - 1) // t
+    if B <= 2048 and sum(ceil(i, 16) * ceil(o, 16) for i, o in dims) * B <= 400_000:
+        return 2
+    side = lambda x: 64 if x > 32 else 16
+    tiles = sum(ceil(i, side(i)) * ceil(o, side(o)) for i, o in dims)
+    return 3 if min(16, 256 // tiles, B // 128) > 1 else 2
 
 
 def adam_slice_traffic(dims, precision, B, P):
@@ -255,14 +267,15 @@ def bench_ppo(args):
     bwd = sum(per_sample) + sum(per_sample[1:]) - (per_sample[-1] if fused_dx else 0)
     flops = B * (fwd + bwd)     # forward, weight and input gradients
     n_launch = (n_layers - (1 if fused_head else 0)) + n_layers - (1 if fused_dx else 0)
-    if precision == "fp32":
-        n_launch = 2   # all per-row work (the forward phase), all per-weight work (the backward phase, Adam included)
+    widths = [D] + [l[1] for l in layers]
+    dims = list(zip(widths[:-1], widths[1:]))
+    if precision == "fp32":   # all per-row work (the forward phase), all per-weight work (the backward phase, Adam included)
+        n_launch = fp32_launches(dims, B)
     gemm_ms = ph["forward_gemm_ms"] + ph["backward_gemm_ms"]
     achieved = flops / (gemm_ms * 1e-3) / 1e12
     P = synth.num_params(layers, (D, 1, 1))
     adam_bytes = (30 if precision == "bf16" else 28) * P               # algorithmic; the kernel also reads gradient slices
-    widths = [D] + [l[1] for l in layers]
-    adam_extra = adam_slice_traffic(list(zip(widths[:-1], widths[1:])), precision, B, P)
+    adam_extra = adam_slice_traffic(dims, precision, B, P)
     gae_bytes = n_env * T * (4 + 4 + 1 + 4 + 4) + n_env * 4      # reward, value, done in; adv, ret out
     out = {
         "metric": "learner transitions consumed/sec at 1 MI355X",
@@ -273,7 +286,7 @@ def bench_ppo(args):
                    "layers": [l[1] for l in layers], "params": P},
         "roofline": {"bound": "mfma", "achieved": achieved, "peak": PEAK_TFLOPS[precision], "unit": "TFLOP/s",
                      "frac": achieved / PEAK_TFLOPS[precision], "traffic": None,
-                     "kernel": "gemm_bf16_dlds + gemm_bf16_dlds_pair + gemm_bf16_dlds_pair_sum (its blocks that add gradient slices included)" if precision == "bf16" else "f32_rows + f32_update",
+                     "kernel": "gemm_bf16_dlds + gemm_bf16_dlds_pair + gemm_bf16_dlds_pair_sum (its blocks that add gradient slices included)" if precision == "bf16" else FP32_KERNELS[n_launch],
                      "launches_per_step": n_launch, "flops_per_launch": flops / n_launch,
                      "avg_launch_ms": gemm_ms / n_launch},
         "phases_ms": ph, "phase_events_on_steps": len(sampled),
@@ -491,8 +504,9 @@ def bench_replay(args, cfg, steps, warmup, with_cpu_baseline):
         n_gemm_launch = (n_layers - 1) + (n_layers - 1) if fused_head else 2 * n_layers
     elif n_conv == 0:
         # fp32 vector networks: one kernel for all per-row work (its time is the forward phase, the TD target and
-        # the input gradients included) and one for all per-weight work (the backward phase, Adam included)
-        n_gemm_launch = 2
+        # the input gradients included), one or two for all per-weight work (the backward phase, Adam included)
+        widths = [wl.obs_elems] + [l[1] for l in wl.layers]
+        n_gemm_launch = fp32_launches(list(zip(widths[:-1], widths[1:])), wl.batch)
     else:
         n_gemm_launch = (n_layers + n_conv - (1 if fused_head else 0)) + n_layers + (n_layers - 1)
         first = wl.layers[0]
@@ -520,7 +534,7 @@ def bench_replay(args, cfg, steps, warmup, with_cpu_baseline):
     flops = gemm_flops_per_step(wl, synth, fused_head)
     # the kernels behind the forward and backward phases (their launches share the MFMA roofline)
     if wl.precision != "bf16":
-        gemm_kernel_name = "f32_rows + f32_update" if n_conv == 0 else "gemm_pq<float>"
+        gemm_kernel_name = FP32_KERNELS[n_gemm_launch] if n_conv == 0 else "gemm_pq<float>"
     elif n_conv == 0:
         gemm_kernel_name = "gemm_bf16_dlds + gemm_bf16_dlds_pair + gemm_bf16_dlds_pair_sum (its blocks that add gradient slices included)"
     else:

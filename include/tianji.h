@@ -506,9 +506,10 @@ int tj_balance_plan(const tj_balance_in *in, tj_balance_out *out);
  *   every tj_ppo_step records [0] after the input cast, [1] after the forward
  *   GEMMs including the head, [2] after the objective kernel, [3] and [4] as
  *   above (the Adam kernel also finalises the step's statistics);
- *   fp32 networks of linear layers up to 512 wide (input up to 1024, head up
- *   to 64) and bf16 ones whose activations fit a compute unit (up to about 700
- *   wide) run a step in two parts: [0] start, [1] and [2] after the kernel of
+ *   networks of linear layers that run as one kernel per block of rows (fp32: up
+ *   to 512 wide, input up to 1024, head up to 64; bf16: activations that fit a
+ *   compute unit, up to about 700 wide; both only up to a max_batch from which
+ *   layer by layer is the faster way) run a step in two parts: [0] start, [1] and [2] after the kernel of
  *   all per-row work (forward passes, target or objective, input gradients),
  *   [3] and [4] after the per-weight work (weight gradients, Adam, copies),
  * on the call's stream.  The caller reads them after synchronising. */

@@ -1,5 +1,5 @@
-// fp32 vector networks as two launches per update (tj_mlp_f32.hip): everything that is per transition in one
-// kernel, everything that is per weight in another.
+// fp32 vector networks as two or three launches per update (tj_mlp_f32.hip): everything that is per transition in one
+// kernel, everything that is per weight in one or two others.
 #pragma once
 #include "tj_mlp_rows.h"
 

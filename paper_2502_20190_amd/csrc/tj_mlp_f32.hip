@@ -2,7 +2,7 @@
 //
 // The networks here are small (layers of at most 512 units), so a pass is not bound by arithmetic but by the
 // number of dependent kernels (about 2.4 us each before the first instruction runs) and by memory
-// latency inside each of them.  An update is therefore two launches:
+// latency inside each of them.  An update is therefore two launches, three on long batches:
 //
 //   f32_rows    one block per 4 NR transitions: all layers of all forward passes, the TD target (or the
 //               clipped objective), and the input gradients back to the first hidden layer.  Activations
@@ -10,6 +10,7 @@
 //               of s, output gradients) is written to memory.
 //   f32_update  one block per tile of a weight matrix: its gradient over the whole batch, then Adam on the
 //               tile, the transposed copy the forward pass reads, and the target network where it is due.
+//   f32_adam    where update_plan cuts a long batch into slices: their sum, and everything behind it.
 //
 // f32_rows multiplies with v_mfma_f32_4x4x1_16b_f32: sixteen independent 4 x 4 products per instruction,
 // the A operand (4 rows x 1) broadcast to all of them, so one instruction is 4 rows x 64 features x one k at

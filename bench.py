@@ -32,8 +32,8 @@ sys.path.insert(0, ROOT)
 # reads half the bytes, WRITE_SIZE all of them).  Valid for the sources it was taken with: the contraction
 # kernels and the learner that decides which of them a step launches.
 GEMM_SOURCES = ("tj_gemm.h", "tj_gemm.hip", "tj_conv_first.hip", "tj_conv_wgrad.hip", "tj_conv.h", "tj_learner.hip")
-GEMM_TRAFFIC = {"c3": {"bytes_per_step": 738.6e6, "gemm_source_sha256_16": "db2a35045902baea"},
-                "c5": {"bytes_per_step": 1354.0e6, "gemm_source_sha256_16": "db2a35045902baea"}}
+GEMM_TRAFFIC = {"c3": {"bytes_per_step": 738.9e6, "gemm_source_sha256_16": "258254a5647cdea6"},
+                "c5": {"bytes_per_step": 1353.4e6, "gemm_source_sha256_16": "258254a5647cdea6"}}
 PEAK_HBM_GBS = 8000.0
 FP32_KERNELS = {2: "f32_rows + f32_update", 3: "f32_rows + f32_update + f32_adam"}   # by launches of an update
 PEAK_TFLOPS = {"bf16": 2500.0, "fp32": 157.3}

@@ -245,23 +245,6 @@ __global__ __launch_bounds__(256) void col2im_mask_v8(const tj_bf16 *__restrict_
     *(uint4 *)(dz + p * g.C + c0) = make_uint4(o[0], o[1], o[2], o[3]);
 }
 
-// Copy of a channels-last tensor [n][OH][OW][O] into the interior of a zero-bordered one
-// [n][OH + 2 pad][OW + 2 pad][O] (the border is never written).  16 bytes per thread; O % 8 == 0.
-__global__ __launch_bounds__(256) void pad_halo(const tj_bf16 *__restrict__ src, tj_bf16 *__restrict__ dst, size_t n,
-                                                int OH, int OW, int O, int pad)
-{
-    const int O8 = O / 8;
-    const size_t total = n * OH * OW * O8;
-    const size_t t = (size_t)blockIdx.x * 256 + threadIdx.x;
-    if (t >= total) return;
-    const int c = (int)(t % O8);
-    const size_t p = t / O8;
-    const int x = (int)(p % OW), y = (int)((p / OW) % OH);
-    const size_t img = p / ((size_t)OW * OH);
-    const size_t d = ((img * (OH + 2 * pad) + y + pad) * (OW + 2 * pad) + x + pad) * O + c * 8;
-    *(uint4 *)(dst + d) = *(const uint4 *)(src + p * O + c * 8);
-}
-
 // Weights of the input-gradient GEMM of a convolution (kernel k, stride s, A = ceil(k / s) taps per
 // dimension): row j = (py, px, c) over the s x s pixel block and the input channels, column
 // (a, b, o) over the taps and the output channels:

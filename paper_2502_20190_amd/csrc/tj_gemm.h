@@ -53,6 +53,9 @@ struct TjGather {
     int64_t img_stride;          // elements between images
     int oh_stride, ow_stride;    // elements between patch origins (stride * W * C, stride * C)
     int run, krow_stride;        // elements per kernel row, elements between image rows (W * C)
+    // border > 0 (stride 1 only): the image is read as if it had a border of that many zero pixels.  Patch (oh, ow) then
+    // starts at pixel (oh - border, ow - border), and pixels outside in_h x in_w count as zero.
+    int border, in_h, in_w, chan;
 };
 
 __host__ __device__ inline int64_t tj_gather_origin(const TjGather &g, uint32_t m)
@@ -89,6 +92,7 @@ inline bool tj_gather_make(TjGather &g, int C, int H, int W, int ksz, int stride
     g.img_stride = (int64_t)H * W * C;
     g.oh_stride = stride * W * C; g.ow_stride = stride * C;
     g.run = ksz * C; g.krow_stride = W * C;
+    g.border = 0; g.in_h = H; g.in_w = W; g.chan = C;
     if (g.ohw < 2 || g.ow < 2) return false;   // ceil(2^32 / 1) does not fit 32 bits
     if (max_rows * (uint64_t)g.ohw >= ((uint64_t)1 << 32)) return false;
     // every 8-element vector of a patch row must be 16-byte aligned and inside one kernel row
@@ -122,6 +126,7 @@ template <typename T> struct TjGemmArgs {
     int n_split;         // gridDim.z
     float *qsum;         // optional: qsum[z*qsum_zstride + j] = sum over this z's k of Q[j][k]
     size_t qsum_zstride;
+    const T *zeros;      // with gather.border: 16 bytes of zeros
     TjGather gather;     // gather.on: P rows are patches of seg[0].P (bf16, one segment of at most 128
                          // columns, whole 64-k stages, no split); ldp is ignored
     TjGather out_map;    // with gather.on and out_map.on: D(i,j) -> Cj[origin(out_map, i) + koff(out_map, j)]
@@ -153,6 +158,10 @@ struct TjSliceSum {
 // tj_gemm_pair and the optimizer has to add those slices itself.
 int tj_gemm_pair_sum(const TjGemmArgs<tj_bf16> &a0, const TjGemmArgs<tj_bf16> &a1, const TjSliceSum &r,
                      hipStream_t st, bool *fused);
+struct TjConvWgradArgs;
+// A convolution's input gradient (gathered operand with a border, mapped output) and its weight gradient, which both
+// start from the same output gradient, as one launch.
+int tj_gemm_conv_backward(const TjGemmArgs<tj_bf16> &dgrad, const TjConvWgradArgs &wgrad, hipStream_t st);
 // bf16 with gathered operands: the same for two convolutions of equal shape class
 int tj_gemm_gather_pair(const TjGemmArgs<tj_bf16> &a0, const TjGemmArgs<tj_bf16> &a1, hipStream_t st);
 // fp32: the same for two small problems (falls back to two launches otherwise)

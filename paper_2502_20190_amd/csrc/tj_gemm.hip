@@ -13,6 +13,7 @@
 // Accumulator element r of lane l is D(i, j) with i = 8*(r/4) + 4*(l/32) + r%4
 // and j = l % 32, so a lane owns runs of four consecutive i: outputs that are
 // contiguous in i get vector stores.
+#include "tj_conv_wgrad.h"
 #include "tj_gemm.h"
 
 namespace {
@@ -921,7 +922,7 @@ template <int NFJ, int BKB, int NSTAGE> constexpr int dlds_lds_bytes() { return 
 // the row-major weights); Q keeps its contraction-contiguous rows, 32 elements of them per stage.
 // OUTS: 0, or the set of outputs (kOutCi | kOutCj | kOutCf) the launch can have: the epilogue of the others
 // is not compiled in (shorter code, fewer live registers after the main loop).
-template <int NFJ, int BKB, int NSTAGE, bool QSUM, bool GATHER = false, int TRANS = 0, int OUTS = 0>
+template <int NFJ, int BKB, int NSTAGE, bool QSUM, int GATHER = 0, int TRANS = 0, int OUTS = 0>
 __device__ __forceinline__ void dlds_body(const TjGemmArgs<tj_bf16> &a_in, const int tiles_seg0, const TileMap &tm,
                                           const int block_id, uint8_t *lds)
 {
@@ -991,6 +992,11 @@ __device__ __forceinline__ void dlds_body(const TjGemmArgs<tj_bf16> &a_in, const
     auto swizzle = [](int row) { return VPR == 8 ? (row >> 1) & 7 : (row >> 2) & 3; };
     const T *gsrcP[LP];
     const T *gsrcQ[LQ];
+    // GATHER = 2: the pixel a row's patch starts at (inside the border it is negative or past the image), and the
+    // tap (row, column, first channel) the next stage starts at: stages are issued in order and lie within one tap
+    int py[LP], px[LP];
+    int tap_y = 0, tap_x = 0, tap_c = 0;
+    (void)py; (void)px; (void)tap_y; (void)tap_x; (void)tap_c;
     if constexpr (TRANS != 0) {
         // P: load instruction c = wave + 8 t fills rows 2c, 2c+1 (512 bytes each).  Columns past the end
         // repeat the last valid vector.
@@ -1005,7 +1011,15 @@ __device__ __forceinline__ void dlds_body(const TjGemmArgs<tj_bf16> &a_in, const
         for (int t = 0; t < LP; ++t) {
             const int row = (wave + 8 * t) * RPI + lrow;
             const int i = min(i0 + row, a.I - 1);
-            if constexpr (GATHER)
+            if constexpr (GATHER == 2) {
+                const TjGather &g = a.gather;
+                const uint32_t img = __umulhi((uint32_t)i, g.mg_ohw), r = (uint32_t)i - img * (uint32_t)g.ohw;
+                const uint32_t oh = __umulhi(r, g.mg_ow), ow = r - oh * (uint32_t)g.ow;
+                py[t] = (int)oh - g.border;
+                px[t] = (int)ow - g.border;
+                gsrcP[t] = seg.P + (int64_t)img * g.img_stride + (int64_t)py[t] * g.oh_stride + (int64_t)px[t] * g.ow_stride +
+                           (lpos ^ swizzle(row)) * 8;
+            } else if constexpr (GATHER == 1)
                 gsrcP[t] = seg.P + tj_gather_origin(a.gather, (uint32_t)i);
             else
                 gsrcP[t] = seg.P + (size_t)i * a.ldp + (lpos ^ swizzle(row)) * 8 + k_begin;
@@ -1041,10 +1055,24 @@ __device__ __forceinline__ void dlds_body(const TjGemmArgs<tj_bf16> &a_in, const
         asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds_addr), "v"(src)
                      : "memory");
     };
-    auto issue = [&](uint8_t *sA, uint8_t *sB, int s) {
-        const size_t offP = GATHER ? (size_t)tj_gather_koff(a.gather, kposP + s * KE) : s * stepP;
+    auto issue = [&](uint8_t *sA, uint8_t *sB, int s) {   // called for s = 0, 1, 2, ... in order
+        if constexpr (GATHER == 2) {
+            const TjGather &g = a.gather;
+            const int off = tap_y * g.oh_stride + tap_x * g.ow_stride + tap_c;
 #pragma unroll
-        for (int t = 0; t < LP; ++t) dma16(gsrcP[t] + offP, sA + (wave + 8 * t) * 1024);
+            for (int t = 0; t < LP; ++t) {
+                const bool inside = (uint32_t)(py[t] + tap_y) < (uint32_t)g.in_h && (uint32_t)(px[t] + tap_x) < (uint32_t)g.in_w;
+                dma16(inside ? gsrcP[t] + off : a.zeros, sA + (wave + 8 * t) * 1024);
+            }
+            if ((tap_c += KE) == g.chan) {
+                tap_c = 0;
+                if (++tap_x * g.chan == g.run) { tap_x = 0; ++tap_y; }
+            }
+        } else {
+            const size_t offP = GATHER ? (size_t)tj_gather_koff(a.gather, kposP + s * KE) : s * stepP;
+#pragma unroll
+            for (int t = 0; t < LP; ++t) dma16(gsrcP[t] + offP, sA + (wave + 8 * t) * 1024);
+        }
 #pragma unroll
         for (int t = 0; t < LQ; ++t) {
             const int c = (wave + 8 * t) % CHQ;   // wave-uniform
@@ -1176,8 +1204,8 @@ __device__ __forceinline__ void dlds_body(const TjGemmArgs<tj_bf16> &a_in, const
         }
     }
 
-    if constexpr (GATHER) {
-        if (a.out_map.on) {
+    if constexpr (GATHER == 2) {
+        {
             // Mapped output (input gradient of a convolution): each 32 x 32 tile is staged in the wave's LDS
             // scratch as bf16 rows of 32 columns; a lane then owns 8 consecutive columns (channels of one
             // pixel) of a row: one 16-byte mask load and one 16-byte store at the mapped address.
@@ -1343,7 +1371,7 @@ __device__ __forceinline__ void dlds_body(const TjGemmArgs<tj_bf16> &a_in, const
     __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(((NFJ) <= 2 && (BKB) * (NSTAGE) <= 192) ? 4 : 2, \
                                                               ((NFJ) <= 2 && (BKB) * (NSTAGE) <= 192) ? 4 : 2)))
 
-template <int NFJ, int BKB, int NSTAGE, bool QSUM, bool GATHER = false, int TRANS = 0, int OUTS = 0>
+template <int NFJ, int BKB, int NSTAGE, bool QSUM, int GATHER = 0, int TRANS = 0, int OUTS = 0>
 __global__ TJ_DLDS_ATTRS(NFJ, BKB, NSTAGE) void gemm_bf16_dlds(const TjGemmArgs<tj_bf16> a, const int tiles_seg0,
                                                               const TileMap tm)
 {
@@ -1371,25 +1399,25 @@ __global__ TJ_DLDS_ATTRS(NFJ, BKB, NSTAGE) void gemm_bf16_dlds_pair(const GemmPa
     const int which = (int)blockIdx.x >= p.nblk0 ? 1 : 0;
     const int id = (int)blockIdx.x - which * p.nblk0;
     if constexpr (HIDDEN == 3) {   // two split weight gradients: fp32 slices only
-        dlds_body<NFJ, BKB, NSTAGE, true, false, 0, kOutCf>(p.a[which], p.tiles_seg0[which], p.tm[which], id, lds);
+        dlds_body<NFJ, BKB, NSTAGE, true, 0, 0, kOutCf>(p.a[which], p.tiles_seg0[which], p.tm[which], id, lds);
         return;
     }
     if constexpr (HIDDEN == 1 || HIDDEN == 2) {
         static_assert(BKB == 64 && NFJ == 2, "transposed operands: 256 x 128 tiles");
         if (p.a[which].trans == 1)   // block-uniform
-            dlds_body<NFJ, BKB, NSTAGE, true, false, 1, kOutCf>(p.a[which], p.tiles_seg0[which], p.tm[which], id, lds);
+            dlds_body<NFJ, BKB, NSTAGE, true, 0, 1, kOutCf>(p.a[which], p.tiles_seg0[which], p.tm[which], id, lds);
         else
-            dlds_body<NFJ, BKB, NSTAGE, false, false, 2, HIDDEN == 2 ? (kOutCi | kOutCj) : kOutCi>(
+            dlds_body<NFJ, BKB, NSTAGE, false, 0, 2, HIDDEN == 2 ? (kOutCi | kOutCj) : kOutCi>(
                 p.a[which], p.tiles_seg0[which], p.tm[which], id, lds);
         return;
     }
     if constexpr (BKB == 64 && NFJ == 2) {
         if (p.a[which].trans == 1) {   // block-uniform
-            dlds_body<NFJ, BKB, NSTAGE, true, false, 1>(p.a[which], p.tiles_seg0[which], p.tm[which], id, lds);
+            dlds_body<NFJ, BKB, NSTAGE, true, 0, 1>(p.a[which], p.tiles_seg0[which], p.tm[which], id, lds);
             return;
         }
         if (p.a[which].trans == 2) {
-            dlds_body<NFJ, BKB, NSTAGE, false, false, 2>(p.a[which], p.tiles_seg0[which], p.tm[which], id, lds);
+            dlds_body<NFJ, BKB, NSTAGE, false, 0, 2>(p.a[which], p.tiles_seg0[which], p.tm[which], id, lds);
             return;
         }
     }
@@ -1441,7 +1469,7 @@ __global__ TJ_DLDS_ATTRS(2, 64, 3) void gemm_bf16_dlds_pair_sum(const GemmPair p
         return;
     }
     const int which = (int)blockIdx.x >= p.nblk0 ? 1 : 0;
-    dlds_body<2, 64, 3, true, false, 1, kOutCf>(p.a[which], p.tiles_seg0[which], p.tm[which],
+    dlds_body<2, 64, 3, true, 0, 1, kOutCf>(p.a[which], p.tiles_seg0[which], p.tm[which],
                                                 (int)blockIdx.x - which * p.nblk0, lds);
 }
 
@@ -1452,8 +1480,32 @@ __global__ TJ_DLDS_ATTRS(NFJ, 64, 3) void gemm_bf16_dlds_gpair(const GemmPair p)
 {
     __shared__ __align__(1024) uint8_t lds[dlds_lds_bytes<NFJ, 64, 3>()];
     const int which = (int)blockIdx.x >= p.nblk0 ? 1 : 0;
-    dlds_body<NFJ, 64, 3, false, true>(p.a[which], p.tiles_seg0[which], p.tm[which],
+    dlds_body<NFJ, 64, 3, false, 1>(p.a[which], p.tiles_seg0[which], p.tm[which],
                                        (int)blockIdx.x - which * p.nblk0, lds);
+}
+
+// A convolution's input gradient (blocks [0, n0): gathered output gradient with a zero border, mapped output) and its
+// weight gradient.  Both only need the output gradient, and at small batches neither fills the chip (Nature-DQN network,
+// batch 256: 81 + 100 blocks of input gradients and 280 + 352 of weight gradients for 512 places), so they share a launch, the longer
+// input-gradient blocks first.  The border is not stored: a lane whose pixel lies outside loads zeros from elsewhere (two compares
+// and a select per load), which takes two copies of the gradient per update out.  An update at batch 256: 193.5 -> 169.2 us
+// (two border copies of 5 us, two launches of 8 us that now run beside another), at 2048: 517 -> 479 us.
+struct ConvBackward {
+    TjGemmArgs<tj_bf16> dgrad;
+    TjConvWgradArgs wgrad;
+    TileMap tm;
+    int tiles_seg0, n0, njb;
+};
+
+template <int NFJ, int NFI>
+__global__ TJ_DLDS_ATTRS(NFJ, 64, 3) void conv_backward_bf16(const ConvBackward p)
+{
+    constexpr int kGemm = dlds_lds_bytes<NFJ, 64, 3>(), kWgrad = tjwgrad::lds_bytes<NFI>();
+    __shared__ __align__(1024) uint8_t lds[kGemm > kWgrad ? kGemm : kWgrad];
+    if ((int)blockIdx.x < p.n0)
+        dlds_body<NFJ, 64, 3, false, 2>(p.dgrad, p.tiles_seg0, p.tm, (int)blockIdx.x, lds);
+    else
+        tjwgrad::body<NFI>(p.wgrad, p.njb, (int)blockIdx.x - p.n0, lds);
 }
 
 // Tile map and grid size of one problem for the 256 x 64*NFJ tiles.
@@ -1468,20 +1520,20 @@ template <int NFJ> unsigned plan_dlds(const TjGemmArgs<tj_bf16> &a, TileMap &tm,
     return a.n_split > 1 ? (unsigned)tm.tiles_i * tm.tiles_j * a.n_split : xcd_grid(tm);
 }
 
-template <int NFJ, int BKB, int NSTAGE, bool GATHER = false>
+template <int NFJ, int BKB, int NSTAGE, int GATHER = 0>
 int launch_dlds(const TjGemmArgs<tj_bf16> &a, hipStream_t st)
 {
     TileMap tm;
     int tiles[2];
     const unsigned nblk = plan_dlds<NFJ>(a, tm, tiles);
     if constexpr (GATHER)
-        gemm_bf16_dlds<NFJ, BKB, NSTAGE, false, true><<<nblk, 512, 0, st>>>(a, tiles[0], tm);
+        gemm_bf16_dlds<NFJ, BKB, NSTAGE, false, GATHER><<<nblk, 512, 0, st>>>(a, tiles[0], tm);
     else if (a.qsum)
         gemm_bf16_dlds<NFJ, BKB, NSTAGE, true><<<nblk, 512, 0, st>>>(a, tiles[0], tm);
     else if (a.Ci && !a.Cj && !a.Cf)   // a hidden layer's forward: one bf16 output
-        gemm_bf16_dlds<NFJ, BKB, NSTAGE, false, false, 0, kOutCi><<<nblk, 512, 0, st>>>(a, tiles[0], tm);
+        gemm_bf16_dlds<NFJ, BKB, NSTAGE, false, 0, 0, kOutCi><<<nblk, 512, 0, st>>>(a, tiles[0], tm);
     else if (a.Ci && a.Cj && !a.Cf)   // ... in both layouts
-        gemm_bf16_dlds<NFJ, BKB, NSTAGE, false, false, 0, kOutCi | kOutCj><<<nblk, 512, 0, st>>>(a, tiles[0], tm);
+        gemm_bf16_dlds<NFJ, BKB, NSTAGE, false, 0, 0, kOutCi | kOutCj><<<nblk, 512, 0, st>>>(a, tiles[0], tm);
     else
         gemm_bf16_dlds<NFJ, BKB, NSTAGE, false><<<nblk, 512, 0, st>>>(a, tiles[0], tm);
     return hipGetLastError() == hipSuccess ? TJ_OK : TJ_ERR_DEVICE;
@@ -1525,19 +1577,18 @@ int launch_bf16(const TjGemmArgs<tj_bf16> &a, const int tiles[2], hipStream_t st
         int t2[2];
         const unsigned nblk = plan_dlds<2>(a, tm, t2);
         if (a.trans == 2)
-            gemm_bf16_dlds<2, 64, 3, false, false, 2><<<nblk, 512, 0, st>>>(a, t2[0], tm);
+            gemm_bf16_dlds<2, 64, 3, false, 0, 2><<<nblk, 512, 0, st>>>(a, t2[0], tm);
         else if (a.qsum)
-            gemm_bf16_dlds<2, 64, 3, true, false, 1><<<nblk, 512, 0, st>>>(a, t2[0], tm);
+            gemm_bf16_dlds<2, 64, 3, true, 0, 1><<<nblk, 512, 0, st>>>(a, t2[0], tm);
         else
-            gemm_bf16_dlds<2, 64, 3, false, false, 1><<<nblk, 512, 0, st>>>(a, t2[0], tm);
+            gemm_bf16_dlds<2, 64, 3, false, 0, 1><<<nblk, 512, 0, st>>>(a, t2[0], tm);
         return hipGetLastError() == hipSuccess ? TJ_OK : TJ_ERR_DEVICE;
     }
     if (a.gather.on) {
         if (a.n_seg != 1 || jtot > 128 || a.K % 64 || a.n_split != 1 || a.qsum || a.I < 1) return TJ_ERR_SHAPE;
-        if (a.out_map.on && (!a.Cj || a.Ci || a.Cf || a.relu || a.bias_j || a.seg[0].bias || a.mask))
-            return TJ_ERR_SHAPE;
+        if (a.out_map.on || a.gather.border) return TJ_ERR_SHAPE;   // tj_gemm_conv_backward's
         // short contractions: two blocks per CU overlap their phases
-        return jtot > 64 ? launch_dlds<2, 64, 3, true>(a, st) : launch_dlds<1, 64, 3, true>(a, st);
+        return jtot > 64 ? launch_dlds<2, 64, 3, 1>(a, st) : launch_dlds<1, 64, 3, 1>(a, st);
     }
     if (a.out_map.on) return TJ_ERR_SHAPE;
     if (uses_dlds(a)) {
@@ -1717,6 +1768,32 @@ int tj_gemm_gather_pair(const TjGemmArgs<tj_bf16> &a0, const TjGemmArgs<tj_bf16>
         gemm_bf16_dlds_gpair<1><<<n0 + n1, 512, 0, st>>>(p);
     }
     return hipGetLastError() == hipSuccess ? TJ_OK : TJ_ERR_DEVICE;
+}
+
+int tj_gemm_conv_backward(const TjGemmArgs<tj_bf16> &a, const TjConvWgradArgs &w, hipStream_t st)
+{
+    int tiles[2], rc;
+    if ((rc = check_args(a, tiles)) != TJ_OK) return rc;
+    const TjGather &g = a.gather;
+    const int jtot = a.seg[0].j_end - a.seg[0].j_begin;
+    if (!g.on || !a.out_map.on || a.n_seg != 1 || jtot > 128 || a.K % 64 || a.n_split != 1 || a.qsum || a.I < 1) return TJ_ERR_SHAPE;
+    // the gathered loads: stages of 32 elements inside one tap, stride 1, zeros to read outside the image
+    if (!a.zeros || ((uintptr_t)a.zeros & 15) || g.chan % 32 || g.run % g.chan || g.ow_stride != g.chan || a.K % g.run) return TJ_ERR_SHAPE;
+    if (!a.Cj || a.Ci || a.Cf || a.relu || a.bias_j || a.seg[0].bias || a.mask) return TJ_ERR_SHAPE;
+    ConvBackward p;
+    unsigned n1;
+    if ((rc = tjwgrad::plan(w, p.njb, n1)) != TJ_OK) return rc;
+    p.dgrad = a; p.wgrad = w;
+    auto launch = [&](auto nfj, auto nfi) {
+        constexpr int NFJ = decltype(nfj)::value, NFI = decltype(nfi)::value;
+        int t2[2];
+        p.n0 = (int)plan_dlds<NFJ>(a, p.tm, t2);
+        p.tiles_seg0 = t2[0];
+        conv_backward_bf16<NFJ, NFI><<<(unsigned)p.n0 + n1, 512, 0, st>>>(p);
+        return hipGetLastError() == hipSuccess ? TJ_OK : TJ_ERR_DEVICE;
+    };
+    if (jtot > 64) return w.O == 64 ? launch(IntC<2>{}, IntC<2>{}) : launch(IntC<2>{}, IntC<1>{});
+    return w.O == 64 ? launch(IntC<1>{}, IntC<2>{}) : launch(IntC<1>{}, IntC<1>{});
 }
 
 // Tile counts of the 32 x 32 tiling, and whether the problem is small enough for it

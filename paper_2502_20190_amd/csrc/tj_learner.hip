@@ -2313,11 +2313,11 @@ template <typename T> struct ConvLearner : tj_learner {
         size_t part_stride;
         bool implicit;                  // conv without patch matrices: operand gathers (bf16, 32/64 channels)
         TjGather gth;
-        // input gradient as one gathered GEMM over the zero-bordered output gradient (see backward)
+        // input gradient as one gathered GEMM over the output gradient, read as if it had a zero border (see backward)
         bool dgrad_gather;
         TjGather dg_in, dg_out;
         int A, Kd, Nd, pad;             // taps per dimension, A*A*O, s*s*C, A-1
-        T *dZh, *Wd;
+        T *Wd;
         T *Wc_on, *WcT_on, *Wc_tg, *patches, *patchesT, *XT, *dZ, *dZT, *dpatch;
         float *part;
         // linear layer whose forward fills too few tiles: the contraction is split f_split ways into
@@ -2381,9 +2381,9 @@ template <typename T> struct ConvLearner : tj_learner {
                     const int Hc = g.H / g.s, Wc = g.W / g.s;
                     if (y.Kd % 64 == 0 && y.Nd <= 128)
                         y.dgrad_gather =
-                            tj_gather_make(y.dg_in, y.O, g.OH + 2 * y.pad, g.OW + 2 * y.pad, y.A, 1, Hc, Wc,
-                                           (size_t)Bmax * Hc * Wc) &&
+                            tj_gather_make(y.dg_in, y.O, g.OH, g.OW, y.A, 1, Hc, Wc, (size_t)Bmax * Hc * Wc) &&
                             tj_gather_make(y.dg_out, g.C, g.H, g.W, g.s, g.s, Hc, Wc, (size_t)Bmax * Hc * Wc);
+                    y.dg_in.border = y.pad;
                 }
                 c = g.OC; h = g.OH; w = g.OW;
                 prev_conv = true;
@@ -2465,8 +2465,6 @@ template <typename T> struct ConvLearner : tj_learner {
                 }
                 y.f_split = 1; y.f_chunk = 0; y.f_part = nullptr;
                 y.dpatch = (l > 0 && !y.dgrad_gather) ? (T *)a.take(B * y.OHW * y.ldK * sizeof(T)) : nullptr;
-                y.dZh = y.dgrad_gather ? (T *)a.take(B * (y.g.OH + 2 * y.pad) * (y.g.OW + 2 * y.pad) * y.O * sizeof(T))
-                                       : nullptr;
             } else {
                 act[l] = (T *)a.take(3 * B * y.ldK * sizeof(T));
                 y.patches = y.patchesT = y.dpatch = nullptr;
@@ -2794,6 +2792,7 @@ template <typename T> struct ConvLearner : tj_learner {
             const int Kc = conv ? round_up((int)Ms, VE) : Kb;      // contraction of the weight gradient
             const int ldm = conv ? round_up((int)((size_t)Bmax * y.OHW), VE) : ldB;
             bool wgrad_done = false;
+            TjConvWgradArgs wa;
             if constexpr (sizeof(T) == 2) {
                 if (l == 0 && first_done && first_wgrad_u8) {   // from the u8 stacks, one slice per block
                     if (n_cu == 0) {
@@ -2804,25 +2803,25 @@ template <typename T> struct ConvLearner : tj_learner {
                             n_cu = v;
                     }
                     const tjconv::ConvGeom &g = y.g;
-                    TjConvFirstWgradArgs wa;
-                    wa.obs = (const uint8_t *)mb->obs; wa.dZ = y.dZ;
-                    wa.B = B; wa.H = g.H; wa.W = g.W; wa.k = g.k; wa.s = g.s; wa.OH = g.OH; wa.OW = g.OW;
-                    wa.scale = 1.0f / 255.0f;
-                    wa.rows = mb->row_index; wa.n_rows = (uint32_t)mb->n_rows; wa.planes = mb->plane_index;
-                    wa.part = y.part; wa.zstride = y.part_stride;
-                    wa.n_part = std::min(B, std::min(n_cu, y.n_split));
-                    if ((rc = tj_conv_first_wgrad(wa, st)) != TJ_OK) return rc;
-                    add_slices(y, wa.n_part);
+                    TjConvFirstWgradArgs fa;
+                    fa.obs = (const uint8_t *)mb->obs; fa.dZ = y.dZ;
+                    fa.B = B; fa.H = g.H; fa.W = g.W; fa.k = g.k; fa.s = g.s; fa.OH = g.OH; fa.OW = g.OW;
+                    fa.scale = 1.0f / 255.0f;
+                    fa.rows = mb->row_index; fa.n_rows = (uint32_t)mb->n_rows; fa.planes = mb->plane_index;
+                    fa.part = y.part; fa.zstride = y.part_stride;
+                    fa.n_part = std::min(B, std::min(n_cu, y.n_split));
+                    if ((rc = tj_conv_first_wgrad(fa, st)) != TJ_OK) return rc;
+                    add_slices(y, fa.n_part);
                     wgrad_done = true;
                 }
                 if (!wgrad_done && conv && y.implicit) {   // straight from dZ and the layer input
-                    TjConvWgradArgs wa;
                     wa.dZ = y.dZ; wa.O = y.O; wa.act = act[l]; wa.g = y.gth;
                     wa.M = (int)Ms; wa.K = y.K;
                     wa.part = y.part; wa.zstride = y.part_stride;
                     wa.n_split = y.n_split;
                     wa.m_chunk = round_up((int)((Ms + y.n_split - 1) / y.n_split), 64);
-                    if ((rc = tj_conv_wgrad(wa, st)) != TJ_OK) return rc;
+                    // shares a launch with the input gradient where that is a gathered GEMM
+                    if (!y.dgrad_gather && (rc = tj_conv_wgrad(wa, st)) != TJ_OK) return rc;
                     add_slices(y, y.n_split);
                     wgrad_done = true;
                 }
@@ -2891,25 +2890,24 @@ template <typename T> struct ConvLearner : tj_learner {
                 }
             } else if (y.dgrad_gather) {
                 // dX[img, s yy + py, s xx + px, c] = sum_{a,b,o} dZ0[img, yy + a, xx + b, o] * Wd[(py,px,c)][(a,b,o)],
-                // dZ0 = the output gradient with a zero border of A-1: a stride-1 gathered GEMM whose row is a
-                // coarse position (yy, xx) and whose columns are the s x s pixel block times the channels
+                // dZ0 = the output gradient with a zero border of A-1 (not stored: the loads of pixels outside read
+                // zeros from elsewhere): a stride-1 gathered GEMM whose row is a coarse position (yy, xx) and whose
+                // columns are the s x s pixel block times the channels.  The layer's weight gradient rides along.
                 if constexpr (sizeof(T) == 2) {
                     const tjconv::ConvGeom &g = y.g;
-                    const size_t np = (size_t)B * g.OH * g.OW * (y.O / 8);
-                    tjconv::pad_halo<<<grid1(np), 256, 0, st>>>(y.dZ, y.dZh, (size_t)B, g.OH, g.OW, y.O, y.pad);
-                    if (hipGetLastError() != hipSuccess) return TJ_ERR_DEVICE;
                     TjGemmArgs<T> gm;
                     memset(&gm, 0, sizeof(gm));
                     gm.n_seg = 1;
-                    gm.seg[0] = {0, y.Nd, y.dZh, nullptr, 0};
+                    gm.seg[0] = {0, y.Nd, y.dZ, nullptr, 0};
                     gm.gather = y.dg_in;
+                    gm.zeros = y.dZ + Ms * y.O;   // the rows behind the last one
                     gm.Q = y.Wd;
                     gm.ldp = y.Kd; gm.ldq = y.Kd;
                     gm.I = B * (g.H / g.s) * (g.W / g.s); gm.K = y.Kd; gm.k_chunk = gm.K; gm.n_split = 1;
                     gm.out_map = y.dg_out;
                     gm.Cj = below.dZ; gm.cj_jmax = y.Nd;
                     gm.mask_cj = act[l];
-                    if ((rc = tj_gemm<T>(gm, st)) != TJ_OK) return rc;
+                    if ((rc = tj_gemm_conv_backward(gm, wa, st)) != TJ_OK) return rc;
                 }
             } else {       // patch gradients, then the gather back onto the input pixels with the ReLU mask
                 TjGemmArgs<T> gm;

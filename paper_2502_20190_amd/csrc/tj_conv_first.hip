@@ -16,9 +16,11 @@
 // LDS for the block's lifetime; an s' image is multiplied with both while it is resident.
 // MFMA: v_mfma_f32_32x32x16_bf16 with a = weights (rows = channels), b = patches (columns), so
 // a lane ends up with runs of four consecutive channels of one patch: 8-byte stores.
-#include "tj_gemm.h"
+#include "tj_conv_planes.h"
 
 namespace {
+
+using namespace tjplanes;
 
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
@@ -27,44 +29,11 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 constexpr int kThreads = 1024;    // 16 waves: the 13 patch tiles of an 84 x 84 frame in one round
 constexpr int kMaxRounds = 4;     // 4-pixel tasks per thread per image: H*W <= 4 * 1024 * 4
 
-typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
-typedef float f32x2_t __attribute__((ext_vector_type(2)));
-
-// round to nearest even in hardware (v_cvt_pk_bf16_f32); the inputs here are finite
-__device__ __forceinline__ uint32_t pack2(float a, float b)
-{
-    const f32x2_t f = {a, b};
-    return __builtin_bit_cast(uint32_t, __builtin_convertvector(f, bf16x2_t));
-}
-
 // The four planes of an image as 4-byte pieces (task t = pixels 4t .. 4t+3 of every plane), up to
 // kMaxRounds tasks per thread.
 struct PlaneRegs {
     uint32_t px[kMaxRounds][4];
 };
-
-// Byte offsets of an image's four planes inside its source table: the planes of batch position b, of the
-// table row an index names for it, or four planes named one by one (a frame ring's frames).  Indices
-// are clamped to the table.
-struct PlaneOff {
-    size_t o[4];
-};
-
-__device__ __forceinline__ PlaneOff plane_offsets(const uint32_t *rows, const uint32_t *planes, const uint32_t n_rows,
-                                                  const int b, const bool next, const int HW)
-{
-    PlaneOff p;
-    if (planes) {
-        const uint32_t *q = planes + (size_t)b * 8 + (next ? 4 : 0);
-#pragma unroll
-        for (int c = 0; c < 4; ++c) p.o[c] = (size_t)min(q[c], n_rows - 1u) * HW;
-    } else {
-        const uint32_t r = rows ? min(rows[b], n_rows - 1u) : (uint32_t)b;
-#pragma unroll
-        for (int c = 0; c < 4; ++c) p.o[c] = ((size_t)r * 4 + c) * HW;
-    }
-    return p;
-}
 
 __device__ __forceinline__ void fetch_planes(PlaneRegs &p, const uint8_t *src, const PlaneOff &off, const int n_task,
                                              const int n_round, const int tid)

@@ -200,6 +200,21 @@ struct TjConvFirstArgs {
 bool tj_conv_first_fits(int C, int H, int W, int k, int s, int O);
 int tj_conv_first(const TjConvFirstArgs &a, hipStream_t st);
 
+// All three convolutions of a pixel network in one launch (tj_conv_tower.hip): the first as above, then 32 -> 64 channels (4 x 4
+// kernel, stride 2) and 64 -> 64 (3 x 3), each relu(conv + b).  Pass p of 3B (next_obs null: of B) is s_p under the online
+// weights, s'_(p-B) under the online ones, s'_(p-2B) under the target's; `out` receives their last activations
+// [passes][OH3*OW3][64].  first.out (channels-last [B*OH*OW][32]) and act2 ([B*OH2*OW2][64]) receive those of s, both or neither.
+struct TjConvTowerArgs {
+    TjConvFirstArgs first;           // act0 unused
+    int OH2, OW2, s3, OH3, OW3;
+    const tj_bf16 *W2_on, *W2_tg, *W3_on, *W3_tg;   // [64][512], [64][576], k ordered (kh, kw, c)
+    const float *b2_on, *b2_tg, *b3_on, *b3_tg;
+    tj_bf16 *act2, *out;
+};
+struct TjConvShape { int C, H, W, O, k, s, OH, OW; };
+bool tj_conv_tower_fits(const TjConvShape *three);
+int tj_conv_tower(const TjConvTowerArgs &a, hipStream_t st);
+
 // Weight and bias gradient of that first convolution, also straight from the u8 stacks of the s
 // images (no channels-last copy of them is needed then) and the channels-last output gradient
 // dZ [B*OH*OW][32].  Block z of n_part (1 <= n_part <= B) sums the images z, z + n_part, ...:

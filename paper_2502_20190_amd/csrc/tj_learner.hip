@@ -2341,6 +2341,7 @@ template <typename T> struct ConvLearner : tj_learner {
     int last_batch = -1;
     bool shape_ok = true;
     bool first_fused = false;   // layer 0 runs straight from the u8 frames (tj_conv_first)
+    bool tower = false;         // the first three layers run as one kernel (tj_conv_tower)
     bool first_wgrad_u8 = false;   // ... and so does its weight gradient: no channels-last copy of the s images
     int n_cu = 0;                  // compute units of the device (asked once)
 
@@ -2426,6 +2427,13 @@ template <typename T> struct ConvLearner : tj_learner {
                       tj_conv_first_fits(lay[0].g.C, lay[0].g.H, lay[0].g.W, lay[0].g.k, lay[0].g.s, lay[0].O);
         first_wgrad_u8 = first_fused && tj_conv_first_wgrad_fits(lay[0].g.C, lay[0].g.H, lay[0].g.W, lay[0].g.k,
                                                                  lay[0].g.s, lay[0].O);
+        tower = first_wgrad_u8 && L >= 4 && lay[1].kind == TJ_LAYER_CONV2D && lay[2].kind == TJ_LAYER_CONV2D &&
+                lay[1].implicit && lay[2].implicit;   // whose backward passes need no patch matrices
+        if (tower) {
+            TjConvShape c[3];
+            for (int l = 0; l < 3; ++l) c[l] = {lay[l].g.C, lay[l].g.H, lay[l].g.W, lay[l].O, lay[l].g.k, lay[l].g.s, lay[l].g.OH, lay[l].g.OW};
+            tower = tj_conv_tower_fits(c);
+        }
         P = off;
         Ppad = tj_align_up(P, 64);
         A = lay[L - 1].O;
@@ -2616,7 +2624,7 @@ template <typename T> struct ConvLearner : tj_learner {
         }
         const int Kb = round_up(B, VE);
 
-        bool first_done = false;
+        int fwd_done = 0;   // layers whose forward passes have been launched
         if constexpr (sizeof(T) == 2) {
             if (first_fused && (((uintptr_t)mb->obs | (uintptr_t)mb->next_obs) & 3) == 0) {
                 const tjconv::ConvGeom &g = lay[0].g;
@@ -2629,10 +2637,16 @@ template <typename T> struct ConvLearner : tj_learner {
                 fa.scale = 1.0f / 255.0f;
                 fa.rows = mb->row_index; fa.n_rows = (uint32_t)mb->n_rows; fa.planes = mb->plane_index;
                 if ((rc = mark(0, st)) != TJ_OK) return rc;
-                if ((rc = tj_conv_first(fa, st)) != TJ_OK) return rc;
-                first_done = true;
+                if (tower) {
+                    if ((rc = run_tower(fa, true, st)) != TJ_OK) return rc;
+                    fwd_done = 3;
+                } else {
+                    if ((rc = tj_conv_first(fa, st)) != TJ_OK) return rc;
+                    fwd_done = 1;
+                }
             }
         }
+        const bool first_done = fwd_done > 0;
         if (!first_done) {   // observations -> channels-last compute type, images s | s'
             const tjconv::ConvGeom &g = lay[0].g;
             const size_t px = (size_t)B * g.H * g.W, img = (size_t)g.H * g.W * g.C;
@@ -2672,7 +2686,7 @@ template <typename T> struct ConvLearner : tj_learner {
         }
 
         // ---- forward
-        for (int l = first_done ? 1 : 0; l < L; ++l) {
+        for (int l = fwd_done; l < L; ++l) {
             NLayer &y = lay[l];
             if (y.kind == TJ_LAYER_CONV2D) {
                 const tjconv::ConvGeom &g = y.g;
@@ -2979,6 +2993,24 @@ template <typename T> struct ConvLearner : tj_learner {
         return TJ_OK;
     }
 
+    // The first three layers of all passes; `keep`: the activations of s, which the backward pass needs, are written.
+    int run_tower(const TjConvFirstArgs &first, bool keep, hipStream_t st)
+    {
+        if constexpr (sizeof(T) == 2) {
+            const NLayer &y = lay[1], &z = lay[2];
+            TjConvTowerArgs ta;
+            ta.first = first;
+            if (!keep) ta.first.out = nullptr;
+            ta.OH2 = y.g.OH; ta.OW2 = y.g.OW; ta.s3 = z.g.s; ta.OH3 = z.g.OH; ta.OW3 = z.g.OW;
+            ta.W2_on = y.Wc_on; ta.W2_tg = y.Wc_tg; ta.b2_on = theta_on + y.b_off; ta.b2_tg = theta_tg + y.b_off;
+            ta.W3_on = z.Wc_on; ta.W3_tg = z.Wc_tg; ta.b3_on = theta_on + z.b_off; ta.b3_tg = theta_tg + z.b_off;
+            ta.act2 = keep ? act[2] : nullptr;
+            ta.out = act[3];
+            return tj_conv_tower(ta, st);
+        }
+        return TJ_ERR_SHAPE;
+    }
+
     // Slices of the last hidden layer's contraction when acting on n observations; 0: that layer, the head and the
     // action selection run as separate kernels.  The partial sums take the place of the layer's weight-gradient
     // slices, which live within a step.  Slices of at least four 64-element stages until the 256 x 64 tiles
@@ -3000,8 +3032,7 @@ template <typename T> struct ConvLearner : tj_learner {
         const int n = (int)n_;
         if (n < 1 || n > 2 * Bmax) return TJ_ERR_SHAPE;
         if (!d_obs || !d_action || !d_version || !(epsilon >= 0.f && epsilon <= 1.f)) return TJ_ERR_INVALID_ARG;
-        int rc;
-        bool first_done = false;
+        int rc, fwd_done = 0;
         if constexpr (sizeof(T) == 2) {
             if (first_fused && ((uintptr_t)d_obs & 3) == 0) {   // as in the step: straight from the u8 stacks
                 const tjconv::ConvGeom &g = lay[0].g;
@@ -3013,11 +3044,16 @@ template <typename T> struct ConvLearner : tj_learner {
                 fa.act0 = nullptr; fa.out = act[1];
                 fa.scale = 1.0f / 255.0f;
                 fa.rows = nullptr; fa.n_rows = 0; fa.planes = nullptr;
-                if ((rc = tj_conv_first(fa, st)) != TJ_OK) return rc;
-                first_done = true;
+                if (tower) {
+                    if ((rc = run_tower(fa, false, st)) != TJ_OK) return rc;
+                    fwd_done = 3;
+                } else {
+                    if ((rc = tj_conv_first(fa, st)) != TJ_OK) return rc;
+                    fwd_done = 1;
+                }
             }
         }
-        if (!first_done) {
+        if (fwd_done == 0) {
             const tjconv::ConvGeom &g = lay[0].g;
             const size_t px = (size_t)n * g.H * g.W;
             bool fast = false;
@@ -3038,7 +3074,7 @@ template <typename T> struct ConvLearner : tj_learner {
             if (hipGetLastError() != hipSuccess) return TJ_ERR_DEVICE;
         }
         const int act_split = act_head_split(n);
-        for (int l = first_done ? 1 : 0; l < L; ++l) {
+        for (int l = fwd_done; l < L; ++l) {
             NLayer &y = lay[l];
             TjGemmArgs<T> gm;
             memset(&gm, 0, sizeof(gm));

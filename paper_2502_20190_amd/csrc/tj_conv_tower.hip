@@ -16,6 +16,8 @@
 // consecutive rows.
 // While an image is in the second layer the next one, fetched into registers a layer ahead, is converted into the image buffer.
 #include "tj_conv_planes.h"
+#include <algorithm>
+#include <type_traits>
 
 namespace {
 
@@ -25,6 +27,7 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef __attribute__((address_space(3))) uint8_t *lds_ptr_t;
 
 constexpr int kThreads = 512, kWaves = 8;
 constexpr int K1 = 8, C1 = 32, K2 = 4, S2 = 2, C2 = 64, K3 = 3, C3 = 64;   // kernels, strides, output channels
@@ -36,7 +39,7 @@ constexpr int kW1Pitch = (4 * K1 * K1 + 8) * 2;           // ... between the fir
 constexpr size_t kLdsLimit = 160 * 1024;
 
 struct TowerPlan {
-    int w1, out1, out2, bias, total;   // byte offsets in LDS (the image is at 0)
+    int w1, bias, out1, out2, total;   // byte offsets in LDS (the image is at 0)
     int half1, pitch1;                       // columns per parity of the first layer's output, rows of LDS per image row
     uint32_t mg_ow1, mg_ow2, mg_ow3;         // ceil(2^32 / OW)
     int n_pass;
@@ -51,10 +54,11 @@ TowerPlan tower_plan(int H, int W, int OH1, int OW1, int OH2, int OW2, int OW3)
     p.pitch1 = S2 * p.half1;
     int at = H * W * 8;
     p.w1 = at; at += C1 * kW1Pitch;
+    p.bias = at; at += (C1 + C2 + C3) * 4;
     p.out1 = at; at += OH1 * p.pitch1 * kRow1;
     p.out2 = at; at += OH2 * OW2 * kRow2;
-    p.bias = at; at += (C1 + C2 + C3) * 4;
-    p.total = at;
+    const int staged = C2 * (4 * (kSteps3 > kSteps2 ? kSteps3 : kSteps2) + 1) * 16;   // whole instructions of a KiB
+    p.total = std::max(at, p.out1 + (staged + 1023) / 1024 * 1024);
     p.mg_ow1 = magic(OW1); p.mg_ow2 = magic(OW2); p.mg_ow3 = magic(OW3);
     p.n_pass = 0;
     return p;
@@ -73,22 +77,27 @@ void conv_tower(const TjConvTowerArgs a, const TowerPlan p)
     uint8_t *const img = lds, *const w1 = lds + p.w1, *const out1 = lds + p.out1, *const out2 = lds + p.out2;
     float *const bias = (float *)(lds + p.bias);
     const TjConvFirstArgs &f = a.first;
-    const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, h = lane >> 5, l16 = lane & 15, q4 = lane >> 4;
+    const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, q4 = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int ct = wave & 3, rh = wave >> 2;
     const int HW = f.H * f.W, W = f.W, OHW1 = f.OH * f.OW, OHW2 = a.OH2 * a.OW2, OHW3 = a.OH3 * a.OW3;
     const int begin = (int)((long)blockIdx.x * p.n_pass / gridDim.x), end = (int)((long)(blockIdx.x + 1) * p.n_pass / gridDim.x);
     if (begin >= end) return;
 
-    // ---- images.  Unit = 16 bytes of LDS = two pixels; the units of odd groups of 16 are exchanged in pairs, so that the 16
-    // patches an operand read touches (every other unit) fall on 16 distinct units of a 256-byte line
+    // ---- images.  Unit = 16 bytes of LDS = two pixels.  Even and odd units lie apart: with a stride of four pixels the operand
+    // reads of consecutive patches are consecutive units of one half, which one is fixed by the lane
     const int n_task = HW / 4;
     uint32_t px[kRounds][4];
-    auto fetch = [&](int pass) {
-        const int g = pass < 2 * f.B ? pass : pass - f.B;   // s, s', and s' again for the target network
-        const bool next = g >= f.B;
-        const PlaneOff off = plane_offsets(f.rows, f.planes, f.n_rows, next ? g - f.B : g, next, HW);
-        const uint8_t *src = next ? f.next_obs : f.obs;
+    // Image of a pass: s, s', and s' again for the target network.  Fetches go through the run in order, and the place of the next
+    // one is looked up right after the current one was issued, off the critical path.
+    auto image_of = [&](int pass) { return pass < 2 * f.B ? pass : pass - f.B; };
+    auto where = [&](int pass) {
+        const int g = image_of(pass);
+        return plane_offsets(f.rows, f.planes, f.n_rows, g < f.B ? g : g - f.B, g >= f.B, HW);
+    };
+    PlaneOff off = where(begin);
+    auto fetch = [&](int pass, int tid) {
+        const uint8_t *src = image_of(pass) >= f.B ? f.next_obs : f.obs;
 #pragma unroll
         for (int r = 0; r < kRounds; ++r) {
             const int t = tid + r * kThreads;
@@ -97,10 +106,10 @@ void conv_tower(const TjConvTowerArgs a, const TowerPlan p)
                 for (int c = 0; c < 4; ++c) px[r][c] = *(const uint32_t *)(src + off.o[c] + 4 * t);
             }
         }
+        if (pass + 1 < end) off = where(pass + 1);
     };
-    auto convert = [&]() {
-#pragma unroll
-        for (int r = 0; r < kRounds; ++r) {
+    auto convert = [&](int r, int tid) {
+        {
             const int t = tid + r * kThreads;
             if (t < n_task) {
                 u32x4 v[2];
@@ -112,36 +121,24 @@ void conv_tower(const TjConvTowerArgs a, const TowerPlan p)
                     v[q >> 1][2 * (q & 1)] = pack2(x[0], x[1]);
                     v[q >> 1][2 * (q & 1) + 1] = pack2(x[2], x[3]);
                 }
-                uint8_t *dst = img + (size_t)t * 32;
-                const int swap = (t >> 3) & 1;
-                *(u32x4 *)(dst + 16 * swap) = v[0];
-                *(u32x4 *)(dst + 16 * (swap ^ 1)) = v[1];
+                *(u32x4 *)(img + t * 16) = v[0];
+                *(u32x4 *)(img + HW * 4 + t * 16) = v[1];
             }
         }
     };
 
-    // ---- weights of one network
+    // ---- weights of one network.  The second and third layer's rows come through LDS (behind the first layer's weights, where
+    // nothing else lives between two runs): whole lines, each once, instead of 64-byte pieces of 16 rows per load, twice
     u32x4 w2[kSteps2], w3[kSteps3];
-    auto load_net = [&](int net) {
-        const tj_bf16 *W2 = (net ? a.W2_tg : a.W2_on) + (size_t)(16 * ct + l16) * (K2 * K2 * C1) + 8 * q4;
-        const tj_bf16 *W3 = (net ? a.W3_tg : a.W3_on) + (size_t)(16 * ct + l16) * (K3 * K3 * C2) + 8 * q4;
-#pragma unroll
-        for (int i = 0; i < kSteps2; ++i) w2[i] = *(const u32x4 *)(W2 + 32 * i);
-#pragma unroll
-        for (int i = 0; i < kSteps3; ++i) w3[i] = *(const u32x4 *)(W3 + 32 * i);
-        constexpr int VR = 4 * K1 * K1 / 8;   // 16-byte vectors per row of the first layer's weights
-        for (int v = tid; v < C1 * VR; v += kThreads)
-            *(u32x4 *)(w1 + (v / VR) * kW1Pitch + (v % VR) * 16) = *(const u32x4 *)((net ? f.W_tg : f.W_on) + (size_t)v * 8);
-        if (tid < C1) bias[tid] = (net ? f.b_tg : f.b_on)[tid];
-        else if (tid < C1 + C2) bias[tid] = (net ? a.b2_tg : a.b2_on)[tid - C1];
-        else if (tid < C1 + C2 + C3) bias[tid] = (net ? a.b3_tg : a.b3_on)[tid - C1 - C2];
+    auto stage = [&](const tj_bf16 *src, auto row_units) {   // 64 rows of row_units 16-byte units, one unit apart
+        constexpr int N = decltype(row_units)::value, total = C2 * (N + 1);
+        for (int i = wave; i < (total + 63) / 64; i += kWaves) {
+            const uint32_t u = min(64 * i + lane, total - 1), row = u / (N + 1), col = min(u % (N + 1), N - 1);
+            const uint32_t at = (uint32_t)(uintptr_t)(lds_ptr_t)(out1 + i * 1024);
+            asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(at), "v"(src + (row * N + col) * 8) : "memory");
+        }
     };
-
-    fetch(begin);
-    int net = begin >= 2 * f.B;
-    load_net(net);
-    convert();
-    if (begin + 1 < end) fetch(begin + 1);
+    auto landed = [&]() { asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory"); };
 
     // where this wave's patches start in the activations of the layer below (tiles past the last patch repeat it)
     int at2[kTiles2], at3[kTiles3];
@@ -160,44 +157,76 @@ void conv_tower(const TjConvTowerArgs a, const TowerPlan p)
         return out1 + (oh * p.pitch1 + (ow & 1) * p.half1 + (ow >> 1)) * kRow1;
     };
 
-    for (int pass = begin; pass < end; ++pass) {
-        if ((pass >= 2 * f.B) != net) {   // the run goes on with the target network
-            lds_sync();
-            net = 1;
-            load_net(net);
-        }
-        lds_sync();   // the image and the first layer's weights are in place; the last pass is out of out1
+    bool first_run = true;
+    for (int pass = begin; pass < end;) {   // runs under one network's weights: one, or two where the block's passes meet the target's
+    const int net = pass >= 2 * f.B, run_end = net ? end : min(end, 2 * f.B);
+    if (first_run) fetch(pass, tid);
+    lds_sync();   // nobody reads the last run's activations, weights and biases any more
+    stage(net ? a.W2_tg : a.W2_on, std::integral_constant<int, kSteps2 * 4>{});
+    {
+        constexpr int VR = 4 * K1 * K1 / 8;   // 16-byte vectors per row of the first layer's weights
+        for (int v = tid; v < C1 * VR; v += kThreads)
+            *(u32x4 *)(w1 + (v / VR) * kW1Pitch + (v % VR) * 16) = *(const u32x4 *)((net ? f.W_tg : f.W_on) + (size_t)v * 8);
+        if (tid < C1) bias[tid] = (net ? f.b_tg : f.b_on)[tid];
+        else if (tid < C1 + C2) bias[tid] = (net ? a.b2_tg : a.b2_on)[tid - C1];
+        else if (tid < C1 + C2 + C3) bias[tid] = (net ? a.b3_tg : a.b3_on)[tid - C1 - C2];
+    }
+    landed();
+#pragma unroll
+    for (int i = 0; i < kSteps2; ++i) w2[i] = *(const u32x4 *)(out1 + ((16 * ct + l16) * (kSteps2 * 4 + 1) + 4 * i + q4) * 16);
+    lds_sync();
+    stage(net ? a.W3_tg : a.W3_on, std::integral_constant<int, kSteps3 * 4>{});
+    if (first_run) {
+#pragma unroll
+        for (int r = 0; r < kRounds; ++r) convert(r, tid);
+        if (begin + 1 < end) fetch(begin + 1, tid);
+        first_run = false;
+    }
+    landed();
+#pragma unroll
+    for (int i = 0; i < kSteps3; ++i) w3[i] = *(const u32x4 *)(out1 + ((16 * ct + l16) * (kSteps3 * 4 + 1) + 4 * i + q4) * 16);
+
+    for (; pass < run_end; ++pass) {
+        lds_sync();   // the image is in place; the last pass is out of out1 (the first one: every weight has been read)
 
         // ---- first layer: image -> out1
         const int n_tile = (OHW1 + 31) / 32;
+        // opaque, so that addresses are not kept in registers (or rather in memory) from pass to pass
+        int tid1 = tid;
+        asm volatile("" : "+v"(tid1));
+        const int lane1 = tid1 & 31, h1 = (tid1 >> 5) & 1, p16 = tid1 & 15, c4 = 16 * ct + 4 * ((tid1 >> 4) & 3);
         for (int tile = wave; tile < n_tile; tile += 2 * kWaves) {   // two tiles share the weight reads
             const bool two = tile + kWaves < n_tile;
-            int unit[2];
+            const uint8_t *src[2];
             uint8_t *dst[2];
 #pragma unroll
             for (int t = 0; t < 2; ++t) {
-                const uint32_t m = min(32 * (tile + t * kWaves) + l32, OHW1 - 1), oh = __umulhi(m, p.mg_ow1), ow = m - oh * f.OW;
-                unit[t] = (int)(oh * f.s * W + ow * f.s) / 2 + h;
-                dst[t] = row1(m) + 8 * h;
+                const uint32_t m = min(32 * (tile + t * kWaves) + lane1, OHW1 - 1), oh = __umulhi(m, p.mg_ow1), ow = m - oh * f.OW;
+                src[t] = img + h1 * HW * 4 + (oh * f.s * W + ow * f.s) * 4;
+                dst[t] = row1(m) + 8 * h1;
             }
+            const uint8_t *const wsrc = w1 + lane1 * kW1Pitch + 16 * h1;
             f32x16 acc[2];
 #pragma unroll
             for (int t = 0; t < 2; ++t)
 #pragma unroll
                 for (int r = 0; r < 16; ++r) acc[t][r] = 0.f;
-#pragma unroll 2
-            for (int kh = 0; kh < K1; ++kh) {
+            // steps of 16 contraction values (4 pixels x 4 channels), the next one's operands on their way
+            u32x4 wv[2], pv[2][2];
+            auto read = [&](int n) {
+                wv[n & 1] = *(const u32x4 *)(wsrc + n * 32);
 #pragma unroll
-                for (int kw0 = 0; kw0 < K1; kw0 += 4) {   // 16 contraction values: 4 pixels x 4 channels
-                    const u32x4 wv = *(const u32x4 *)(w1 + l32 * kW1Pitch + ((kh * K1 + kw0) * 4 + 8 * h) * 2);
+                for (int t = 0; t < 2; ++t) pv[n & 1][t] = *(const u32x4 *)(src[t] + (n >> 1) * W * 4 + (n & 1) * 16);
+            };
+            read(0);
 #pragma unroll
-                    for (int t = 0; t < 2; ++t) {
-                        if (t == 1 && !two) continue;
-                        const int u = unit[t] + (kh * W + kw0) / 2;
-                        const u32x4 pv = *(const u32x4 *)(img + (u ^ ((u >> 4) & 1)) * 16);
-                        acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, wv), __builtin_bit_cast(bf16x8, pv),
-                                                                         acc[t], 0, 0, 0);
-                    }
+            for (int n = 0; n < 2 * K1; ++n) {
+                if (n + 1 < 2 * K1) read(n + 1);
+#pragma unroll
+                for (int t = 0; t < 2; ++t) {
+                    if (t == 1 && !two) continue;
+                    acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, wv[n & 1]), __builtin_bit_cast(bf16x8, pv[n & 1][t]),
+                                                                     acc[t], 0, 0, 0);
                 }
             }
             // acc[4q + e] = channel 8q + 4h + e of a patch; tiles past the last patch repeat it, into the same place
@@ -206,7 +235,7 @@ void conv_tower(const TjConvTowerArgs a, const TowerPlan p)
                 if (t == 1 && !two) continue;
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
-                    const f32x4 b = *(const f32x4 *)(bias + 8 * q + 4 * h);
+                    const f32x4 b = *(const f32x4 *)(bias + 8 * q + 4 * h1);
                     float x[4];
 #pragma unroll
                     for (int e = 0; e < 4; ++e) x[e] = fmaxf(acc[t][4 * q + e] + b[e], 0.f);
@@ -217,37 +246,41 @@ void conv_tower(const TjConvTowerArgs a, const TowerPlan p)
         lds_sync();
 
         // ---- second layer: out1 -> out2; the image buffer takes the next image
-        if (pass + 1 < end) {
-            convert();
-            if (pass + 2 < end) fetch(pass + 2);
-        }
         const bool keep = f.out && pass < f.B;
         if (keep) {
             tj_bf16 *dst = f.out + (size_t)pass * OHW1 * C1;
-            for (int v = tid; v < OHW1 * 4; v += kThreads) *(u32x4 *)(dst + (size_t)v * 8) = *(const u32x4 *)(row1(v >> 2) + (v & 3) * 16);
+            for (int v = tid1; v < OHW1 * 4; v += kThreads) *(u32x4 *)(dst + (size_t)v * 8) = *(const u32x4 *)(row1(v >> 2) + (v & 3) * 16);
         }
         f32x4 acc2[kTiles2];
 #pragma unroll
         for (int i = 0; i < kTiles2; ++i) acc2[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+        // a step is one tap of 32 channels; between the reads of four steps and their use a quarter of the next image is converted
+        static_assert(kRounds == K2, "a round of the image per row of the kernel");
 #pragma unroll
-        for (int n = 0; n < kSteps2; ++n) {   // a step is one tap of 32 channels
-            const int kh = n / K2, kw = n % K2;
-            const int off = (kh * p.pitch1 + (kw % S2) * p.half1 + kw / S2) * kRow1;
+        for (int kh = 0; kh < K2; ++kh) {
+            u32x4 x[K2][kTiles2];
 #pragma unroll
-            for (int i = 0; i < kTiles2; ++i) {
-                const u32x4 x = *(const u32x4 *)(out1 + at2[i] + off);
-                acc2[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, w2[n]), __builtin_bit_cast(bf16x8, x),
-                                                                  acc2[i], 0, 0, 0);
-            }
+            for (int kw = 0; kw < K2; ++kw)
+#pragma unroll
+                for (int i = 0; i < kTiles2; ++i)
+                    x[kw][i] = *(const u32x4 *)(out1 + at2[i] + (kh * p.pitch1 + (kw % S2) * p.half1 + kw / S2) * kRow1);
+            if (pass + 1 < end) convert(kh, tid1);
+#pragma unroll
+            for (int kw = 0; kw < K2; ++kw)
+#pragma unroll
+                for (int i = 0; i < kTiles2; ++i)
+                    acc2[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, w2[kh * K2 + kw]),
+                                                                      __builtin_bit_cast(bf16x8, x[kw][i]), acc2[i], 0, 0, 0);
         }
+        if (pass + 2 < end) fetch(pass + 2, tid1);
         {   // acc[r] = channel 16 ct + 4 q4 + r of patch l16
-            const f32x4 b = *(const f32x4 *)(bias + C1 + 16 * ct + 4 * q4);
+            const f32x4 b = *(const f32x4 *)(bias + C1 + c4);
 #pragma unroll
             for (int i = 0; i < kTiles2; ++i) {
-                const int m = (rh * kTiles2 + i) * 16 + l16;
+                const int m = (rh * kTiles2 + i) * 16 + p16;
                 const f32x4 s = acc2[i] + b;
                 if (m < OHW2)
-                    *(uint2 *)(out2 + m * kRow2 + (16 * ct + 4 * q4) * 2) =
+                    *(uint2 *)(out2 + m * kRow2 + c4 * 2) =
                         make_uint2(pack2(fmaxf(s[0], 0.f), fmaxf(s[1], 0.f)), pack2(fmaxf(s[2], 0.f), fmaxf(s[3], 0.f)));
             }
         }
@@ -256,7 +289,7 @@ void conv_tower(const TjConvTowerArgs a, const TowerPlan p)
         // ---- third layer: out2 -> out
         if (keep) {
             tj_bf16 *dst = a.act2 + (size_t)pass * OHW2 * C2;
-            for (int v = tid; v < OHW2 * 8; v += kThreads) *(u32x4 *)(dst + (size_t)v * 8) = *(const u32x4 *)(out2 + (v >> 3) * kRow2 + (v & 7) * 16);
+            for (int v = tid1; v < OHW2 * 8; v += kThreads) *(u32x4 *)(dst + (size_t)v * 8) = *(const u32x4 *)(out2 + (v >> 3) * kRow2 + (v & 7) * 16);
         }
         f32x4 acc3[kTiles3];
 #pragma unroll
@@ -272,15 +305,16 @@ void conv_tower(const TjConvTowerArgs a, const TowerPlan p)
                                                                   acc3[i], 0, 0, 0);
             }
         }
-        const f32x4 b3 = *(const f32x4 *)(bias + C1 + C2 + 16 * ct + 4 * q4);
+        const f32x4 b3 = *(const f32x4 *)(bias + C1 + C2 + c4);
 #pragma unroll
         for (int i = 0; i < kTiles3; ++i) {
-            const int m = (rh * kTiles3 + i) * 16 + l16;
+            const int m = (rh * kTiles3 + i) * 16 + p16;
             const f32x4 s = acc3[i] + b3;
             if (m < OHW3)
-                *(uint2 *)(a.out + ((size_t)pass * OHW3 + m) * C3 + 16 * ct + 4 * q4) =
+                *(uint2 *)(a.out + ((size_t)pass * OHW3 + m) * C3 + c4) =
                     make_uint2(pack2(fmaxf(s[0], 0.f), fmaxf(s[1], 0.f)), pack2(fmaxf(s[2], 0.f), fmaxf(s[3], 0.f)));
         }
+    }
     }
 }
 
@@ -291,7 +325,7 @@ void conv_tower(const TjConvTowerArgs a, const TowerPlan p)
 bool tj_conv_tower_fits(const TjConvShape *c)
 {
     const TjConvShape &x = c[0], &y = c[1], &z = c[2];
-    if (!tj_conv_first_fits(x.C, x.H, x.W, x.k, x.s, x.O) || x.k != K1) return false;
+    if (!tj_conv_first_fits(x.C, x.H, x.W, x.k, x.s, x.O) || x.k != K1 || x.s % 4 || x.W % 4) return false;
     if (y.C != C1 || y.O != C2 || y.k != K2 || y.s != S2 || z.C != C2 || z.O != C3 || z.k != K3) return false;
     if (x.H * x.W > 4 * kThreads * kRounds) return false;
     if (y.OH * y.OW > 2 * kTiles2 * 16 || z.OH * z.OW > 2 * kTiles3 * 16) return false;

@@ -36,10 +36,13 @@ constexpr int kTiles2 = 3, kTiles3 = 2; // tiles of 16 patches per wave (two wav
 constexpr int kSteps2 = K2 * K2 * C1 / 32, kSteps3 = K3 * K3 * C2 / 32;   // 32-value steps of a contraction
 constexpr int kRow1 = C1 * 2 + 16, kRow2 = C2 * 2 + 16;   // bytes between activation rows in LDS
 constexpr int kW1Pitch = (4 * K1 * K1 + 8) * 2;           // ... between the first layer's weight rows
+constexpr int kUnits2 = 4 * kSteps2, kUnits3 = 4 * kSteps3;               // 16-byte units of a weight row of the other two,
+constexpr int kGroup2 = 16 * (kUnits2 + 1) * 16, kGroup3 = 16 * (kUnits3 + 1) * 16;   // bytes of 16 such rows, a unit apart, in LDS
 constexpr size_t kLdsLimit = 160 * 1024;
 
 struct TowerPlan {
     int w1, bias, out1, out2, total;   // byte offsets in LDS (the image is at 0)
+    int groups_img;                          // groups of 16 rows of the third layer's weights that the image buffer holds
     int half1, pitch1;                       // columns per parity of the first layer's output, rows of LDS per image row
     uint32_t mg_ow1, mg_ow2, mg_ow3;         // ceil(2^32 / OW)
     int n_pass;
@@ -57,8 +60,10 @@ TowerPlan tower_plan(int H, int W, int OH1, int OW1, int OH2, int OW2, int OW3)
     p.bias = at; at += (C1 + C2 + C3) * 4;
     p.out1 = at; at += OH1 * p.pitch1 * kRow1;
     p.out2 = at; at += OH2 * OW2 * kRow2;
-    const int staged = C2 * (4 * (kSteps3 > kSteps2 ? kSteps3 : kSteps2) + 1) * 16;   // whole instructions of a KiB
-    p.total = std::max(at, p.out1 + (staged + 1023) / 1024 * 1024);
+    auto whole = [](int bytes) { return (bytes + 1023) / 1024 * 1024; };   // a load instruction fills a KiB
+    p.groups_img = 4;
+    while (whole(p.groups_img * kGroup3) > H * W * 8) --p.groups_img;
+    p.total = std::max(at, p.out1 + std::max(whole(4 * kGroup3), 4 * kGroup2 + whole((4 - p.groups_img) * kGroup3)));
     p.mg_ow1 = magic(OW1); p.mg_ow2 = magic(OW2); p.mg_ow3 = magic(OW3);
     p.n_pass = 0;
     return p;
@@ -127,17 +132,25 @@ void conv_tower(const TjConvTowerArgs a, const TowerPlan p)
         }
     };
 
-    // ---- weights of one network.  The second and third layer's rows come through LDS (behind the first layer's weights, where
-    // nothing else lives between two runs): whole lines, each once, instead of 64-byte pieces of 16 rows per load, twice
+    // ---- weights of one network.  The second and third layer's rows come through LDS, where between two runs nothing lives behind the
+    // first layer's weights, and in front of the first image nothing in the image buffer: whole lines, each once, instead of
+    // 64-byte pieces of 16 rows per load, twice.  A group is the 16 rows of one ct.
     u32x4 w2[kSteps2], w3[kSteps3];
-    auto stage = [&](const tj_bf16 *src, auto row_units) {   // 64 rows of row_units 16-byte units, one unit apart
-        constexpr int N = decltype(row_units)::value, total = C2 * (N + 1);
+    auto stage = [&](const tj_bf16 *src, auto row_units, int groups, uint8_t *dst, int lane) {
+        constexpr int N = decltype(row_units)::value;
+        const int total = groups * 16 * (N + 1);
         for (int i = wave; i < (total + 63) / 64; i += kWaves) {
             const uint32_t u = min(64 * i + lane, total - 1), row = u / (N + 1), col = min(u % (N + 1), N - 1);
-            const uint32_t at = (uint32_t)(uintptr_t)(lds_ptr_t)(out1 + i * 1024);
+            const uint32_t at = (uint32_t)(uintptr_t)(lds_ptr_t)(dst + i * 1024);
             asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(at), "v"(src + (row * N + col) * 8) : "memory");
         }
     };
+    auto take = [&](auto &w, const uint8_t *group, int units, int lane) {
+#pragma unroll
+        for (int i = 0; i < (int)(sizeof(w) / sizeof(w[0])); ++i) w[i] = *(const u32x4 *)(group + ((lane & 15) * (units + 1) + 4 * i + (lane >> 4)) * 16);
+    };
+    typedef std::integral_constant<int, kUnits2> Units2;
+    typedef std::integral_constant<int, kUnits3> Units3;
     auto landed = [&]() { asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory"); };
 
     // where this wave's patches start in the activations of the layer below (tiles past the last patch repeat it)
@@ -160,31 +173,40 @@ void conv_tower(const TjConvTowerArgs a, const TowerPlan p)
     bool first_run = true;
     for (int pass = begin; pass < end;) {   // runs under one network's weights: one, or two where the block's passes meet the target's
     const int net = pass >= 2 * f.B, run_end = net ? end : min(end, 2 * f.B);
-    if (first_run) fetch(pass, tid);
+    int tid0 = tid;   // opaque, as in the loop below
+    asm volatile("" : "+v"(tid0));
+    const int lane0 = tid0 & 63;
+    const tj_bf16 *const W2 = net ? a.W2_tg : a.W2_on, *const W3 = net ? a.W3_tg : a.W3_on;
+    if (first_run) {
+        stage(W3, Units3{}, p.groups_img, img, lane0);
+        stage(W3 + p.groups_img * 16 * kUnits3 * 8, Units3{}, 4 - p.groups_img, out1 + 4 * kGroup2, lane0);
+    }
     lds_sync();   // nobody reads the last run's activations, weights and biases any more
-    stage(net ? a.W2_tg : a.W2_on, std::integral_constant<int, kSteps2 * 4>{});
+    stage(W2, Units2{}, 4, out1, lane0);
     {
         constexpr int VR = 4 * K1 * K1 / 8;   // 16-byte vectors per row of the first layer's weights
-        for (int v = tid; v < C1 * VR; v += kThreads)
+        for (int v = tid0; v < C1 * VR; v += kThreads)
             *(u32x4 *)(w1 + (v / VR) * kW1Pitch + (v % VR) * 16) = *(const u32x4 *)((net ? f.W_tg : f.W_on) + (size_t)v * 8);
-        if (tid < C1) bias[tid] = (net ? f.b_tg : f.b_on)[tid];
-        else if (tid < C1 + C2) bias[tid] = (net ? a.b2_tg : a.b2_on)[tid - C1];
-        else if (tid < C1 + C2 + C3) bias[tid] = (net ? a.b3_tg : a.b3_on)[tid - C1 - C2];
+        if (tid0 < C1) bias[tid0] = (net ? f.b_tg : f.b_on)[tid0];
+        else if (tid0 < C1 + C2) bias[tid0] = (net ? a.b2_tg : a.b2_on)[tid0 - C1];
+        else if (tid0 < C1 + C2 + C3) bias[tid0] = (net ? a.b3_tg : a.b3_on)[tid0 - C1 - C2];
     }
+    if (first_run) fetch(pass, tid0);
     landed();
-#pragma unroll
-    for (int i = 0; i < kSteps2; ++i) w2[i] = *(const u32x4 *)(out1 + ((16 * ct + l16) * (kSteps2 * 4 + 1) + 4 * i + q4) * 16);
-    lds_sync();
-    stage(net ? a.W3_tg : a.W3_on, std::integral_constant<int, kSteps3 * 4>{});
+    take(w2, out1 + ct * kGroup2, kUnits2, lane0);
     if (first_run) {
+        take(w3, ct < p.groups_img ? img + ct * kGroup3 : out1 + 4 * kGroup2 + (ct - p.groups_img) * kGroup3, kUnits3, lane0);
+        lds_sync();
 #pragma unroll
-        for (int r = 0; r < kRounds; ++r) convert(r, tid);
-        if (begin + 1 < end) fetch(begin + 1, tid);
+        for (int r = 0; r < kRounds; ++r) convert(r, tid0);
+        if (begin + 1 < end) fetch(begin + 1, tid0);
         first_run = false;
+    } else {
+        lds_sync();
+        stage(W3, Units3{}, 4, out1, lane0);
+        landed();
+        take(w3, out1 + ct * kGroup3, kUnits3, lane0);
     }
-    landed();
-#pragma unroll
-    for (int i = 0; i < kSteps3; ++i) w3[i] = *(const u32x4 *)(out1 + ((16 * ct + l16) * (kSteps3 * 4 + 1) + 4 * i + q4) * 16);
 
     for (; pass < run_end; ++pass) {
         lds_sync();   // the image is in place; the last pass is out of out1 (the first one: every weight has been read)

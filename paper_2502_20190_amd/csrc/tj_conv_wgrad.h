@@ -111,7 +111,7 @@ __device__ __forceinline__ void body(const TjConvWgradArgs &a, const int njb, co
             const int m = min(m0 + browB[t], a.M - 1);   // rows past M meet zero rows of dZ
             dma16(a.act + tj_gather_origin(a.g, (uint32_t)m) + koffB, sB + u * SZB + (wave + 8 * t) * 1024);
         }
-        dma16(a.dZ + (size_t)(m0 + arow) * O + acol, sA + u * SZA + ia * 1024);
+        dma16(a.dZ + (size_t)(m0 + arow) * a.ldz + acol, sA + u * SZA + ia * 1024);
     };
 
     // ---- consumer roles: lane (n = lane % 32, h = lane / 32) of a wave feeds column n of the MFMA
@@ -194,14 +194,14 @@ __device__ __forceinline__ void body(const TjConvWgradArgs &a, const int njb, co
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
                 const int o = 32 * fi + 8 * (r >> 2) + 4 * h + (r & 3);
-                out[(size_t)o * a.K + kk] = acc[fi][r];
+                if (o < a.O_out) out[(size_t)o * a.K + kk] = acc[fi][r];
             }
     }
     if (do_bias) {
 #pragma unroll
         for (int fi = 0; fi < NFI; ++fi) {
             const float sum = bs[fi] + __shfl_xor(bs[fi], 32, 64);
-            if (h == 0) out[(size_t)O * a.K + 32 * fi + (lane & 31)] = sum;
+            if (h == 0 && 32 * fi + (lane & 31) < a.O_out) out[(size_t)a.O_out * a.K + 32 * fi + (lane & 31)] = sum;
         }
     }
 }
@@ -213,7 +213,8 @@ inline int plan(const TjConvWgradArgs &a, int &njb, unsigned &nblk)
     if ((a.O != 32 && a.O != 64) || a.M < 1 || a.K < 8 || a.K % 8) return TJ_ERR_SHAPE;
     if (a.n_split < 1 || a.m_chunk < kBM || a.m_chunk % kBM) return TJ_ERR_SHAPE;
     if ((size_t)a.m_chunk * a.n_split < (size_t)a.M) return TJ_ERR_SHAPE;
-    if (a.zstride < (size_t)a.O * a.K + a.O) return TJ_ERR_SHAPE;
+    if (a.ldz < a.O || a.ldz % 8 || a.O_out < 1 || a.O_out > a.O || ((uintptr_t)a.dZ & 15)) return TJ_ERR_SHAPE;
+    if (a.zstride < (size_t)a.O_out * a.K + a.O_out) return TJ_ERR_SHAPE;
     njb = (a.K + kBJ - 1) / kBJ;
     nblk = 8u * njb * ((a.n_split + 7) / 8);
     return TJ_OK;

@@ -99,6 +99,19 @@ inline bool tj_gather_make(TjGather &g, int C, int H, int W, int ksz, int stride
     return g.run % 8 == 0 && g.ow_stride % 8 == 0 && g.krow_stride % 8 == 0 && (H * W * C) % 8 == 0;
 }
 
+// The gather of plain rows: row m of `width` elements at m * ld (both multiples of 8).
+inline TjGather tj_gather_rows(int width, int ld)
+{
+    TjGather g;
+    g.on = 1;
+    g.ohw = g.ow = 2;                      // two rows are an image
+    g.mg_ohw = g.mg_ow = 0x80000000u;
+    g.img_stride = 2 * (int64_t)ld; g.oh_stride = 0; g.ow_stride = ld;
+    g.run = width; g.krow_stride = 0;
+    g.border = 0; g.in_h = 1; g.in_w = 2; g.chan = width;
+    return g;
+}
+
 // A run of output columns j that share one P operand (weights) and bias.
 template <typename T> struct TjGemmSeg {
     int j_begin, j_end;  // columns [j_begin, j_end) of D
@@ -162,6 +175,8 @@ struct TjConvWgradArgs;
 // A convolution's input gradient (gathered operand with a border, mapped output) and its weight gradient, which both
 // start from the same output gradient, as one launch.
 int tj_gemm_conv_backward(const TjGemmArgs<tj_bf16> &dgrad, const TjConvWgradArgs &wgrad, hipStream_t st);
+// tj_gemm_pair with a third member: another weight gradient that nothing waits for (a network's head beside its last hidden layer).
+int tj_gemm_pair_wgrad(const TjGemmArgs<tj_bf16> &a0, const TjGemmArgs<tj_bf16> &a1, const TjConvWgradArgs &w, hipStream_t st);
 // bf16 with gathered operands: the same for two convolutions of equal shape class
 int tj_gemm_gather_pair(const TjGemmArgs<tj_bf16> &a0, const TjGemmArgs<tj_bf16> &a1, hipStream_t st);
 // fp32: the same for two small problems (falls back to two launches otherwise)
@@ -169,9 +184,11 @@ int tj_gemm_pair_f32(const TjGemmArgs<float> &a0, const TjGemmArgs<float> &a1, h
 
 // Weight and bias gradient of a convolution layer from the channels-last output gradient and the
 // channels-last layer input (bf16, 32 or 64 output channels), split over the patch rows:
-//   part[z][o*K + k] = sum over slice z of dZ[m][o] * patch[m][k],  part[z][O*K + o] = sum dZ[m][o].
+//   part[z][o*K + k] = sum over slice z of dZ[m][o] * patch[m][k],  part[z][O_out*K + o] = sum dZ[m][o].
+// A linear layer of at most 64 outputs is one too: its input rows are the patches (tj_gather_rows).
 struct TjConvWgradArgs {
-    const tj_bf16 *dZ; int O;   // [M rounded up to 64][O]; rows past M must be zero
+    const tj_bf16 *dZ; int O;   // [M rounded up to 64][ldz], O = 32 or 64 columns of it; rows past M must be zero
+    int ldz, O_out;             // row pitch; results of the first O_out columns are kept, in rows of part
     const tj_bf16 *act;         // layer input [img][H][W][C]
     TjGather g;                 // patch geometry of this layer
     int M, K;                   // patches, patch length

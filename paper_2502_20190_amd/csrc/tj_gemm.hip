@@ -1484,6 +1484,25 @@ __global__ TJ_DLDS_ATTRS(NFJ, 64, 3) void gemm_bf16_dlds_gpair(const GemmPair p)
                                        (int)blockIdx.x - which * p.nblk0, lds);
 }
 
+// A hidden layer's weight and input gradient from row-major operands (blocks [0, n_gemm)) and the weight gradient of the layer
+// above it, a head of at most 32 outputs: 4 blocks per 256 rows, which as a launch of their own took 7 - 9 us.
+__global__ TJ_DLDS_ATTRS(2, 64, 3) void gemm_bf16_dlds_pair_wgrad(const GemmPair p, const int n_gemm, const TjConvWgradArgs w,
+                                                                  const int njb)
+{
+    constexpr int kGemm = dlds_lds_bytes<2, 64, 3>(), kWgrad = tjwgrad::lds_bytes<1>();
+    __shared__ __align__(1024) uint8_t lds[kGemm > kWgrad ? kGemm : kWgrad];
+    if ((int)blockIdx.x >= n_gemm) {
+        tjwgrad::body<1>(w, njb, (int)blockIdx.x - n_gemm, lds);
+        return;
+    }
+    const int which = (int)blockIdx.x >= p.nblk0 ? 1 : 0;
+    const int id = (int)blockIdx.x - which * p.nblk0;
+    if (p.a[which].trans == 1)   // block-uniform
+        dlds_body<2, 64, 3, true, 0, 1, kOutCf>(p.a[which], p.tiles_seg0[which], p.tm[which], id, lds);
+    else
+        dlds_body<2, 64, 3, false, 0, 2, kOutCi>(p.a[which], p.tiles_seg0[which], p.tm[which], id, lds);
+}
+
 // A convolution's input gradient (blocks [0, n0): gathered output gradient with a zero border, mapped output) and its
 // weight gradient.  Both only need the output gradient, and at small batches neither fills the chip (Nature-DQN network,
 // batch 256: 81 + 100 blocks of input gradients and 280 + 352 of weight gradients for 512 places), so they share a launch, the longer
@@ -1705,6 +1724,30 @@ int tj_gemm_pair(const TjGemmArgs<tj_bf16> &a0, const TjGemmArgs<tj_bf16> &a1, h
         gemm_bf16_dlds_pair<2, 64, 3, 2><<<n0 + n1, 512, 0, st>>>(p);
     else
         gemm_bf16_dlds_pair<2, 64, 3><<<n0 + n1, 512, 0, st>>>(p);
+    return hipGetLastError() == hipSuccess ? TJ_OK : TJ_ERR_DEVICE;
+}
+
+int tj_gemm_pair_wgrad(const TjGemmArgs<tj_bf16> &a0, const TjGemmArgs<tj_bf16> &a1, const TjConvWgradArgs &w, hipStream_t st)
+{
+    int tiles[2], rc;
+    if ((rc = check_args(a0, tiles)) != TJ_OK || (rc = check_args(a1, tiles)) != TJ_OK) return rc;
+    const bool hidden = a0.trans == 1 && trans_ok(a0) && a0.Cf && !a0.Ci && !a0.Cj &&
+                        a1.trans == 2 && trans_ok(a1) && a1.Ci && !a1.Cf && !a1.Cj;
+    GemmPair p;
+    int njb;
+    unsigned n2;
+    if ((rc = tjwgrad::plan(w, njb, n2)) != TJ_OK) return rc;
+    if (!hidden || w.O != 32) {   // no common kernel
+        if ((rc = tj_conv_wgrad(w, st)) != TJ_OK) return rc;
+        return tj_gemm_pair(a0, a1, st);
+    }
+    p.a[0] = a0; p.a[1] = a1;
+    const unsigned n0 = plan_dlds<2>(a0, p.tm[0], tiles);
+    p.tiles_seg0[0] = tiles[0];
+    const unsigned n1 = plan_dlds<2>(a1, p.tm[1], tiles);
+    p.tiles_seg0[1] = tiles[0];
+    p.nblk0 = (int)n0;
+    gemm_bf16_dlds_pair_wgrad<<<n0 + n1 + n2, 512, 0, st>>>(p, (int)(n0 + n1), w, njb);
     return hipGetLastError() == hipSuccess ? TJ_OK : TJ_ERR_DEVICE;
 }
 

@@ -235,12 +235,10 @@ inline uint32_t egreedy_threshold(float epsilon)
     return scaled <= 0.0 ? 0u : (scaled >= 16777216.0 ? 16777216u : (uint32_t)scaled);
 }
 
-// The end of an acting call whose last hidden layer was contracted in S slices (fp32 partial sums, [z][j][k]): one wave
-// per observation adds its row's slices in order, bias, ReLU, rounds to bf16, multiplies with the head and takes
-// the epsilon-greedy action.  Bound by latency: the row is S K / 64 floats a lane, the head's weights come from L2.
-// 256 observations, 3136-512-18: contraction, head GEMM and action kernel took 27 + 23 + 7 us on 16, 8 and 1 blocks;
-// a whole acting call 96 -> 48 us with this kernel and the first convolution from the u8 stacks (n = 32: 85 -> 44, 1024:
-// 155 -> 70).
+// The end of an acting call whose last hidden layer was contracted in S slices (fp32 partial sums, [z][j][k]): a block of two
+// waves per observation adds its row's slices in order, bias, ReLU, rounds to bf16, multiplies with the head and takes
+// the epsilon-greedy action.  Bound by latency, so every load of the row is in flight at once: 11.3 us with four slices in flight
+// and a wave per row, 5.5 us this way (256 observations, 3136-512-18, 12 slices).
 struct ActHeadArgs {
     const float *part; size_t zstride; int S, K;   // K a multiple of 4
     const float *b_hidden;
@@ -253,43 +251,67 @@ struct ActHeadArgs {
     float *q_out;                                  // optional [n][A]
 };
 
-template <int NA>   // at least A
-__global__ __launch_bounds__(256) void act_head(const ActHeadArgs a)
+// Four hidden units of a row (unit k, fp32 partial sums z at src + z * zstride, up to 16) as the layer's output: slices in order,
+// bias, ReLU, bf16.  Every load is in flight before the first is used.
+__device__ __forceinline__ uint2 hidden_from_slices(const float *src, size_t zstride, int S, const float *bias)
 {
-    const int lane = threadIdx.x & 63;
-    const uint32_t j = blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (j >= a.n) return;
+    float4 y[16];
+#pragma unroll
+    for (int z = 0; z < 16; ++z)
+        if (z < S) y[z] = *(const float4 *)(src + (size_t)z * zstride);
+    float4 x = y[0];
+#pragma unroll
+    for (int z = 1; z < 16; ++z)
+        if (z < S) { x.x += y[z].x; x.y += y[z].y; x.z += y[z].z; x.w += y[z].w; }
+    const float h[4] = {x.x + bias[0], x.y + bias[1], x.z + bias[2], x.w + bias[3]};
+    uint32_t b[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) b[e] = tj_f32_to_bf16(fmaxf(h[e], 0.f));
+    return make_uint2(b[0] | (b[1] << 16), b[2] | (b[3] << 16));
+}
+
+__device__ __forceinline__ float dot4(uint2 a, uint2 b, float s)
+{
+    s = fmaf(__uint_as_float(a.x << 16), __uint_as_float(b.x << 16), s);
+    s = fmaf(__uint_as_float(a.x & 0xFFFF0000u), __uint_as_float(b.x & 0xFFFF0000u), s);
+    s = fmaf(__uint_as_float(a.y << 16), __uint_as_float(b.y << 16), s);
+    return fmaf(__uint_as_float(a.y & 0xFFFF0000u), __uint_as_float(b.y & 0xFFFF0000u), s);
+}
+
+constexpr int kActWaves = 2;   // waves per observation: 512 hidden units at once
+
+template <int NA>   // at least A
+__global__ __launch_bounds__(64 * kActWaves) void act_head(const ActHeadArgs a)
+{
+    __shared__ float qs[kActWaves][NA];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const uint32_t j = blockIdx.x;
     float p[NA];
 #pragma unroll
     for (int o = 0; o < NA; ++o) p[o] = 0.f;
-    for (int k = 4 * lane; k < a.K; k += 256) {
-        uint2 w[NA];
+    for (int k = 4 * threadIdx.x; k < a.K; k += 256 * kActWaves) {
+        uint2 wv[NA];
 #pragma unroll
-        for (int o = 0; o < NA; ++o) w[o] = *(const uint2 *)(a.W + (size_t)min(o, a.A - 1) * a.ldw + k);
-        const float *src = a.part + (size_t)j * a.K + k;
-        float4 x = *(const float4 *)src;
-#pragma unroll 4
-        for (int z = 1; z < a.S; ++z) {
-            const float4 y = *(const float4 *)(src + (size_t)z * a.zstride);
-            x.x += y.x; x.y += y.y; x.z += y.z; x.w += y.w;
-        }
-        const float *b = a.b_hidden + k;
-        float h[4] = {x.x + b[0], x.y + b[1], x.z + b[2], x.w + b[3]};
+        for (int o = 0; o < NA; ++o) wv[o] = *(const uint2 *)(a.W + (size_t)min(o, a.A - 1) * a.ldw + k);
+        const uint2 h = hidden_from_slices(a.part + (size_t)j * a.K + k, a.zstride, a.S, a.b_hidden + k);
 #pragma unroll
-        for (int e = 0; e < 4; ++e) h[e] = tj_bf16_to_f32(tj_f32_to_bf16(fmaxf(h[e], 0.f)));
-#pragma unroll
-        for (int o = 0; o < NA; ++o) {
-            p[o] = fmaf(h[0], __uint_as_float(w[o].x << 16), p[o]);
-            p[o] = fmaf(h[1], __uint_as_float(w[o].x & 0xFFFF0000u), p[o]);
-            p[o] = fmaf(h[2], __uint_as_float(w[o].y << 16), p[o]);
-            p[o] = fmaf(h[3], __uint_as_float(w[o].y & 0xFFFF0000u), p[o]);
-        }
+        for (int o = 0; o < NA; ++o) p[o] = dot4(h, wv[o], p[o]);
     }
-    float q = -INFINITY;
+    float mine = 0.f;
 #pragma unroll
     for (int o = 0; o < NA; ++o) {
         const float s = wave_sum(p[o]);
-        if (o < a.A && lane == o) q = s + a.b_head[o];
+        if (lane == o) mine = s;
+    }
+    if (lane < NA) qs[w][lane] = mine;
+    __syncthreads();
+    if (w) return;
+    float q = -INFINITY;
+    if (lane < a.A) {
+        q = qs[0][lane];
+#pragma unroll
+        for (int v = 1; v < kActWaves; ++v) q += qs[v][lane];
+        q += a.b_head[lane];
     }
     const int best = wave_argmax(q);
     if (lane < a.A) {
@@ -305,11 +327,12 @@ __global__ __launch_bounds__(256) void act_head(const ActHeadArgs a)
 
 int launch_act_head(const ActHeadArgs &a, hipStream_t st)
 {
-    const unsigned grid = (a.n + 3) / 4;
-    if (a.A <= 8) act_head<8><<<grid, 256, 0, st>>>(a);
-    else if (a.A <= 16) act_head<16><<<grid, 256, 0, st>>>(a);
-    else if (a.A <= 24) act_head<24><<<grid, 256, 0, st>>>(a);
-    else act_head<32><<<grid, 256, 0, st>>>(a);
+    if (a.S > 16) return TJ_ERR_SHAPE;
+    const unsigned grid = a.n;
+    if (a.A <= 8) act_head<8><<<grid, 64 * kActWaves, 0, st>>>(a);
+    else if (a.A <= 16) act_head<16><<<grid, 64 * kActWaves, 0, st>>>(a);
+    else if (a.A <= 24) act_head<24><<<grid, 64 * kActWaves, 0, st>>>(a);
+    else act_head<32><<<grid, 64 * kActWaves, 0, st>>>(a);
     return hipGetLastError() == hipSuccess ? TJ_OK : TJ_ERR_DEVICE;
 }
 
@@ -561,6 +584,116 @@ __global__ __launch_bounds__(kHeadThreads) void head_td(const HeadTdArgs a)
             *(headu32x4 *)(a.dXT + (size_t)k * a.lddxt + j0 + 8 * vc) = *(const headu32x4 *)(tile + (k - k0) * kPitch + 8 * vc);
         }
     }
+}
+
+// The same from the partial sums of the layer below, for batches so small that its contraction is split (f_split): slices, bias and
+// ReLU of the three passes, the head, the TD step and the head's input gradient of one transition per block, two waves per
+// pass.  As sum_bias_relu and head_td (8 blocks at batch 256) these were two launches of 5.5 and 12.4 us.
+struct HeadSlicesArgs {
+    HeadTdArgs h;                          // X: rows of s are written here; no dZT, no dXT
+    const float *part; size_t zstride; int S;
+    const float *bias_on, *bias_tg;        // the hidden layer's
+    tj_bf16 *X;
+};
+constexpr int kHeadSliceUnits = 1024;      // widest hidden layer (NC = 2)
+
+template <int NA, int NC>   // at least A; at least K / 512
+__global__ __launch_bounds__(384) void head_td_slices(const HeadSlicesArgs s)
+{
+    const HeadTdArgs &a = s.h;
+    __shared__ float qs[3][2][NA];
+    __shared__ float s_g;
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, g = w >> 1, j = blockIdx.x;
+    const tj_bf16 *W = g == 2 ? a.W_tg : a.W_on;
+    const float *bias = g == 2 ? s.bias_tg : s.bias_on;
+    const int aj = min(max(a.action[j], 0), a.A - 1);
+    const float reward = a.reward[j], not_done = a.done[j] ? 0.f : 1.f;
+    float p[NA];
+#pragma unroll
+    for (int o = 0; o < NA; ++o) p[o] = 0.f;
+    uint2 x[NC], wa[NC];
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+        const int k = 512 * c + 4 * (threadIdx.x & 127);
+        x[c] = wa[c] = make_uint2(0u, 0u);
+        if (k >= a.K) continue;
+        uint2 wv[NA];
+#pragma unroll
+        for (int o = 0; o < NA; ++o) wv[o] = *(const uint2 *)(W + (size_t)min(o, a.A - 1) * a.ldw + k);
+        if (g == 0) wa[c] = *(const uint2 *)(W + (size_t)aj * a.ldw + k);
+        x[c] = hidden_from_slices(s.part + (size_t)(g * a.B + j) * a.K + k, s.zstride, s.S, bias + k);
+        if (g == 0) *(uint2 *)(s.X + (size_t)j * a.ldx + k) = x[c];
+#pragma unroll
+        for (int o = 0; o < NA; ++o) p[o] = dot4(x[c], wv[o], p[o]);
+    }
+    float mine = 0.f;
+#pragma unroll
+    for (int o = 0; o < NA; ++o) {
+        const float t = wave_sum(p[o]);
+        if (lane == o) mine = t;
+    }
+    if (lane < NA) qs[g][w & 1][lane] = mine;
+    __syncthreads();
+    if (w == 0) {
+        float q[3] = {0.f, 0.f, 0.f};
+        if (lane < a.A) {
+#pragma unroll
+            for (int r = 0; r < 3; ++r) {
+                q[r] = qs[r][0][lane] + qs[r][1][lane] + (r == 2 ? a.b_tg : a.b_on)[lane];
+                a.Q[((size_t)r * a.B + j) * a.ldq + lane] = q[r];
+            }
+        }
+        const int best = wave_argmax(lane < a.A ? q[1] : -INFINITY);
+        const float y = reward + a.gamma * not_done * __shfl(q[2], best, 64);
+        float grad;
+        const float loss = huber_and_grad(__shfl(q[0], aj, 64) - y, a.kappa, a.B, &grad);
+        if (lane == 0) {
+            a.astar[j] = best;
+            a.loss_part[j] = loss;
+            s_g = grad;
+        }
+    }
+    __syncthreads();
+    const uint32_t gz = tj_f32_to_bf16(s_g);
+    if (g == 0) {   // as in head_td: exact products, the ReLU mask, rounded to bf16
+        const float gf = tj_bf16_to_f32((tj_bf16)gz);
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+            const int k = 512 * c + 4 * threadIdx.x;
+            if (k >= a.K) continue;
+            const uint32_t xv[2] = {x[c].x, x[c].y}, wv[2] = {wa[c].x, wa[c].y};
+            uint32_t o[2];
+#pragma unroll
+            for (int e = 0; e < 2; ++e) {
+                const uint32_t lo = (int16_t)(xv[e] & 0xFFFFu) > 0 ? tj_f32_to_bf16(gf * __uint_as_float(wv[e] << 16)) : 0u;
+                const uint32_t hi = (int16_t)(xv[e] >> 16) > 0 ? tj_f32_to_bf16(gf * __uint_as_float(wv[e] & 0xFFFF0000u)) : 0u;
+                o[e] = lo | (hi << 16);
+            }
+            *(uint2 *)(a.dX + (size_t)j * a.lddx + k) = make_uint2(o[0], o[1]);
+        }
+    } else if (w == 2 && lane < (a.A + 7) / 8) {   // the row of dL/dQ, pad columns zero
+        headu32x4 o = {0u, 0u, 0u, 0u};
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            if (aj >> 1 == 4 * lane + u) o[u] = gz << (16 * (aj & 1));
+        *(headu32x4 *)(a.dZ + (size_t)j * a.lddz + 8 * lane) = o;
+    }
+}
+
+int launch_head_td_slices(const HeadSlicesArgs &s, hipStream_t st)
+{
+    const int A = s.h.A, K = s.h.K;
+    if (K > kHeadSliceUnits || K % 4 || s.S < 1 || s.S > 16 || A > 32) return TJ_ERR_SHAPE;
+    auto go = [&](auto na) {
+        constexpr int NA = decltype(na)::value;
+        if (K <= 512) head_td_slices<NA, 1><<<s.h.B, 384, 0, st>>>(s);
+        else head_td_slices<NA, 2><<<s.h.B, 384, 0, st>>>(s);
+    };
+    if (A <= 8) go(std::integral_constant<int, 8>{});
+    else if (A <= 16) go(std::integral_constant<int, 16>{});
+    else if (A <= 24) go(std::integral_constant<int, 24>{});
+    else go(std::integral_constant<int, 32>{});
+    return hipGetLastError() == hipSuccess ? TJ_OK : TJ_ERR_DEVICE;
 }
 
 // Streaming (nontemporal) 16-byte accesses: optimizer state and gradient slices are touched once
@@ -1445,6 +1578,10 @@ template <typename T> struct HeadTd {
     // where the fused kernel runs it also writes the gradient wrt the head's input (rows of s) and
     // its transpose, if dX is set
     T *dX; int lddx; T *dXT; int lddxt; int Kin;
+    // optional: the hidden layer below as partial sums; its rows of s are then written to X
+    const float *part = nullptr; size_t zstride = 0; int S = 0;
+    const float *bias_on = nullptr, *bias_tg = nullptr;
+    T *X_out = nullptr;
 };
 
 template <typename T> constexpr bool head_fused(int A) { return sizeof(T) == 2 && A <= 32; }
@@ -1471,6 +1608,10 @@ int run_head_td(tj_learner *self, const HeadTd<T> &h, const tj_minibatch *mb, fl
             a.dZ = h.dZ; a.lddz = h.lddz; a.dZT = h.dZT; a.lddzt = h.lddzt;
             a.astar = h.astar; a.loss_part = h.loss_part;
             a.dX = h.dX; a.lddx = h.lddx; a.dXT = h.dXT; a.lddxt = h.lddxt; a.Kin = h.Kin;
+            if (h.part) {
+                const HeadSlicesArgs sa = {a, h.part, h.zstride, h.S, h.bias_on, h.bias_tg, h.X_out};
+                return launch_head_td_slices(sa, st);
+            }
             head_td<<<td_blocks<T>(h.B, h.A), kHeadThreads, 0, st>>>(a);
             return hipGetLastError() == hipSuccess ? TJ_OK : TJ_ERR_DEVICE;
         }
@@ -2489,15 +2630,16 @@ template <typename T> struct ConvLearner : tj_learner {
                         y.f_part = (float *)a.take((size_t)y.f_split * 3 * B * y.O * 4);
                     }
                 }
-                y.XT = (T *)a.take((size_t)y.K * ldB * sizeof(T));
-                y.dZ = (T *)a.take(B * y.ldO * sizeof(T));
-                y.dZT = (T *)a.take((size_t)y.O * ldB * sizeof(T));
+                const bool rows = head_wgrad_rows(l);   // dZ rows padded (zero) to whole 64-row stages instead of the copies
+                y.XT = rows ? nullptr : (T *)a.take((size_t)y.K * ldB * sizeof(T));
+                y.dZ = (T *)a.take((B + (rows ? 64 : 0)) * y.ldO * sizeof(T));
+                y.dZT = rows ? nullptr : (T *)a.take((size_t)y.O * ldB * sizeof(T));
             }
         }
         act_bytes = a.off - act0;
         Qout = (float *)a.take(3 * B * ldA * 4);
         astar = (int32_t *)a.take(B * 4);
-        loss_part = (float *)a.take((size_t)((Bmax + kHeadRows - 1) / kHeadRows) * 4);
+        loss_part = (float *)a.take((size_t)Bmax * 4);
         stats_internal = (tj_step_stats *)a.take(sizeof(tj_step_stats));
         return a.off;
     }
@@ -2572,6 +2714,22 @@ template <typename T> struct ConvLearner : tj_learner {
         if (sizeof(T) != 2 || l < 1 || l >= L - 1 || lay[l].kind != TJ_LAYER_LINEAR) return false;
         return B % 32 == 0 && lay[l].K % 8 == 0 && lay[l].O % 8 == 0 && lay[l].K >= 256 && lay[l].O >= 128;
     }
+
+    // The head's weight gradient from row-major operands, as the convolutions' (a contraction over rows with 32 columns on one
+    // side): wherever the head's kernel writes the gradient of its input, so that a hidden layer lies below.
+    bool head_wgrad_rows(int l) const
+    {
+        return sizeof(T) == 2 && l == L - 1 && l >= 1 && lay[l - 1].kind == TJ_LAYER_LINEAR && lay[l].O <= 32 && lay[l].K % 8 == 0 &&
+               lay[l].ldK == lay[l].K && lay[l].ldO >= 32;
+    }
+    // The last hidden layer's split contraction is finished by the head's kernel: nobody needs its output transposed.
+    bool head_from_slices(int l, int B) const
+    {
+        return l == L - 2 && l >= 1 && lay[l].kind == TJ_LAYER_LINEAR && lay[l].f_split > 1 && lay[l].O <= kHeadSliceUnits &&
+               head_wgrad_rows(L - 1) && lin_wgrad_trans(l, B);
+    }
+    // Layer l's weight gradient reads a transposed copy of its input
+    bool wants_xt(int l, int B) const { return !lin_wgrad_trans(l, B) && !head_wgrad_rows(l); }
 
     // A linear layer's input gradient with the row-major weight copy as its first operand (transposing LDS
     // reads): bf16, a contraction over whole 32-row stages of the weight matrix, and a batch whose weight gradient takes
@@ -2737,7 +2895,7 @@ template <typename T> struct ConvLearner : tj_learner {
                     for (int net = 0; net < 2; ++net)
                         if ((rc = tj_gemm<T>(both[net], st)) != TJ_OK) return rc;
             } else {
-                if (l > 0 && lay[l - 1].kind == TJ_LAYER_CONV2D && !lin_wgrad_trans(l, B))   // transposed input of the s rows
+                if (l > 0 && lay[l - 1].kind == TJ_LAYER_CONV2D && wants_xt(l, B))   // transposed input of the s rows
                     if ((rc = transpose(act[l], y.ldK, y.XT, ldB, B, y.K, st)) != TJ_OK) return rc;
                 TjGemmArgs<T> gm;
                 memset(&gm, 0, sizeof(gm));
@@ -2753,20 +2911,23 @@ template <typename T> struct ConvLearner : tj_learner {
                     gm.n_split = y.f_split; gm.k_chunk = y.f_chunk;
                     gm.Cf = y.f_part; gm.ldcf = y.O; gm.cf_zstride = (size_t)3 * B * y.O;
                     if ((rc = tj_gemm<T>(gm, st)) != TJ_OK) return rc;
+                    if (head_from_slices(l, B)) continue;
                     const size_t nvec = (size_t)3 * B * (y.O / 4);
                     sum_bias_relu<T><<<grid1(nvec), 256, 0, st>>>(y.f_part, gm.cf_zstride, y.f_split, 3 * B, y.O,
                                                                theta_on + y.b_off, theta_tg + y.b_off, 2 * B,
-                                                               act[l + 1], lay[l + 1].ldK, lay[l + 1].XT, ldB, B);
+                                                               act[l + 1], lay[l + 1].ldK, lay[l + 1].XT, ldB,
+                                                               wants_xt(l + 1, B) ? B : 0);
                     if (hipGetLastError() != hipSuccess) return TJ_ERR_DEVICE;
                     continue;
                 }
                 gm.relu = 1;
                 gm.Ci = act[l + 1]; gm.ldci = lay[l + 1].ldK;
-                if (!lin_wgrad_trans(l + 1, B)) { gm.Cj = lay[l + 1].XT; gm.ldcj = ldB; gm.cj_jmax = B; }
+                if (wants_xt(l + 1, B)) { gm.Cj = lay[l + 1].XT; gm.ldcj = ldB; gm.cj_jmax = B; }
                 if ((rc = tj_gemm<T>(gm, st)) != TJ_OK) return rc;
             }
         }
         bool head_dx_done = false;
+        int n_loss = td_blocks<T>(B, A);
         {   // head layer and TD step
             NLayer &y = lay[L - 1];
             HeadTd<T> h;
@@ -2784,6 +2945,13 @@ template <typename T> struct ConvLearner : tj_learner {
                 h.dX = lay[L - 2].dZ; h.lddx = y.ldK;
                 if (!lin_wgrad_trans(L - 2, B)) { h.dXT = lay[L - 2].dZT; h.lddxt = ldB; }
             }
+            if (head_from_slices(L - 2, B)) {
+                const NLayer &b = lay[L - 2];
+                h.part = b.f_part; h.zstride = (size_t)3 * B * b.O; h.S = b.f_split;
+                h.bias_on = theta_on + b.b_off; h.bias_tg = theta_tg + b.b_off;
+                h.X_out = act[L - 1];
+                n_loss = B;
+            }
             if ((rc = run_head_td<T>(this, h, mb, d.gamma, d.huber_delta, st)) != TJ_OK) return rc;
         }
         if ((rc = mark(2, st)) != TJ_OK) return rc;
@@ -2799,6 +2967,7 @@ template <typename T> struct ConvLearner : tj_learner {
             jobs.begin[q] = y.w_off; jobs.n[q] = (size_t)y.O * y.K + y.O;
             jobs.block_begin[q + 1] = jobs.block_begin[q] + slice_blocks(jobs.n[q], n_part);
         };
+        TjConvWgradArgs head_w;
         for (int l = L - 1; l >= 0; --l) {
             NLayer &y = lay[l];
             const bool conv = y.kind == TJ_LAYER_CONV2D;
@@ -2829,7 +2998,7 @@ template <typename T> struct ConvLearner : tj_learner {
                     wgrad_done = true;
                 }
                 if (!wgrad_done && conv && y.implicit) {   // straight from dZ and the layer input
-                    wa.dZ = y.dZ; wa.O = y.O; wa.act = act[l]; wa.g = y.gth;
+                    wa.dZ = y.dZ; wa.O = wa.O_out = wa.ldz = y.O; wa.act = act[l]; wa.g = y.gth;
                     wa.M = (int)Ms; wa.K = y.K;
                     wa.part = y.part; wa.zstride = y.part_stride;
                     wa.n_split = y.n_split;
@@ -2842,6 +3011,18 @@ template <typename T> struct ConvLearner : tj_learner {
             }
             TjGemmArgs<T> gw;            // a linear layer's weight gradient waits for its input gradient:
             bool gw_pending = false;     // the two share one launch (bf16)
+            if constexpr (sizeof(T) == 2) {
+                if (head_wgrad_rows(l)) {   // shares the launch of the layer below
+                    head_w.dZ = y.dZ; head_w.O = 32; head_w.ldz = y.ldO; head_w.O_out = y.O;
+                    head_w.act = act[l]; head_w.g = tj_gather_rows(y.K, y.ldK);
+                    head_w.M = B; head_w.K = y.K;
+                    head_w.part = y.part; head_w.zstride = y.part_stride;
+                    head_w.n_split = y.n_split;
+                    head_w.m_chunk = round_up((B + y.n_split - 1) / y.n_split, 64);
+                    add_slices(y, y.n_split);
+                    wgrad_done = true;
+                }
+            }
             if (!wgrad_done) {   // dW[o][k] = sum_m dZ[m][o] X[m][k] (k in kernel order), db[o] = sum_m dZ[m][o]
                 TjGemmArgs<T> &gm = gw;
                 memset(&gm, 0, sizeof(gm));
@@ -2894,7 +3075,8 @@ template <typename T> struct ConvLearner : tj_learner {
                 }
                 if constexpr (sizeof(T) == 2) {
                     if (gw_pending) {
-                        if ((rc = tj_gemm_pair(gw, gm, st)) != TJ_OK) return rc;
+                        rc = l == L - 2 && head_wgrad_rows(L - 1) ? tj_gemm_pair_wgrad(gw, gm, head_w, st) : tj_gemm_pair(gw, gm, st);
+                        if (rc != TJ_OK) return rc;
                         gw_pending = false;
                     } else if ((rc = tj_gemm<T>(gm, st)) != TJ_OK) {
                         return rc;
@@ -2969,7 +3151,7 @@ template <typename T> struct ConvLearner : tj_learner {
             tab.dstT[tab.n] = nullptr; tab.C[tab.n] = 0; tab.ldT[tab.n] = 0;
             tab.dst[tab.n++] = lay[l].Wc_on;
         }
-        const LossFinal lf = {loss_part, td_blocks<T>(B, A), B, (uint32_t)t, d_stats, stats_internal};
+        const LossFinal lf = {loss_part, n_loss, B, (uint32_t)t, d_stats, stats_internal};
         DgradEmit &dg = ad.dg;   // the convolutions' input-gradient weights follow their master weights in the same kernel
         dg.n = 0;
         if constexpr (sizeof(T) == 2) {

@@ -154,6 +154,11 @@ template <typename T> struct TjGemmArgs {
 
 template <typename T> int tj_gemm(const TjGemmArgs<T> &a, hipStream_t st);
 
+// Large hidden layers (tj_gemm_wide.hip): forward pass, and weight gradient with input gradient.  False if the call is left to the
+// kernels of tj_gemm.hip; else *rc is its result.  Arguments as checked there.
+bool tj_gemm_wide_forward(const TjGemmArgs<tj_bf16> &a, hipStream_t st, int *rc);
+bool tj_gemm_wide_pair(const TjGemmArgs<tj_bf16> &w, const TjGemmArgs<tj_bf16> &x, hipStream_t st, int *rc);
+
 // Two independent bf16 GEMMs as one launch where both fit the direct-to-LDS kernel (they share
 // one ramp-up and tail); otherwise the same as two tj_gemm calls.
 int tj_gemm_pair(const TjGemmArgs<tj_bf16> &a0, const TjGemmArgs<tj_bf16> &a1, hipStream_t st);

@@ -1610,6 +1610,8 @@ int launch_bf16(const TjGemmArgs<tj_bf16> &a, const int tiles[2], hipStream_t st
         return jtot > 64 ? launch_dlds<2, 64, 3, 1>(a, st) : launch_dlds<1, 64, 3, 1>(a, st);
     }
     if (a.out_map.on) return TJ_ERR_SHAPE;
+    int rc;
+    if (tj_gemm_wide_forward(a, st, &rc)) return rc;
     if (uses_dlds(a)) {
         // pick the j extent of the tile (128 / 192 / 256) that needs the fewest rounds of 256 blocks,
         // weighted by the tile's work; ties go to the larger tile
@@ -1677,6 +1679,7 @@ int tj_gemm_pair(const TjGemmArgs<tj_bf16> &a0, const TjGemmArgs<tj_bf16> &a1, h
 {
     int tiles[2], rc;
     if ((rc = check_args(a0, tiles)) != TJ_OK || (rc = check_args(a1, tiles)) != TJ_OK) return rc;
+    if (tj_gemm_wide_pair(a0, a1, st, &rc)) return rc;
     auto fits = [](const TjGemmArgs<tj_bf16> &a) { return a.trans ? trans_ok(a) : uses_dlds(a); };
     if (a0.gather.on || a1.gather.on || !fits(a0) || !fits(a1)) {   // no common kernel: one after the other
         if ((rc = tj_gemm<tj_bf16>(a0, st)) != TJ_OK) return rc;

@@ -147,9 +147,11 @@ template <typename T> struct TjGemmArgs {
                          // the s x s pixel block it owns.  The only output of such a launch; no bias / ReLU.
     const T *mask_cj;    // optional with out_map: the result is zeroed where mask_cj[same offset] <= 0
     int trans;           // bf16 only.  1: both operands are stored contraction-major, P as [k][i] (row pitch ldp)
-                         // and Q as [k][j] (row pitch ldq); rows k in [0, K) must exist (K a multiple of 32,
-                         // like every split chunk), I and the columns multiples of 8, one segment, no q_shift.
-                         // 2: only P is stored that way, Q as usual (no qsum)
+                         // and Q as [k][j] (row pitch ldq); one segment, no q_shift.  Rows of Q up to K (a multiple of 32,
+                         // like every split chunk) and columns of both up to whole 16-byte vectors must exist; Q's rows from
+                         // k_valid on must be zero, P's are not read (row k_valid - 1 stands for them, whatever it holds).
+                         // 2: only P is stored that way, Q as usual (no qsum, no k_valid: rows up to K exist)
+    int k_valid;         // trans == 1: contraction rows there are; 0: K
 };
 
 template <typename T> int tj_gemm(const TjGemmArgs<T> &a, hipStream_t st);

@@ -984,6 +984,8 @@ __device__ __forceinline__ void dlds_body(const TjGemmArgs<tj_bf16> &a_in, const
     const int k_begin = z * a.k_chunk;
     const int k_end = min(a.K, k_begin + a.k_chunk);
     const int n_stage = k_end > k_begin ? (k_end - k_begin) / KE : 0;
+    const int k_valid = TRANS == 1 && a.k_valid ? a.k_valid : a.K;
+    (void)k_valid;
 
     // This wave's load instructions per stage: P chunks wave + 8 t (t < LP) and Q chunks wave + 8 t
     // (t < LQ); a chunk = RPI rows.  Q chunk numbers wrap around CHQ: a chunk past the end repeats an
@@ -1003,7 +1005,7 @@ __device__ __forceinline__ void dlds_body(const TjGemmArgs<tj_bf16> &a_in, const
 #pragma unroll
         for (int t = 0; t < LP; ++t) {
             const int row = 2 * (wave + 8 * t) + (lane >> 5);
-            const int col = min(i0 + 8 * ((lane & 31) ^ ((row & 3) << 2)), a.I - 8);
+            const int col = min(i0 + 8 * ((lane & 31) ^ ((row & 3) << 2)), ((a.I + 7) & ~7) - 8);
             gsrcP[t] = seg.P + (size_t)(k_begin + row) * a.ldp + col;
         }
     } else {
@@ -1028,7 +1030,7 @@ __device__ __forceinline__ void dlds_body(const TjGemmArgs<tj_bf16> &a_in, const
     if constexpr (TRANS == 1) {
         // Q: instruction c = wave fills rows 4c .. 4c+3 (256 bytes each)
         const int rowq = 4 * wave + (lane >> 4);
-        const int colq = min(j0 + 8 * ((lane & 15) ^ ((rowq & 3) << 2)), j_end - 8);
+        const int colq = min(j0 + 8 * ((lane & 15) ^ ((rowq & 3) << 2)), ((j_end + 7) & ~7) - 8);
         gsrcQ[0] = a.Q + (size_t)(k_begin + rowq) * a.ldq + colq;
     } else {
 #pragma unroll
@@ -1070,8 +1072,16 @@ __device__ __forceinline__ void dlds_body(const TjGemmArgs<tj_bf16> &a_in, const
             }
         } else {
             const size_t offP = GATHER ? (size_t)tj_gather_koff(a.gather, kposP + s * KE) : s * stepP;
+            if (TRANS == 1 && k_begin + (s + 1) * KE > k_valid) {   // the stage the batch ends in: no rows past the last one
 #pragma unroll
-            for (int t = 0; t < LP; ++t) dma16(gsrcP[t] + offP, sA + (wave + 8 * t) * 1024);
+                for (int t = 0; t < LP; ++t) {
+                    const int past = max(k_begin + s * KE + 2 * (wave + 8 * t) + (lane >> 5) - (k_valid - 1), 0);
+                    dma16(gsrcP[t] + offP - (size_t)past * a.ldp, sA + (wave + 8 * t) * 1024);
+                }
+            } else {
+#pragma unroll
+                for (int t = 0; t < LP; ++t) dma16(gsrcP[t] + offP, sA + (wave + 8 * t) * 1024);
+            }
         }
 #pragma unroll
         for (int t = 0; t < LQ; ++t) {
@@ -1576,11 +1586,12 @@ bool uses_dlds(const TjGemmArgs<tj_bf16> &a)
 bool trans_ok(const TjGemmArgs<tj_bf16> &a)
 {
     if (a.trans < 1 || a.trans > 2 || a.gather.on || a.out_map.on || a.n_seg != 1) return false;
-    if (a.I < 8 || a.I % 8) return false;
+    auto vectors = [](int n) { return (n + 7) & ~7; };   // columns are loaded as whole 16-byte vectors
+    if (vectors(a.I) > a.ldp) return false;
     if (a.trans == 1) {
-        const int cols = a.seg[0].j_end - a.seg[0].j_begin;
-        if (a.seg[0].q_shift != 0 || cols < 8 || cols % 8 || a.seg[0].j_begin % 8) return false;
-    } else if (a.qsum) {
+        if (a.seg[0].q_shift != 0 || a.seg[0].j_begin % 8 || vectors(a.seg[0].j_end) > a.ldq) return false;
+        if (a.k_valid < 0 || a.k_valid > a.K) return false;
+    } else if (a.qsum || a.k_valid) {
         return false;
     }
     return a.K % 32 == 0 && (a.n_split == 1 || a.k_chunk % 32 == 0);

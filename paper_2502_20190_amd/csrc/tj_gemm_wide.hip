@@ -68,7 +68,7 @@ __device__ __forceinline__ void tile(const TjGemmArgs<tj_bf16> &a, const TjGemmS
     auto offset = [&](int c, bool trans, int ld, int left) -> uint32_t {   // instruction c of a stage; `left` rows or columns exist
         if (trans) {
             const int row = 4 * (c & 15) + (lane >> 4), v = (lane & 15) ^ ((row & 3) << 2) ^ ((row >> 2) & 2);
-            return (uint32_t)(row * ld + min((c >> 4) * 128 + v * 8, left - 8)) * 2;
+            return (uint32_t)(row * ld + min((c >> 4) * 128 + v * 8, ((left + 7) & ~7) - 8)) * 2;
         }
         const int row = 8 * c + (lane >> 3), v = (lane & 7) ^ ((row >> 1) & 7);
         return (uint32_t)(min(row, left - 1) * ld + v * 8) * 2;
@@ -85,8 +85,12 @@ __device__ __forceinline__ void tile(const TjGemmArgs<tj_bf16> &a, const TjGemmS
         asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(at), "v"(off), "s"(base) : "memory");
     };
     const uint32_t l0 = (uint32_t)(uintptr_t)(lds_u8)lds + wave * 1024;
+    const int k_valid = KIND == kWeightGrad && a.k_valid ? a.k_valid : a.K;
     auto issue = [&](int s, int t) {   // part t (of four) of stage s
-        dma(bP + (size_t)s * stP, oA[t], l0 + (s & 1) * kBufA + t * 8192);
+        uint32_t off = oA[t];
+        if (KIND == kWeightGrad && k_begin + (s + 1) * 64 > k_valid)   // the stage the batch ends in: no rows past the last one
+            off -= max(k_begin + s * 64 + 4 * ((wave + 8 * t) & 15) + (lane >> 4) - (k_valid - 1), 0) * (uint32_t)a.ldp * 2;
+        dma(bP + (size_t)s * stP, off, l0 + (s & 1) * kBufA + t * 8192);
         if (t < LB) dma(bQ + (size_t)s * stQ, oB[t < LB ? t : 0], l0 + 2 * kBufA + (s & 1) * kBufB + t * 8192);
     };
 
@@ -225,17 +229,26 @@ __device__ __forceinline__ void tile(const TjGemmArgs<tj_bf16> &a, const TjGemmS
         constexpr int W = FI * 16, pitch = W * 4 + 16, V = W / 4, RPI = 64 / V;   // floats and bytes of a row; rows per store
         uint8_t *scr = lds + wave * (16 * pitch);
         float *const out = a.Cf + (size_t)z * a.cf_zstride;
+        const bool vectors = (((uintptr_t)out | (uintptr_t)(a.ldcf * 4)) & 15) == 0 && a.I % 4 == 0;
 #pragma unroll
         for (int g = 0; g < FJ; ++g) {
             wave_sync();
 #pragma unroll
             for (int f = 0; f < FI; ++f) *(f32x4 *)(scr + l16 * pitch + (f * 16 + q4 * 4) * 4) = acc[f][g];
             wave_sync();
+            if (vectors) {
 #pragma unroll
-            for (int t = 0; t < 16 / RPI; ++t) {
-                const int r = t * RPI + lane / V, c = lane % V * 4, j = jb + 16 * g + r, i = ib + c;
-                const f32x4 v = *(const f32x4 *)(scr + r * pitch + c * 4);
-                if (j < j_end && i < a.I) *(f32x4 *)(out + (size_t)j * a.ldcf + i) = v;
+                for (int t = 0; t < 16 / RPI; ++t) {
+                    const int r = t * RPI + lane / V, c = lane % V * 4, j = jb + 16 * g + r, i = ib + c;
+                    const f32x4 v = *(const f32x4 *)(scr + r * pitch + c * 4);
+                    if (j < j_end && i < a.I) *(f32x4 *)(out + (size_t)j * a.ldcf + i) = v;
+                }
+            } else {   // rows of any length and place: 64 neighbouring elements per store
+                for (int r = 0; r < 16; ++r)
+                    for (int c = lane; c < W; c += 64) {
+                        const int j = jb + 16 * g + r, i = ib + c;
+                        if (j < j_end && i < a.I) out[(size_t)j * a.ldcf + i] = *(const float *)(scr + r * pitch + c * 4);
+                    }
             }
         }
         return;
@@ -248,7 +261,7 @@ __device__ __forceinline__ void tile(const TjGemmArgs<tj_bf16> &a, const TjGemmS
         if constexpr (KIND == kInputGrad) {
 #pragma unroll
             for (int t = 0; t < 16 / RPI; ++t) {
-                const int j = min(jb + 16 * g + t * RPI + lane / V, j_end - 1), i = min(ib + lane % V * 8, a.I - 8);
+                const int j = min(jb + 16 * g + t * RPI + lane / V, j_end - 1), i = min(ib + lane % V * 8, ((a.I + 7) & ~7) - 8);
                 mask[t] = *(const u32x4 *)(a.mask + (size_t)j * a.ldmask + i);
             }
         }
@@ -259,7 +272,7 @@ __device__ __forceinline__ void tile(const TjGemmArgs<tj_bf16> &a, const TjGemmS
             if constexpr (KIND == kForward) {
                 const f32x4 b = *(const f32x4 *)(bias + wi * FI * 16 + f * 16 + q4 * 4);
 #pragma unroll
-                for (int e = 0; e < 4; ++e) v[e] = fmaxf(v[e] + b[e], 0.f);
+                for (int e = 0; e < 4; ++e) v[e] = ib + f * 16 + q4 * 4 + e < a.I ? fmaxf(v[e] + b[e], 0.f) : 0.f;   // pads stay zero
             }
             *(uint2 *)(scr + l16 * pitch + (f * 16 + q4 * 4) * 2) = make_uint2(pack2(v[0], v[1]), pack2(v[2], v[3]));
         }
@@ -345,13 +358,15 @@ int up_div(int x, int y) { return (x + y - 1) / y; }
 
 bool aligned16(const void *p, size_t ld_bytes) { return (((uintptr_t)p | ld_bytes) & 15) == 0; }
 
+int vectors8(int n) { return (n + 7) & ~7; }   // columns of whole 16-byte vectors
+
 }  // namespace
 
 bool tj_gemm_wide_forward(const TjGemmArgs<tj_bf16> &a, hipStream_t st, int *rc)
 {
     if (a.trans || a.gather.on || a.out_map.on || a.n_split != 1 || a.qsum || a.bias_j || a.mask || a.Cj || a.Cf || !a.Ci || !a.relu)
         return false;
-    if (a.K % 64 || a.K < 64 || a.I % 8 || a.I < kTile) return false;
+    if (a.K % 64 || a.K < 64 || a.I < kTile || a.ldci < vectors8(a.I)) return false;
     if (!aligned16(a.Q, a.ldq * 2) || !aligned16(a.Ci, a.ldci * 2)) return false;
     WidePlan p;
     p.tiles_i = up_div(a.I, kTile);
@@ -381,9 +396,12 @@ bool tj_gemm_wide_pair(const TjGemmArgs<tj_bf16> &w, const TjGemmArgs<tj_bf16> &
     if (!w.Cf || w.Ci || w.Cj || w.mask || w.relu || w.bias_j || w.seg[0].bias || !w.qsum || w.seg[0].q_shift) return false;
     if (!x.Ci || x.Cf || x.Cj || !x.mask || x.relu || x.bias_j || x.seg[0].bias || x.qsum || x.n_split != 1 || x.seg[0].q_shift) return false;
     const int wj = w.seg[0].j_end - w.seg[0].j_begin, xj = x.seg[0].j_end - x.seg[0].j_begin;
-    if (w.K % 64 || w.k_chunk % 64 || w.k_chunk < 64 || w.I % 8 || wj % 8 || w.I < 8 || wj < 8 || w.seg[0].j_begin % 8) return false;
-    if ((w.n_split - 1) * w.k_chunk >= w.K || x.K % 64 || x.K < 64 || x.I % 8 || x.I < 8) return false;
-    if (!aligned16(w.seg[0].P, w.ldp * 2) || !aligned16(w.Q, w.ldq * 2) || !aligned16(w.Cf, w.ldcf * 4 | w.cf_zstride * 4)) return false;
+    const int valid = w.k_valid ? w.k_valid : w.K;
+    if (w.K % 64 || w.k_chunk % 64 || w.k_chunk < 64 || valid > w.K || w.K - valid >= 64 || w.seg[0].j_begin % 8) return false;
+    if (vectors8(w.I) > w.ldp || vectors8(w.seg[0].j_end) > w.ldq) return false;
+    if ((w.n_split - 1) * w.k_chunk >= w.K || x.K % 64 || x.K < 64) return false;
+    if (vectors8(x.I) > x.ldp || vectors8(x.I) > x.ldci || vectors8(x.I) > x.ldmask) return false;
+    if (!aligned16(w.seg[0].P, w.ldp * 2) || !aligned16(w.Q, w.ldq * 2)) return false;
     if (!aligned16(x.seg[0].P, x.ldp * 2) || !aligned16(x.Q, x.ldq * 2) || !aligned16(x.Ci, x.ldci * 2) || !aligned16(x.mask, x.ldmask * 2))
         return false;
     WidePair p;

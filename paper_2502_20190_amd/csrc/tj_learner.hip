@@ -719,7 +719,39 @@ template <typename T> struct EmitTable {
     // optional transposed copy of a small layer ([C][ldT], element (o, k) of the [O][C] block at k * ldT + o)
     T *dstT[TJ_MAX_LAYERS];
     int C[TJ_MAX_LAYERS], ldT[TJ_MAX_LAYERS];
+    int ld[TJ_MAX_LAYERS];   // row pitch of dst; 0: as the parameters, no pads
 };
+
+// Elements i .. i + 3 of the flat parameters (n of them exist) to the copies they belong to.
+template <typename T> __device__ __forceinline__ void emit4(T *dst, const float (&x)[4]);
+template <typename T>
+__device__ __forceinline__ void emit_copies(const EmitTable<T> &tab, size_t i, int n, const float (&x)[4])
+{
+    for (int k = 0; k < tab.n; ++k) {
+        if (i + n <= tab.begin[k] || i >= tab.end[k]) continue;
+        if (tab.ld[k] == 0) {
+            if (n == 4 && i >= tab.begin[k] && i + 4 <= tab.end[k] && ((i - tab.begin[k]) & 3) == 0) {
+                emit4<T>(tab.dst[k] + (i - tab.begin[k]), x);
+                continue;
+            }
+            for (int e = 0; e < n; ++e)
+                if (i + e >= tab.begin[k] && i + e < tab.end[k]) tab.dst[k][i + e - tab.begin[k]] = TjElem<T>::from_f32(x[e]);
+        } else {   // padded rows
+            const uint32_t C = (uint32_t)tab.C[k], ld = (uint32_t)tab.ld[k];
+            const size_t first = i > tab.begin[k] ? i : tab.begin[k];
+            uint32_t row = (uint32_t)(first - tab.begin[k]) / C, col = (uint32_t)(first - tab.begin[k]) - row * C;
+            if (n == 4 && first == i && i + 4 <= tab.end[k] && (col & 3) == 0 && col + 4 <= C) {
+                emit4<T>(tab.dst[k] + (size_t)row * ld + col, x);
+                continue;
+            }
+            for (int e = 0; e < n; ++e) {
+                if (i + e < tab.begin[k] || i + e >= tab.end[k]) continue;
+                tab.dst[k][(size_t)row * ld + col] = TjElem<T>::from_f32(x[e]);
+                if (++col == C) { col = 0; ++row; }
+            }
+        }
+    }
+}
 
 template <typename T>
 __device__ __forceinline__ void emit_transposed(const EmitTable<T> &tab, int k, size_t e, float th)
@@ -754,7 +786,6 @@ __device__ __forceinline__ void emit_dgrad(const DgradEmit &dg, size_t e, float 
     }
 }
 
-template <typename T> __device__ __forceinline__ void emit4(T *dst, const float (&x)[4]);
 template <> __device__ __forceinline__ void emit4<float>(float *dst, const float (&x)[4])
 {
     *(float4 *)dst = make_float4(x[0], x[1], x[2], x[3]);
@@ -862,18 +893,10 @@ __global__ __launch_bounds__(256) void adam_update(float *__restrict__ theta, fl
         st4_stream(m + i, ma[0], ma[1], ma[2], ma[3]);
         st4_stream(v + i, va[0], va[1], va[2], va[3]);
         st4_stream(theta + i, ta[0], ta[1], ta[2], ta[3]);
-        for (int k = 0; k < tab.n; ++k) {
-            if (i + 4 <= tab.begin[k] || i >= tab.end[k]) continue;
-            if (i >= tab.begin[k] && i + 4 <= tab.end[k] && ((i - tab.begin[k]) & 3) == 0) {
-                emit4<T>(tab.dst[k] + (i - tab.begin[k]), ta);
-            } else {
-                for (int e = 0; e < 4; ++e)
-                    if (i + e >= tab.begin[k] && i + e < tab.end[k])
-                        tab.dst[k][i + e - tab.begin[k]] = TjElem<T>::from_f32(ta[e]);
-            }
+        emit_copies<T>(tab, i, 4, ta);
+        for (int k = 0; k < tab.n; ++k)
 #pragma unroll
             for (int e = 0; e < 4; ++e) emit_transposed<T>(tab, k, i + e, ta[e]);
-        }
     } else {
         for (size_t e = i; e < P; ++e) {
             float g = gpart[e];
@@ -886,10 +909,9 @@ __global__ __launch_bounds__(256) void adam_update(float *__restrict__ theta, fl
             v[e] = vv;
             const float th = theta[e] - lr * (mm / c1) / (sqrtf(vv / c2) + eps);
             theta[e] = th;
-            for (int k = 0; k < tab.n; ++k) {
-                if (e >= tab.begin[k] && e < tab.end[k]) tab.dst[k][e - tab.begin[k]] = TjElem<T>::from_f32(th);
-                emit_transposed<T>(tab, k, e, th);
-            }
+            const float one[4] = {th, 0.f, 0.f, 0.f};
+            emit_copies<T>(tab, e, 1, one);
+            for (int k = 0; k < tab.n; ++k) emit_transposed<T>(tab, k, e, th);
         }
     }
 }
@@ -1013,16 +1035,7 @@ __global__ __launch_bounds__(256) void slices_adam(const SliceJobs jobs, const A
         st4_stream(a.m + i, ma[0], ma[1], ma[2], ma[3]);
         st4_stream(a.v + i, va[0], va[1], va[2], va[3]);
         st4_stream(a.theta + i, ta[0], ta[1], ta[2], ta[3]);
-        for (int k = 0; k < a.tab.n; ++k) {
-            if (i + 4 <= a.tab.begin[k] || i >= a.tab.end[k]) continue;
-            if (i >= a.tab.begin[k] && i + 4 <= a.tab.end[k] && ((i - a.tab.begin[k]) & 3) == 0) {
-                emit4<T>(a.tab.dst[k] + (i - a.tab.begin[k]), ta);
-            } else {
-                for (int x = 0; x < 4; ++x)
-                    if (i + x >= a.tab.begin[k] && i + x < a.tab.end[k])
-                        a.tab.dst[k][i + x - a.tab.begin[k]] = TjElem<T>::from_f32(ta[x]);
-            }
-        }
+        emit_copies<T>(a.tab, i, 4, ta);
         if (a.dg.n > 0)
 #pragma unroll
             for (int k = 0; k < 4; ++k) emit_dgrad(a.dg, i + k, ta[k]);
@@ -1035,9 +1048,8 @@ __global__ __launch_bounds__(256) void slices_adam(const SliceJobs jobs, const A
         a.m[i + k] = ma[k];
         a.v[i + k] = va[k];
         a.theta[i + k] = ta[k];
-        for (int x = 0; x < a.tab.n; ++x)
-            if (i + k >= a.tab.begin[x] && i + k < a.tab.end[x])
-                a.tab.dst[x][i + k - a.tab.begin[x]] = TjElem<T>::from_f32(ta[k]);
+        const float one[4] = {ta[k], 0.f, 0.f, 0.f};
+        emit_copies<T>(a.tab, i + k, 1, one);
         emit_dgrad(a.dg, i + k, ta[k]);
     }
 }
@@ -1636,6 +1648,7 @@ int run_head_td(tj_learner *self, const HeadTd<T> &h, const tj_minibatch *mb, fl
 
 template <typename T> struct MlpLearner : tj_learner {
     static constexpr int VE = TjElem<T>::kVec;
+    static constexpr int kRowPad = sizeof(T) == 2 ? 64 : VE;
     tj_learner_desc d;
     int L = 0, A = 0, Bmax = 0, ldB = 0, ldA = 0, S = 1;
     int S_ends = 1;   // slices of the first and the last layer's weight gradients (>= S)
@@ -1670,10 +1683,10 @@ template <typename T> struct MlpLearner : tj_learner {
         for (int l = 0; l < L; ++l) {
             lay[l].in = in;
             lay[l].out = (int)d.layers[l].out;
-            lay[l].ld_in = round_up(in, VE);
-            // (bf16) a narrow head is padded to one whole 64-k stage, so that the input-gradient
-            // GEMM that contracts over it can use the direct-to-LDS kernel; the pads stay zero
-            lay[l].ld_out = round_up(lay[l].out, (sizeof(T) == 2 && l == L - 1 && in >= 128) ? 64 : VE);
+            // (bf16) every row is whole 64-element stages of a contraction, so that any width takes the
+            // direct-to-LDS kernels; the pads stay zero
+            lay[l].ld_in = round_up(in, kRowPad);
+            lay[l].ld_out = round_up(lay[l].out, kRowPad);
             lay[l].w_off = off; off += (size_t)in * lay[l].out;
             lay[l].b_off = off; off += lay[l].out;
             in = lay[l].out;
@@ -1707,20 +1720,22 @@ template <typename T> struct MlpLearner : tj_learner {
         }
         gpart = (float *)a.take((size_t)S_ends * Ppad * 4);
         size_t wc0 = a.off;
-        for (int l = 0; l < L; ++l) Wc_on[l] = (T *)a.take((size_t)lay[l].out * lay[l].ld_in * sizeof(T));
+        // (bf16) rows up to whole stages too: the input gradient contracts over them
+        auto wc_rows = [&](int l) { return (size_t)(sizeof(T) == 2 ? lay[l].ld_out : lay[l].out); };
+        for (int l = 0; l < L; ++l) Wc_on[l] = (T *)a.take(wc_rows(l) * lay[l].ld_in * sizeof(T));
         wc_bytes = a.off - wc0;
-        for (int l = 0; l < L; ++l) Wc_tg[l] = (T *)a.take((size_t)lay[l].out * lay[l].ld_in * sizeof(T));
-        for (int l = 0; l < L; ++l) WcT_on[l] = (T *)a.take((size_t)lay[l].in * lay[l].ld_out * sizeof(T));
+        for (int l = 0; l < L; ++l) Wc_tg[l] = (T *)a.take(wc_rows(l) * lay[l].ld_in * sizeof(T));
+        for (int l = 0; l < L; ++l) WcT_on[l] = keeps_wct(l) ? (T *)a.take((size_t)lay[l].ld_in * lay[l].ld_out * sizeof(T)) : nullptr;
         size_t act0 = a.off;
         act_begin = base ? (uint8_t *)base + act0 : nullptr;
         for (int l = 0; l < L; ++l) {
             const size_t rows = (size_t)(n_pass == 1 ? 1 : (l == 0 ? 2 : 3)) * Bmax;
             X[l] = (T *)a.take(rows * lay[l].ld_in * sizeof(T));
-            XT[l] = (T *)a.take((size_t)lay[l].in * ldB * sizeof(T));
+            XT[l] = wgrad_trans(l + 1) ? nullptr : (T *)a.take((size_t)lay[l].in * ldB * sizeof(T));
         }
-        for (int l = 1; l <= L; ++l) {
-            dZ[l] = (T *)a.take((size_t)Bmax * lay[l - 1].ld_out * sizeof(T));
-            dZT[l] = (T *)a.take((size_t)lay[l - 1].out * ldB * sizeof(T));
+        for (int l = 1; l <= L; ++l) {   // rows up to a whole stage behind the batch: they stay zero
+            dZ[l] = (T *)a.take((size_t)(Bmax + (wgrad_trans(l) ? 64 : 0)) * lay[l - 1].ld_out * sizeof(T));
+            dZT[l] = wgrad_trans(l) ? nullptr : (T *)a.take((size_t)lay[l - 1].out * ldB * sizeof(T));
         }
         act_bytes = a.off - act0;
         Qout = (float *)a.take((size_t)n_pass * Bmax * ldA * 4);
@@ -1846,7 +1861,7 @@ template <typename T> struct MlpLearner : tj_learner {
 
     // fp32 master -> compute-type copies (and transposes for the online net)
     // Adam writes the straight copy of every weight block whose rows need no padding
-    bool adam_emits(int l) const { return lay[l].ld_in == lay[l].in; }
+    bool adam_emits(int l) const { return sizeof(T) == 2 || lay[l].ld_in == lay[l].in; }
     // ... and the transposed copy of a small block with it (scattered element stores: only worth it where the
     // copy kernel's launch costs more than they do)
     bool adam_emits_t(int l) const
@@ -1855,25 +1870,18 @@ template <typename T> struct MlpLearner : tj_learner {
     }
 
     // Weight gradient of layer l (1-based) straight from the row-major X_{l-1} and dZ_l (transposing LDS
-    // reads) instead of their transposed copies: bf16, whole 32-row stages of the batch, widths that are
-    // whole 16-byte vectors.  The first and the last layer too, although their narrow sides fill few of the
-    // 256 x 128 tiles that form takes (their pair is 96 blocks on the 256-1024-1024-1024-32 net): what
-    // counts is that no transposed copy of X_{l-1} and of dZ_l is written at all where it applies, which
+    // reads) instead of their transposed copies: bf16.  The first and the last layer too, although their narrow sides
+    // fill few of the 256 x 128 tiles that form takes (their pair is 96 blocks on the 256-1024-1024-1024-32 net): what
+    // counts is that no transposed copy of X_{l-1} and of dZ_l is written at all, which
     // makes the forward pass of the last hidden layer and the input-gradient pass of the second layer
-    // one-layout launches like the others.
-    bool wgrad_trans(int l, int B) const
-    {
-        if (sizeof(T) != 2 || B % 32 != 0 || l < 1 || l > L) return false;
-        return lay[l - 1].in % 8 == 0 && lay[l - 1].out % 8 == 0;
-    }
+    // one-layout launches like the others.  Any width and batch: rows are padded to whole stages, and the rows behind the batch
+    // count as zero (as contractions over transposed copies, with element-wise staged loads, an update of
+    // 256-640-640-640-18 took 337 us at batch 3000 against 151 at 2048 and 182 at 4096).
+    bool wgrad_trans(int l) const { return sizeof(T) == 2 && l >= 1 && l <= L; }
 
     // Input gradient of layer l (1-based, l >= 2) with the row-major weight copy as its first operand
-    // (transposing LDS reads): bf16, a contraction over whole 32-row stages of the weight matrix.  Such a
-    // layer keeps no transposed weight copy.
-    bool dgrad_trans(int l) const
-    {
-        return sizeof(T) == 2 && lay[l - 1].in % 8 == 0 && lay[l - 1].out % 32 == 0;
-    }
+    // (transposing LDS reads): bf16.  Such a layer keeps no transposed weight copy.
+    bool dgrad_trans(int) const { return sizeof(T) == 2; }
     // Layer index l (0-based) keeps a transposed weight copy: its input gradient exists, is a contraction
     // (the head's is not where the TD kernel writes it) and does not read the straight copy.
     virtual bool head_input_gradient_fused() const { return false; }   // a derived learner's head kernel reads WcT
@@ -1943,7 +1951,7 @@ template <typename T> struct MlpLearner : tj_learner {
         // gradient still contracts over transposed operands)
         {
             CastJobs<T> jobs;
-            jobs.job[0] = {(const float *)mb->obs, X[0], wgrad_trans(1, B) ? nullptr : XT[0], B, lay[0].in, lay[0].ld_in, ldB};
+            jobs.job[0] = {(const float *)mb->obs, X[0], wgrad_trans(1) ? nullptr : XT[0], B, lay[0].in, lay[0].ld_in, ldB};
             jobs.job[1] = {(const float *)mb->next_obs, X[0] + (size_t)B * lay[0].ld_in, nullptr, B,
                            lay[0].in, lay[0].ld_in, ldB};
             if (mb->row_index) {   // rows of the caller's tables (the ring itself), picked by index
@@ -1967,7 +1975,7 @@ template <typename T> struct MlpLearner : tj_learner {
             g.k_chunk = g.K; g.n_split = 1;
             g.relu = 1;
             g.Ci = X[l + 1]; g.ldci = lay[l].ld_out;
-            if (!wgrad_trans(l + 2, B)) { g.Cj = XT[l + 1]; g.ldcj = ldB; g.cj_jmax = B; }
+            if (!wgrad_trans(l + 2)) { g.Cj = XT[l + 1]; g.ldcj = ldB; g.cj_jmax = B; }
             if ((rc = tj_gemm<T>(g, st)) != TJ_OK) return rc;
         }
         {   // head layer and TD step
@@ -1979,12 +1987,12 @@ template <typename T> struct MlpLearner : tj_learner {
             h.b_on = theta_on + lh.b_off; h.b_tg = theta_tg + lh.b_off;
             h.B = B; h.A = A; h.K = lh.ld_in;
             h.Q = Qout; h.ldq = ldA;
-            h.dZ = dZ[L]; h.lddz = lh.ld_out; h.dZT = wgrad_trans(L, B) ? nullptr : dZT[L]; h.lddzt = ldB;
+            h.dZ = dZ[L]; h.lddz = lh.ld_out; h.dZT = wgrad_trans(L) ? nullptr : dZT[L]; h.lddzt = ldB;
             h.astar = astar; h.loss_part = loss_part;
             h.dX = nullptr; h.lddx = 0; h.dXT = nullptr; h.lddxt = 0; h.Kin = lh.in;
             if (head_fused<T>(A) && L >= 2) {   // the fused kernel also writes the head's input gradient
                 h.dX = dZ[L - 1]; h.lddx = lh.ld_in;
-                if (!wgrad_trans(L - 1, B)) { h.dXT = dZT[L - 1]; h.lddxt = ldB; }
+                if (!wgrad_trans(L - 1)) { h.dXT = dZT[L - 1]; h.lddxt = ldB; }
             }
             if ((rc = run_head_td<T>(this, h, mb, d.gamma, d.huber_delta, st)) != TJ_OK) return rc;
         }
@@ -1998,7 +2006,7 @@ template <typename T> struct MlpLearner : tj_learner {
     int backward_update(int B, int n_loss_part, tj_step_stats *d_stats, hipStream_t st, bool head_dx_done = false)
     {
         int rc;
-        const int Kb = round_up(B, VE);
+        const int Kb = round_up(B, sizeof(T) == 2 ? 64 : VE);
         // backward through the online network on s.  The weight gradient and the input gradient of a layer both
         // start from dZ_l and are independent: one paired launch where the kernels allow it.  The head's weight
         // gradient shares the launch of the first layer's weight gradient instead (neither is a problem that
@@ -2013,11 +2021,11 @@ template <typename T> struct MlpLearner : tj_learner {
                 TjGemmArgs<T> &g = gw;
                 memset(&g, 0, sizeof(g));
                 g.n_seg = 1;
-                if (wgrad_trans(l, B)) {   // row-major operands, contraction over their rows
+                if (wgrad_trans(l)) {   // row-major operands, contraction over their rows
                     g.seg[0] = {0, lp.out, X[l - 1], nullptr, 0};
                     g.Q = dZ[l];
                     g.ldp = lp.ld_in; g.ldq = lp.ld_out;
-                    g.trans = 1;
+                    g.trans = 1; g.k_valid = B;
                 } else {
                     g.seg[0] = {0, lp.out, XT[l - 1], nullptr, 0};
                     g.Q = dZT[l];
@@ -2048,7 +2056,7 @@ template <typename T> struct MlpLearner : tj_learner {
                 g.I = lp.in;
                 if (dgrad_trans(l)) {   // the weights as stored, [n][k]: the contraction runs over their rows
                     g.seg[0] = {0, B, Wc_on[l - 1], nullptr, 0};
-                    g.ldp = lp.ld_in; g.K = lp.out;
+                    g.ldp = lp.ld_in; g.K = lp.ld_out;   // pad rows and columns are zero
                     g.trans = 2;
                 } else {
                     g.seg[0] = {0, B, WcT_on[l - 1], nullptr, 0};
@@ -2057,7 +2065,7 @@ template <typename T> struct MlpLearner : tj_learner {
                 g.k_chunk = g.K; g.n_split = 1;
                 g.mask = X[l - 1]; g.ldmask = lp.ld_in;
                 g.Ci = dZ[l - 1]; g.ldci = lp.ld_in;
-                if (!wgrad_trans(l - 1, B)) { g.Cj = dZT[l - 1]; g.ldcj = ldB; g.cj_jmax = B; }
+                if (!wgrad_trans(l - 1)) { g.Cj = dZT[l - 1]; g.ldcj = ldB; g.cj_jmax = B; }
             }
             if (defer_head) {   // the input gradient alone now
                 if ((rc = tj_gemm<T>(gd, st)) != TJ_OK) return rc;
@@ -2101,6 +2109,7 @@ template <typename T> struct MlpLearner : tj_learner {
             tab.end[tab.n] = lay[l].w_off + (size_t)lay[l].in * lay[l].out;
             tab.dstT[tab.n] = adam_emits_t(l) ? WcT_on[l] : nullptr;
             tab.C[tab.n] = lay[l].in; tab.ldT[tab.n] = lay[l].ld_out;
+            tab.ld[tab.n] = lay[l].ld_in == lay[l].in ? 0 : lay[l].ld_in;
             tab.dst[tab.n++] = Wc_on[l];
         }
         LossFinal lf = {loss_part, n_loss_part, B, (uint32_t)t, d_stats, stats_internal};
@@ -2276,15 +2285,14 @@ template <typename T> struct MlpLearner : tj_learner {
 // the whole batch.  One forward pass (no target network, no s'), so the activation buffers hold
 // max_batch rows; backward, slice reduction, Adam and the weight copies are the Q-learner's.
 template <typename T> struct PpoLearner : MlpLearner<T> {
-    // The objective kernel can also produce the head's input gradient (bf16, at most 32 head outputs, a head
-    // input of whole 32-column tiles without row padding, a transposed weight copy wide enough for its
-    // 16-wide contraction steps); the transposed copy of the head's weights is kept for it.
+    // The objective kernel can also produce the head's input gradient (bf16, at most 32 head outputs, a transposed weight
+    // copy wide enough for its 16-wide contraction steps); the transposed copy of the head's weights is kept for it.
     bool head_input_gradient_fused() const override
     {
         if (sizeof(T) != 2 || this->L < 3 || this->A > 32) return false;
         const auto &lh = this->lay[this->L - 1];
         const int cols16 = (round_up(this->A, 8) + 15) / 16 * 16;
-        return lh.in % 32 == 0 && lh.in <= kPpoFusedMaxK && lh.ld_in == lh.in && lh.ld_out >= cols16;
+        return lh.ld_in <= kPpoFusedMaxK && lh.ld_out >= cols16;
     }
     using Base = MlpLearner<T>;
     tj_ppo_desc pd;
@@ -2309,7 +2317,7 @@ template <typename T> struct PpoLearner : MlpLearner<T> {
         int rc;
         const auto &lay = this->lay;
         CastJobs<T> jobs;
-        jobs.job[0] = {d_obs, this->X[0], keep_transposes && !this->wgrad_trans(1, n) ? this->XT[0] : nullptr, n,
+        jobs.job[0] = {d_obs, this->X[0], keep_transposes && !this->wgrad_trans(1) ? this->XT[0] : nullptr, n,
                        lay[0].in, lay[0].ld_in, this->ldB};
         if ((rc = launch_cast<T>(jobs, 1, st)) != TJ_OK) return rc;
         if (keep_transposes && (rc = this->mark(0, st)) != TJ_OK) return rc;
@@ -2325,7 +2333,7 @@ template <typename T> struct PpoLearner : MlpLearner<T> {
             if (l + 1 < this->L) {
                 g.relu = 1;
                 g.Ci = this->X[l + 1]; g.ldci = lay[l].ld_out;
-                if (keep_transposes && !this->wgrad_trans(l + 2, n)) { g.Cj = this->XT[l + 1]; g.ldcj = this->ldB; g.cj_jmax = n; }
+                if (keep_transposes && !this->wgrad_trans(l + 2)) { g.Cj = this->XT[l + 1]; g.ldcj = this->ldB; g.cj_jmax = n; }
             } else {
                 g.Cf = this->Qout; g.ldcf = this->ldA;
             }
@@ -2354,7 +2362,7 @@ template <typename T> struct PpoLearner : MlpLearner<T> {
         // bf16 with at most 32 head outputs: the head layer's forward runs inside the objective kernel
         const bool fused = sizeof(T) == 2 && this->A <= 32 && this->L >= 2;
         // the same kernel writes the head's input gradient where the layer below takes it row-major
-        const bool fused_dx = fused && head_input_gradient_fused() && this->wgrad_trans(this->L - 1, B);
+        const bool fused_dx = fused && head_input_gradient_fused() && this->wgrad_trans(this->L - 1);
         if ((rc = forward(B, pb->obs, true, st, fused)) != TJ_OK) return rc;
         if ((rc = this->mark(1, st)) != TJ_OK) return rc;
         const auto &lh = this->lay[this->L - 1];
@@ -2363,7 +2371,7 @@ template <typename T> struct PpoLearner : MlpLearner<T> {
         a.action = pb->action; a.old_logp = pb->old_logp; a.adv = pb->adv; a.ret = pb->ret;
         a.clip = pd.clip; a.c_v = pd.c_v; a.c_e = pd.c_e;
         a.dZ = this->dZ[this->L]; a.lddz = lh.ld_out; a.lddzt = this->ldB;
-        a.dZT = this->wgrad_trans(this->L, B) ? nullptr : this->dZT[this->L];
+        a.dZT = this->wgrad_trans(this->L) ? nullptr : this->dZT[this->L];
         a.part = ppo_part;
         const int nblk = (B + kPpoRows - 1) / kPpoRows;
         if constexpr (sizeof(T) == 2) {
@@ -3148,7 +3156,7 @@ template <typename T> struct ConvLearner : tj_learner {
             if (!adam_emits(l)) continue;
             tab.begin[tab.n] = lay[l].w_off;
             tab.end[tab.n] = lay[l].w_off + (size_t)lay[l].O * lay[l].K;
-            tab.dstT[tab.n] = nullptr; tab.C[tab.n] = 0; tab.ldT[tab.n] = 0;
+            tab.dstT[tab.n] = nullptr; tab.C[tab.n] = 0; tab.ldT[tab.n] = 0; tab.ld[tab.n] = 0;
             tab.dst[tab.n++] = lay[l].Wc_on;
         }
         const LossFinal lf = {loss_part, n_loss, B, (uint32_t)t, d_stats, stats_internal};

@@ -1715,7 +1715,10 @@ template <typename T> struct MlpLearner : tj_learner {
         if (sizeof(T) == 2 && L >= 3 && lay[1].w_off % 4 == 0 && lay[L - 1].w_off % 4 == 0) {
             const int tiles = ((lay[0].in + 255) / 256) * ((lay[0].out + 127) / 128) +
                               ((lay[L - 1].in + 255) / 256) * ((lay[L - 1].out + 127) / 128);
-            const int want = Bmax / 1024, fit = 256 / tiles;
+            // a slice per 1024 rows, up to eight down to 256 rows: few tiles are a serial chain as long as their slice
+            // (256-640-640-640-18 at 1024 rows: 143 us with one slice, 134 with two, 129 with four; 1024 units at 8192 rows with 8, 16
+            // and 21 slices: 275, 285, 290)
+            const int want = std::max(Bmax / 1024, std::min(8, Bmax / 256)), fit = 256 / tiles;
             S_ends = std::max(S, std::min(want, fit));
         }
         gpart = (float *)a.take((size_t)S_ends * Ppad * 4);

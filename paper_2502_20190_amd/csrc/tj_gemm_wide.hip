@@ -362,6 +362,12 @@ int vectors8(int n) { return (n + 7) & ~7; }   // columns of whole 16-byte vecto
 
 }  // namespace
 
+// Fewest 256 x 256 tiles.  A forward pass of up to half a round is cut into halves, and wins from a quarter of a round on
+// (updates in us, old kernels : these; 256-700-700-700-18 at batch 2048 155 : 143, 256-768 at 3000 183 : 170, at 4096 183 : 169,
+// 256-1024 at 5000 256 : 221, at 6000 284 : 255); fewer tiles are as fast either way.  The pair has no halves: with fewer than half a
+// round the old tiles, two to a CU, spread better (256-700 at 4096 180 : 184.5; from half a round on 768 at 8192 241 : 236).
+constexpr int kForwardTiles = kCus / 4, kPairTiles = kCus / 2;
+
 bool tj_gemm_wide_forward(const TjGemmArgs<tj_bf16> &a, hipStream_t st, int *rc)
 {
     if (a.trans || a.gather.on || a.out_map.on || a.n_split != 1 || a.qsum || a.bias_j || a.mask || a.Cj || a.Cf || !a.Ci || !a.relu)
@@ -378,7 +384,7 @@ bool tj_gemm_wide_forward(const TjGemmArgs<tj_bf16> &a, hipStream_t st, int *rc)
     p.seg0 = cols[0];
     p.tiles_j = cols[0] + cols[1];
     const int tiles = p.tiles_i * p.tiles_j, rest = tiles % kCus;
-    if (tiles < kCus) return false;
+    if (tiles < kForwardTiles) return false;
     p.whole = rest > 0 && rest <= kCus / 2 ? (tiles - rest) / p.tiles_i : p.tiles_j;
     auto blocks = [&](int cols_) { return p.tiles_i * up_div(cols_, 8) * 8; };
     p.n_whole = blocks(p.whole);
@@ -412,7 +418,7 @@ bool tj_gemm_wide_pair(const TjGemmArgs<tj_bf16> &w, const TjGemmArgs<tj_bf16> &
     p.x_tiles_i = up_div(x.I, kTile);
     p.x_tiles_j = up_div(xj, kTile);
     const int n1 = p.x_tiles_i * p.x_tiles_j;
-    if (p.n0 + n1 < kCus) return false;
+    if (p.n0 + n1 < kPairTiles) return false;
     if ((*rc = lds_attr((const void *)gemm_wide_pair)) != TJ_OK) return true;
     gemm_wide_pair<<<p.n0 + p.x_tiles_i * up_div(p.x_tiles_j, 8) * 8, kThreads, kLds, st>>>(p);
     *rc = hipGetLastError() == hipSuccess ? TJ_OK : TJ_ERR_DEVICE;

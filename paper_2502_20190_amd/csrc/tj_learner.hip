@@ -2641,7 +2641,7 @@ template <typename T> struct ConvLearner : tj_learner {
                         y.f_part = (float *)a.take((size_t)y.f_split * 3 * B * y.O * 4);
                     }
                 }
-                const bool rows = head_wgrad_rows(l);   // dZ rows padded (zero) to whole 64-row stages instead of the copies
+                const bool rows = !wants_xt(l);   // dZ rows padded (zero) to whole 64-row stages instead of the copies
                 y.XT = rows ? nullptr : (T *)a.take((size_t)y.K * ldB * sizeof(T));
                 y.dZ = (T *)a.take((B + (rows ? 64 : 0)) * y.ldO * sizeof(T));
                 y.dZT = rows ? nullptr : (T *)a.take((size_t)y.O * ldB * sizeof(T));
@@ -2716,14 +2716,15 @@ template <typename T> struct ConvLearner : tj_learner {
     static dim3 grid1(size_t n) { return dim3((unsigned)((n + 255) / 256)); }
 
     // A hidden linear layer's weight gradient straight from the row-major input rows and dZ (transposing LDS
-    // reads, as in the MLP learner): bf16, whole 32-row stages of the batch, widths that are whole 16-byte
+    // reads, as in the MLP learner): bf16, any batch, widths that are whole 16-byte
     // vectors and fill 256 x 128 tiles.  Such a layer needs neither the transposed input nor dZ^T, nor, with the input
     // gradient below, a transposed weight copy after every update.  Batch 256, hidden width 512: 210 -> 197 us a step
-    // with it; 128: 179 -> 166; 512: 260 -> 240.  Ragged batches (200: 223 us) keep the transposed copies.
-    bool lin_wgrad_trans(int l, int B) const
+    // with it; 128: 179 -> 166; 512: 260 -> 240.  A batch that ends inside a
+    // stage takes it too (200: 203 us before these launches, of which the transposed copies were about 27; 122.5 now).
+    bool lin_wgrad_trans(int l) const
     {
         if (sizeof(T) != 2 || l < 1 || l >= L - 1 || lay[l].kind != TJ_LAYER_LINEAR) return false;
-        return B % 32 == 0 && lay[l].K % 8 == 0 && lay[l].O % 8 == 0 && lay[l].K >= 256 && lay[l].O >= 128;
+        return lay[l].K % 8 == 0 && lay[l].O % 8 == 0 && lay[l].K >= 256 && lay[l].O >= 128;
     }
 
     // The head's weight gradient from row-major operands, as the convolutions' (a contraction over rows with 32 columns on one
@@ -2734,20 +2735,19 @@ template <typename T> struct ConvLearner : tj_learner {
                lay[l].ldK == lay[l].K && lay[l].ldO >= 32;
     }
     // The last hidden layer's split contraction is finished by the head's kernel: nobody needs its output transposed.
-    bool head_from_slices(int l, int B) const
+    bool head_from_slices(int l) const
     {
         return l == L - 2 && l >= 1 && lay[l].kind == TJ_LAYER_LINEAR && lay[l].f_split > 1 && lay[l].O <= kHeadSliceUnits &&
-               head_wgrad_rows(L - 1) && lin_wgrad_trans(l, B);
+               head_wgrad_rows(L - 1) && lin_wgrad_trans(l);
     }
     // Layer l's weight gradient reads a transposed copy of its input
-    bool wants_xt(int l, int B) const { return !lin_wgrad_trans(l, B) && !head_wgrad_rows(l); }
+    bool wants_xt(int l) const { return !lin_wgrad_trans(l) && !head_wgrad_rows(l); }
 
     // A linear layer's input gradient with the row-major weight copy as its first operand (transposing LDS
-    // reads): bf16, a contraction over whole 32-row stages of the weight matrix, and a batch whose weight gradient takes
-    // that form too, with which it shares a launch.  Decided by the largest batch, so that the set of weight copies is fixed.
+    // reads): bf16, a contraction over whole 32-row stages of the weight matrix.  It shares a launch with the weight gradient.
     bool lin_dgrad_trans(int l) const
     {
-        if (sizeof(T) != 2 || l < 1 || lay[l].kind != TJ_LAYER_LINEAR || (Bmax < 1024 && Bmax % 32)) return false;
+        if (sizeof(T) != 2 || l < 1 || lay[l].kind != TJ_LAYER_LINEAR) return false;
         return lay[l].K % 8 == 0 && lay[l].O % 32 == 0;
     }
     // Layer l keeps a transposed weight copy: its input gradient exists and is a contraction over that copy (a
@@ -2906,7 +2906,7 @@ template <typename T> struct ConvLearner : tj_learner {
                     for (int net = 0; net < 2; ++net)
                         if ((rc = tj_gemm<T>(both[net], st)) != TJ_OK) return rc;
             } else {
-                if (l > 0 && lay[l - 1].kind == TJ_LAYER_CONV2D && wants_xt(l, B))   // transposed input of the s rows
+                if (l > 0 && lay[l - 1].kind == TJ_LAYER_CONV2D && wants_xt(l))   // transposed input of the s rows
                     if ((rc = transpose(act[l], y.ldK, y.XT, ldB, B, y.K, st)) != TJ_OK) return rc;
                 TjGemmArgs<T> gm;
                 memset(&gm, 0, sizeof(gm));
@@ -2922,18 +2922,18 @@ template <typename T> struct ConvLearner : tj_learner {
                     gm.n_split = y.f_split; gm.k_chunk = y.f_chunk;
                     gm.Cf = y.f_part; gm.ldcf = y.O; gm.cf_zstride = (size_t)3 * B * y.O;
                     if ((rc = tj_gemm<T>(gm, st)) != TJ_OK) return rc;
-                    if (head_from_slices(l, B)) continue;
+                    if (head_from_slices(l)) continue;
                     const size_t nvec = (size_t)3 * B * (y.O / 4);
                     sum_bias_relu<T><<<grid1(nvec), 256, 0, st>>>(y.f_part, gm.cf_zstride, y.f_split, 3 * B, y.O,
                                                                theta_on + y.b_off, theta_tg + y.b_off, 2 * B,
                                                                act[l + 1], lay[l + 1].ldK, lay[l + 1].XT, ldB,
-                                                               wants_xt(l + 1, B) ? B : 0);
+                                                               wants_xt(l + 1) ? B : 0);
                     if (hipGetLastError() != hipSuccess) return TJ_ERR_DEVICE;
                     continue;
                 }
                 gm.relu = 1;
                 gm.Ci = act[l + 1]; gm.ldci = lay[l + 1].ldK;
-                if (wants_xt(l + 1, B)) { gm.Cj = lay[l + 1].XT; gm.ldcj = ldB; gm.cj_jmax = B; }
+                if (wants_xt(l + 1)) { gm.Cj = lay[l + 1].XT; gm.ldcj = ldB; gm.cj_jmax = B; }
                 if ((rc = tj_gemm<T>(gm, st)) != TJ_OK) return rc;
             }
         }
@@ -2954,9 +2954,9 @@ template <typename T> struct ConvLearner : tj_learner {
             head_dx_done = head_fused<T>(A) && L >= 2 && lay[L - 2].kind == TJ_LAYER_LINEAR;
             if (head_dx_done) {   // the fused kernel also writes the head's input gradient
                 h.dX = lay[L - 2].dZ; h.lddx = y.ldK;
-                if (!lin_wgrad_trans(L - 2, B)) { h.dXT = lay[L - 2].dZT; h.lddxt = ldB; }
+                if (!lin_wgrad_trans(L - 2)) { h.dXT = lay[L - 2].dZT; h.lddxt = ldB; }
             }
-            if (head_from_slices(L - 2, B)) {
+            if (head_from_slices(L - 2)) {
                 const NLayer &b = lay[L - 2];
                 h.part = b.f_part; h.zstride = (size_t)3 * B * b.O; h.S = b.f_split;
                 h.bias_on = theta_on + b.b_off; h.bias_tg = theta_tg + b.b_off;
@@ -3038,21 +3038,21 @@ template <typename T> struct ConvLearner : tj_learner {
                 TjGemmArgs<T> &gm = gw;
                 memset(&gm, 0, sizeof(gm));
                 gm.n_seg = 1;
-                if (lin_wgrad_trans(l, B)) {   // row-major operands, contraction over their rows
+                if (lin_wgrad_trans(l)) {   // row-major operands, contraction over their rows
                     gm.seg[0] = {0, y.O, act[l], nullptr, 0};
                     gm.Q = y.dZ;
                     gm.ldp = y.ldK; gm.ldq = y.ldO;
-                    gm.trans = 1;
+                    gm.trans = 1; gm.k_valid = B;
                 } else {
                     gm.seg[0] = {0, y.O, conv ? y.patchesT : y.XT, nullptr, 0};
                     gm.Q = y.dZT;
                     gm.ldp = ldm;   // pitches follow the largest batch, so pad columns are never written
                     gm.ldq = ldm;
                 }
-                gm.I = y.K; gm.K = Kc;
+                gm.I = y.K; gm.K = gm.trans ? round_up(B, 64) : Kc;
                 int ns = y.n_split;
                 const int ke = 128 / (int)sizeof(T);
-                gm.k_chunk = round_up((Kc + ns - 1) / ns, ke);
+                gm.k_chunk = round_up((gm.K + ns - 1) / ns, ke);
                 gm.n_split = ns;
                 gm.Cf = y.part; gm.ldcf = y.K; gm.cf_zstride = y.part_stride;
                 gm.qsum = y.part + (size_t)y.O * y.K; gm.qsum_zstride = y.part_stride;
@@ -3081,7 +3081,7 @@ template <typename T> struct ConvLearner : tj_learner {
                 gm.k_chunk = gm.K; gm.n_split = 1;
                 gm.mask = act[l]; gm.ldmask = y.ldK;
                 gm.Ci = below.dZ; gm.ldci = y.ldK;
-                if (below.kind == TJ_LAYER_LINEAR && !lin_wgrad_trans(l - 1, B)) {
+                if (below.kind == TJ_LAYER_LINEAR && !lin_wgrad_trans(l - 1)) {
                     gm.Cj = below.dZT; gm.ldcj = ldB; gm.cj_jmax = B;
                 }
                 if constexpr (sizeof(T) == 2) {

@@ -993,22 +993,28 @@ __device__ __forceinline__ void dlds_body(const TjGemmArgs<tj_bf16> &a_in, const
     const int lrow = lane / VPR, lpos = lane % VPR;
     auto swizzle = [](int row) { return VPR == 8 ? (row >> 1) & 7 : (row >> 2) & 3; };
     const T *gsrcP[LP];
-    const T *gsrcQ[LQ];
     // GATHER = 2: the pixel a row's patch starts at (inside the border it is negative or past the image), and the
     // tap (row, column, first channel) the next stage starts at: stages are issued in order and lie within one tap
     int py[LP], px[LP];
     int tap_y = 0, tap_x = 0, tap_c = 0;
     (void)py; (void)px; (void)tap_y; (void)tap_x; (void)tap_c;
+    // Without a gather a load's address is a scalar (the stage's first row and column) plus a 32-bit lane offset that
+    // is the same for every stage: half the registers of 64-bit lane addresses, and none of the additions.
+    const T *baseP = nullptr, *baseQ = nullptr;
+    uint32_t offP[LP], offQ[LQ];
+    (void)baseP; (void)offP; (void)gsrcP;
     if constexpr (TRANS != 0) {
         // P: load instruction c = wave + 8 t fills rows 2c, 2c+1 (512 bytes each).  Columns past the end
         // repeat the last valid vector.
+        baseP = seg.P + (size_t)k_begin * a.ldp + i0;
 #pragma unroll
         for (int t = 0; t < LP; ++t) {
             const int row = 2 * (wave + 8 * t) + (lane >> 5);
-            const int col = min(i0 + 8 * ((lane & 31) ^ ((row & 3) << 2)), ((a.I + 7) & ~7) - 8);
-            gsrcP[t] = seg.P + (size_t)(k_begin + row) * a.ldp + col;
+            const int col = min(8 * ((lane & 31) ^ ((row & 3) << 2)), ((a.I + 7) & ~7) - 8 - i0);
+            offP[t] = 2u * (uint32_t)(row * a.ldp + col);
         }
     } else {
+        baseP = seg.P + (size_t)i0 * a.ldp + k_begin;
 #pragma unroll
         for (int t = 0; t < LP; ++t) {
             const int row = (wave + 8 * t) * RPI + lrow;
@@ -1024,21 +1030,23 @@ __device__ __forceinline__ void dlds_body(const TjGemmArgs<tj_bf16> &a_in, const
             } else if constexpr (GATHER == 1)
                 gsrcP[t] = seg.P + tj_gather_origin(a.gather, (uint32_t)i);
             else
-                gsrcP[t] = seg.P + (size_t)i * a.ldp + (lpos ^ swizzle(row)) * 8 + k_begin;
+                offP[t] = 2u * (uint32_t)((i - i0) * a.ldp + (lpos ^ swizzle(row)) * 8);
         }
     }
     if constexpr (TRANS == 1) {
         // Q: instruction c = wave fills rows 4c .. 4c+3 (256 bytes each)
         const int rowq = 4 * wave + (lane >> 4);
-        const int colq = min(j0 + 8 * ((lane & 15) ^ ((rowq & 3) << 2)), ((j_end + 7) & ~7) - 8);
-        gsrcQ[0] = a.Q + (size_t)(k_begin + rowq) * a.ldq + colq;
+        const int colq = min(8 * ((lane & 15) ^ ((rowq & 3) << 2)), ((j_end + 7) & ~7) - 8 - j0);
+        baseQ = a.Q + (size_t)k_begin * a.ldq + j0;
+        offQ[0] = 2u * (uint32_t)(rowq * a.ldq + colq);
     } else {
+        baseQ = a.Q + (size_t)(j0 - seg.q_shift) * a.ldq + k_begin;
 #pragma unroll
         for (int t = 0; t < LQ; ++t) {
             const int c = (wave + 8 * t) % CHQ;
             const int row = c * RPI + lrow;
             const int j = min(j0 + row, j_end - 1);
-            gsrcQ[t] = a.Q + (size_t)(j - seg.q_shift) * a.ldq + (lpos ^ swizzle(row)) * 8 + k_begin;
+            offQ[t] = 2u * (uint32_t)((j - j0) * a.ldq + (lpos ^ swizzle(row)) * 8);
         }
     }
     // gather form: the k of this lane's vector is the same for all its P rows (the swizzle of a
@@ -1057,6 +1065,18 @@ __device__ __forceinline__ void dlds_body(const TjGemmArgs<tj_bf16> &a_in, const
         asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds_addr), "v"(src)
                      : "memory");
     };
+    // The same from a scalar base.  A vector instruction may have written the base (uniform() below), after which a
+    // memory instruction may read it five wait states later at the earliest: the move and the s_nop are six.
+    auto dma16_at = [](const T *base, uint32_t off, uint8_t *dst) {
+        const uint32_t lds_addr = (uint32_t)(uintptr_t)(lds_ptr_t)dst;
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds_addr), "v"(off), "s"(base)
+                     : "memory");
+    };
+    auto uniform = [](const T *p) {   // the same in every lane already; this says so
+        const uint64_t v = (uint64_t)p;
+        return (const T *)(((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(v >> 32)) << 32) |
+                           (uint32_t)__builtin_amdgcn_readfirstlane((int)v));
+    };
     auto issue = [&](uint8_t *sA, uint8_t *sB, int s) {   // called for s = 0, 1, 2, ... in order
         if constexpr (GATHER == 2) {
             const TjGather &g = a.gather;
@@ -1070,23 +1090,29 @@ __device__ __forceinline__ void dlds_body(const TjGemmArgs<tj_bf16> &a_in, const
                 tap_c = 0;
                 if (++tap_x * g.chan == g.run) { tap_x = 0; ++tap_y; }
             }
-        } else {
-            const size_t offP = GATHER ? (size_t)tj_gather_koff(a.gather, kposP + s * KE) : s * stepP;
-            if (TRANS == 1 && k_begin + (s + 1) * KE > k_valid) {   // the stage the batch ends in: no rows past the last one
+        } else if constexpr (GATHER == 1) {
+            const size_t koff = (size_t)tj_gather_koff(a.gather, kposP + s * KE);
 #pragma unroll
-                for (int t = 0; t < LP; ++t) {
-                    const int past = max(k_begin + s * KE + 2 * (wave + 8 * t) + (lane >> 5) - (k_valid - 1), 0);
-                    dma16(gsrcP[t] + offP - (size_t)past * a.ldp, sA + (wave + 8 * t) * 1024);
-                }
-            } else {
+            for (int t = 0; t < LP; ++t) dma16(gsrcP[t] + koff, sA + (wave + 8 * t) * 1024);
+        } else if (TRANS == 1 && k_begin + (s + 1) * KE > k_valid) {
+            // a stage with rows past the last valid one reads that one instead; it may hold no valid row at all
+            const int row0 = min(s * KE, k_valid - 1 - k_begin), last = k_valid - 1 - k_begin - row0;
+            const T *base = uniform(baseP + (int64_t)row0 * a.ldp);
 #pragma unroll
-                for (int t = 0; t < LP; ++t) dma16(gsrcP[t] + offP, sA + (wave + 8 * t) * 1024);
+            for (int t = 0; t < LP; ++t) {
+                const int past = max(2 * (wave + 8 * t) + (lane >> 5) - last, 0);
+                dma16_at(base, offP[t] - 2u * (uint32_t)(past * a.ldp), sA + (wave + 8 * t) * 1024);
             }
+        } else {
+            const T *base = uniform(baseP + s * stepP);
+#pragma unroll
+            for (int t = 0; t < LP; ++t) dma16_at(base, offP[t], sA + (wave + 8 * t) * 1024);
         }
+        const T *base = uniform(baseQ + s * stepQ);
 #pragma unroll
         for (int t = 0; t < LQ; ++t) {
             const int c = (wave + 8 * t) % CHQ;   // wave-uniform
-            dma16(gsrcQ[t] + s * stepQ, sB + c * 1024);
+            dma16_at(base, offQ[t], sB + c * 1024);
         }
     };
 

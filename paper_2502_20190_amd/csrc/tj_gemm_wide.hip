@@ -81,8 +81,10 @@ __device__ __forceinline__ void tile(const TjGemmArgs<tj_bf16> &a, const TjGemmS
     const tj_bf16 *const bQ = TQ ? a.Q + (size_t)k_begin * a.ldq + j0 : a.Q + (size_t)(j0 - seg.q_shift) * a.ldq + k_begin;
     const size_t stP = TP ? (size_t)64 * a.ldp : 64, stQ = TQ ? (size_t)64 * a.ldq : 64;
     // Inline assembly, so that the compiler's wait counts do not see these loads; M0 is written here and nowhere else.
+    // Should the compiler keep the base in lanes of a vector register, reading it back is a vector instruction's write of a
+    // scalar, which a memory instruction may read five wait states later: the move and the s_nop are six.
     auto dma = [](const tj_bf16 *base, uint32_t off, uint32_t at) {
-        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(at), "v"(off), "s"(base) : "memory");
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(at), "v"(off), "s"(base) : "memory");
     };
     const uint32_t l0 = (uint32_t)(uintptr_t)(lds_u8)lds + wave * 1024;
     const int k_valid = KIND == kWeightGrad && a.k_valid ? a.k_valid : a.K;

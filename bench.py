@@ -31,11 +31,13 @@ sys.path.insert(0, ROOT)
 # same counters read for a streaming kernel of known size in the same runs (adam_update: FETCH_SIZE
 # reads half the bytes, WRITE_SIZE all of them).  Valid for the sources it was taken with: the contraction
 # kernels and the learner that decides which of them a step launches.
-GEMM_SOURCES = ("tj_gemm.h", "tj_gemm.hip", "tj_conv_first.hip", "tj_conv_wgrad.hip", "tj_conv.h", "tj_learner.hip")
-GEMM_TRAFFIC = {"c3": {"bytes_per_step": 738.9e6, "gemm_source_sha256_16": "258254a5647cdea6"},
-                "c5": {"bytes_per_step": 1353.4e6, "gemm_source_sha256_16": "258254a5647cdea6"}}
+GEMM_SOURCES = ("tj_gemm.h", "tj_gemm.hip", "tj_gemm_wide.hip", "tj_conv_first.hip", "tj_conv_tower.hip", "tj_conv_planes.h",
+                "tj_conv_wgrad.h", "tj_conv_wgrad.hip", "tj_conv.h", "tj_learner.hip")
+GEMM_TRAFFIC = {"c3": {"bytes_per_step": 730.0e6, "gemm_source_sha256_16": "9558393ed8b08053"},
+                "c5": {"bytes_per_step": 972.7e6, "gemm_source_sha256_16": "9558393ed8b08053"}}
 PEAK_HBM_GBS = 8000.0
 FP32_KERNELS = {2: "f32_rows + f32_update", 3: "f32_rows + f32_update + f32_adam"}   # by launches of an update
+WIDE_KERNELS = "gemm_wide_forward + gemm_wide_pair + gemm_bf16_dlds_pair_sum (its blocks that add gradient slices included)"
 PEAK_TFLOPS = {"bf16": 2500.0, "fp32": 157.3}
 
 
@@ -53,19 +55,20 @@ def fp32_launches(dims, B):
 def adam_slice_traffic(dims, precision, B, P):
     """Bytes the optimizer kernel of an MLP moves on top of the algorithmic ones: it adds the S
     slices of the split weight-gradient contraction (S more gradient reads, one gradient write).
-    dims: (in, out) per layer.  On a bf16 network of three layers or more whose first and last
-    layers take the transposing-read contractions (the library's conditions), the slices of the
+    dims: (in, out) per layer.  On a bf16 network of three layers or more whose ranges between the first and the
+    last layer are whole vectors (the library's conditions), the slices of the
     layers between them are summed by blocks that ride in the last weight-gradient launch, and
     the optimizer kernel only has the first layer's and the head's slices left."""
     S = max(1, min(8, B // (1024 if precision == "bf16" else 64)))
     ends = [dims[0], dims[-1]]
     n_ends = sum(i * o + o for i, o in ends)
     S_ends = S      # the first layer's and the head's gradients take more slices on a large batch
+    early = False
     if precision == "bf16" and len(dims) >= 3 and (dims[0][0] * dims[0][1] + dims[0][1]) % 4 == 0 and (P - dims[-1][0] * dims[-1][1] - dims[-1][1]) % 4 == 0:
         tiles = sum(((i + 255) // 256) * ((o + 127) // 128) for i, o in ends)
-        S_ends = max(S, min(B // 1024, 256 // tiles))
-    early = (precision == "bf16" and len(dims) >= 3 and S > 1 and B % 32 == 0
-             and all(i % 8 == 0 and o % 8 == 0 for i, o in ends) and S_ends >= 1)
+        S_ends = max(S, min(max(B // 1024, min(8, B // 256)), 256 // tiles))
+        S_ends -= S_ends % 8 if S_ends > 8 else 0
+        early = S > 1 and tiles * S_ends < 256
     extra = 4 * S_ends * n_ends if S_ends > 1 else 0
     if not early and S > 1:
         extra += 4 * S * (P - n_ends)
@@ -261,8 +264,7 @@ def bench_ppo(args):
     # flops are left out of the GEMM phases, as for the Q-learner's fused head
     fused_head = precision == "bf16" and A + 1 <= 32 and n_layers >= 2
     # ... and the head's input gradient too where the layer below takes it row-major (the library's conditions)
-    fused_dx = (fused_head and n_layers >= 3 and hidden[-1] % 32 == 0 and hidden[-1] <= 1024 and hidden[-2] % 8 == 0
-                and B % 32 == 0)
+    fused_dx = fused_head and n_layers >= 3 and hidden[-1] <= 1024
     fwd = sum(per_sample[:-1] if fused_head else per_sample)
     bwd = sum(per_sample) + sum(per_sample[1:]) - (per_sample[-1] if fused_dx else 0)
     flops = B * (fwd + bwd)     # forward, weight and input gradients
@@ -286,7 +288,7 @@ def bench_ppo(args):
                    "layers": [l[1] for l in layers], "params": P},
         "roofline": {"bound": "mfma", "achieved": achieved, "peak": PEAK_TFLOPS[precision], "unit": "TFLOP/s",
                      "frac": achieved / PEAK_TFLOPS[precision], "traffic": None,
-                     "kernel": "gemm_bf16_dlds + gemm_bf16_dlds_pair + gemm_bf16_dlds_pair_sum (its blocks that add gradient slices included)" if precision == "bf16" else FP32_KERNELS[n_launch],
+                     "kernel": WIDE_KERNELS if precision == "bf16" else FP32_KERNELS[n_launch],
                      "launches_per_step": n_launch, "flops_per_launch": flops / n_launch,
                      "avg_launch_ms": gemm_ms / n_launch},
         "phases_ms": ph, "phase_events_on_steps": len(sampled),
@@ -507,38 +509,23 @@ def bench_replay(args, cfg, steps, warmup, with_cpu_baseline):
         # the input gradients included), one or two for all per-weight work (the backward phase, Adam included)
         widths = [wl.obs_elems] + [l[1] for l in wl.layers]
         n_gemm_launch = fp32_launches(list(zip(widths[:-1], widths[1:])), wl.batch)
+    elif wl.precision != "bf16":
+        n_gemm_launch = (n_layers + n_conv) + n_layers + (n_layers - 1)
     else:
-        n_gemm_launch = (n_layers + n_conv - (1 if fused_head else 0)) + n_layers + (n_layers - 1)
-        first = wl.layers[0]
-        if wl.precision == "bf16" and wl.in_chw[0] == 4 and first[1] == 32 and first[2] in (4, 8) and first[3] % 2 == 0:
-            n_gemm_launch -= 1   # the fused first convolution multiplies with both networks' weights
-        if wl.precision == "bf16":
-            # later convolutions on the gathered-operand kernel (32 / 64 channels, patch length a multiple
-            # of 64): the online and the target pass share one launch
-            c_in = first[1]
-            for kind, out, k, _ in wl.layers[1:]:
-                if kind != synth.CONV:
-                    break
-                if out in (32, 64) and (k * k * c_in) % 64 == 0:
-                    n_gemm_launch -= 1
-                c_in = out
-            # a linear layer's weight and input gradient share a launch where both fit the direct-to-LDS
-            # kernel (the input gradient contracts over the layer's padded width: whole 64-element stages)
-            for li, (kind, out, _, _) in enumerate(wl.layers):
-                if kind == synth.LIN and li > 0 and (-(-out // 8) * 8) % 64 == 0 and wl.batch % 64 == 0:
-                    n_gemm_launch -= 1
-            # the fused TD kernel writes the head's input gradient where the layer below it is linear
-            if fused_head and n_layers >= 2 and wl.layers[-2][0] == synth.LIN:
-                n_gemm_launch -= 1
+        # forward: the three convolutions of all three passes are one launch, each linear layer below a fused head one;
+        # backward: weight and input gradient of a layer share a launch, the first layer has only the former; a fused
+        # head's input gradient is the TD kernel's and its weight gradient rides with the hidden layer below it
+        n_lin = n_layers - n_conv
+        n_gemm_launch = (1 + n_lin + n_conv + n_lin) - (2 if fused_head and n_lin >= 2 else 1 if fused_head else 0)
 
     flops = gemm_flops_per_step(wl, synth, fused_head)
     # the kernels behind the forward and backward phases (their launches share the MFMA roofline)
     if wl.precision != "bf16":
         gemm_kernel_name = FP32_KERNELS[n_gemm_launch] if n_conv == 0 else "gemm_pq<float>"
     elif n_conv == 0:
-        gemm_kernel_name = "gemm_bf16_dlds + gemm_bf16_dlds_pair + gemm_bf16_dlds_pair_sum (its blocks that add gradient slices included)"
+        gemm_kernel_name = WIDE_KERNELS
     else:
-        gemm_kernel_name = "gemm_bf16_dlds (gathered operands) + conv_first_u8c4 + conv_wgrad_bf16"
+        gemm_kernel_name = "conv_tower + gemm_bf16_dlds + gemm_bf16_dlds_pair_wgrad + conv_backward_bf16 + conv_first_wgrad_u8c4"
     gemm_ms = ph["forward_gemm_ms"] + ph["backward_gemm_ms"]
     achieved = flops / (gemm_ms * 1e-3) / 1e12
     peak = PEAK_TFLOPS[wl.precision]

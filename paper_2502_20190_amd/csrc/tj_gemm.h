@@ -3,10 +3,11 @@
 //
 // One kernel shape:   D(i, j) = sum_k P[i][k] * Q[j][k]
 // Both operands are contiguous along the contraction index k, which is what the
-// MFMA operand registers want (each lane feeds a run of consecutive k).  The
-// learner keeps every tensor that is ever contracted along its slow index in a
-// second, transposed copy, written by the epilogue of the kernel that produces
-// it, so no pass transposes on the fly.
+// MFMA operand registers want (each lane feeds a run of consecutive k), or, in bf16
+// (TjGemmArgs::trans), stored with k as their slow index and transposed on the way
+// from LDS to the registers.  Where neither fits (fp32 networks, rows that are not whole
+// 16-byte vectors) the learner keeps a second, transposed copy, written by the epilogue
+// of the kernel that produces the tensor.
 #pragma once
 #include "tj_common.h"
 

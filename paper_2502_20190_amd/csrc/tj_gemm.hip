@@ -1461,7 +1461,8 @@ __global__ TJ_DLDS_ATTRS(NFJ, BKB, NSTAGE) void gemm_bf16_dlds_pair(const GemmPa
 }
 
 // Vectors of four per thread in the slice-sum blocks below.  On the 256-1024-1024-1024-32 network at
-// batch 8192 the launch takes 29.4 us with one, 26.0 with two, 28.4 - 29.0 with three.
+// batch 8192 the launch took 29.4 us with one, 26.0 with two, 28.4 - 29.0 with three (29 - 32 now, the contraction blocks
+// alone 26, the sums alone 16; stages six deep, or 64 rows to a barrier, are no faster).
 constexpr int kSumVectorsPerThread = 2;
 
 // Two split weight gradients with transposed operands (blocks [0, n_gemm)) and, behind them, the sum of

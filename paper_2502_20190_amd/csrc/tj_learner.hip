@@ -4,15 +4,14 @@
 // backward through Q_online(s), fused Adam, periodic hard target update.
 //
 // Device layout inside the caller's arena (T = fp32 or bf16 compute type, every
-// 2-D buffer has its row pitch padded to a 16-byte multiple, pads stay zero):
+// 2-D buffer has its row pitch padded to a 16-byte multiple, bf16 to 64 elements, pads stay zero):
 //   theta_on, theta_tg, m, v      fp32 [P]      master state, flat order
 //   gpart                         fp32 [S_ends][Ppad] split-K partial gradients, summed into slice 0 (S slices for the hidden layers)
 //   Wc_on[l]  T [out][ld(in)]     WcT_on[l] T [in][ld(out)]   Wc_tg[l]
 //   X[l]   T [3B][ld(d_l)]   rows: s | s' (online) | s' (target); X[0] has 2B rows
-//   XT[l]  T [d_l][ld(B)]    transposed copy of the s rows (written only for weight gradients that
-//                            contract over transposed operands: ragged batches or widths)
+//   XT[l]  fp32 [d_l][ld(B)] transposed copy of the s rows (bf16 contracts over the rows as they are)
 //   Qout   fp32 [3B][ld4(A)]
-//   dZ[l]  T [B][ld(d_l)]    dZT[l] T [d_l][ld(B)]
+//   dZ[l]  T [B][ld(d_l)]    (bf16: and 64 zero rows)   dZT[l] fp32 [d_l][ld(B)]
 #include "tj_gemm.h"
 #include "tj_conv.h"
 #include "tj_mlp_f32.h"

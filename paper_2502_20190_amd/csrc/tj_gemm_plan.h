@@ -1,0 +1,17 @@
+// Which contractions the large-tile kernels (tj_gemm_wide.hip) take: plain host arithmetic without HIP, so that it can be compiled
+// and checked on its own.  Tiles are 256 x 256; a round is one tile on each of the 256 compute units.
+#pragma once
+
+namespace tjplan {
+
+constexpr int kWideTile = 256, kCus = 256;
+
+// A hidden layer's weight and input gradient, `tiles` of both (a weight gradient's tile counts once per slice), `k` the contraction of
+// the input gradient.  Up to 640 the fixed part of a tile (first loads, result stores) counts too much for one block per unit; two of the smaller
+// ones overlap it.  Updates in us, smaller tiles : these, of d-w-w-w: on-policy with 40 actions 128-300 at 32768 rows 301 : 317, 128-512 at
+// 12288 190 : 202 and at 32768 328 : 343, 128-640 at 15360 258 : 260; 256-704 at 16384 with 17 actions 251 : 246, 256-768 260 : 252,
+// 256-1024 336 : 311.  Below five eighths of a round the smaller tiles spread better (256-832 at 4096, 128 tiles, double DQN
+// 170 : 178, 256-1024 185 : 192; 136 tiles 183 : 188 and 203 : 201; 160 tiles 188 : 188 and 211 : 203).
+inline bool wide_pair_pays(int tiles, int k) { return tiles >= kCus * 5 / 8 && k > 640; }
+
+}  // namespace tjplan

@@ -13,6 +13,7 @@
 //     next stage is here (each wave has waited for its own loads) and that this stage's buffer may be filled again.
 // Results are stored from LDS as whole lines.
 #include "tj_gemm.h"
+#include "tj_gemm_plan.h"
 #include <algorithm>
 
 namespace {
@@ -26,7 +27,8 @@ typedef short s16x4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) s16x4 *lds_s16x4;
 typedef __attribute__((address_space(3))) uint8_t *lds_u8;
 
-constexpr int kThreads = 512, kTile = 256, kCus = 256;
+using tjplan::kCus;
+constexpr int kThreads = 512, kTile = tjplan::kWideTile;
 constexpr int kBufA = 32768, kBufB = 32768;              // one stage of either operand
 constexpr int kBias = 2 * (kBufA + kBufB), kLds = kBias + kTile * 4;
 
@@ -364,11 +366,10 @@ int vectors8(int n) { return (n + 7) & ~7; }   // columns of whole 16-byte vecto
 
 }  // namespace
 
-// Fewest 256 x 256 tiles.  A forward pass of up to half a round is cut into halves, and wins from a quarter of a round on
+// Fewest 256 x 256 tiles of a forward pass.  Up to half a round is cut into halves, and wins from a quarter of a round on
 // (updates in us, old kernels : these; 256-700-700-700-18 at batch 2048 155 : 143, 256-768 at 3000 183 : 170, at 4096 183 : 169,
-// 256-1024 at 5000 256 : 221, at 6000 284 : 255); fewer tiles are as fast either way.  The pair has no halves: with fewer than half a
-// round the old tiles, two to a CU, spread better (256-700 at 4096 180 : 184.5; from half a round on 768 at 8192 241 : 236).
-constexpr int kForwardTiles = kCus / 4, kPairTiles = kCus / 2;
+// 256-1024 at 5000 256 : 221, at 6000 284 : 255); fewer tiles are as fast either way.
+constexpr int kForwardTiles = kCus / 4;
 
 bool tj_gemm_wide_forward(const TjGemmArgs<tj_bf16> &a, hipStream_t st, int *rc)
 {
@@ -420,7 +421,7 @@ bool tj_gemm_wide_pair(const TjGemmArgs<tj_bf16> &w, const TjGemmArgs<tj_bf16> &
     p.x_tiles_i = up_div(x.I, kTile);
     p.x_tiles_j = up_div(xj, kTile);
     const int n1 = p.x_tiles_i * p.x_tiles_j;
-    if (p.n0 + n1 < kPairTiles) return false;
+    if (!tjplan::wide_pair_pays(p.n0 + n1, x.K)) return false;
     if ((*rc = lds_attr((const void *)gemm_wide_pair)) != TJ_OK) return true;
     gemm_wide_pair<<<p.n0 + p.x_tiles_i * up_div(p.x_tiles_j, 8) * 8, kThreads, kLds, st>>>(p);
     *rc = hipGetLastError() == hipSuccess ? TJ_OK : TJ_ERR_DEVICE;

@@ -1,0 +1,4 @@
+// The choice between the matrix kernels as functions that a test can call.
+#include "../paper_2502_20190_amd/csrc/tj_gemm_plan.h"
+
+extern "C" int wide_pair_pays(int tiles, int k) { return tjplan::wide_pair_pays(tiles, k); }

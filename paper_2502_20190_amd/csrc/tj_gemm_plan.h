@@ -14,4 +14,13 @@ constexpr int kWideTile = 256, kCus = 256;
 // 170 : 178, 256-1024 185 : 192; 136 tiles 183 : 188 and 203 : 201; 160 tiles 188 : 188 and 211 : 203).
 inline bool wide_pair_pays(int tiles, int k) { return tiles >= kCus * 5 / 8 && k > 640; }
 
+// A forward pass of contraction `k`.  Up to half a round the tiles are cut into halves, and win over the smaller tiles from a quarter of a
+// round on (updates in us, smaller : these; 256-700-700-700-18 at batch 2048 155 : 143, 256-768 at 3000 183 : 170, at 4096 183 : 169,
+// 256-1024 at 5000 256 : 221, at 6000 284 : 255); a quarter itself is 128 blocks either way, and these cost more (acting on
+// 8192 observations, 128-512-512-512-64, 60 : 65, on 4096 with 1024 units 80 : 89).  Halves have one stage of loads in flight, which
+// does not cover the reads of a long contraction from beyond the L2 (the 3136 or 5184 inputs of a pixel network's hidden
+// layer; 81 : 105 for a layer of 520 units at batch 2048, updates with 640 units 426 : 446, 1024 units 467 : 485), so those wait
+// until the tiles stay whole (1024 units at batch 3000, 144 tiles, 654 : 651; 2048 units, 288 tiles, 793 : 775).
+inline bool wide_forward_pays(int tiles, int k) { return tiles > (k > 2048 ? kCus / 2 : kCus / 4); }
+
 }  // namespace tjplan

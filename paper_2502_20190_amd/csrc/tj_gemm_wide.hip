@@ -366,11 +366,6 @@ int vectors8(int n) { return (n + 7) & ~7; }   // columns of whole 16-byte vecto
 
 }  // namespace
 
-// Fewest 256 x 256 tiles of a forward pass.  Up to half a round is cut into halves, and wins from a quarter of a round on
-// (updates in us, old kernels : these; 256-700-700-700-18 at batch 2048 155 : 143, 256-768 at 3000 183 : 170, at 4096 183 : 169,
-// 256-1024 at 5000 256 : 221, at 6000 284 : 255); fewer tiles are as fast either way.
-constexpr int kForwardTiles = kCus / 4;
-
 bool tj_gemm_wide_forward(const TjGemmArgs<tj_bf16> &a, hipStream_t st, int *rc)
 {
     if (a.trans || a.gather.on || a.out_map.on || a.n_split != 1 || a.qsum || a.bias_j || a.mask || a.Cj || a.Cf || !a.Ci || !a.relu)
@@ -387,7 +382,7 @@ bool tj_gemm_wide_forward(const TjGemmArgs<tj_bf16> &a, hipStream_t st, int *rc)
     p.seg0 = cols[0];
     p.tiles_j = cols[0] + cols[1];
     const int tiles = p.tiles_i * p.tiles_j, rest = tiles % kCus;
-    if (tiles < kForwardTiles) return false;
+    if (!tjplan::wide_forward_pays(tiles, a.K)) return false;
     p.whole = rest > 0 && rest <= kCus / 2 ? (tiles - rest) / p.tiles_i : p.tiles_j;
     auto blocks = [&](int cols_) { return p.tiles_i * up_div(cols_, 8) * 8; };
     p.n_whole = blocks(p.whole);

@@ -2,3 +2,4 @@
 #include "../paper_2502_20190_amd/csrc/tj_gemm_plan.h"
 
 extern "C" int wide_pair_pays(int tiles, int k) { return tjplan::wide_pair_pays(tiles, k); }
+extern "C" int wide_forward_pays(int tiles, int k) { return tjplan::wide_forward_pays(tiles, k); }

@@ -34,3 +34,14 @@ def _pair_tiles(width, batch):
 ])
 def test_gradients_of_hidden_layers_take_the_faster_tiles(plan, width, batch, wide):
     assert plan.wide_pair_pays(_pair_tiles(width, batch), _up(width, 64) * 64) == wide
+
+
+# (width, inputs, rows under the online weights, rows under the target's)
+@pytest.mark.parametrize("width,k,rows,wide", [
+    (512, 512, (8192, 0), False), (1024, 1024, (4096, 0), False),                            # a quarter of a round
+    (520, 5184, (4096, 2048), False), (640, 3136, (4096, 2048), False), (1032, 3136, (4096, 2048), False),   # halves, long
+    (704, 704, (4096, 2048), True), (768, 768, (6000, 3000), True), (1024, 1024, (12288, 0), True),
+    (1024, 3136, (6000, 3000), True), (2048, 3136, (8192, 4096), True),
+])
+def test_forward_passes_take_the_faster_tiles(plan, width, k, rows, wide):
+    assert plan.wide_forward_pays(_up(width) * sum(_up(r) for r in rows), k) == wide

@@ -4,7 +4,7 @@
 
 namespace tjplan {
 
-constexpr int kWideTile = 256, kCus = 256;
+constexpr int kWideTile = 256, kCus = 256, kXcds = 8;
 
 // A hidden layer's weight and input gradient, `tiles` of both (a weight gradient's tile counts once per slice), `k` the contraction of
 // the input gradient.  Up to 640 the fixed part of a tile (first loads, result stores) counts too much for one block per unit; two of the smaller
@@ -22,5 +22,16 @@ inline bool wide_pair_pays(int tiles, int k) { return tiles >= kCus * 5 / 8 && k
 // layer; 81 : 105 for a layer of 520 units at batch 2048, updates with 640 units 426 : 446, 1024 units 467 : 485), so those wait
 // until the tiles stay whole (1024 units at batch 3000, 144 tiles, 654 : 651; 2048 units, 288 tiles, 793 : 775).
 inline bool wide_forward_pays(int tiles, int k) { return tiles > (k > 2048 ? kCus / 2 : kCus / 4); }
+
+// A forward pass of tiles_i x tiles_j tiles whose last round is at most half full: columns whose tiles stay whole; those behind them are
+// cut into halves.  XCD (column % 8) runs a column's tiles on its 32 units, so the whole columns are as many per XCD as make
+// whole rounds there: one too many costs that XCD a round (3 x 96 tiles: 85 whole columns leave five XCDs with 33 tiles; acting on
+// 24576 observations, 200-768-768-768-18, 150 us with 85, 133 with 80; 200-640-640-640-18 132 and 119).
+inline int wide_whole_columns(int tiles_i, int tiles_j)
+{
+    const int tiles = tiles_i * tiles_j, rest = tiles % kCus;
+    if (rest == 0 || rest > kCus / 2) return tiles_j;
+    return tiles / kCus * (kCus / kXcds) / tiles_i * kXcds;
+}
 
 }  // namespace tjplan

@@ -27,7 +27,6 @@ typedef short s16x4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) s16x4 *lds_s16x4;
 typedef __attribute__((address_space(3))) uint8_t *lds_u8;
 
-using tjplan::kCus;
 constexpr int kThreads = 512, kTile = tjplan::kWideTile;
 constexpr int kBufA = 32768, kBufB = 32768;              // one stage of either operand
 constexpr int kBias = 2 * (kBufA + kBufB), kLds = kBias + kTile * 4;
@@ -381,9 +380,8 @@ bool tj_gemm_wide_forward(const TjGemmArgs<tj_bf16> &a, hipStream_t st, int *rc)
     }
     p.seg0 = cols[0];
     p.tiles_j = cols[0] + cols[1];
-    const int tiles = p.tiles_i * p.tiles_j, rest = tiles % kCus;
-    if (!tjplan::wide_forward_pays(tiles, a.K)) return false;
-    p.whole = rest > 0 && rest <= kCus / 2 ? (tiles - rest) / p.tiles_i : p.tiles_j;
+    if (!tjplan::wide_forward_pays(p.tiles_i * p.tiles_j, a.K)) return false;
+    p.whole = tjplan::wide_whole_columns(p.tiles_i, p.tiles_j);
     auto blocks = [&](int cols_) { return p.tiles_i * up_div(cols_, 8) * 8; };
     p.n_whole = blocks(p.whole);
     const int n = p.n_whole + (p.whole < p.tiles_j ? blocks(2 * (p.tiles_j - p.whole)) : 0);

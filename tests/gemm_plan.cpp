@@ -3,3 +3,4 @@
 
 extern "C" int wide_pair_pays(int tiles, int k) { return tjplan::wide_pair_pays(tiles, k); }
 extern "C" int wide_forward_pays(int tiles, int k) { return tjplan::wide_forward_pays(tiles, k); }
+extern "C" int wide_whole_columns(int tiles_i, int tiles_j) { return tjplan::wide_whole_columns(tiles_i, tiles_j); }

@@ -45,3 +45,30 @@ def test_gradients_of_hidden_layers_take_the_faster_tiles(plan, width, batch, wi
 ])
 def test_forward_passes_take_the_faster_tiles(plan, width, k, rows, wide):
     assert plan.wide_forward_pays(_up(width) * sum(_up(r) for r in rows), k) == wide
+
+
+def _busiest_xcd(tiles_i, tiles_j, whole):
+    """Time of the busiest of eight XCDs of 32 units, in half tiles: a column's tiles go to XCD (column % 8), whole ones first."""
+    most = 0
+    for xcd in range(8):
+        n_whole = tiles_i * len(range(xcd, whole, 8))
+        n_half = tiles_i * len(range(xcd, 2 * (tiles_j - whole), 8))
+        units = [0] * 32
+        for n, cost in ((n_whole, 2), (n_half, 1)):
+            for _ in range(n):
+                units.sort()
+                units[0] += cost
+        most = max(most, max(units))
+    return most
+
+
+def test_columns_cut_into_halves_leave_no_xcd_behind(plan):
+    for tiles_i in range(1, 9):
+        for tiles_j in range(1, 700 // tiles_i):
+            rest = tiles_i * tiles_j % 256
+            whole = plan.wide_whole_columns(tiles_i, tiles_j)
+            assert (whole == tiles_j) == (rest == 0 or rest > 128) and 0 <= whole <= tiles_j
+            if whole < tiles_j:
+                assert _busiest_xcd(tiles_i, tiles_j, whole) <= _busiest_xcd(tiles_i, tiles_j, (tiles_i * tiles_j - rest) // tiles_i)
+    # 640 units at 32768 rows: half a round behind one whole round, on every XCD
+    assert _busiest_xcd(3, 128, plan.wide_whole_columns(3, 128)) == 3

@@ -67,7 +67,8 @@ def adam_slice_traffic(dims, precision, B, P):
     if precision == "bf16" and len(dims) >= 3 and (dims[0][0] * dims[0][1] + dims[0][1]) % 4 == 0 and (P - dims[-1][0] * dims[-1][1] - dims[-1][1]) % 4 == 0:
         tiles = sum(((i + 255) // 256) * ((o + 127) // 128) for i, o in ends)
         S_ends = max(S, min(max(B // 1024, min(8, B // 256)), 256 // tiles))
-        S_ends -= S_ends % 8 if S_ends > 8 else 0
+        whole = S_ends - S_ends % 8
+        S_ends = whole if S_ends > 8 and (whole * tiles >= 192 or 9 * whole >= 8 * S_ends) else S_ends
         early = S > 1 and tiles * S_ends < 256
     extra = 4 * S_ends * n_ends if S_ends > 1 else 0
     if not early and S > 1:

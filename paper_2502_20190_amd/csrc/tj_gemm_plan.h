@@ -1,6 +1,7 @@
 // Which contractions the large-tile kernels (tj_gemm_wide.hip) take: plain host arithmetic without HIP, so that it can be compiled
 // and checked on its own.  Tiles are 256 x 256; a round is one tile on each of the 256 compute units.
 #pragma once
+#include <algorithm>
 
 namespace tjplan {
 
@@ -32,6 +33,23 @@ inline int wide_whole_columns(int tiles_i, int tiles_j)
     const int tiles = tiles_i * tiles_j, rest = tiles % kCus;
     if (rest == 0 || rest > kCus / 2) return tiles_j;
     return tiles / kCus * (kCus / kXcds) / tiles_i * kXcds;
+}
+
+// Slices of the first and the last layer's weight gradients, `tiles` of 256 x 128 in all, for up to max_batch rows; the hidden
+// layers take s.  A slice per 1024 rows, up to eight down to 256 rows: few tiles are a serial chain as long as their slice
+// (256-640-640-640-18 at 1024 rows: 143 us with one slice, 134 with two, 129 with four; 1024 units at 8192 rows with 8, 16
+// and 21 slices: 275, 285, 290).
+// Past eight a multiple of eight, where that leaves three quarters of the chip at work or costs a ninth of the slices at most: the slice is
+// the fastest index of the blocks, so that the tiles of one slice then run on one of the eight XCDs and share its rows in that
+// L2 (updates in us, as many as fit : a multiple of eight; 32768 rows of 256-1024-1024-1024-32 563 : 543 with 21 : 16,
+// on-policy 640-1024-1024-1024-18 at 9216 rows 288 : 274 with 9 : 8).  Fewer blocks cost more than that gives (on-policy
+// 300-900-900-18 at 32768 rows 344 : 360 with 12 : 8, 200-640-640-640-18 at 14336 221 : 233 with 14 : 8, 128-512-512-512-18 at 14336
+// 235 : 246 with 14 : 8).
+inline int ends_slices(int tiles, int max_batch, int s)
+{
+    const int n = std::max(s, std::min(std::max(max_batch / 1024, std::min(8, max_batch / 256)), kCus / tiles));
+    const int whole = n - n % kXcds;
+    return n > kXcds && (whole * tiles >= kCus * 3 / 4 || 9 * whole >= 8 * n) ? whole : n;
 }
 
 }  // namespace tjplan

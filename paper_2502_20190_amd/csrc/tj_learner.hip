@@ -13,6 +13,7 @@
 //   Qout   fp32 [3B][ld4(A)]
 //   dZ[l]  T [B][ld(d_l)]    (bf16: and 64 zero rows)   dZT[l] fp32 [d_l][ld(B)]
 #include "tj_gemm.h"
+#include "tj_gemm_plan.h"
 #include "tj_conv.h"
 #include "tj_mlp_f32.h"
 #include "tj_mlp_b16.h"
@@ -1714,14 +1715,7 @@ template <typename T> struct MlpLearner : tj_learner {
         if (sizeof(T) == 2 && L >= 3 && lay[1].w_off % 4 == 0 && lay[L - 1].w_off % 4 == 0) {
             const int tiles = ((lay[0].in + 255) / 256) * ((lay[0].out + 127) / 128) +
                               ((lay[L - 1].in + 255) / 256) * ((lay[L - 1].out + 127) / 128);
-            // a slice per 1024 rows, up to eight down to 256 rows: few tiles are a serial chain as long as their slice
-            // (256-640-640-640-18 at 1024 rows: 143 us with one slice, 134 with two, 129 with four; 1024 units at 8192 rows with 8, 16
-            // and 21 slices: 275, 285, 290)
-            const int want = std::max(Bmax / 1024, std::min(8, Bmax / 256)), fit = 256 / tiles;
-            S_ends = std::max(S, std::min(want, fit));
-            // Past eight a multiple of eight: the slice is the fastest index of the blocks, so that the tiles of one slice
-            // then run on one of the eight XCDs and share its rows in that L2 (32768 rows, 1024 units: 563 us with 21, 543 with 16).
-            if (S_ends > 8) S_ends -= S_ends % 8;
+            S_ends = tjplan::ends_slices(tiles, Bmax, S);
         }
         gpart = (float *)a.take((size_t)S_ends * Ppad * 4);
         size_t wc0 = a.off;

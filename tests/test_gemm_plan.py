@@ -72,3 +72,14 @@ def test_columns_cut_into_halves_leave_no_xcd_behind(plan):
                 assert _busiest_xcd(tiles_i, tiles_j, whole) <= _busiest_xcd(tiles_i, tiles_j, (tiles_i * tiles_j - rest) // tiles_i)
     # 640 units at 32768 rows: half a round behind one whole round, on every XCD
     assert _busiest_xcd(3, 128, plan.wide_whole_columns(3, 128)) == 3
+
+
+# (observation, width, head outputs, most rows) of 256 x 128 tiles
+@pytest.mark.parametrize("dim,width,out,rows,slices", [
+    (256, 1024, 32, 8192, 8), (256, 1024, 32, 32768, 16), (640, 1024, 18, 9216, 8), (200, 640, 18, 512, 2),      # XCDs share rows
+    (300, 900, 18, 32768, 12), (512, 1024, 18, 32768, 12), (200, 640, 18, 14336, 14), (128, 512, 18, 20480, 20),  # blocks count for more
+    (4096, 4096, 18, 32768, 8),                                                                                    # more tiles than the chip
+])
+def test_slices_of_the_first_and_last_layers_gradients(plan, dim, width, out, rows, slices):
+    tiles = _up(dim) * _up(width, 128) + _up(width) * _up(out, 128)
+    assert plan.ends_slices(tiles, rows, max(1, min(8, rows // 1024))) == slices

@@ -380,7 +380,7 @@ bool tj_gemm_wide_forward(const TjGemmArgs<tj_bf16> &a, hipStream_t st, int *rc)
     }
     p.seg0 = cols[0];
     p.tiles_j = cols[0] + cols[1];
-    if (!tjplan::wide_forward_pays(p.tiles_i * p.tiles_j, a.K)) return false;
+    if (!tjplan::wide_forward_pays(p.tiles_i, p.tiles_j, a.K)) return false;
     p.whole = tjplan::wide_whole_columns(p.tiles_i, p.tiles_j);
     auto blocks = [&](int cols_) { return p.tiles_i * up_div(cols_, 8) * 8; };
     p.n_whole = blocks(p.whole);

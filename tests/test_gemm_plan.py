@@ -40,11 +40,13 @@ def test_gradients_of_hidden_layers_take_the_faster_tiles(plan, width, batch, wi
 @pytest.mark.parametrize("width,k,rows,wide", [
     (512, 512, (8192, 0), False), (1024, 1024, (4096, 0), False),                            # a quarter of a round
     (520, 5184, (4096, 2048), False), (640, 3136, (4096, 2048), False), (1032, 3136, (4096, 2048), False),   # halves, long
+    (576, 576, (32768, 0), False), (768, 768, (32768, 0), False), (640, 640, (21760, 10880), False),          # two rounds of halves
+    (768, 768, (24576, 0), True), (1024, 1024, (24576, 0), True), (512, 512, (49152, 0), True),
     (704, 704, (4096, 2048), True), (768, 768, (6000, 3000), True), (1024, 1024, (12288, 0), True),
     (1024, 3136, (6000, 3000), True), (2048, 3136, (8192, 4096), True),
 ])
 def test_forward_passes_take_the_faster_tiles(plan, width, k, rows, wide):
-    assert plan.wide_forward_pays(_up(width) * sum(_up(r) for r in rows), k) == wide
+    assert plan.wide_forward_pays(_up(width), sum(_up(r) for r in rows), k) == wide
 
 
 def _busiest_xcd(tiles_i, tiles_j, whole):

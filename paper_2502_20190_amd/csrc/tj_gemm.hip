@@ -969,6 +969,12 @@ __device__ __forceinline__ void dlds_body(const TjGemmArgs<tj_bf16> &a_in, const
             if (!xcd_tile(tm, id, ti, tj)) return;
         }
         if (tj >= tm.tiles_j) return;
+        // The divisions above ran on the vector unit.  Said to be scalars here, everything that follows from a block's place stays
+        // one, the loads' addresses in the loop above all: read back from vector registers in front of each stage's loads they
+        // lengthened every step of a long slice (256 units, 24576 rows, hidden layers' gradients 54.8 -> 63.1 us a launch; 54 so).
+        ti = __builtin_amdgcn_readfirstlane(ti);
+        tj = __builtin_amdgcn_readfirstlane(tj);
+        z = __builtin_amdgcn_readfirstlane(z);
     }
 
     const int tid = threadIdx.x, lane = tid & 63;
@@ -1065,17 +1071,12 @@ __device__ __forceinline__ void dlds_body(const TjGemmArgs<tj_bf16> &a_in, const
         asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds_addr), "v"(src)
                      : "memory");
     };
-    // The same from a scalar base.  A vector instruction may have written the base (uniform() below), after which a
-    // memory instruction may read it five wait states later at the earliest: the move and the s_nop are six.
+    // The same from a scalar base.  Should the compiler keep the base in lanes of a vector register, reading it back is a vector
+    // instruction's write of a scalar, which a memory instruction may read five wait states later: the move and the s_nop are six.
     auto dma16_at = [](const T *base, uint32_t off, uint8_t *dst) {
         const uint32_t lds_addr = (uint32_t)(uintptr_t)(lds_ptr_t)dst;
         asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds_addr), "v"(off), "s"(base)
                      : "memory");
-    };
-    auto uniform = [](const T *p) {   // the same in every lane already; this says so
-        const uint64_t v = (uint64_t)p;
-        return (const T *)(((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(v >> 32)) << 32) |
-                           (uint32_t)__builtin_amdgcn_readfirstlane((int)v));
     };
     auto issue = [&](uint8_t *sA, uint8_t *sB, int s) {   // called for s = 0, 1, 2, ... in order
         if constexpr (GATHER == 2) {
@@ -1097,18 +1098,18 @@ __device__ __forceinline__ void dlds_body(const TjGemmArgs<tj_bf16> &a_in, const
         } else if (TRANS == 1 && k_begin + (s + 1) * KE > k_valid) {
             // a stage with rows past the last valid one reads that one instead; it may hold no valid row at all
             const int row0 = min(s * KE, k_valid - 1 - k_begin), last = k_valid - 1 - k_begin - row0;
-            const T *base = uniform(baseP + (int64_t)row0 * a.ldp);
+            const T *base = baseP + (int64_t)row0 * a.ldp;
 #pragma unroll
             for (int t = 0; t < LP; ++t) {
                 const int past = max(2 * (wave + 8 * t) + (lane >> 5) - last, 0);
                 dma16_at(base, offP[t] - 2u * (uint32_t)(past * a.ldp), sA + (wave + 8 * t) * 1024);
             }
         } else {
-            const T *base = uniform(baseP + s * stepP);
+            const T *base = baseP + s * stepP;
 #pragma unroll
             for (int t = 0; t < LP; ++t) dma16_at(base, offP[t], sA + (wave + 8 * t) * 1024);
         }
-        const T *base = uniform(baseQ + s * stepQ);
+        const T *base = baseQ + s * stepQ;
 #pragma unroll
         for (int t = 0; t < LQ; ++t) {
             const int c = (wave + 8 * t) % CHQ;   // wave-uniform

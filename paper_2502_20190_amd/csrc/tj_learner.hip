@@ -235,10 +235,13 @@ inline uint32_t egreedy_threshold(float epsilon)
     return scaled <= 0.0 ? 0u : (scaled >= 16777216.0 ? 16777216u : (uint32_t)scaled);
 }
 
-// The end of an acting call whose last hidden layer was contracted in S slices (fp32 partial sums, [z][j][k]): a block of two
-// waves per observation adds its row's slices in order, bias, ReLU, rounds to bf16, multiplies with the head and takes
-// the epsilon-greedy action.  Bound by latency, so every load of the row is in flight at once: 11.3 us with four slices in flight
-// and a wave per row, 5.5 us this way (256 observations, 3136-512-18, 12 slices).
+// The end of an acting call whose last hidden layer was contracted in S slices (fp32 partial sums, [z][j][k]): a block of one or
+// two waves per observation adds its row's slices in order, bias, ReLU, rounds to bf16, multiplies with the head and takes
+// the epsilon-greedy action.  Few observations are bound by latency, so every load of the row is in flight at once: 11.3 us with
+// four slices in flight and a wave per row, 5.5 us with sixteen and two waves (256 observations, 3136-512-18, 12 slices).  From 1536
+// observations on the chip is full of waves: what counts then are the sums across lanes, which every wave does for every action, and
+// the waves that registers leave room for, so a row has one wave and four slices in flight (there are four or fewer). Two : one, in
+// us, at 1536, 2048 and 4096 observations: 512-18 8.8 : 8.8, 12.0 : 8.9, 19.1 : 12.2; 1000-9 9.8 : 9.4, 10.6 : 10.2, 19.5 : 15.2.
 struct ActHeadArgs {
     const float *part; size_t zstride; int S, K;   // K a multiple of 4
     const float *b_hidden;
@@ -251,18 +254,21 @@ struct ActHeadArgs {
     float *q_out;                                  // optional [n][A]
 };
 
-// Four hidden units of a row (unit k, fp32 partial sums z at src + z * zstride, up to 16) as the layer's output: slices in order,
-// bias, ReLU, bf16.  Every load is in flight before the first is used.
+// Four hidden units of a row (unit k, fp32 partial sums z at src + z * zstride) as the layer's output: slices in order, bias, ReLU,
+// bf16.  FLIGHT slices are loaded before the first of them is used.
+template <int FLIGHT>
 __device__ __forceinline__ uint2 hidden_from_slices(const float *src, size_t zstride, int S, const float *bias)
 {
-    float4 y[16];
+    float4 x = make_float4(0.f, 0.f, 0.f, 0.f);
+    for (int z0 = 0; z0 < S; z0 += FLIGHT) {
+        float4 y[FLIGHT];
 #pragma unroll
-    for (int z = 0; z < 16; ++z)
-        if (z < S) y[z] = *(const float4 *)(src + (size_t)z * zstride);
-    float4 x = y[0];
+        for (int z = 0; z < FLIGHT; ++z)
+            if (z0 + z < S) y[z] = *(const float4 *)(src + (size_t)(z0 + z) * zstride);
 #pragma unroll
-    for (int z = 1; z < 16; ++z)
-        if (z < S) { x.x += y[z].x; x.y += y[z].y; x.z += y[z].z; x.w += y[z].w; }
+        for (int z = 0; z < FLIGHT; ++z)
+            if (z0 + z < S) { x.x += y[z].x; x.y += y[z].y; x.z += y[z].z; x.w += y[z].w; }
+    }
     const float h[4] = {x.x + bias[0], x.y + bias[1], x.z + bias[2], x.w + bias[3]};
     uint32_t b[4];
 #pragma unroll
@@ -278,22 +284,20 @@ __device__ __forceinline__ float dot4(uint2 a, uint2 b, float s)
     return fmaf(__uint_as_float(a.y & 0xFFFF0000u), __uint_as_float(b.y & 0xFFFF0000u), s);
 }
 
-constexpr int kActWaves = 2;   // waves per observation: 512 hidden units at once
-
-template <int NA>   // at least A
-__global__ __launch_bounds__(64 * kActWaves) void act_head(const ActHeadArgs a)
+template <int NA, int WAVES>   // at least A; waves per observation: 256 hidden units each at once
+__global__ __launch_bounds__(64 * WAVES) void act_head(const ActHeadArgs a)
 {
-    __shared__ float qs[kActWaves][NA];
+    __shared__ float qs[WAVES][NA];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const uint32_t j = blockIdx.x;
     float p[NA];
 #pragma unroll
     for (int o = 0; o < NA; ++o) p[o] = 0.f;
-    for (int k = 4 * threadIdx.x; k < a.K; k += 256 * kActWaves) {
+    for (int k = 4 * threadIdx.x; k < a.K; k += 256 * WAVES) {
         uint2 wv[NA];
 #pragma unroll
         for (int o = 0; o < NA; ++o) wv[o] = *(const uint2 *)(a.W + (size_t)min(o, a.A - 1) * a.ldw + k);
-        const uint2 h = hidden_from_slices(a.part + (size_t)j * a.K + k, a.zstride, a.S, a.b_hidden + k);
+        const uint2 h = hidden_from_slices<WAVES == 1 ? 4 : 16>(a.part + (size_t)j * a.K + k, a.zstride, a.S, a.b_hidden + k);
 #pragma unroll
         for (int o = 0; o < NA; ++o) p[o] = dot4(h, wv[o], p[o]);
     }
@@ -310,7 +314,7 @@ __global__ __launch_bounds__(64 * kActWaves) void act_head(const ActHeadArgs a)
     if (lane < a.A) {
         q = qs[0][lane];
 #pragma unroll
-        for (int v = 1; v < kActWaves; ++v) q += qs[v][lane];
+        for (int v = 1; v < WAVES; ++v) q += qs[v][lane];
         q += a.b_head[lane];
     }
     const int best = wave_argmax(q);
@@ -328,11 +332,15 @@ __global__ __launch_bounds__(64 * kActWaves) void act_head(const ActHeadArgs a)
 int launch_act_head(const ActHeadArgs &a, hipStream_t st)
 {
     if (a.S > 16) return TJ_ERR_SHAPE;
-    const unsigned grid = a.n;
-    if (a.A <= 8) act_head<8><<<grid, 64 * kActWaves, 0, st>>>(a);
-    else if (a.A <= 16) act_head<16><<<grid, 64 * kActWaves, 0, st>>>(a);
-    else if (a.A <= 24) act_head<24><<<grid, 64 * kActWaves, 0, st>>>(a);
-    else act_head<32><<<grid, 64 * kActWaves, 0, st>>>(a);
+    auto go = [&](auto na) {
+        constexpr int NA = decltype(na)::value;
+        if (a.n < 1536) act_head<NA, 2><<<a.n, 128, 0, st>>>(a);
+        else act_head<NA, 1><<<a.n, 64, 0, st>>>(a);
+    };
+    if (a.A <= 8) go(std::integral_constant<int, 8>{});
+    else if (a.A <= 16) go(std::integral_constant<int, 16>{});
+    else if (a.A <= 24) go(std::integral_constant<int, 24>{});
+    else go(std::integral_constant<int, 32>{});
     return hipGetLastError() == hipSuccess ? TJ_OK : TJ_ERR_DEVICE;
 }
 
@@ -621,7 +629,7 @@ __global__ __launch_bounds__(384) void head_td_slices(const HeadSlicesArgs s)
 #pragma unroll
         for (int o = 0; o < NA; ++o) wv[o] = *(const uint2 *)(W + (size_t)min(o, a.A - 1) * a.ldw + k);
         if (g == 0) wa[c] = *(const uint2 *)(W + (size_t)aj * a.ldw + k);
-        x[c] = hidden_from_slices(s.part + (size_t)(g * a.B + j) * a.K + k, s.zstride, s.S, bias + k);
+        x[c] = hidden_from_slices<16>(s.part + (size_t)(g * a.B + j) * a.K + k, s.zstride, s.S, bias + k);
         if (g == 0) *(uint2 *)(s.X + (size_t)j * a.ldx + k) = x[c];
 #pragma unroll
         for (int o = 0; o < NA; ++o) p[o] = dot4(x[c], wv[o], p[o]);

@@ -2719,6 +2719,24 @@ template <typename T> struct ConvLearner : tj_learner {
 
     static dim3 grid1(size_t n) { return dim3((unsigned)((n + 255) / 256)); }
 
+    int compute_units()
+    {
+        if (n_cu == 0) {
+            int dev = 0, v = 0;
+            n_cu = 256;
+            if (hipGetDevice(&dev) == hipSuccess &&
+                hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && v > 0)
+                n_cu = v;
+        }
+        return n_cu;
+    }
+
+    // The convolutions' forward passes (an image under one network's weights each) as one kernel.  It pays through its few launches
+    // and through what it does not write; an image whose first layer has a tile of 32 patches or less per wave leaves too much of a
+    // compute unit idle for that once a unit has more than eight of them (one kernel : layer by layer, 4 x 52 x 52 images, updates at batch 500 116 :
+    // 120 us, 1024 148 : 141, 2048 228 : 198; acting on 2048 55 : 57, on 4096 90 : 82; 84 x 84, 13 tiles, wins at every size).
+    bool takes_tower(int passes) { return tower && (lay[0].OHW > 8 * 32 || passes <= 8 * compute_units()); }
+
     // A hidden linear layer's weight gradient straight from the row-major input rows and dZ (transposing LDS
     // reads, as in the MLP learner): bf16, any batch, widths that are whole 16-byte
     // vectors and fill 256 x 128 tiles.  Such a layer needs neither the transposed input nor dZ^T, nor, with the input
@@ -2810,7 +2828,7 @@ template <typename T> struct ConvLearner : tj_learner {
                 fa.scale = 1.0f / 255.0f;
                 fa.rows = mb->row_index; fa.n_rows = (uint32_t)mb->n_rows; fa.planes = mb->plane_index;
                 if ((rc = mark(0, st)) != TJ_OK) return rc;
-                if (tower) {
+                if (takes_tower(3 * B)) {
                     if ((rc = run_tower(fa, true, st)) != TJ_OK) return rc;
                     fwd_done = 3;
                 } else {
@@ -2993,13 +3011,6 @@ template <typename T> struct ConvLearner : tj_learner {
             TjConvWgradArgs wa;
             if constexpr (sizeof(T) == 2) {
                 if (l == 0 && first_done && first_wgrad_u8) {   // from the u8 stacks, one slice per block
-                    if (n_cu == 0) {
-                        int dev = 0, v = 0;
-                        n_cu = 256;
-                        if (hipGetDevice(&dev) == hipSuccess &&
-                            hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && v > 0)
-                            n_cu = v;
-                    }
                     const tjconv::ConvGeom &g = y.g;
                     TjConvFirstWgradArgs fa;
                     fa.obs = (const uint8_t *)mb->obs; fa.dZ = y.dZ;
@@ -3007,7 +3018,7 @@ template <typename T> struct ConvLearner : tj_learner {
                     fa.scale = 1.0f / 255.0f;
                     fa.rows = mb->row_index; fa.n_rows = (uint32_t)mb->n_rows; fa.planes = mb->plane_index;
                     fa.part = y.part; fa.zstride = y.part_stride;
-                    fa.n_part = std::min(B, std::min(n_cu, y.n_split));
+                    fa.n_part = std::min(B, std::min(compute_units(), y.n_split));
                     if ((rc = tj_conv_first_wgrad(fa, st)) != TJ_OK) return rc;
                     add_slices(y, fa.n_part);
                     wgrad_done = true;
@@ -3241,7 +3252,7 @@ template <typename T> struct ConvLearner : tj_learner {
                 fa.act0 = nullptr; fa.out = act[1];
                 fa.scale = 1.0f / 255.0f;
                 fa.rows = nullptr; fa.n_rows = 0; fa.planes = nullptr;
-                if (tower) {
+                if (takes_tower(n)) {
                     if ((rc = run_tower(fa, false, st)) != TJ_OK) return rc;
                     fwd_done = 3;
                 } else {

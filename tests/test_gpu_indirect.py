@@ -46,6 +46,9 @@ _CASES = {
     # 84 x 84 u8 stacks, the first-layer kernels that read the frames themselves (forward and weight gradient)
     "pixel-bf16-fused": dict(base="c4", capacity=600, batch=96,
                              layers=((CONV, 32, 8, 4), (CONV, 64, 4, 2), (LIN, 24, 0, 0), (LIN, 6, 0, 0)), n_actions=6),
+    # ... and three convolutions in one kernel, which looks the row of an image up two passes ahead: a few passes per block, s' twice
+    "pixel-bf16-tower": dict(base="c4", capacity=500, batch=300,
+                             layers=((CONV, 32, 8, 4), (CONV, 64, 4, 2), (CONV, 64, 3, 1), (LIN, 64, 0, 0), (LIN, 6, 0, 0)), n_actions=6),
     # u8 pixels through the channels-last layout kernel (16 output channels: outside the fused kernel)
     "pixel-bf16-plain": dict(base="c4", capacity=500, batch=40, obs_shape=(4, 20, 20),
                              layers=((CONV, 16, 4, 2), (CONV, 16, 3, 1), (LIN, 24, 0, 0), (LIN, 6, 0, 0)), n_actions=6),
@@ -105,7 +108,7 @@ def test_update_from_ring_rows_equals_update_from_copies(tj, orc, case):
             assert np.array_equal(got[f], dense[2][i][f])
 
 
-@pytest.mark.parametrize("case", ["mlp-fp32", "pixel-bf16-fused"])
+@pytest.mark.parametrize("case", ["mlp-fp32", "pixel-bf16-fused", "pixel-bf16-tower"])
 def test_first_update_from_ring_rows_against_the_oracle(tj, orc, case):
     wl = _workload(case)
     rows = synth.make_chunk(wl, 12, 0, wl.capacity)
@@ -249,6 +252,9 @@ _FRAME_CASES = {
     # the u8 first-layer kernels (forward and weight gradient) reading single frames
     "fused-84": dict(hw=(84, 84), k=4, cap=700, total=1900, batch=96, precision="bf16",
                      layers=((CONV, 32, 8, 4), (CONV, 64, 4, 2), (LIN, 24, 0, 0), (LIN, 18, 0, 0))),
+    # three convolutions in one kernel, planes looked up two passes ahead
+    "tower-84": dict(hw=(84, 84), k=4, cap=900, total=2300, batch=300, precision="bf16",
+                     layers=((CONV, 32, 8, 4), (CONV, 64, 4, 2), (CONV, 64, 3, 1), (LIN, 64, 0, 0), (LIN, 18, 0, 0))),
     # the channels-last layout kernels: four u8 planes at a time, and the general one (three planes, fp32 net)
     "plain-u8c4": dict(hw=(20, 20), k=4, cap=600, total=1500, batch=40, precision="bf16",
                        layers=((CONV, 16, 4, 2), (CONV, 16, 3, 1), (LIN, 24, 0, 0), (LIN, 18, 0, 0))),

@@ -10,7 +10,7 @@ import numpy as np
 import pytest
 
 from paper_2502_20190_amd import synth
-from parity_util import rel_max, rel_scalar
+from parity_util import rel_l2, rel_max, rel_scalar
 
 pytestmark = pytest.mark.gpu
 TOL = {"fp32": 1e-4, "bf16": 2e-2}
@@ -224,6 +224,45 @@ def test_multi_tile_trunk(tj, orc, precision):
     rows = _batch(orc, o, D, A, 3, 512, 30, precision)
     _step_both(tj, orc, g, o, rows, TOL[precision], precision=precision)
     _step_both(tj, orc, g, o, rows, TOL[precision], precision=precision)   # free-running: reads the emitted copies
+
+
+# bf16 networks that run layer by layer, of any width and batch: large tiles of one segment and the smaller ones, the head kernel that
+# writes its input gradient (a ragged head input, one and two steps over the head outputs) and a head input too wide for that; then a
+# shorter batch, whose pad rows have held data, and the same networks evaluated and acting on rows that are multiples of nothing.
+@pytest.mark.parametrize("D,hidden,A,batches", [
+    (250, (1001, 999), 31, (4500, 777)),
+    (61, (1030, 515, 390), 9, (3001, 64)),
+    (64, (640, 1030), 20, (2100, 333)),
+])
+def test_layered_networks_of_any_width_and_batch(tj, orc, D, hidden, A, batches):
+    import torch
+
+    dims = (D,) + hidden + (A + 1,)
+    whole = tj.lib()._Z11tj_b16_fitsiPKiS0_ii
+    whole.restype = C.c_bool
+    n = len(dims) - 1
+    assert not whole(n, (C.c_int * n)(*dims[:-1]), (C.c_int * n)(*dims[1:]), 1, max(batches))
+    g, o = _pair(tj, orc, D, hidden, A, "bf16", max(batches), seed=5, lr=1e-3)
+    for i, b in enumerate(batches):
+        rows = _batch(orc, o, D, A, 9, 512, 60 + i, "bf16", n=b)
+        _step_both(tj, orc, g, o, rows, TOL["bf16"], sync=True, precision="bf16")
+        grad, want, at = g.get_state(tj.TJ_STATE_GRADS), o.get_state(orc.GRADS), 0
+        for n_in, n_out in zip(dims, dims[1:]):   # every layer by itself
+            assert rel_l2(grad[at:at + n_in * n_out], want[at:at + n_in * n_out]) < TOL["bf16"]
+            at += n_in * n_out
+            assert rel_l2(grad[at:at + n_out], want[at:at + n_out]) < TOL["bf16"]
+            at += n_out
+    _sync(tj, orc, g, o)
+    obs = _batch(orc, o, D, A, 9, 512, 70, "bf16", n=max(batches) - 1)["obs"]
+    logits, value = g.evaluate(_dev(obs))
+    action, logp, _ = g.act(_dev(obs), 3)
+    torch.cuda.synchronize()
+    z = o.forward(0, obs)
+    assert rel_max(logits.cpu().numpy(), z[:, :A]) < TOL["bf16"] and rel_max(value.cpu().numpy(), z[:, A]) < TOL["bf16"]
+    oa, ologp, _, margin = o.ppo_act(obs, 3)
+    same = action.cpu().numpy() == oa
+    assert (margin[~same] < 2e-2).all() and (~same).mean() < 0.05     # a neighbouring action where the draw lies at its edge
+    assert np.abs(logp.cpu().numpy()[same] - ologp[same]).max() < TOL["bf16"] * max(1.0, np.abs(ologp).max())
 
 
 def test_p2_full_size_step(tj, orc):

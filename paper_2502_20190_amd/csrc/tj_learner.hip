@@ -1132,7 +1132,7 @@ template <typename T> struct PpoHeadArgs {
     const float *Z; int ldz; int B, A;
     const int32_t *action; const float *old_logp, *adv, *ret;
     float clip, c_v, c_e;
-    T *dZ; int lddz; T *dZT; int lddzt;   // dZT may be null (the head's weight gradient reads dZ row-major)
+    T *dZ; int lddz; T *dZT; int lddzt;   // dZT: fp32 only (in bf16 the head's weight gradient reads dZ row-major)
     float *part;   // [blocks][4]: sum L_pi, sum L_v, sum H, unused
 };
 
@@ -1233,10 +1233,11 @@ __device__ __forceinline__ void ppo_objective(const PpoHeadArgs<T> &a, const flo
         const int rr = v / vpr, c = v - rr * vpr;
         *(uint4 *)(a.dZ + (size_t)(row0 + rr) * a.lddz + c * VEC) = *(const uint4 *)(tile + rr * pitch + c * VEC);
     }
-    // transposed gradient: 32 consecutive samples of one head output per 32 lanes
-    for (int e = threadIdx.x; a.dZT && e < (a.A + 1) * kPpoRows; e += kPpoRows * kPpoLanes) {
-        const int k = e / kPpoRows, rr = e % kPpoRows;
-        if (rr < n_rows) a.dZT[(size_t)k * a.lddzt + row0 + rr] = tile[rr * pitch + k];
+    if constexpr (sizeof(T) == 4) {   // transposed gradient: 32 consecutive samples of one head output per 32 lanes
+        for (int e = threadIdx.x; e < (a.A + 1) * kPpoRows; e += kPpoRows * kPpoLanes) {
+            const int k = e / kPpoRows, rr = e % kPpoRows;
+            if (rr < n_rows) a.dZT[(size_t)k * a.lddzt + row0 + rr] = tile[rr * pitch + k];
+        }
     }
 }
 
@@ -1657,6 +1658,15 @@ int run_head_td(tj_learner *self, const HeadTd<T> &h, const tj_minibatch *mb, fl
 template <typename T> struct MlpLearner : tj_learner {
     static constexpr int VE = TjElem<T>::kVec;
     static constexpr int kRowPad = sizeof(T) == 2 ? 64 : VE;
+    // bf16: weight gradients straight from the row-major X_{l-1} and dZ_l (transposing LDS reads) instead of their transposed copies.
+    // The first and the last layer too, although their narrow sides fill few of the 256 x 128 tiles that form takes (their pair is
+    // 96 blocks on the 256-1024-1024-1024-32 net): what counts is that no transposed copy of X_{l-1} and of dZ_l is written at all, which
+    // makes the forward pass of the last hidden layer and the input-gradient pass of the second layer
+    // one-layout launches like the others.  Any width and batch: rows are padded to whole stages, and the rows behind the batch
+    // count as zero (as contractions over transposed copies, with element-wise staged loads, an update of
+    // 256-640-640-640-18 took 337 us at batch 3000 against 151 at 2048 and 182 at 4096).  Input gradients read the row-major weight
+    // copy the same way, so no layer keeps a transposed one but for the on-policy head's kernel.
+    static constexpr bool kRowMajor = sizeof(T) == 2;
     tj_learner_desc d;
     int L = 0, A = 0, Bmax = 0, ldB = 0, ldA = 0, S = 1;
     int S_ends = 1;   // slices of the first and the last layer's weight gradients (>= S)
@@ -1738,11 +1748,11 @@ template <typename T> struct MlpLearner : tj_learner {
         for (int l = 0; l < L; ++l) {
             const size_t rows = (size_t)(n_pass == 1 ? 1 : (l == 0 ? 2 : 3)) * Bmax;
             X[l] = (T *)a.take(rows * lay[l].ld_in * sizeof(T));
-            XT[l] = wgrad_trans(l + 1) ? nullptr : (T *)a.take((size_t)lay[l].in * ldB * sizeof(T));
+            XT[l] = kRowMajor ? nullptr : (T *)a.take((size_t)lay[l].in * ldB * sizeof(T));
         }
         for (int l = 1; l <= L; ++l) {   // rows up to a whole stage behind the batch: they stay zero
-            dZ[l] = (T *)a.take((size_t)(Bmax + (wgrad_trans(l) ? 64 : 0)) * lay[l - 1].ld_out * sizeof(T));
-            dZT[l] = wgrad_trans(l) ? nullptr : (T *)a.take((size_t)lay[l - 1].out * ldB * sizeof(T));
+            dZ[l] = (T *)a.take((size_t)(Bmax + (kRowMajor ? 64 : 0)) * lay[l - 1].ld_out * sizeof(T));
+            dZT[l] = kRowMajor ? nullptr : (T *)a.take((size_t)lay[l - 1].out * ldB * sizeof(T));
         }
         act_bytes = a.off - act0;
         Qout = (float *)a.take((size_t)n_pass * Bmax * ldA * 4);
@@ -1876,19 +1886,6 @@ template <typename T> struct MlpLearner : tj_learner {
         return adam_emits(l) && keeps_wct(l) && (size_t)lay[l].in * lay[l].out <= ((size_t)1 << 18);
     }
 
-    // Weight gradient of layer l (1-based) straight from the row-major X_{l-1} and dZ_l (transposing LDS
-    // reads) instead of their transposed copies: bf16.  The first and the last layer too, although their narrow sides
-    // fill few of the 256 x 128 tiles that form takes (their pair is 96 blocks on the 256-1024-1024-1024-32 net): what
-    // counts is that no transposed copy of X_{l-1} and of dZ_l is written at all, which
-    // makes the forward pass of the last hidden layer and the input-gradient pass of the second layer
-    // one-layout launches like the others.  Any width and batch: rows are padded to whole stages, and the rows behind the batch
-    // count as zero (as contractions over transposed copies, with element-wise staged loads, an update of
-    // 256-640-640-640-18 took 337 us at batch 3000 against 151 at 2048 and 182 at 4096).
-    bool wgrad_trans(int l) const { return sizeof(T) == 2 && l >= 1 && l <= L; }
-
-    // Input gradient of layer l (1-based, l >= 2) with the row-major weight copy as its first operand
-    // (transposing LDS reads): bf16.  Such a layer keeps no transposed weight copy.
-    bool dgrad_trans(int) const { return sizeof(T) == 2; }
     // Layer index l (0-based) keeps a transposed weight copy: its input gradient exists, is a contraction
     // (the head's is not where the TD kernel writes it) and does not read the straight copy.
     virtual bool head_input_gradient_fused() const { return false; }   // a derived learner's head kernel reads WcT
@@ -1897,7 +1894,7 @@ template <typename T> struct MlpLearner : tj_learner {
         if (l == 0) return false;
         if (l == L - 1 && head_input_gradient_fused()) return true;
         if (l == L - 1 && n_pass == 3 && head_fused<T>(A)) return false;
-        return !dgrad_trans(l + 1);
+        return !kRowMajor;
     }
 
     int recast(bool online, hipStream_t st, bool after_adam = false)
@@ -1958,7 +1955,7 @@ template <typename T> struct MlpLearner : tj_learner {
         // gradient still contracts over transposed operands)
         {
             CastJobs<T> jobs;
-            jobs.job[0] = {(const float *)mb->obs, X[0], wgrad_trans(1) ? nullptr : XT[0], B, lay[0].in, lay[0].ld_in, ldB};
+            jobs.job[0] = {(const float *)mb->obs, X[0], kRowMajor ? nullptr : XT[0], B, lay[0].in, lay[0].ld_in, ldB};
             jobs.job[1] = {(const float *)mb->next_obs, X[0] + (size_t)B * lay[0].ld_in, nullptr, B,
                            lay[0].in, lay[0].ld_in, ldB};
             if (mb->row_index) {   // rows of the caller's tables (the ring itself), picked by index
@@ -1982,7 +1979,7 @@ template <typename T> struct MlpLearner : tj_learner {
             g.k_chunk = g.K; g.n_split = 1;
             g.relu = 1;
             g.Ci = X[l + 1]; g.ldci = lay[l].ld_out;
-            if (!wgrad_trans(l + 2)) { g.Cj = XT[l + 1]; g.ldcj = ldB; g.cj_jmax = B; }
+            if (!kRowMajor) { g.Cj = XT[l + 1]; g.ldcj = ldB; g.cj_jmax = B; }
             if ((rc = tj_gemm<T>(g, st)) != TJ_OK) return rc;
         }
         {   // head layer and TD step
@@ -1994,12 +1991,11 @@ template <typename T> struct MlpLearner : tj_learner {
             h.b_on = theta_on + lh.b_off; h.b_tg = theta_tg + lh.b_off;
             h.B = B; h.A = A; h.K = lh.ld_in;
             h.Q = Qout; h.ldq = ldA;
-            h.dZ = dZ[L]; h.lddz = lh.ld_out; h.dZT = wgrad_trans(L) ? nullptr : dZT[L]; h.lddzt = ldB;
+            h.dZ = dZ[L]; h.lddz = lh.ld_out; h.dZT = kRowMajor ? nullptr : dZT[L]; h.lddzt = ldB;
             h.astar = astar; h.loss_part = loss_part;
             h.dX = nullptr; h.lddx = 0; h.dXT = nullptr; h.lddxt = 0; h.Kin = lh.in;
             if (head_fused<T>(A) && L >= 2) {   // the fused kernel also writes the head's input gradient
                 h.dX = dZ[L - 1]; h.lddx = lh.ld_in;
-                if (!wgrad_trans(L - 1)) { h.dXT = dZT[L - 1]; h.lddxt = ldB; }
             }
             if ((rc = run_head_td<T>(this, h, mb, d.gamma, d.huber_delta, st)) != TJ_OK) return rc;
         }
@@ -2028,7 +2024,7 @@ template <typename T> struct MlpLearner : tj_learner {
                 TjGemmArgs<T> &g = gw;
                 memset(&g, 0, sizeof(g));
                 g.n_seg = 1;
-                if (wgrad_trans(l)) {   // row-major operands, contraction over their rows
+                if (kRowMajor) {   // row-major operands, contraction over their rows
                     g.seg[0] = {0, lp.out, X[l - 1], nullptr, 0};
                     g.Q = dZ[l];
                     g.ldp = lp.ld_in; g.ldq = lp.ld_out;
@@ -2061,7 +2057,7 @@ template <typename T> struct MlpLearner : tj_learner {
                 g.Q = dZ[l];
                 g.ldq = lp.ld_out;
                 g.I = lp.in;
-                if (dgrad_trans(l)) {   // the weights as stored, [n][k]: the contraction runs over their rows
+                if (kRowMajor) {   // the weights as stored, [n][k]: the contraction runs over their rows
                     g.seg[0] = {0, B, Wc_on[l - 1], nullptr, 0};
                     g.ldp = lp.ld_in; g.K = lp.ld_out;   // pad rows and columns are zero
                     g.trans = 2;
@@ -2072,7 +2068,7 @@ template <typename T> struct MlpLearner : tj_learner {
                 g.k_chunk = g.K; g.n_split = 1;
                 g.mask = X[l - 1]; g.ldmask = lp.ld_in;
                 g.Ci = dZ[l - 1]; g.ldci = lp.ld_in;
-                if (!wgrad_trans(l - 1)) { g.Cj = dZT[l - 1]; g.ldcj = ldB; g.cj_jmax = B; }
+                if (!kRowMajor) { g.Cj = dZT[l - 1]; g.ldcj = ldB; g.cj_jmax = B; }
             }
             if (defer_head) {   // the input gradient alone now
                 if ((rc = tj_gemm<T>(gd, st)) != TJ_OK) return rc;
@@ -2324,7 +2320,7 @@ template <typename T> struct PpoLearner : MlpLearner<T> {
         int rc;
         const auto &lay = this->lay;
         CastJobs<T> jobs;
-        jobs.job[0] = {d_obs, this->X[0], keep_transposes && !this->wgrad_trans(1) ? this->XT[0] : nullptr, n,
+        jobs.job[0] = {d_obs, this->X[0], keep_transposes && !Base::kRowMajor ? this->XT[0] : nullptr, n,
                        lay[0].in, lay[0].ld_in, this->ldB};
         if ((rc = launch_cast<T>(jobs, 1, st)) != TJ_OK) return rc;
         if (keep_transposes && (rc = this->mark(0, st)) != TJ_OK) return rc;
@@ -2340,7 +2336,7 @@ template <typename T> struct PpoLearner : MlpLearner<T> {
             if (l + 1 < this->L) {
                 g.relu = 1;
                 g.Ci = this->X[l + 1]; g.ldci = lay[l].ld_out;
-                if (keep_transposes && !this->wgrad_trans(l + 2)) { g.Cj = this->XT[l + 1]; g.ldcj = this->ldB; g.cj_jmax = n; }
+                if (keep_transposes && !Base::kRowMajor) { g.Cj = this->XT[l + 1]; g.ldcj = this->ldB; g.cj_jmax = n; }
             } else {
                 g.Cf = this->Qout; g.ldcf = this->ldA;
             }
@@ -2369,7 +2365,7 @@ template <typename T> struct PpoLearner : MlpLearner<T> {
         // bf16 with at most 32 head outputs: the head layer's forward runs inside the objective kernel
         const bool fused = sizeof(T) == 2 && this->A <= 32 && this->L >= 2;
         // the same kernel writes the head's input gradient where the layer below takes it row-major
-        const bool fused_dx = fused && head_input_gradient_fused() && this->wgrad_trans(this->L - 1);
+        const bool fused_dx = fused && head_input_gradient_fused();
         if ((rc = forward(B, pb->obs, true, st, fused)) != TJ_OK) return rc;
         if ((rc = this->mark(1, st)) != TJ_OK) return rc;
         const auto &lh = this->lay[this->L - 1];
@@ -2378,7 +2374,7 @@ template <typename T> struct PpoLearner : MlpLearner<T> {
         a.action = pb->action; a.old_logp = pb->old_logp; a.adv = pb->adv; a.ret = pb->ret;
         a.clip = pd.clip; a.c_v = pd.c_v; a.c_e = pd.c_e;
         a.dZ = this->dZ[this->L]; a.lddz = lh.ld_out; a.lddzt = this->ldB;
-        a.dZT = this->wgrad_trans(this->L) ? nullptr : this->dZT[this->L];
+        a.dZT = this->dZT[this->L];
         a.part = ppo_part;
         const int nblk = (B + kPpoRows - 1) / kPpoRows;
         if constexpr (sizeof(T) == 2) {

@@ -1004,8 +1004,9 @@ __device__ __forceinline__ void dlds_body(const TjGemmArgs<tj_bf16> &a_in, const
     int py[LP], px[LP];
     int tap_y = 0, tap_x = 0, tap_c = 0;
     (void)py; (void)px; (void)tap_y; (void)tap_x; (void)tap_c;
-    // Without a gather a load's address is a scalar (the stage's first row and column) plus a 32-bit lane offset that
-    // is the same for every stage: half the registers of 64-bit lane addresses, and none of the additions.
+    // Without a gather a load's address is a scalar (the next stage's first row and column, moved on as stages are issued)
+    // plus a 32-bit lane offset that is the same for every stage: half the registers of 64-bit lane addresses, and none of
+    // the additions.
     const T *baseP = nullptr, *baseQ = nullptr;
     uint32_t offP[LP], offQ[LQ];
     (void)baseP; (void)offP; (void)gsrcP;
@@ -1098,23 +1099,23 @@ __device__ __forceinline__ void dlds_body(const TjGemmArgs<tj_bf16> &a_in, const
         } else if (TRANS == 1 && k_begin + (s + 1) * KE > k_valid) {
             // a stage with rows past the last valid one reads that one instead; it may hold no valid row at all
             const int row0 = min(s * KE, k_valid - 1 - k_begin), last = k_valid - 1 - k_begin - row0;
-            const T *base = baseP + (int64_t)row0 * a.ldp;
+            const T *base = baseP - (int64_t)(s * KE - row0) * a.ldp;
 #pragma unroll
             for (int t = 0; t < LP; ++t) {
                 const int past = max(2 * (wave + 8 * t) + (lane >> 5) - last, 0);
                 dma16_at(base, offP[t] - 2u * (uint32_t)(past * a.ldp), sA + (wave + 8 * t) * 1024);
             }
         } else {
-            const T *base = baseP + s * stepP;
 #pragma unroll
-            for (int t = 0; t < LP; ++t) dma16_at(base, offP[t], sA + (wave + 8 * t) * 1024);
+            for (int t = 0; t < LP; ++t) dma16_at(baseP, offP[t], sA + (wave + 8 * t) * 1024);
         }
-        const T *base = baseQ + s * stepQ;
 #pragma unroll
         for (int t = 0; t < LQ; ++t) {
             const int c = (wave + 8 * t) % CHQ;   // wave-uniform
-            dma16_at(base, offQ[t], sB + c * 1024);
+            dma16_at(baseQ, offQ[t], sB + c * 1024);
         }
+        baseP += stepP;
+        baseQ += stepQ;
     };
 
     f32x16 acc[2][NFJ];

@@ -14,8 +14,10 @@
 // Rows of the activations in LDS are padded by 16 bytes: 80 and 144 bytes apart, 16 consecutive patches read 16 distinct 16-byte
 // columns.  The second layer has stride 2, so its input keeps even and odd columns apart, which makes consecutive patches
 // consecutive rows.  Sixteen patches mostly end one output row and begin another: the rows of the image they read (even and odd ones
-// apart as well) have a pitch that continues the sequence of columns there (tower_plan).  Without it 44 % of the cycles in
-// which the LDS was busy were conflicts: 171 -> 160 us at 3 x 2048 passes, 31.6 -> 30.4 at 3 x 256.
+// apart as well) have a pitch that continues the sequence of columns there (tower_plan).  With it 34 % of the cycles in which the LDS
+// is busy are conflicts instead of 44 %: 171 -> 160 us at 3 x 2048 passes, 31.6 -> 30.4 at 3 x 256.  What is left comes from the
+// four lane groups of a fragment, whose pieces of 8 channels lie in one row: a 16-byte read serves lanes of several groups at a time.
+// Octets of channels in two planes would halve it (18 %) and took nothing off a pass.
 // While an image is in the second layer the next one, fetched into registers a layer ahead, is converted into the image buffer.
 #include "tj_conv_planes.h"
 #include <algorithm>

@@ -1,6 +1,6 @@
 // The large contractions of wide vector networks (hidden layers at batches of thousands): 256 x 256 tiles, one block of eight
 // waves per compute unit.  Same problems, operand forms and sums as gemm_bf16_dlds (tj_gemm.hip), bit for bit where a
-// result is one accumulation; tj_gemm_wide_* say which calls they take.
+// result is one accumulation; tj_gemm_wide_* and the rules of tj_gemm_plan.h say which calls they take.
 //
 // What bounds these contractions is power: with all matrix cores busy on real data the clock falls from 2.4 to 1.5 - 1.8 GHz (the same
 // kernel on zeros runs at 2.2).  A bare loop of v_mfma_f32_32x32x16_bf16 reaches 1.84 PFLOP/s on random operands, of

@@ -971,7 +971,7 @@ __device__ __forceinline__ void dlds_body(const TjGemmArgs<tj_bf16> &a_in, const
         if (tj >= tm.tiles_j) return;
         // The divisions above ran on the vector unit.  Said to be scalars here, everything that follows from a block's place stays
         // one, the loads' addresses in the loop above all: read back from vector registers in front of each stage's loads they
-        // lengthened every step of a long slice (256 units, 24576 rows, hidden layers' gradients 54.8 -> 63.1 us a launch; 54 so).
+        // lengthened every step of a long slice (256 units, 24576 rows, hidden layers' gradients 63 us a launch, 56 so).
         ti = __builtin_amdgcn_readfirstlane(ti);
         tj = __builtin_amdgcn_readfirstlane(tj);
         z = __builtin_amdgcn_readfirstlane(z);

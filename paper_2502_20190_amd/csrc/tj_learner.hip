@@ -1784,7 +1784,7 @@ template <typename T> struct MlpLearner : tj_learner {
             y.W = theta_on + y.w_off; y.bias = theta_on + y.b_off;
             y.W_tg = theta_tg + y.w_off; y.bias_tg = theta_tg + y.b_off;
             if constexpr (sizeof(T) == 4) {
-                y.kp = round_up(y.in, 16); y.ldn = round_up(y.out, 64);
+                tj_f32_copy_shape(y, l == L - 1);
                 y.ldx = round_up(y.in, 64); y.lddz = y.ldn;
                 y.WT = (float *)a.take((size_t)y.kp * y.ldn * 4);
                 y.WT_tg = (float *)a.take((size_t)y.kp * y.ldn * 4);
@@ -1831,8 +1831,7 @@ template <typename T> struct MlpLearner : tj_learner {
         if constexpr (sizeof(T) == 4) {
             TjF32Rows r;
             static_cast<TjRowsCall &>(r) = call;
-            for (int l = 0; l < TJ_MAX_LAYERS; ++l) r.lay[l] = wlay[l];
-            r.bias = wlay[0].BP; r.bias_tg = wlay[0].BP_tg;
+            r.lay = wlay;
             if (n_part) *n_part = tj_f32_blocks(r, mode);
             return tj_f32_rows(r, mode, st);
         } else {
@@ -1909,14 +1908,7 @@ template <typename T> struct MlpLearner : tj_learner {
         int n = 0;
         if (whole) {   // the weight copies and padded biases of one network
             if constexpr (sizeof(T) == 4) {
-                CastJobs<T> bias;
-                for (int l = 0; l < L; ++l) {
-                    const TjF32Layer &y = wlay[l];
-                    jobs.job[l] = {online ? y.W : y.W_tg, nullptr, online ? y.WT : y.WT_tg, y.out, y.in, 0, y.ldn};
-                    bias.job[l] = {online ? y.bias : y.bias_tg, online ? y.BP : y.BP_tg, nullptr, 1, y.out, y.ldn, 0};
-                }
-                const int rc = launch_cast<T>(jobs, L, st);
-                return rc != TJ_OK ? rc : launch_cast<T>(bias, L, st);
+                return tj_f32_cast(L, wlay, online, st);
             } else {
                 return tj_b16_cast(L, wlay, online, st);
             }
@@ -2223,7 +2215,7 @@ template <typename T> struct MlpLearner : tj_learner {
                         if (!tr) continue;
                         if ((rc = fetch_as_float<float>(y.WT, (size_t)y.kp * y.ldn, w, st)) != TJ_OK) return rc;
                         for (int o = 0; o < lp.out; ++o)
-                            for (int k = 0; k < lp.in; ++k) dst[(size_t)o * lp.in + k] = w[(size_t)k * y.ldn + o];
+                            for (int k = 0; k < lp.in; ++k) dst[(size_t)o * lp.in + k] = w[tj_f32_copy_at(y, o, k)];
                     } else {
                         const bool wb = tr && l > 0;
                         const size_t nf = tj_b16_wf_elems(lp.in, lp.out);

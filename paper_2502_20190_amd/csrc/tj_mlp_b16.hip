@@ -367,7 +367,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
     block_sync_lds();
 
     if constexpr (KIND == TJ_ROWS_ACT) {
-        for (int row = wave; row < R && j0 + row < a.B; row += kWaves) act_row(a, mode, j0 + row, A, qs + row * kQPitch);
+        for (int row = wave; row < R && j0 + row < a.B; row += kWaves) act_row(a, mode, j0 + row, A, qs[row * kQPitch + (lane & 31)]);
         return;
     }
 
@@ -376,16 +376,18 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
     for (int i = 0; i < RW; ++i) {
         const int row = wave + i * kWaves;
         const bool valid = j0 + row < a.B;
+        act_w[i] = __builtin_amdgcn_readfirstlane(act_w[i]);
         float g;
         if constexpr (DQN) {
-            const TdRow t = td_row(a, A, qs + row * kQPitch, qs + (R + row) * kQPitch, qs + (2 * R + row) * kQPitch, act_w[i], rew_w[i], nd_w[i], valid);
+            const TdRow t = td_row(a, A, qs[row * kQPitch + (lane & 31)], qs[(R + row) * kQPitch + (lane & 31)],
+                                   qs[(2 * R + row) * kQPitch + (lane & 31)], act_w[i], rew_w[i], nd_w[i], valid);
             if (lane == 0) {
                 sm[row] = t.loss;
                 if (valid) a.astar[j0 + row] = t.best;
             }
             g = lane == act_w[i] ? t.g : 0.f;
         } else {
-            const PpoRow t = ppo_row(a, A - 1, qs + row * kQPitch, act_w[i], olp_w[i], adv_w[i], ret_w[i], valid);
+            const PpoRow t = ppo_row(a, A - 1, qs[row * kQPitch + (lane & 31)], act_w[i], olp_w[i], adv_w[i], ret_w[i], valid);
             if (lane == 0) { sm[row] = t.pi; sm[R + row] = t.v; sm[2 * R + row] = t.H; }
             g = t.g;
         }

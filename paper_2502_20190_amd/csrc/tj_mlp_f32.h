@@ -8,8 +8,9 @@ constexpr int kF32MaxInput = 1024;   // widest observation
 constexpr int kF32MaxOut = 64;       // head outputs: one lane each
 constexpr int kF32MaxSlices = 16;    // slices of the batch in the weight gradient
 
-// One layer.  W and bias are the fp32 master parameters themselves.  WT is the transposed weight copy
-// [kp][ldn] (row k = input feature, kp = in rounded up to 16, ldn = out rounded up to 64; pads are zero).
+// One layer.  W and bias are the fp32 master parameters themselves.  WT is the weight copy that the forward pass reads,
+// [kp / 4][ldn][4]: four input features k of an output feature, then the next output feature (kp and ldn from
+// tj_f32_copy_shape; pads are zero).
 // X [B][ldx] receives the layer's input rows of s (layer 0: a dense copy of the observations), dZ [B][lddz] the
 // gradient wrt its output; both feed the weight-gradient kernel.
 struct TjF32Layer {
@@ -23,8 +24,7 @@ struct TjF32Layer {
 };
 
 struct TjF32Rows : TjRowsCall {
-    TjF32Layer lay[TJ_MAX_LAYERS];
-    const float *bias, *bias_tg;     // lay[0].BP, lay[0].BP_tg
+    const TjF32Layer *lay;           // L of them, on the host
 };
 
 // True if the networks of this shape, in updates of up to max_batch rows, run in these kernels; decides the learner's layout.
@@ -37,5 +37,8 @@ int tj_f32_rows(const TjF32Rows &a, int mode, hipStream_t st);
 struct TjF32Update : TjUpdateCall {
     TjF32Layer lay[TJ_MAX_LAYERS];
 };
+void tj_f32_copy_shape(TjF32Layer &y, bool head);                // kp and ldn of a layer, from in and out
+size_t tj_f32_copy_at(const TjF32Layer &y, int n, int k);         // element of WT that is W[n][k]
+int tj_f32_cast(int L, const TjF32Layer *lay, bool online, hipStream_t st);   // WT and BP of one network from its parameters
 int tj_f32_slices(int L, const TjF32Layer *lay, int B);
 int tj_f32_update(const TjF32Update &a, hipStream_t st);

@@ -15,45 +15,67 @@
 // f32_rows multiplies with v_mfma_f32_4x4x1_16b_f32: sixteen independent 4 x 4 products per instruction,
 // the A operand (4 rows x 1) broadcast to all of them, so one instruction is 4 rows x 64 features x one k at
 // the full fp32 matrix rate (136 TFLOP/s measured on the bare instruction).  Rows come in groups of four, not
-// 16 or 32: a batch of 512 spreads over 128 blocks without padding.  What bounds the kernel is the stream of
-// weights from the L2 into a CU: each is read once per block, from a matrix with the features contiguous (the
-// transposed copy in the forward pass, the parameters as stored in the backward pass), by 16-byte loads whose
-// 16-lane quarters take 64 features of four consecutive k (4-byte loads, one k each, moved 24 bytes per clock
-// and CU).  The instruction's broadcast is limited to a quarter of the wave, so each quarter multiplies its own
-// k; the quarters are added by lane swaps at the end of a layer.  Eight waves split a layer into groups of 64
-// features x slices of k; the slices are added through LDS in slice order.  Weight loads do not depend on activations, so a wave has its first loads of the next
-// layer in flight across the barriers between two layers.
+// 16 or 32: a batch of 512 spreads over 128 blocks without padding.
+//
+// What bounds the kernel is the stream of weights from the L2 into a CU, each read once per block (41 - 46 bytes per clock where a
+// layer is wide), and everything between two layers, which a nearly empty chip cannot hide: with two waves per SIMD an instruction costs
+// 5 - 10 clocks, so 150 of them between two layers cost as much as a 64 KB layer.  Hence, in the forward pass:
+//   - The weight copy is [k / 4][features][4]: a lane's 16-byte load is four k of one feature, and a wave is given fewer features and more
+//     of k side by side (64 / q features, q parts) until eight waves cover the layer.  A wave then ends with whole sums after at most
+//     two lane exchanges, writes the activations and meets one barrier; slices of k over the waves, added through LDS, took two barriers
+//     and 1.5 - 2 times a 64-wide layer's products.
+//   - The layers' shapes come worked out by the host, loads take a scalar base and lane offsets that do not change within a layer, and
+//     the head is apart from the loop over the hidden layers: weights loaded ahead across a barrier may not meet a register copy there.
+//   - A load that finds nothing is not issued at all: it would still take its 16 clocks on the way back.
+// Rows of the objective stay in registers (one lane per output).  The backward pass reads the parameters as stored.  There eight waves split a
+// matrix into groups of 64 columns x slices of rows, the slices added through LDS; sixteen rows (NR = 4) are as wide as
+// v_mfma_f32_16x16x4_f32, whose sums need neither slices nor exchanges.
+// Against partial sums of every layer in LDS, loads of four features per lane and 1.2 times the arguments, us per call of the whole update:
+// 4-64-64-2 at 32 rows 21.9 -> 18.9, 128-256-256-18 at 512 41.1 -> 37.2, on-policy 4-256-256-3 at 4096 54.6 -> 47.8.
 #include "tj_mlp_f32.h"
 #include "tj_mlp_plan.h"
 #include <math.h>
 #include <algorithm>
+#include <type_traits>
 
 namespace {
 
+typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef const __attribute__((address_space(1))) uint8_t *gbytes;
 typedef const __attribute__((address_space(1))) __attribute__((aligned(4))) f32x4 *gf32x4;
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef __amdgpu_buffer_rsrc_t buf_rsrc;
+
+// A wave-uniform stretch of memory; loads at or past its end are zeros and touch nothing.
+__device__ __forceinline__ buf_rsrc row_buffer(const float *p, int bytes)
+{
+    return __builtin_amdgcn_make_buffer_rsrc((void *)p, 0, bytes, 0x00027000);
+}
+__device__ __forceinline__ f32x4 load16(buf_rsrc r, uint32_t at, int base)
+{
+    return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(r, (int)at, base, 0));
+}
+__device__ __forceinline__ float load4(buf_rsrc r, int at) { return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, at, 0, 0)); }
 
 constexpr int kWaves = tjplan::kF32Waves, kThreads = 64 * kWaves;   // f32_rows: two waves per SIMD, 256 registers each
 constexpr size_t kLdsMax = 160 * 1024;
 
 __host__ __device__ inline int up(int x, int a) { return (x + a - 1) / a * a; }
 
-// LDS layout of f32_rows in floats.  Activation rows are `pitch` floats apart, pitch % 64 == 16: the four
-// rows x 16 k of an A operand fall on 64 distinct banks.
+// LDS layout of f32_rows in floats.  Activation rows are `pitch` floats apart, pitch % 64 == 16: the 16-byte pieces that a
+// quarter of a wave reads (four rows x 16 k) cover the 64 banks once.
 struct RowsLds {
-    int pitch, keep, pp, part, dz, wa, qs, bias, small, total;
+    int pitch, dzp, keep, pp, part, dz, wa, bias, small, total;
 };
 
 RowsLds rows_lds(int L, const TjF32Layer *lay, int nr, bool dqn, bool backward)
 {
     RowsLds o;
-    int w = 0, nb = 0, waves = 0;   // waves: those with a part of some phase
+    int w = 0, nb = 0, waves = 0;   // waves: those with a part of some phase of the backward pass
     for (int l = 0; l < L; ++l) {
-        waves = std::max(waves, tjplan::f32_part_waves(tjplan::f32_phase(lay[l].ldn, lay[l].kp, lay[l].ldn)));
         if (backward && l) waves = std::max(waves, tjplan::f32_part_waves(tjplan::f32_phase(lay[l].in, lay[l].out, lay[l].in)));
-        w = lay[l].kp > w ? lay[l].kp : w;
-        if (l + 1 < L) w = lay[l].ldn > w ? lay[l].ldn : w;
+        w = std::max(w, std::max(lay[l].kp, lay[l].ldn));
         nb += lay[l].ldn;
     }
     o.pitch = up(w, 64) + 16;
@@ -61,37 +83,72 @@ RowsLds rows_lds(int L, const TjF32Layer *lay, int nr, bool dqn, bool backward)
     int at = 0;
     o.keep = at; at += (backward ? L : std::min(L, 2)) * R * o.pitch;   // input rows of every layer, s; acting: two layers in turn
     o.pp = at; at += dqn ? 2 * 2 * R * o.pitch : 0;     // s' (online), s' (target), two layers in turn
-    o.part = at; at += waves * 2 * NG * 256;            // the k slices of one layer
-    o.dz = at; at += backward ? 2 * R * o.pitch : 0;    // output gradients, two layers in turn
+    o.part = at; at += std::max(nr == 4 ? 0 : waves * nr * 256, tjplan::kF32Waves * NG * 64);   // the slices of a backward phase; of the head
+    // output gradients, two layers in turn; sixteen rows are read side by side, 16 bytes each: their pitch keeps them on distinct banks
+    o.dzp = o.pitch + (nr == 4 ? 4 : 0);
+    o.dz = at; at += backward ? 2 * R * o.dzp : 0;
     o.wa = at; at += dqn ? R * o.pitch : 0;             // head weights of the actions taken
-    o.qs = at; at += 4 * NG * 64;                       // head outputs
     o.bias = at; at += nb * (dqn ? 2 : 1);
     o.small = at; at += 64;                             // per row: loss terms, gradient
     o.total = at;
     return o;
 }
 
+// A layer's forward pass as the kernel reads it.  Scalar arithmetic is on every wave's critical path: what the host can work out, it does.
+struct Forward {
+    const float *w0, *w1;        // w1: the target network's (Q-learner; elsewhere never used)
+    uint32_t bytes;              // of a weight copy
+    int pitch, lq, wstep, xstep; // bytes of a step of 16 q k: in the copy, in an activation row
+    int KS, bias, cols;          // slices; the layer's biases in LDS, bytes; 16 tiles
+    uint32_t wave[tjplan::kF32Waves];   // tile | slice << 8 | steps << 16
+};
+
+Forward make_forward(const TjF32Layer &y, bool head, int bias)
+{
+    const tjplan::F32Forward p = tjplan::f32_forward(y.in, y.out, head);
+    Forward d;
+    d.w0 = y.WT; d.w1 = y.WT_tg;
+    d.bytes = (uint32_t)(y.kp * y.ldn * sizeof(float));
+    d.pitch = p.pitch; d.lq = p.lq;
+    d.wstep = (64 << p.lq) * p.pitch;
+    d.xstep = 64 << p.lq;
+    d.KS = p.KS; d.bias = 4 * bias; d.cols = 16 * p.tiles;
+    for (int w = 0; w < tjplan::kF32Waves; ++w) {
+        const tjplan::F32Wave x = tjplan::f32_wave(p, w);
+        d.wave[w] = (uint32_t)x.tile | (uint32_t)x.ks << 8 | (uint32_t)x.n << 16;
+    }
+    return d;
+}
+
 struct Phase : tjplan::F32Phase {
-    const float *w0, *w1;     // w1: the target network's (forward of the Q-learner; elsewhere never used)
+    const float *w;
+    int cols;
     uint32_t rF;              // u / F = u * rF >> 16 (u < 4096, F <= 16)
 };
 
-struct RowsArgs {
-    TjF32Rows a;
-    RowsLds o;
-    Phase fwd[TJ_MAX_LAYERS], bwd[TJ_MAX_LAYERS];   // bwd[l]: gradient wrt layer l's input
-    int n_bias;
+// What else the kernel wants of a layer.  The arguments are kept short: the host writes them, and every block waits for them to arrive.
+struct RowsLayer {
+    float *X, *dZ;
+    int in, ldx, lddz, ldn;
 };
 
-Phase make_phase(const float *w0, const float *w1, int pitch, int rows, int cols)
+struct RowsArgs {
+    TjRowsCall a;
+    RowsLds o;
+    const float *bias, *bias_tg, *head_W;
+    int A, n_bias, head_slices, kp;    // head outputs; kp: columns of the first layer's input rows
+    RowsLayer lay[TJ_MAX_LAYERS];
+    Forward fwd[TJ_MAX_LAYERS];
+    Phase bwd[TJ_MAX_LAYERS];          // bwd[l]: gradient wrt layer l's input
+};
+
+Phase make_phase(const float *w, int pitch, int rows, int cols)
 {
     Phase p;
     static_cast<tjplan::F32Phase &>(p) = tjplan::f32_phase(pitch, rows, cols);
-    p.w0 = w0; p.w1 = w1; p.rF = 65535u / (uint32_t)p.F + 1u;
+    p.w = w; p.cols = cols; p.rF = 65535u / (uint32_t)p.F + 1u;
     return p;
 }
-
-template <bool V> struct Two { static constexpr bool value = V; };   // both networks' weights, or one's
 
 // KIND: TJ_ROWS_DQN (three passes, backward), TJ_ROWS_PPO (one pass, backward), TJ_ROWS_ACT (forward only; `mode`
 // says what is done with the head outputs)
@@ -102,7 +159,8 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, KIN
     constexpr int R = 4 * NR;                       // transitions per block
     constexpr int NG = DQN ? 3 * NR : NR;           // row groups: s | s' online | s' target
     constexpr int NON = DQN ? 2 * NR : NR;          // ... of the online network
-    const TjF32Rows &a = args.a;
+    const TjRowsCall &a = args.a;
+    const RowsLayer *const lay = args.lay;
     {   // the argument block is read all over the kernel: its cache lines are fetched together, once
         uint32_t t = 0;
 #pragma unroll
@@ -117,222 +175,374 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, KIN
     const int P = o.pitch;
     float *const keep = lds + o.keep, *const pp = lds + o.pp, *const part = lds + o.part, *const dzb = lds + o.dz;
     auto kept = [&](int l) { return keep + (BACK ? l : l & 1) * R * P; };
-    float *const qs = lds + o.qs, *const bs = lds + o.bias, *const sm = lds + o.small;
-    const int last = L - 1, A = a.lay[last].out;
+    float *const bs = lds + o.bias, *const sm = lds + o.small;
+    const int last = L - 1, A = args.A;
 
-    // A chunk is 16 k; load b of it takes k = 4 b + q in lane quarter q, features 4 n .. 4 n + 3 (n = lane % 16) of the
-    // wave's 64.  Weights come in two sets of one chunk, set 0 loaded ahead of the phase that uses it.  In the backward
-    // pass the last group's columns may run past the matrix into the parameters behind it: features that nobody reads.
-    struct Mine {             // this wave's part of a phase
+    // ---- forward: this wave's part of a layer, a tile of 64 / q features x every KS-th step of 16 q k.  A load is 16 bytes per
+    // lane, four k of its own feature; lane part h of q takes chunk h of a step (16 k).  Weights come in two sets of one step, both loaded
+    // ahead of the layer that uses them.
+    struct Mine {
         const float *w0, *w1;
+        uint32_t bytes, at[4];             // lane's bytes from a step's start, per load
+        int n, w_at, wstep, x_at, xstep;   // steps; the first one's offset and the distance, in the copy and in a row
+        int lq, f, part;                   // f: this lane's feature
+    };
+    const uint32_t quarter = lane >> 4;
+    auto mine = [&](const Forward &p) {
+        Mine m;
+        const uint32_t w = p.wave[wave];
+        const int ks = (int)(w >> 8 & 255u);
+        m.lq = p.lq; m.n = (int)(w >> 16);
+        m.w_at = ks * p.wstep; m.wstep = p.KS * p.wstep;
+        m.x_at = ks * p.xstep; m.xstep = p.KS * p.xstep;
+        m.w0 = p.w0; m.w1 = p.w1; m.bytes = p.bytes;
+        m.part = tjplan::f32_part(lane, p.lq);
+        m.f = tjplan::f32_feature(lane, (int)(w & 255u), p.lq);
+#pragma unroll
+        for (int b = 0; b < 4; ++b) m.at[b] = 4u * tjplan::f32_weight_at(m.part, b, m.f, p.pitch);
+        return m;
+    };
+    f32x4 wa[2][4], wb[2][4];
+    auto fetch = [&](auto set, const Mine &p, int i) {
+        constexpr int s = decltype(set)::value;
+        if (i >= p.n) return;   // a load that finds nothing would still take its turn on the way back
+        const int at = p.w_at + i * p.wstep;
+        const buf_rsrc r0 = row_buffer(p.w0, (int)p.bytes), r1 = row_buffer(p.w1, (int)p.bytes);
+#pragma unroll
+        for (int b = 0; b < 4; ++b) wa[s][b] = load16(r0, p.at[b], at);
+        if constexpr (DQN) {
+#pragma unroll
+            for (int b = 0; b < 4; ++b) wb[s][b] = load16(r1, p.at[b], at);
+        }
+        __builtin_amdgcn_sched_barrier(0);   // issued here, not where the registers run short
+    };
+    const std::integral_constant<int, 0> set0;
+    const std::integral_constant<int, 1> set1;
+
+    // ---- backward: chunks of 16 rows of the matrix as stored, [n][k]; load b of one takes row 4 b + q in lane quarter q, columns 4 c .. 4 c + 3
+    // (c = lane % 16) of the wave's 64.  One set is loaded ahead of the phase that uses it.  The last group's columns may run past the
+    // matrix: zeros or the next row's, features that nobody reads.
+    struct Back {             // this wave's part of a phase
+        const float *w;
         int pitch, rows, nk, F, KS, f, ks;
         uint32_t rF, row[4];
     };
-    const uint32_t quarter = lane >> 4;
-    auto mine = [&](const Phase &p) {
-        Mine m;
-        m.w0 = p.w0; m.w1 = p.w1; m.pitch = p.pitch; m.rows = p.rows; m.nk = p.nk; m.F = p.F; m.KS = p.KS; m.rF = p.rF;
+    auto back = [&](const Phase &p) {
+        Back m;
+        m.w = p.w; m.pitch = p.pitch; m.rows = p.rows; m.nk = p.nk; m.F = p.F; m.KS = p.KS; m.rF = p.rF;
         m.ks = (int)((uint32_t)wave * p.rF >> 16);
         m.f = wave - m.ks * p.F;
 #pragma unroll
         for (int b = 0; b < 4; ++b) m.row[b] = tjplan::f32_row_at(lane, b, p.pitch);
         return m;
     };
-    auto active = [](const Mine &p) { return p.ks < p.KS && p.ks < p.nk; };
-    auto load = [&](f32x4 (&w)[4], const float *base, const Mine &p, int c) {
-        gbytes rows = (gbytes)(uintptr_t)(base + tjplan::f32_chunk_at(c, p.pitch));
-        asm("" : "+s"(rows));                // wave-uniform: the scalar base of the loads
+    auto active = [&](const Back &p) { return p.ks < p.KS && p.ks < p.nk; };
+    auto load_chunk = [&](f32x4 (&w)[4], const Back &p, int c, bool have) {
+        const buf_rsrc r = row_buffer(p.w, have ? 4 * p.rows * p.pitch : 0);
+        const int at = have ? 4 * (int)tjplan::f32_chunk_at(c, p.pitch) : 0;
         const uint32_t last_row = tjplan::f32_last_row_at(c, p.rows, p.pitch);
 #pragma unroll
-        for (int b = 0; b < 4; ++b) w[b] = *(gf32x4)(rows + 4u * tjplan::f32_lane_at(p.row[b], last_row, lane, p.f));
-        __builtin_amdgcn_sched_barrier(0);   // issued here, not where the registers run short
+        for (int b = 0; b < 4; ++b) w[b] = load16(r, 4u * tjplan::f32_lane_at(p.row[b], last_row, lane, p.f), at);
+        __builtin_amdgcn_sched_barrier(0);
     };
-    f32x4 wa[2][4], wb[2][4];
-    auto load_first = [&](const Mine &p, auto two) {
-        const int c = tjplan::f32_first_chunk(p.ks, p.nk);
-        load(wa[0], p.w0, p, c);
-        if constexpr (decltype(two)::value) load(wb[0], p.w1, p, c);
-    };
+    auto load_first = [&](const Back &p, bool have) { load_chunk(wa[0], p, tjplan::f32_first_chunk(p.ks, p.nk), have && active(p)); };
     // this wave's chunks of a phase; mul(set, chunk) multiplies a set.  The last round is apart: a loop that loads in
     // every round has no wait that covers more than it must.
-    auto chunks = [&](const Mine &p, auto two_nets, auto &&mul) {
-        constexpr bool two = decltype(two_nets)::value;
+    auto chunks = [&](const Back &p, auto &&mul) {
         int c = p.ks;
         for (; c + 2 * p.KS < p.nk; c += 2 * p.KS) {
-            load(wa[1], p.w0, p, c + p.KS);
-            if constexpr (two) load(wb[1], p.w1, p, c + p.KS);
-            mul(wa[0], wb[0], c);
-            load(wa[0], p.w0, p, c + 2 * p.KS);
-            if constexpr (two) load(wb[0], p.w1, p, c + 2 * p.KS);
-            mul(wa[1], wb[1], c + p.KS);
+            load_chunk(wa[1], p, c + p.KS, true);
+            mul(wa[0], c);
+            load_chunk(wa[0], p, c + 2 * p.KS, true);
+            mul(wa[1], c + p.KS);
         }
         if (c + p.KS < p.nk) {
-            load(wa[1], p.w0, p, c + p.KS);
-            if constexpr (two) load(wb[1], p.w1, p, c + p.KS);
-            mul(wa[0], wb[0], c);
-            mul(wa[1], wb[1], c + p.KS);
+            load_chunk(wa[1], p, c + p.KS, true);
+            mul(wa[0], c);
+            mul(wa[1], c + p.KS);
         } else {
-            mul(wa[0], wb[0], c);
+            mul(wa[0], c);
         }
     };
-    // Partial sums of a layer in LDS: [wave][2][group][position][4 rows], two per wave.  acc[e] holds, for the k of this
-    // lane quarter, feature 4 n + e; one exchange of wave halves adds quarters q and q + 2, after which lane
-    // (q, n) has features 4 n + e + 2 (q / 2), e < 2, of slice q % 2.  Feature 4 n + e lies at position 16 e + n: writes
-    // and reads touch consecutive 16-byte pieces.
-    auto put_part = [&](f32x4 (&acc)[4], int g, int ng) {
-        f32x4 *dst = (f32x4 *)part + (((wave * 2 + (quarter & 1)) * ng + g) * 64 + 32 * (quarter >> 1) + (lane & 15));
+    // ---- backward of sixteen rows (NR = 4): v_mfma_f32_16x16x4_f32, the weights its first operand (columns of the matrix as stored), the rows
+    // the second, so that a wave ends with whole sums: a tile of 32 columns, every eighth one.  Load j of a step of 32 matrix rows takes row
+    // 16 (j / 4) + 4 q + j % 4 in lane quarter q, columns 2 c, 2 c + 1; what lies past the matrix is zero.
+    struct Back16 { const float *w; int bytes, pitch, steps, tiles; };
+    auto back16 = [&](const Phase &p) { return Back16{p.w, 4 * p.rows * p.pitch, 4 * p.pitch, (p.rows + 31) / 32, (p.cols + 31) / 32}; };
+    auto load_step = [&](f32x4 (&w)[4], const Back16 &p, int tile, int s) {
+        const buf_rsrc r = row_buffer(p.w, p.bytes);
+        const int at = (32 * s + 4 * (int)quarter) * p.pitch + 128 * tile + 8 * (lane & 15);   // past the end in the lane's part: a scalar part must not be
 #pragma unroll
-        for (int e = 0; e < 2; ++e) {
-            f32x4 s;
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(acc[e][i]), __float_as_uint(acc[e + 2][i]), false, false);
-                s[i] = __uint_as_float(r[0]) + __uint_as_float(r[1]);
-            }
-            dst[16 * e] = s;
+        for (int j = 0; j < 8; ++j) {
+            const f32x2 v = __builtin_bit_cast(f32x2, __builtin_amdgcn_raw_buffer_load_b64(r, at + (16 * (j / 4) + j % 4) * p.pitch, 0, 0));
+            w[j / 2][j % 2 * 2] = v[0]; w[j / 2][j % 2 * 2 + 1] = v[1];
         }
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    auto back_of = [&](const Phase &p) {
+        if constexpr (NR == 4) return back16(p);
+        else return back(p);
+    };
+    auto back_first = [&](const auto &p, bool have) {
+        if constexpr (NR == 4) { if (have && wave < p.tiles) load_step(wa[0], p, wave, 0); }
+        else load_first(p, have);
+    };
+    // Sums over the wave's parts: x = {low half of x, low half of y} + {high half of x, high half of y}, and the same
+    // for the odd and even quarters of a half.
+    auto add_halves = [](float x, float y) {
+        const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(y), false, false);
+        return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+    };
+    auto add_quarters = [](float x, float y) {
+        const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(y), false, false);
+        return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+    };
+    // Partial sums of a backward phase in LDS: [wave][group][position][4 rows].  acc[e] holds, for the rows n of this lane quarter,
+    // feature 4 c + e; two exchanges add the quarters, after which lane (q, c) has feature 4 c + q.  Its position is the lane.
+    auto put_part = [&](f32x4 (&acc)[4], int g) {
+        f32x4 s;
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            s[i] = add_quarters(add_halves(acc[0][i], acc[2][i]), add_halves(acc[1][i], acc[3][i]));
+        ((f32x4 *)part)[(wave * NR + g) * 64 + lane] = s;
     };
     // ... and their sum, in slice order, for group g, features 64 f ..; lane = position
-    auto get_part = [&](const Mine &p, int g, int ng, int f) {
-        const f32x4 *src = (const f32x4 *)part + ((f * 2 * ng + g) * 64 + lane);
-        const int step = p.F * 2 * ng * 64, n = min(p.KS, p.nk);
-        f32x4 s = src[0] + src[ng * 64];
-        for (int k = 1; k < n; ++k) { src += step; s += src[0] + src[ng * 64]; }
+    auto get_part = [&](const Back &p, int g, int f) {
+        const f32x4 *src = (const f32x4 *)part + (f * NR + g) * 64 + lane;
+        const int step = p.F * NR * 64, n = min(p.KS, p.nk);
+        f32x4 s = src[0];
+        for (int k = 1; k < n; k += 3) {
+            f32x4 p[3];
+#pragma unroll
+            for (int i = 0; i < 3; ++i) p[i] = src[min(k + i, n - 1) * step];
+#pragma unroll
+            for (int i = 0; i < 3; ++i)
+                if (k + i < n) s += p[i];
+        }
         return s;
     };
-    const int fpos = 4 * (lane & 15) + (lane >> 4);   // feature at position `lane`
+    const int fpos = 4 * (lane & 15) + (int)quarter;   // feature at position `lane`
 
     Mine ph = mine(args.fwd[0]);
-    load_first(ph, Two<DQN>{});
+    fetch(set0, ph, 0);
+    fetch(set1, ph, 1);
 
-    // ---- the block's inputs: biases, observation rows, the head weights of the actions taken
-    {
-        for (int i = tid; i < args.n_bias; i += kThreads) {
-            const float b = a.bias[i], bt = DQN ? a.bias_tg[i] : 0.f;
-            bs[i] = b;
-            if (DQN) bs[args.n_bias + i] = bt;
-        }
-        const int D = a.lay[0].in, kp = a.lay[0].kp;
-        constexpr int NO = (DQN ? 2 : 1) * R;
-        for (int r = wave; r < NO; r += kWaves) {
-            const int jr = DQN ? r % R : r, j = min(j0 + jr, a.B - 1);
-            const size_t srow = a.rows ? (size_t)min(a.rows[j], a.n_rows - 1u) : (size_t)j;
-            const float *src = (r < R ? a.obs : a.next_obs) + srow * D;
-            float *dst = r < R ? keep + r * P : pp + (r - R) * P;
-            float *x0 = BACK && r < R && j0 + jr < a.B ? a.lay[0].X + (size_t)j * a.lay[0].ldx : nullptr;
-            for (int c0 = 0; c0 < kp; c0 += 256) {
-                float x[4];
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const int c = c0 + 64 * q + lane;
-                    x[q] = c < D ? src[c] : 0.f;
-                }
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const int c = c0 + 64 * q + lane;
-                    if (c < kp) dst[c] = x[q];
-                    if (x0 && c < D) x0[c] = x[q];
-                }
-            }
-        }
-        if (DQN && L >= 2) {
-            const int in = a.lay[last].in;
-            for (int r = kWaves - 1 - wave; r < R; r += kWaves) {
-                const int act = a.action[min(j0 + r, a.B - 1)], aj = min(max(act, 0), A - 1);
-                const float *src = a.lay[last].W + (size_t)aj * in;
-                for (int c = lane; c < in; c += 64) lds[o.wa + r * P + c] = src[c];
-            }
-        }
-    }
-    // what this wave's rows of the objective need, long before it is used
-    constexpr int RW = (R + kWaves - 1) / kWaves;
+    // ---- the block's inputs: observation rows, the head weights of the actions taken, biases.  Everything that leads to an address
+    // is asked for first, then what lies there, then it is stored: two latencies in all.
+    constexpr int RW = (R + kWaves - 1) / kWaves;   // transitions per wave in the objective
     int act_w[RW];
     float rew_w[RW], nd_w[RW], olp_w[RW], adv_w[RW], ret_w[RW];
+    {
+        const int D = lay[0].in, kp = args.kp, in_h = lay[last].in;
+        constexpr int NO = (DQN ? 2 : 1) * R, NOW = (NO + kWaves - 1) / kWaves;
+        buf_rsrc src[NOW], head_w[RW];
+        uint32_t idx[NOW];
+        int aj[RW];
 #pragma unroll
-    for (int q = 0; q < RW; ++q) {
-        const int j = min(j0 + wave + q * kWaves, a.B - 1);
-        if (DQN) { act_w[q] = min(max(a.action[j], 0), A - 1); rew_w[q] = a.reward[j]; nd_w[q] = a.done[j] ? 0.f : 1.f; }
-        if (KIND == TJ_ROWS_PPO) {
-            act_w[q] = min(max(a.action[j], 0), A - 2);
-            olp_w[q] = a.old_logp[j]; adv_w[q] = a.adv[j]; ret_w[q] = a.ret[j];
+        for (int i = 0; i < NOW; ++i) {
+            const int r = min(wave + kWaves * i, NO - 1), j = min(j0 + (DQN ? r % R : r), a.B - 1);
+            idx[i] = a.rows ? a.rows[j] : (uint32_t)j;
+        }
+        if (DQN)   // the actions' rows are fetched by the waves from the last one on
+#pragma unroll
+            for (int i = 0; i < RW; ++i) aj[i] = a.action[min(j0 + min(kWaves - 1 - wave + kWaves * i, R - 1), a.B - 1)];
+        // what this wave's rows of the objective need, long before it is used
+#pragma unroll
+        for (int i = 0; i < RW; ++i) {
+            const int j = min(j0 + wave + i * kWaves, a.B - 1);
+            if (DQN) { act_w[i] = a.action[j]; rew_w[i] = a.reward[j]; nd_w[i] = a.done[j] ? 0.f : 1.f; }
+            if (KIND == TJ_ROWS_PPO) {
+                act_w[i] = a.action[j];
+                olp_w[i] = a.old_logp[j]; adv_w[i] = a.adv[j]; ret_w[i] = a.ret[j];
+            }
+        }
+        const int nb = args.n_bias;
+        const buf_rsrc b_on = row_buffer(args.bias, 4 * nb), b_tg = row_buffer(args.bias_tg, DQN ? 4 * nb : 0);
+        float b[2], bt[2];
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            b[i] = load4(b_on, 4 * (tid + i * kThreads));
+            if (DQN) bt[i] = load4(b_tg, 4 * (tid + i * kThreads));
+        }
+#pragma unroll
+        for (int i = 0; i < NOW; ++i) {
+            const int r = wave + kWaves * i;
+            const uint32_t row = __builtin_amdgcn_readfirstlane(a.rows ? min(idx[i], a.n_rows - 1u) : idx[i]);
+            src[i] = row_buffer((!DQN || r < R ? a.obs : a.next_obs) + (size_t)row * D, r < NO ? 4 * D : 0);
+        }
+        if (DQN && L >= 2)
+#pragma unroll
+            for (int i = 0; i < RW; ++i) {
+                const int aw = __builtin_amdgcn_readfirstlane(min(max(aj[i], 0), A - 1));
+                head_w[i] = row_buffer(args.head_W + (size_t)aw * in_h, kWaves - 1 - wave + kWaves * i < R ? 4 * in_h : 0);
+            }
+        const int width = max(kp, DQN && L >= 2 ? in_h : 0);
+        for (int c0 = 0; c0 < width; c0 += 128) {   // columns past a row are zeros
+            float x[NOW][2], y[RW][2];
+#pragma unroll
+            for (int e = 0; e < 2; ++e) {
+#pragma unroll
+                for (int i = 0; i < NOW; ++i) x[i][e] = load4(src[i], 4 * (c0 + 64 * e + lane));
+                if (DQN && L >= 2)
+#pragma unroll
+                    for (int i = 0; i < RW; ++i) y[i][e] = load4(head_w[i], 4 * (c0 + 64 * e + lane));
+            }
+#pragma unroll
+            for (int e = 0; e < 2; ++e) {
+                const int c = c0 + 64 * e;
+                if (c >= width) break;
+#pragma unroll
+                for (int i = 0; i < NOW; ++i) {
+                    const int r = wave + kWaves * i;
+                    if (r < NO) (r < R ? keep + r * P : pp + (r - R) * P)[c + lane] = x[i][e];
+                }
+                if (DQN && L >= 2)
+#pragma unroll
+                    for (int i = 0; i < RW; ++i) {
+                        const int r = kWaves - 1 - wave + kWaves * i;
+                        if (r < R) lds[o.wa + r * P + c + lane] = y[i][e];
+                    }
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+            if (tid + i * kThreads < nb) {
+                bs[tid + i * kThreads] = b[i];
+                if (DQN) bs[nb + tid + i * kThreads] = bt[i];
+            }
+        for (int i = tid + 2 * kThreads; i < nb; i += kThreads) {
+            bs[i] = args.bias[i];
+            if (DQN) bs[nb + i] = args.bias_tg[i];
         }
     }
     block_sync();
 
-    // A operand: row lane % 4 of a group, k of a chunk as the loads above have it
-    const int arow = (lane & 3) * P + 4 * ((lane >> 2) & 3) + (int)quarter;
-    f32x4 acc[NG][4];
+    // A operand: row lane % 4 of a group, four k from 4 (lane / 4 % 4) on of this lane part's chunk
+    const int arow = (lane & 3) * P + 4 * ((lane >> 2) & 3);
+
+    // row r of layer l's input, for the weight gradients
+    auto store_input = [&](int l, int r) {
+        if (j0 + r >= a.B) return;
+        float *const x = lay[l].X + (size_t)(j0 + r) * lay[l].ldx;
+        for (int c = 4 * lane; c < lay[l].in; c += 256) *(f32x4 *)(x + c) = *(const f32x4 *)(keep + (l * R + r) * P + c);
+    };
 
     // ---- forward
-    int boff = 0;
-    for (int l = 0; l < L; ++l) {
+    f32x4 acc[NG];
+    // this wave's part of layer l, and the first loads of the next one (`first(set)`), in flight across the barrier behind it
+    auto contract = [&](int l, const Mine &m, auto &&first) {
         // rows of this layer's input, group g
         const float *xs = kept(l), *xn = pp + (l & 1) * 2 * R * P, *xt = l == 0 ? xn : xn + R * P;
-        Mine nx = ph;
-        if (l + 1 < L) nx = mine(args.fwd[l + 1]);
-        else if (BACK && (DQN ? L - 2 : L - 1) >= 1) nx = mine(args.bwd[DQN ? L - 2 : L - 1]);   // the Q-learner's head gradient is no contraction
-        if (active(ph)) {
+        const int x_at = 4 * (arow + 16 * m.part) + m.x_at;
 #pragma unroll
-            for (int g = 0; g < NG; ++g)
+        for (int g = 0; g < NG; ++g) acc[g] = f32x4{0.f, 0.f, 0.f, 0.f};
+        auto mul = [&](const f32x4 (&w)[4], const f32x4 (&wt)[4], int i) {
+            f32x4 x[NG];
 #pragma unroll
-                for (int e = 0; e < 4; ++e) acc[g][e] = f32x4{0.f, 0.f, 0.f, 0.f};
-            chunks(ph, Two<DQN>{}, [&](const f32x4 (&w)[4], const f32x4 (&wt)[4], int c) {
-                float ax[NG];
-#pragma unroll
-                for (int g = 0; g < NG; ++g) {
-                    const float *base = g < NR ? xs + 4 * g * P : g < NON ? xn + 4 * (g - NR) * P : xt + 4 * (g - NON) * P;
-                    ax[g] = base[arow + 16 * c];
-                }
-#define TJ_STEP(b)                                                                                                    \
-    _Pragma("unroll") for (int e = 0; e < 4; ++e) _Pragma("unroll") for (int g = 0; g < NG; ++g) acc[g][e] =          \
-        __builtin_amdgcn_mfma_f32_4x4x1f32(ax[g], g < NON ? w[b][e] : wt[b][e], acc[g][e], 2, b, 0);
-                TJ_STEP(0) TJ_STEP(1) TJ_STEP(2) TJ_STEP(3)
-#undef TJ_STEP
-            });
-        }
-        load_first(nx, Two<DQN>{});   // in flight across the barriers; nobody's if nothing follows
-        if (active(ph)) {
-#pragma unroll
-            for (int g = 0; g < NG; ++g) put_part(acc[g], g, NG);
-        }
-        block_sync();
-        const int F = ph.F;
-        for (int u = wave; u < NG * F; u += kWaves) {
-            const int g = (int)((uint32_t)u * ph.rF >> 16), f = u - g * F, col = f * 64 + fpos;
-            const float b = bs[(g < NON ? boff : args.n_bias + boff) + col];
-            f32x4 s = get_part(ph, g, NG, f) + b;
-            if (l < last) {
-                float *dst = g < NR ? kept(l + 1) + 4 * g * P + col : pp + (((l + 1) & 1) * 2 * R + 4 * (g - NR)) * P + col;
-#pragma unroll
-                for (int i = 0; i < 4; ++i) { s[i] = fmaxf(s[i], 0.f); dst[i * P] = s[i]; }
-                if (BACK && g < NR) {
-                    const int j = j0 + 4 * g, ldx = a.lay[l + 1].ldx;
-                    float *x = a.lay[l + 1].X + (size_t)j * ldx + col;
-#pragma unroll
-                    for (int i = 0; i < 4; ++i)
-                        if (j + i < a.B) x[i * ldx] = s[i];
-                }
-            } else {
-                const int gr = DQN ? g % NR : g, pass = DQN ? g / NR : 0;
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    qs[(4 * g + i) * 64 + fpos] = s[i];
-                    const int j = j0 + 4 * gr + i;
-                    if (BACK && fpos < A && j < a.B) a.Q[((size_t)pass * a.B + j) * a.ldq + fpos] = s[i];
-                }
+            for (int g = 0; g < NG; ++g) {
+                const float *base = g < NR ? xs + 4 * g * P : g < NON ? xn + 4 * (g - NR) * P : xt + 4 * (g - NON) * P;
+                x[g] = *(const f32x4 *)((const uint8_t *)base + x_at + i * m.xstep);
             }
+#define TJ_STEP(b)                                                                                                    \
+    _Pragma("unroll") for (int e = 0; e < 4; ++e) _Pragma("unroll") for (int g = 0; g < NG; ++g) acc[g] =             \
+        __builtin_amdgcn_mfma_f32_4x4x1f32(x[g][e], g < NON ? w[b][e] : wt[b][e], acc[g], 2, b, 0);
+            TJ_STEP(0) TJ_STEP(1) TJ_STEP(2) TJ_STEP(3)
+#undef TJ_STEP
+        };
+        int i = 0;
+        for (; i + 2 < m.n; i += 2) {
+            mul(wa[0], wb[0], i);
+            fetch(set0, m, i + 2);
+            mul(wa[1], wb[1], i + 1);
+            fetch(set1, m, i + 3);
+        }
+        if (i < m.n) mul(wa[0], wb[0], i);
+        first(set0);
+        if constexpr (BACK && NR > 1)
+            for (int r = wave; r < R; r += kWaves) store_input(l, r);
+        if (i + 1 < m.n) mul(wa[1], wb[1], i + 1);
+        first(set1);
+    };
+    // the lane parts' sums: 4 / q rows are left in a lane, from r0 = part << (2 - lq) on
+    auto add_halves_of = [&]() {
+#pragma unroll
+        for (int g = 0; g < NG; ++g) { acc[g][0] = add_halves(acc[g][0], acc[g][2]); acc[g][1] = add_halves(acc[g][1], acc[g][3]); }
+    };
+    auto add_quarters_of = [&]() {
+#pragma unroll
+        for (int g = 0; g < NG; ++g) acc[g][0] = add_quarters(acc[g][0], acc[g][1]);
+    };
+    for (int l = 0; l < last; ++l) {
+        const Mine nx = mine(args.fwd[l + 1]);
+        const int bias = args.fwd[l].bias;
+        const float b0 = *(const float *)((const uint8_t *)bs + bias + 4 * ph.f);
+        const float b1 = DQN ? *(const float *)((const uint8_t *)(bs + args.n_bias) + bias + 4 * ph.f) : 0.f;
+        contract(l, ph, [&](auto set) { fetch(set, nx, decltype(set)::value); });
+        if (ph.n > 0) {
+            const int to = (ph.part << (2 - ph.lq)) * P + ph.f;
+            float *const ds = kept(l + 1) + to, *const dn = pp + ((l + 1) & 1) * 2 * R * P + to;
+            auto put_row = [&](int e) {
+#pragma unroll
+                for (int g = 0; g < NG; ++g)
+                    (g < NR ? ds + (4 * g + e) * P : dn + (4 * (g - NR) + e) * P)[0] = fmaxf(acc[g][e] + (g < NON ? b0 : b1), 0.f);
+            };
+            if (ph.lq > 0) add_halves_of();
+            if (ph.lq > 1) add_quarters_of();
+            put_row(0);
+            if (ph.lq < 2) put_row(1);
+            if (ph.lq == 0) { put_row(2); put_row(3); }
         }
         block_sync();
-        boff += a.lay[l].ldn;
         ph = nx;
     }
+    // the head's slices of k: [slice][row][cols]
+    const int cols = args.fwd[last].cols;
+    const int top = DQN ? L - 2 : L - 1;   // first layer whose input gradient is a contraction; the Q-learner's head's is none
+    auto bk = back_of(args.bwd[max(top, 0)]);
+    contract(last, ph, [&](auto set) {
+        if (BACK && decltype(set)::value == 0) back_first(bk, top >= 1);
+    });
+    if (ph.n > 0) {
+        add_halves_of();
+        add_quarters_of();
+        float *const to = part + ((args.fwd[last].wave[wave] >> 8 & 255u) * NG * 4 + ph.part) * cols + ph.f;
+#pragma unroll
+        for (int g = 0; g < NG; ++g) to[4 * g * cols] = acc[g][0];
+    }
+    block_sync();
 
-    if constexpr (KIND == TJ_ROWS_ACT) {   // one wave per row, one lane per head output
-        for (int row = wave; row < R && j0 + row < a.B; row += kWaves) {
-            act_row(a, mode, j0 + row, A, qs + row * 64);
+    // Head output `lane` of transition `row` under every pass, by one wave: the slices in order, then the bias.
+    struct Out { float z[NG / NR]; };
+    auto head_out = [&](int row) {
+        const int w = cols, n = args.head_slices, ob = args.n_bias - lay[last].ldn + lane;
+        const float *src = part + row * w + min(lane, w - 1);
+        Out out;
+        float p[NG / NR][4];
+#pragma unroll
+        for (int pass = 0; pass < NG / NR; ++pass)
+#pragma unroll
+            for (int k = 0; k < 4; ++k) p[pass][k] = src[(min(k, n - 1) * NG * 4 + pass * R) * w];
+#pragma unroll
+        for (int pass = 0; pass < NG / NR; ++pass) {
+            float s = p[pass][0];
+#pragma unroll
+            for (int k = 1; k < 4; ++k)
+                if (k < n) s += p[pass][k];
+            s += bs[(pass == 2 ? args.n_bias : 0) + ob];
+            out.z[pass] = s;
+            const int j = j0 + row;
+            if (BACK && lane < A && j < a.B) a.Q[((size_t)pass * a.B + j) * a.ldq + lane] = s;
         }
+        return out;
+    };
+    if constexpr (KIND == TJ_ROWS_ACT) {   // one wave per row, one lane per head output
+        for (int row = wave; row < R && j0 + row < a.B; row += kWaves) act_row(a, mode, j0 + row, A, head_out(row).z[0]);
         return;
     }
+
+    // one group of rows leaves four waves without a transition: they store the inputs meanwhile
+    if (NR == 1 && wave >= 4)
+        for (int l = 0; l < L; ++l) store_input(l, wave - 4);
 
     // ---- the objective: one wave per transition, one lane per head output
 #pragma unroll
@@ -340,26 +550,145 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, KIN
         const int row = wave + q * kWaves;
         if (row >= R) break;
         const bool valid = j0 + row < a.B;
+        const Out out = head_out(row);
+        act_w[q] = __builtin_amdgcn_readfirstlane(min(max(act_w[q], 0), A - (DQN ? 1 : 2)));
         if constexpr (DQN) {
-            const TdRow t = td_row(a, A, qs + row * 64, qs + (R + row) * 64, qs + (2 * R + row) * 64, act_w[q], rew_w[q], nd_w[q], valid);
+            const TdRow t = td_row(a, A, out.z[0], out.z[1], out.z[2], act_w[q], rew_w[q], nd_w[q], valid);
             if (lane == 0) {
                 sm[row] = t.loss;
                 sm[16 + row] = t.g;
                 if (valid) a.astar[j0 + row] = t.best;
             }
-            if (valid) a.lay[last].dZ[(size_t)(j0 + row) * a.lay[last].lddz + lane] = lane == act_w[q] ? t.g : 0.f;
+            if (valid) lay[last].dZ[(size_t)(j0 + row) * lay[last].lddz + lane] = lane == act_w[q] ? t.g : 0.f;
         } else {
-            const PpoRow t = ppo_row(a, A - 1, qs + row * 64, act_w[q], olp_w[q], adv_w[q], ret_w[q], valid);
+            const PpoRow t = ppo_row(a, A - 1, out.z[0], act_w[q], olp_w[q], adv_w[q], ret_w[q], valid);
             if (lane == 0) {
                 sm[row] = t.pi;
                 sm[16 + row] = t.v;
                 sm[32 + row] = t.H;
             }
-            dzb[row * P + lane] = t.g;
-            if (valid) a.lay[last].dZ[(size_t)(j0 + row) * a.lay[last].lddz + lane] = t.g;
+            dzb[row * o.dzp + lane] = t.g;
+            if (valid) lay[last].dZ[(size_t)(j0 + row) * lay[last].lddz + lane] = t.g;
         }
     }
     block_sync();
+    // ---- input gradients.  dZ of layer l - 1 = relu'(X_l) (dZ_l W_l)
+    int cur = 0;
+    auto put = [&](int l, int g, int col, f32x4 s, int buf) {   // layer l's input gradient, rows of group g
+        const RowsLayer &b = lay[l - 1];
+        const int in = lay[l].in, j = j0 + 4 * g;
+        const float *x = keep + (l * R + 4 * g) * P + col;
+        float *dst = dzb + (buf * R + 4 * g) * P + col, *z = b.dZ + (size_t)j * b.lddz + col;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const float v = col < in && x[i * P] > 0.f ? s[i] : 0.f;
+            dst[i * P] = v;
+            if (j + i < a.B) z[i * b.lddz] = v;
+        }
+    };
+    if (DQN && L >= 2) {   // the head's: one non-zero per row of dL/dQ, no contraction
+        const int F = (lay[last].in + 63) / 64;
+        for (int u = wave; u < NR * F; u += kWaves) {
+            const int g = NR == 1 ? 0 : u / F, col = (u - g * F) * 64 + lane;
+            f32x4 s;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) s[i] = sm[16 + 4 * g + i] * lds[o.wa + (4 * g + i) * P + col];
+            put(last, g, col, s, 0);
+        }
+        block_sync();
+    }
+    // A operand: row lane % 4 of a group, row n of a chunk as the loads have it
+    const int brow = (lane & 3) * P + 4 * ((lane >> 2) & 3) + (int)quarter;
+    if constexpr (NR == 4) {
+        const int r = lane & 15;
+        for (int l = top; l >= 1; --l) {
+            const float *const src = dzb + cur * R * o.dzp + r * o.dzp + 4 * (int)quarter;
+            float *const dst = dzb + (cur ^ 1) * R * o.dzp + r * o.dzp;
+            const Back16 nx = back16(args.bwd[max(l - 1, 1)]);
+            const int in = lay[l].in, ldz = lay[l - 1].lddz;
+            float *const z = lay[l - 1].dZ + (size_t)(j0 + r) * ldz;
+            if (wave >= bk.tiles) back_first(nx, l > 1);
+            for (int tile = wave; tile < bk.tiles; tile += kWaves) {
+                f32x4 ab[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
+                auto mul = [&](const f32x4 (&w)[4], int st) {
+                    const f32x4 v[2] = {*(const f32x4 *)(src + 32 * st), *(const f32x4 *)(src + 32 * st + 16)};
+#pragma unroll
+                    for (int j = 0; j < 8; ++j)
+#pragma unroll
+                        for (int e = 0; e < 2; ++e)
+                            ab[e] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[j / 2][j % 2 * 2 + e], v[j / 4][j % 4], ab[e], 0, 0, 0);
+                };
+                int st = 0;
+                for (; st + 2 < bk.steps; st += 2) {
+                    load_step(wa[1], bk, tile, st + 1);
+                    mul(wa[0], st);
+                    load_step(wa[0], bk, tile, st + 2);
+                    mul(wa[1], st + 1);
+                }
+                if (st + 1 < bk.steps) {
+                    load_step(wa[1], bk, tile, st + 1);
+                    mul(wa[0], st);
+                    mul(wa[1], st + 1);
+                } else {
+                    mul(wa[0], st);
+                }
+                if (tile + kWaves < bk.tiles) load_step(wa[0], bk, tile + kWaves, 0);
+                else back_first(nx, l > 1);
+                // columns c .. c + 7 of row r: element 2 i + e is register i of operand e
+                const int c = 32 * tile + 8 * (int)quarter;
+                const float *const x = keep + (l * R + r) * P + c;
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    const f32x4 m = *(const f32x4 *)(x + 4 * h);
+                    f32x4 v;
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) v[u] = c + 4 * h + u < in && m[u] > 0.f ? ab[u % 2][2 * h + u / 2] : 0.f;
+                    *(f32x4 *)(dst + c + 4 * h) = v;
+                    if (j0 + r < a.B) *(f32x4 *)(z + c + 4 * h) = v;
+                }
+            }
+            block_sync();
+            cur ^= 1;
+            bk = nx;
+        }
+    } else {
+        for (int l = top; l >= 1; --l) {
+            const float *src = dzb + cur * R * P;
+            const Back nx = back(args.bwd[max(l - 1, 1)]);
+            f32x4 ab[NR][4];
+            if (active(bk)) {
+#pragma unroll
+                for (int g = 0; g < NR; ++g)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) ab[g][e] = f32x4{0.f, 0.f, 0.f, 0.f};
+                chunks(bk, [&](const f32x4 (&w)[4], int c) {
+                    float ax[NR];
+#pragma unroll
+                    for (int g = 0; g < NR; ++g) ax[g] = src[4 * g * P + brow + 16 * c];
+#define TJ_STEP(b)                                                                                            \
+        _Pragma("unroll") for (int e = 0; e < 4; ++e) _Pragma("unroll") for (int g = 0; g < NR; ++g) ab[g][e] =   \
+            __builtin_amdgcn_mfma_f32_4x4x1f32(ax[g], w[b][e], ab[g][e], 2, b, 0);
+                    TJ_STEP(0) TJ_STEP(1) TJ_STEP(2) TJ_STEP(3)
+#undef TJ_STEP
+                });
+            }
+            load_first(nx, l > 1);
+            if (active(bk)) {
+#pragma unroll
+                for (int g = 0; g < NR; ++g) put_part(ab[g], g);
+            }
+            block_sync();
+            const int F = bk.F;
+            for (int u = wave; u < NR * F; u += kWaves) {
+                const int g = (int)((uint32_t)u * bk.rF >> 16), f = u - g * F;
+                put(l, g, f * 64 + fpos, get_part(bk, g, f), cur ^ 1);
+            }
+            block_sync();
+            cur ^= 1;
+            bk = nx;
+        }
+    }
+
     if (wave == 0) {   // the block's sums, in a fixed order
         if (DQN) {
             const float s = wave_sum(lane < R ? sm[lane] : 0.f);
@@ -371,68 +700,6 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, KIN
                 if (lane == 0) a.loss_part[(size_t)blockIdx.x * 4 + q] = s;
             }
         }
-    }
-
-    // ---- input gradients.  dZ of layer l - 1 = relu'(X_l) (dZ_l W_l)
-    int cur = 0;
-    auto put = [&](int l, int g, int col, f32x4 s, int buf) {   // layer l's input gradient, rows of group g
-        const TjF32Layer &b = a.lay[l - 1];
-        const int in = a.lay[l].in, j = j0 + 4 * g;
-        const float *x = keep + (l * R + 4 * g) * P + col;
-        float *dst = dzb + (buf * R + 4 * g) * P + col, *z = b.dZ + (size_t)j * b.lddz + col;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const float v = col < in && x[i * P] > 0.f ? s[i] : 0.f;
-            dst[i * P] = v;
-            if (j + i < a.B) z[i * b.lddz] = v;
-        }
-    };
-    if (DQN && L >= 2) {   // the head's: one non-zero per row of dL/dQ, no contraction
-        const int F = (a.lay[last].in + 63) / 64;
-        for (int u = wave; u < NR * F; u += kWaves) {
-            const int g = NR == 1 ? 0 : u / F, col = (u - g * F) * 64 + lane;
-            f32x4 s;
-#pragma unroll
-            for (int i = 0; i < 4; ++i) s[i] = sm[16 + 4 * g + i] * lds[o.wa + (4 * g + i) * P + col];
-            put(last, g, col, s, 0);
-        }
-        block_sync();
-    }
-    for (int l = DQN ? L - 2 : L - 1; l >= 1; --l) {
-        const float *src = dzb + cur * R * P;
-        Mine nx = ph;
-        if (l - 1 >= 1) nx = mine(args.bwd[l - 1]);
-        f32x4 ab[NR][4];
-        if (active(ph)) {
-#pragma unroll
-            for (int g = 0; g < NR; ++g)
-#pragma unroll
-                for (int e = 0; e < 4; ++e) ab[g][e] = f32x4{0.f, 0.f, 0.f, 0.f};
-            chunks(ph, Two<false>{}, [&](const f32x4 (&w)[4], const f32x4 (&)[4], int c) {
-                float ax[NR];
-#pragma unroll
-                for (int g = 0; g < NR; ++g) ax[g] = src[4 * g * P + arow + 16 * c];
-#define TJ_STEP(b)                                                                                            \
-    _Pragma("unroll") for (int e = 0; e < 4; ++e) _Pragma("unroll") for (int g = 0; g < NR; ++g) ab[g][e] =   \
-        __builtin_amdgcn_mfma_f32_4x4x1f32(ax[g], w[b][e], ab[g][e], 2, b, 0);
-                TJ_STEP(0) TJ_STEP(1) TJ_STEP(2) TJ_STEP(3)
-#undef TJ_STEP
-            });
-        }
-        if (l > 1) load_first(nx, Two<false>{});
-        if (active(ph)) {
-#pragma unroll
-            for (int g = 0; g < NR; ++g) put_part(ab[g], g, NR);
-        }
-        block_sync();
-        const int F = ph.F;
-        for (int u = wave; u < NR * F; u += kWaves) {
-            const int g = (int)((uint32_t)u * ph.rF >> 16), f = u - g * F;
-            put(l, g, f * 64 + fpos, get_part(ph, g, NR, f), cur ^ 1);
-        }
-        block_sync();
-        cur ^= 1;
-        ph = nx;
     }
 }
 
@@ -636,9 +903,9 @@ __device__ __forceinline__ void update_tile(const TjF32Update &a, const UpdatePl
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < (TN * TK + kUThreads - 1) / kUThreads; ++i) {
-        const int e = tid + i * kUThreads, kk = e / TN, nn = e % TN;
+        const int e = tid + i * kUThreads, kk = e / (4 * TN) * 4 + e % 4, nn = e / 4 % TN;
         if (kk < TK && k0 + kk < y.in && n0 + nn < y.out) {
-            const size_t at = (size_t)(k0 + kk) * y.ldn + n0 + nn;
+            const size_t at = tjplan::f32_copy_at(n0 + nn, k0 + kk, y.ldn);
             const float th = lds[kk * TP + nn];
             y.WT[at] = th;
             if (a.sync_target) y.WT_tg[at] = th;
@@ -680,6 +947,8 @@ __global__ __launch_bounds__(kUThreads) void f32_update(const TjF32Update a, con
         else update_tile<16, 16>(a, plan, l, t, z, lds);
     }
 }
+
+struct F32Cast { TjF32Layer lay[TJ_MAX_LAYERS]; int online; };
 
 // Second half of an update whose gradient came in slices: their sum in slice order, Adam, the transposed copy.  A
 // block owns 16 x 32 weights, a thread two of them; every load is issued before the first use.
@@ -743,13 +1012,25 @@ __global__ __launch_bounds__(256) void f32_adam(const TjF32Update a, const Updat
     __syncthreads();
 #pragma unroll
     for (int v = 0; v < 2; ++v) {
-        const int kk = (tid >> 4) + 16 * v, nn = tid & 15;
+        const int kk = (tid >> 6) * 4 + (tid & 3) + 16 * v, nn = (tid >> 2) & 15;
         if (k0 + kk < y.in && n0 + nn < y.out) {
-            const size_t to = (size_t)(k0 + kk) * y.ldn + n0 + nn;
+            const size_t to = tjplan::f32_copy_at(n0 + nn, k0 + kk, y.ldn);
             y.WT[to] = tile[kk][nn];
             if (a.sync_target) y.WT_tg[to] = tile[kk][nn];
         }
     }
+}
+
+// The copies that the forward pass reads, from the master parameters (creation and set_state only): a layer per blockIdx.y.
+__global__ __launch_bounds__(256) void f32_cast(const F32Cast a)
+{
+    const TjF32Layer &y = a.lay[blockIdx.y];
+    const float *W = a.online ? y.W : y.W_tg, *b = a.online ? y.bias : y.bias_tg;
+    float *WT = a.online ? y.WT : y.WT_tg, *BP = a.online ? y.BP : y.BP_tg;
+    for (size_t e = (size_t)blockIdx.x * 256 + threadIdx.x; e < (size_t)y.in * y.out; e += (size_t)gridDim.x * 256)
+        WT[tjplan::f32_copy_at((int)(e / y.in), (int)(e % y.in), y.ldn)] = W[e];
+    if (blockIdx.x == 0)
+        for (int n = threadIdx.x; n < y.out; n += 256) BP[n] = b[n];
 }
 
 // Tiles of every layer, tn x tk wide.
@@ -822,14 +1103,19 @@ template <int KIND, int NR> int launch_rows(const TjF32Rows &a, int mode, hipStr
     RowsArgs r;
     r.a = a;
     r.o = rows_lds(a.L, a.lay, NR, dqn, back);
+    r.bias = a.lay[0].BP; r.bias_tg = a.lay[0].BP_tg; r.head_W = a.lay[a.L - 1].W;
+    r.A = a.lay[a.L - 1].out;
+    r.kp = a.lay[0].kp;
     r.n_bias = 0;
     for (int l = 0; l < a.L; ++l) {
         const TjF32Layer &y = a.lay[l];
-        r.fwd[l] = make_phase(y.WT, y.WT_tg, y.ldn, y.kp, y.ldn);
-        r.bwd[l] = make_phase(y.W, y.W, y.in, y.out, y.in);
+        r.lay[l] = {y.X, y.dZ, y.in, y.ldx, y.lddz, y.ldn};
+        r.fwd[l] = make_forward(y, l == a.L - 1, r.n_bias);
+        r.bwd[l] = make_phase(y.W, y.in, y.out, y.in);
         r.n_bias += y.ldn;
     }
-    for (int l = a.L; l < TJ_MAX_LAYERS; ++l) r.fwd[l] = r.bwd[l] = r.fwd[0];
+    const tjplan::F32Forward head = tjplan::f32_forward(a.lay[a.L - 1].in, a.lay[a.L - 1].out, true);
+    r.head_slices = std::min(head.KS, head.steps);
     f32_rows<KIND, NR><<<(a.B + 4 * NR - 1) / (4 * NR), kThreads, bytes, st>>>(r, mode);
     return hipGetLastError() == hipSuccess ? TJ_OK : TJ_ERR_DEVICE;
 }
@@ -849,7 +1135,7 @@ bool tj_f32_fits(int L, const int *in, const int *out, int passes, int max_batch
     for (int l = 0; l < L; ++l) {
         if (l + 1 < L && out[l] > kF32MaxWidth) return false;
         lay[l].in = in[l]; lay[l].out = out[l];
-        lay[l].kp = up(in[l], 16); lay[l].ldn = up(out[l], 64);
+        tj_f32_copy_shape(lay[l], l == L - 1);
     }
     const RowsLds o = rows_lds(L, lay, 1, passes == 3, true);
     if (passes == 3 && max_batch > (o.pitch > kQWide ? kQRowsWide : kQRows)) return false;
@@ -894,5 +1180,27 @@ int tj_f32_update(const TjF32Update &a, hipStream_t st)
         const int n_adam = plan_tiles(a.L, a.lay, p);
         f32_adam<<<n_adam + 1, 256, 0, st>>>(a, p);
     }
+    return hipGetLastError() == hipSuccess ? TJ_OK : TJ_ERR_DEVICE;
+}
+
+void tj_f32_copy_shape(TjF32Layer &y, bool head)
+{
+    const tjplan::F32Forward p = tjplan::f32_forward(y.in, y.out, head);
+    y.kp = (16 << p.lq) * p.steps;
+    y.ldn = p.pitch;
+}
+
+size_t tj_f32_copy_at(const TjF32Layer &y, int n, int k) { return tjplan::f32_copy_at(n, k, y.ldn); }
+
+int tj_f32_cast(int L, const TjF32Layer *lay, bool online, hipStream_t st)
+{
+    F32Cast a;
+    size_t most = 0;
+    for (int l = 0; l < TJ_MAX_LAYERS; ++l) {
+        a.lay[l] = lay[l < L ? l : 0];
+        most = std::max(most, (size_t)a.lay[l].in * a.lay[l].out);
+    }
+    a.online = online;
+    f32_cast<<<dim3((unsigned)((most + 255) / 256), L), 256, 0, st>>>(a);
     return hipGetLastError() == hipSuccess ? TJ_OK : TJ_ERR_DEVICE;
 }

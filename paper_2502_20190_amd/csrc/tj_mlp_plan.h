@@ -13,10 +13,44 @@
 
 namespace tjplan {
 
-// ---- the row kernel of fp32 networks: one contraction of a block's rows with a weight matrix [k][features], as F groups of
-// 64 features x KS slices of the nk chunks of 16 k, one per wave.
+// ---- the row kernel of fp32 networks
 constexpr int kF32Waves = 8;
 
+// The forward pass of a layer.  The weight copy is [k / 4][pitch][4]; a wave takes a tile of 64 / q features, its q lane
+// parts a chunk of 16 k each of a step of 16 q, and every KS-th step from its slice's on.  A hidden layer has as many tiles as eight
+// waves can be given and no slices, so that a wave ends with whole sums; the head, whose few outputs make few tiles, has slices
+// instead, which whoever needs the outputs adds.
+struct F32Forward {
+    int pitch, lq, tiles, KS, steps;     // q = 1 << lq
+};
+inline F32Forward f32_forward(int in, int out, bool head)
+{
+    F32Forward p;
+    p.pitch = (out + 63) / 64 * 64;
+    p.lq = head || p.pitch <= 128 ? 2 : p.pitch <= 256 ? 1 : 0;
+    p.tiles = head ? (out + 15) / 16 : (p.pitch << p.lq) / 64;
+    p.KS = head ? std::min(4, kF32Waves / p.tiles) : 1;
+    p.steps = (in + (16 << p.lq) - 1) / (16 << p.lq);
+    return p;
+}
+// A wave's tile, slice and number of steps (wave = slice tiles + tile): steps slice, slice + KS, ... < p.steps, or none.
+struct F32Wave { int tile, ks, n; };
+inline F32Wave f32_wave(const F32Forward &p, int wave)
+{
+    F32Wave w;
+    w.ks = wave / p.tiles;
+    w.tile = wave - w.ks * p.tiles;
+    w.n = w.ks < p.KS && w.ks < p.steps ? (p.steps - w.ks + p.KS - 1) / p.KS : 0;
+    return w;
+}
+TJ_HD inline int f32_part(int lane, int lq) { return lane >> (6 - lq); }   // lane part
+TJ_HD inline int f32_feature(int lane, int tile, int lq) { return (tile << (6 - lq)) + (lane & ((64 >> lq) - 1)); }
+// Element from a step's first k on that load b takes for feature f, with the three behind it: k = 16 part + 4 b ..
+TJ_HD inline unsigned f32_weight_at(int part, int b, int f, int pitch) { return (4u * part + b) * 4u * pitch + 4u * f; }
+TJ_HD inline size_t f32_copy_at(int n, int k, int pitch) { return ((size_t)(k >> 2) * pitch + n) * 4 + (k & 3); }
+
+// A phase of the backward pass: one contraction of a block's rows with a weight matrix [rows][columns] as stored, as F groups
+// of 64 columns x KS slices of the nk chunks of 16 rows, one per wave.
 struct F32Phase {
     int pitch, rows, nk, F, KS;     // pitch: elements between rows of the matrix
 };

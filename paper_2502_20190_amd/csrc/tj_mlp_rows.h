@@ -81,37 +81,40 @@ __device__ __forceinline__ int wave_argmax(float v)
     return m ? __ffsll((long long)m) - 1 : 0;
 }
 
-// The objective of transition j, by one wave with one lane per head output; `valid` is false for rows past the batch.
+// The value that one lane of the wave holds; `lane` is the same on all of them.
+__device__ __forceinline__ float lane_value(float v, int lane) { return __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(v), lane)); }
+
+// The objective of transition j, by one wave with one lane per head output (lanes from A on hold anything); act is the same on all
+// lanes; `valid` is false for rows past the batch.
 struct TdRow { float loss, g; int best; };   // g = dL/dQ(s, action)
-__device__ __forceinline__ TdRow td_row(const TjRowsCall &a, int A, const float *q_s, const float *q_next,
-                                        const float *q_next_tg, int act, float reward, float not_done, bool valid)
+__device__ __forceinline__ TdRow td_row(const TjRowsCall &a, int A, float q_s, float q_next, float q_next_tg, int act, float reward, float not_done, bool valid)
 {
     const int lane = threadIdx.x & 63;
     TdRow t;
-    t.best = wave_argmax(lane < A ? q_next[lane] : -INFINITY);
-    const float target = reward + a.gamma * not_done * q_next_tg[t.best];
-    const float d = q_s[act] - target, ad = fabsf(d);
+    t.best = wave_argmax(lane < A ? q_next : -INFINITY);
+    const float target = reward + a.gamma * not_done * lane_value(q_next_tg, t.best);
+    const float d = lane_value(q_s, act) - target, ad = fabsf(d);
     t.g = valid ? fminf(fmaxf(d, -a.kappa), a.kappa) / (float)a.B : 0.f;
     t.loss = !valid ? 0.f : ad <= a.kappa ? 0.5f * d * d : a.kappa * (ad - 0.5f * a.kappa);
     return t;
 }
 
 struct PpoRow { float pi, v, H, g; };        // g: this lane's dL/dz
-__device__ __forceinline__ PpoRow ppo_row(const TjRowsCall &a, int n, const float *zs, int act, float old_logp, float adv,
+__device__ __forceinline__ PpoRow ppo_row(const TjRowsCall &a, int n, float zs, int act, float old_logp, float adv,
                                           float ret, bool valid)
 {
     const int lane = threadIdx.x & 63;
-    const float z = lane <= n ? zs[lane] : 0.f;
+    const float z = lane <= n ? zs : 0.f;
     const float mx = wave_max(lane < n ? z : -INFINITY);
     const float lse = mx + logf(wave_sum(lane < n ? expf(z - mx) : 0.f));
     const float lp = z - lse, pk = lane < n ? expf(lp) : 0.f;
     PpoRow r;
     r.H = wave_sum(lane < n ? -pk * lp : 0.f);
-    const float rho = expf(zs[act] - lse - old_logp);
+    const float rho = expf(lane_value(zs, act) - lse - old_logp);
     const float rc = fminf(fmaxf(rho, 1.f - a.clip), 1.f + a.clip);
     const float s1 = rho * adv, s2 = rc * adv;
     const bool unclipped = s1 <= s2;   // the minimum is the unclipped term: it carries the gradient
-    const float verr = zs[n] - ret, inv_b = 1.f / (float)a.B;
+    const float verr = lane_value(zs, n) - ret, inv_b = 1.f / (float)a.B;
     r.g = 0.f;
     if (lane < n) {
         r.g = a.c_e * pk * (lp + r.H);
@@ -127,11 +130,11 @@ __device__ __forceinline__ PpoRow ppo_row(const TjRowsCall &a, int n, const floa
     return r;
 }
 
-// What acting does with the head outputs of observation j (zs; A of them), by one wave.
-__device__ __forceinline__ void act_row(const TjRowsCall &a, int mode, int j, int A, const float *zs)
+// What acting does with the head outputs of observation j (A of them, one per lane), by one wave.
+__device__ __forceinline__ void act_row(const TjRowsCall &a, int mode, int j, int A, float zs)
 {
     const int lane = threadIdx.x & 63;
-    const float z = lane < A ? zs[lane] : 0.f;
+    const float z = lane < A ? zs : 0.f;
     if (mode == TJ_ROWS_ACT) {
         const int best = wave_argmax(lane < A ? z : -INFINITY);
         if (a.q_out && lane < A) a.q_out[(size_t)j * A + lane] = z;

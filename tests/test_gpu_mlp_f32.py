@@ -131,3 +131,27 @@ def test_acting_on_many_observations(tj, orc, D, widths, A):
     g, o = T._pair(tj, orc, wl, seed=7)
     for n in (1024, 1025, 2048, 2053, 4999):
         T._check_act(tj, orc, g, o, wl, T._batch(wl, 61, n)["obs"], 0.1, n, TOL)
+
+
+@pytest.mark.parametrize("D,widths,A,B", [(20, (192, 320), 18, 70), (300, (257, 129, 64), 33, 1030), (65, (256, 255), 17, 9)])
+def test_q_learner_at_the_edges_of_the_feature_tiles(tj, orc, D, widths, A, B):
+    """Tiles of 16, 32 and 64 features (128 | 129 and 256 | 257 wide), steps of 64, 32 and 16 k with a remainder, one to three tiles of the
+    head.  Tolerance as above: at most 1030 terms."""
+    layers = tuple((LIN, w, 0, 0) for w in widths) + ((LIN, A, 0, 0),)
+    wl = replace(synth.WORKLOADS["c2"], obs_shape=(D,), n_actions=A, batch=B, layers=layers, precision="fp32", lr=1e-3, target_interval=2)
+    g, o = T._pair(tj, orc, wl, seed=9)
+    for step in range(2):
+        T._step_both(tj, orc, g, o, wl, T._batch_clear_of_kinks(o, wl, 97 + step, B), TOL, check_state=False, sync=step > 0)
+        T._check_compute_copies(tj, g, wl)
+
+
+@pytest.mark.parametrize("D,widths,A,B", [(12, (129, 257), 18, 2101), (5, (33, 512), 2, 2049), (70, (64, 31, 96), 33, 4099)])
+def test_on_policy_learner_with_sixteen_rows_per_block(tj, orc, D, widths, A, B):
+    """From 2049 rows on: column tiles of 32 with a remainder, more tiles than waves (512 wide), contractions over fewer rows of a matrix
+    than a step and over a remainder, a last block of 1 to 5 rows.  Sums over 4099 rows: 4099 * 2^-24 = 2.4e-4 at the worst, some
+    64 * 2^-24 = 4e-6 where the roundings are independent."""
+    g, o = P._pair(tj, orc, D, widths, A, "fp32", B, seed=5, lr=1e-3)
+    for step in range(2):
+        rows = P._batch(orc, o, D, A, 1 + B // 8, 8, 74 + step, "fp32", n=B)
+        P._step_both(tj, orc, g, o, rows, TOL, sync=step > 0)
+        P._check_compute_copies(tj, g, "fp32")

@@ -44,19 +44,10 @@ typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef const __attribute__((address_space(1))) uint8_t *gbytes;
 typedef const __attribute__((address_space(1))) __attribute__((aligned(4))) f32x4 *gf32x4;
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-typedef __amdgpu_buffer_rsrc_t buf_rsrc;
-
-// A wave-uniform stretch of memory; loads at or past its end are zeros and touch nothing.
-__device__ __forceinline__ buf_rsrc row_buffer(const float *p, int bytes)
-{
-    return __builtin_amdgcn_make_buffer_rsrc((void *)p, 0, bytes, 0x00027000);
-}
 __device__ __forceinline__ f32x4 load16(buf_rsrc r, uint32_t at, int base)
 {
     return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(r, (int)at, base, 0));
 }
-__device__ __forceinline__ float load4(buf_rsrc r, int at) { return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, at, 0, 0)); }
 
 constexpr int kWaves = tjplan::kF32Waves, kThreads = 64 * kWaves;   // f32_rows: two waves per SIMD, 256 registers each
 constexpr size_t kLdsMax = 160 * 1024;
@@ -207,7 +198,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, KIN
         constexpr int s = decltype(set)::value;
         if (i >= p.n) return;   // a load that finds nothing would still take its turn on the way back
         const int at = p.w_at + i * p.wstep;
-        const buf_rsrc r0 = row_buffer(p.w0, (int)p.bytes), r1 = row_buffer(p.w1, (int)p.bytes);
+        const buf_rsrc r0 = buf_of(p.w0, (int)p.bytes), r1 = buf_of(p.w1, (int)p.bytes);
 #pragma unroll
         for (int b = 0; b < 4; ++b) wa[s][b] = load16(r0, p.at[b], at);
         if constexpr (DQN) {
@@ -238,7 +229,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, KIN
     };
     auto active = [&](const Back &p) { return p.ks < p.KS && p.ks < p.nk; };
     auto load_chunk = [&](f32x4 (&w)[4], const Back &p, int c, bool have) {
-        const buf_rsrc r = row_buffer(p.w, have ? 4 * p.rows * p.pitch : 0);
+        const buf_rsrc r = buf_of(p.w, have ? 4 * p.rows * p.pitch : 0);
         const int at = have ? 4 * (int)tjplan::f32_chunk_at(c, p.pitch) : 0;
         const uint32_t last_row = tjplan::f32_last_row_at(c, p.rows, p.pitch);
 #pragma unroll
@@ -270,7 +261,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, KIN
     struct Back16 { const float *w; int bytes, pitch, steps, tiles; };
     auto back16 = [&](const Phase &p) { return Back16{p.w, 4 * p.rows * p.pitch, 4 * p.pitch, (p.rows + 31) / 32, (p.cols + 31) / 32}; };
     auto load_step = [&](f32x4 (&w)[4], const Back16 &p, int tile, int s) {
-        const buf_rsrc r = row_buffer(p.w, p.bytes);
+        const buf_rsrc r = buf_of(p.w, p.bytes);
         const int at = (32 * s + 4 * (int)quarter) * p.pitch + 128 * tile + 8 * (lane & 15);   // past the end in the lane's part: a scalar part must not be
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
@@ -357,7 +348,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, KIN
             }
         }
         const int nb = args.n_bias;
-        const buf_rsrc b_on = row_buffer(args.bias, 4 * nb), b_tg = row_buffer(args.bias_tg, DQN ? 4 * nb : 0);
+        const buf_rsrc b_on = buf_of(args.bias, 4 * nb), b_tg = buf_of(args.bias_tg, DQN ? 4 * nb : 0);
         float b[2], bt[2];
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
@@ -368,13 +359,13 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, KIN
         for (int i = 0; i < NOW; ++i) {
             const int r = wave + kWaves * i;
             const uint32_t row = __builtin_amdgcn_readfirstlane(a.rows ? min(idx[i], a.n_rows - 1u) : idx[i]);
-            src[i] = row_buffer((!DQN || r < R ? a.obs : a.next_obs) + (size_t)row * D, r < NO ? 4 * D : 0);
+            src[i] = buf_of((!DQN || r < R ? a.obs : a.next_obs) + (size_t)row * D, r < NO ? 4 * D : 0);
         }
         if (DQN && L >= 2)
 #pragma unroll
             for (int i = 0; i < RW; ++i) {
                 const int aw = __builtin_amdgcn_readfirstlane(min(max(aj[i], 0), A - 1));
-                head_w[i] = row_buffer(args.head_W + (size_t)aw * in_h, kWaves - 1 - wave + kWaves * i < R ? 4 * in_h : 0);
+                head_w[i] = buf_of(args.head_W + (size_t)aw * in_h, kWaves - 1 - wave + kWaves * i < R ? 4 * in_h : 0);
             }
         const int width = max(kp, DQN && L >= 2 ? in_h : 0);
         for (int c0 = 0; c0 < width; c0 += 128) {   // columns past a row are zeros

@@ -48,6 +48,14 @@ struct TjUpdateCall {
     tj_ppo_stats *ppo_stats, *ppo_internal;
 };
 
+// A wave-uniform stretch of memory; loads at or past its end are zeros and touch nothing.
+typedef __amdgpu_buffer_rsrc_t buf_rsrc;
+__device__ __forceinline__ buf_rsrc buf_of(const void *p, int bytes)
+{
+    return __builtin_amdgcn_make_buffer_rsrc((void *)p, 0, bytes, 0x00027000);
+}
+__device__ __forceinline__ float load4(buf_rsrc r, int at) { return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, at, 0, 0)); }
+
 // Orders LDS accesses across the block without waiting for global loads: those in flight belong to the next
 // layer (a __syncthreads() may drain them).
 __device__ __forceinline__ void block_sync()

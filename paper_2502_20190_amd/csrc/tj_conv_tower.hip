@@ -11,13 +11,12 @@
 //                 256 that eight waves leave each).  Every sum runs over its whole contraction in one accumulator, in the order of
 //                 the gathered GEMMs (one 16 x 16 x 32 step adds in the order of two 32 x 32 x 16 steps: checked bit for bit), so
 //                 that greedy actions do not move between this kernel and those.
-// Rows of the activations in LDS are padded by 16 bytes: 80 and 144 bytes apart, 16 consecutive patches read 16 distinct 16-byte
-// columns.  The second layer has stride 2, so its input keeps even and odd columns apart, which makes consecutive patches
+// Rows of the activations in LDS are padded by 32 bytes, to 96 and 160.  A 16-byte read serves sixteen lanes at a time, not consecutive ones
+// but rows 0 - 3 and 12 - 15 of one lane group of the fragment and rows 4 - 11 of the next one (8 channels on): rows an odd number of 16-byte
+// units apart (80, 144 bytes) meet there and run at half rate, 6.0 against 3.2 clocks per wave read in a bare loop; rows 2 mod 4 units
+// apart do not.  The second layer has stride 2, so its input keeps even and odd columns apart, which makes consecutive patches
 // consecutive rows.  Sixteen patches mostly end one output row and begin another: the rows of the image they read (even and odd ones
-// apart as well) have a pitch that continues the sequence of columns there (tower_plan).  With it 34 % of the cycles in which the LDS
-// is busy are conflicts instead of 44 %: 171 -> 160 us at 3 x 2048 passes, 31.6 -> 30.4 at 3 x 256.  What is left comes from the
-// four lane groups of a fragment, whose pieces of 8 channels lie in one row: a 16-byte read serves lanes of several groups at a time.
-// Octets of channels in two planes would halve it (18 %) and took nothing off a pass.
+// apart as well) have a pitch that continues the sequence of columns there (tower_plan).
 // While an image is in the second layer the next one, fetched into registers a layer ahead, is converted into the image buffer.
 #include "tj_conv_planes.h"
 #include <algorithm>
@@ -38,7 +37,7 @@ constexpr int K1 = 8, C1 = 32, K2 = 4, S2 = 2, C2 = 64, K3 = 3, C3 = 64;   // ke
 constexpr int kRounds = 4;              // 4-pixel tasks per thread and image
 constexpr int kTiles2 = 3, kTiles3 = 2; // tiles of 16 patches per wave (two waves share the patches)
 constexpr int kSteps2 = K2 * K2 * C1 / 32, kSteps3 = K3 * K3 * C2 / 32;   // 32-value steps of a contraction
-constexpr int kRow1 = C1 * 2 + 16, kRow2 = C2 * 2 + 16;   // bytes between activation rows in LDS
+constexpr int kRow1 = C1 * 2 + 32, kRow2 = C2 * 2 + 32;   // bytes between activation rows in LDS
 constexpr int kW1Pitch = (4 * K1 * K1 + 8) * 2;           // ... between the first layer's weight rows
 constexpr int kUnits2 = 4 * kSteps2, kUnits3 = 4 * kSteps3;               // 16-byte units of a weight row of the other two,
 constexpr int kGroup2 = 16 * (kUnits2 + 1) * 16, kGroup3 = 16 * (kUnits3 + 1) * 16;   // bytes of 16 such rows, a unit apart, in LDS
@@ -358,6 +357,333 @@ void conv_tower(const TjConvTowerArgs a, const TowerPlan p)
     }
 }
 
+// ---- many passes per block: the layers of two images side by side
+
+struct PipePlan {
+    int bias, out1, out1_bytes, out2, total; // byte offsets in LDS (the image is at 0); two outputs of the first layer, out1_bytes apart
+    int half1, rows1, pitch1, pitch2;        // as in TowerPlan
+    uint32_t mg_ow1, mg_ow2, mg_ow3;
+    int n_pass;
+};
+
+PipePlan pipe_plan(int H, int W, int OH1, int OW1, int OH2, int OW2, int OW3)
+{
+    const TowerPlan t = tower_plan(H, W, OH1, OW1, OH2, OW2, OW3);
+    PipePlan p;
+    p.half1 = t.half1; p.rows1 = t.rows1; p.pitch1 = t.pitch1; p.pitch2 = t.pitch2;
+    p.mg_ow1 = t.mg_ow1; p.mg_ow2 = t.mg_ow2; p.mg_ow3 = t.mg_ow3;
+    p.bias = H * W * 8;
+    p.out1 = p.bias + (C1 + C2 + C3) * 4;
+    p.out1_bytes = std::max(S2 * p.rows1 * p.pitch1, C1 * kW1Pitch);   // the second one takes the first layer's weights before a run
+    p.out2 = p.out1 + 2 * p.out1_bytes;
+    p.total = p.out2 + OH2 * p.pitch2;
+    p.n_pass = 0;
+    return p;
+}
+
+// The same layers, sums and results as conv_tower for blocks with several passes.  There eight waves go through the layers of one image
+// together and wait for each other behind each: LDS reads, the image's conversion and the products take turns.  Here four waves (one
+// per SIMD) take the first layer of an image while the other four take the second and third of the one before it:
+//             first four waves                                       last four waves
+//   phase 1   first layer of image i -> out1[i % 2]                  second layer of image i - 1 -> out2
+//   phase 2   image i + 1 into the image buffer, i + 2 asked for     third layer of image i - 1
+// with a barrier behind each phase.  The first layer's weights live in the first waves' registers (they took a third of that layer's LDS
+// reads), a last wave has 16 channels of the other two layers and all patches.  What bounds it: 4350 clocks of products per SIMD and pass and
+// the reads that feed them (700 KB per pass) in 10200, phase 1 about 6200 of them.  Measured, us per update of 3 x 2048 passes from a
+// frame ring: 430 -> 402.  Reads further ahead change nothing, priority for either half costs 1 - 4 %, and loads of the image spread over both
+// phases take 0.4 % off 24 passes per block and add 1.2 % to three.
+constexpr int kHalf = kThreads / 2;
+constexpr int kFetch = 2;                    // 16-pixel tasks per thread of the first four waves
+
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2)))
+void conv_tower_pipe(const TjConvTowerArgs a, const PipePlan p)
+{
+    extern __shared__ __align__(16) uint8_t lds[];
+    uint8_t *const img = lds, *const out2 = lds + p.out2;
+    float *const bias = (float *)(lds + p.bias);
+    const TjConvFirstArgs &f = a.first;
+    const int tid = threadIdx.x;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int HW = f.H * f.W, W = f.W, OHW1 = f.OH * f.OW, OHW2 = a.OH2 * a.OW2, OHW3 = a.OH3 * a.OW3;
+    const int begin = (int)((long)blockIdx.x * p.n_pass / gridDim.x), end = (int)((long)(blockIdx.x + 1) * p.n_pass / gridDim.x);
+    if (begin >= end) return;
+    auto out1 = [&](int pass) { return lds + p.out1 + (pass & 1 ? p.out1_bytes : 0); };
+    auto row1 = [&](uint8_t *base, uint32_t m) -> uint8_t * {   // patch m of the first layer's output
+        const uint32_t oh = __umulhi(m, p.mg_ow1), ow = m - oh * f.OW;
+        return base + ((oh & 1) * p.rows1 + (oh >> 1)) * p.pitch1 + ((ow & 1) * p.half1 + (ow >> 1)) * kRow1;
+    };
+    auto row2 = [&](uint32_t m) -> uint8_t * {   // the second layer's
+        const uint32_t oh = __umulhi(m, p.mg_ow2), ow = m - oh * a.OW2;
+        return out2 + oh * p.pitch2 + ow * kRow2;
+    };
+
+    if (wave < 4) {
+        // ---- images.  Unit = 16 bytes of LDS = two pixels, even and odd units apart, as in conv_tower
+        typedef u32x4 u32x4_a4 __attribute__((aligned(4)));
+        typedef const __attribute__((address_space(1))) uint8_t *gbytes;
+        u32x4 px[kFetch][4];
+        uint32_t idx[4];
+        auto image_of = [&](int pass) { return pass < 2 * f.B ? pass : pass - f.B; };
+        const bool named = f.planes || f.rows;
+        // What names the pass's planes, a fetch ahead of their use.  One load whatever names them (a float's bits where nothing
+        // does): values that meet behind branches would be waited for there.
+        auto look_up = [&](int pass) {
+            const int g = image_of(pass), b = g < f.B ? g : g - f.B;
+            const uint32_t *at = f.planes ? f.planes + (size_t)b * 8 + (g >= f.B ? 4 : 0) : f.rows ? f.rows + b : (const uint32_t *)f.b_on;
+            const int step = f.planes ? 1 : 0;
+#pragma unroll
+            for (int c = 0; c < 4; ++c) idx[c] = at[c * step];
+        };
+        auto fetch = [&](int pass) {
+            const int g = image_of(pass), b = g < f.B ? g : g - f.B;
+            const uint8_t *src = g >= f.B ? f.next_obs : f.obs;
+            int t0 = tid;
+            asm volatile("" : "+v"(t0));
+            // the last task may begin before its turn, and threads without one repeat it: a load under a condition leaves its register
+            // with two possible values, and the copy that joins them waits for it (12000 -> 10200 clocks per pass with what follows)
+            const uint32_t at0 = min(16 * t0, HW - 16), at1 = min(16 * (t0 + kHalf), HW - 16);
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                const uint32_t i = named ? min((uint32_t)__builtin_amdgcn_readfirstlane(idx[c]), f.n_rows - 1u) : (uint32_t)b;
+                gbytes plane = (gbytes)(uintptr_t)(src + (f.planes ? (size_t)i : (size_t)i * 4 + c) * HW);
+                asm("" : "+s"(plane));
+                px[0][c] = *(const __attribute__((address_space(1))) u32x4_a4 *)(plane + at0);
+                px[1][c] = *(const __attribute__((address_space(1))) u32x4_a4 *)(plane + at1);
+            }
+        };
+        auto convert = [&]() {
+            int t0 = tid;
+            asm volatile("" : "+v"(t0));
+#pragma unroll
+            for (int r = 0; r < kFetch; ++r) {
+                const int t = t0 + r * kHalf;
+                if (16 * t >= HW) break;
+                uint8_t *const dst = img + min(16 * t, HW - 16) * 4;
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    u32x4 v[2];
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {     // a pixel, channels 0..3
+                        float x[4];
+#pragma unroll
+                        for (int c = 0; c < 4; ++c) x[c] = (float)((px[r][c][j] >> (8 * q)) & 0xFF) * f.scale;
+                        v[q >> 1][2 * (q & 1)] = pack2(x[0], x[1]);
+                        v[q >> 1][2 * (q & 1) + 1] = pack2(x[2], x[3]);
+                    }
+                    *(u32x4 *)(dst + j * 16) = v[0];
+                    *(u32x4 *)(dst + HW * 4 + j * 16) = v[1];
+                }
+            }
+        };
+        look_up(begin);
+        for (int pass = begin; pass < end;) {   // runs under one network's weights
+            const int net = pass >= 2 * f.B, run_end = net ? end : min(end, 2 * f.B);
+            fetch(pass);
+            if (pass + 1 < end) look_up(pass + 1);
+            lds_sync();   // the last run is through
+            constexpr int VR = 4 * K1 * K1 / 8;   // 16-byte vectors per row of the first layer's weights
+            uint8_t *const w1 = lds + p.out1 + p.out1_bytes;
+            for (int v = tid; v < C1 * VR; v += kHalf)
+                *(u32x4 *)(w1 + (v / VR) * kW1Pitch + (v % VR) * 16) = *(const u32x4 *)((net ? f.W_tg : f.W_on) + (size_t)v * 8);
+            if (tid < C1) bias[tid] = (net ? f.b_tg : f.b_on)[tid];
+            else if (tid < C1 + C2) bias[tid] = (net ? a.b2_tg : a.b2_on)[tid - C1];
+            else if (tid < C1 + C2 + C3) bias[tid] = (net ? a.b3_tg : a.b3_on)[tid - C1 - C2];
+            convert();
+            lds_sync();
+            u32x4 wv[2 * K1];
+#pragma unroll
+            for (int n = 0; n < 2 * K1; ++n) wv[n] = *(const u32x4 *)(w1 + (tid & 31) * kW1Pitch + 16 * ((tid >> 5) & 1) + n * 32);
+            lds_sync();   // the weights have been read: their memory is out1 of the odd passes
+            if (pass + 1 < run_end) {
+                fetch(pass + 1);
+                if (pass + 2 < end) look_up(pass + 2);
+            }
+            for (; pass < run_end; ++pass) {
+                // ---- phase 1: first layer
+                int tid1 = tid;   // opaque, so that addresses are not kept in registers from pass to pass
+                asm volatile("" : "+v"(tid1));
+                const int lane1 = tid1 & 31, h1 = (tid1 >> 5) & 1, n_tile = (OHW1 + 31) / 32;
+                uint8_t *const out = out1(pass);
+                auto tiles = [&](int tile, auto count) {
+                    constexpr int N = decltype(count)::value;
+                    const uint8_t *src[N];
+                    uint8_t *dst[N];
+                    f32x16 acc[N];
+#pragma unroll
+                    for (int t = 0; t < N; ++t) {
+                        const uint32_t m = min(32 * (tile + t * 4) + lane1, OHW1 - 1), oh = __umulhi(m, p.mg_ow1), ow = m - oh * f.OW;
+                        src[t] = img + h1 * HW * 4 + (oh * f.s * W + ow * f.s) * 4;
+                        dst[t] = row1(out, m) + 8 * h1;
+#pragma unroll
+                        for (int r = 0; r < 16; ++r) acc[t][r] = 0.f;
+                    }
+                    // steps of 16 contraction values (4 pixels x 4 channels), the next ones' operands on their way
+                    u32x4 pv[4][N];
+                    auto read = [&](int n) {
+#pragma unroll
+                        for (int t = 0; t < N; ++t) pv[n & 3][t] = *(const u32x4 *)(src[t] + (n >> 1) * W * 4 + (n & 1) * 16);
+                    };
+                    read(0); read(1); read(2);
+#pragma unroll
+                    for (int n = 0; n < 2 * K1; ++n) {
+                        if (n + 3 < 2 * K1) read(n + 3);
+                        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                        for (int t = 0; t < N; ++t)
+                            acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, wv[n]), __builtin_bit_cast(bf16x8, pv[n & 3][t]),
+                                                                             acc[t], 0, 0, 0);
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+                    // acc[4q + e] = channel 8q + 4h + e of a patch; tiles past the last patch repeat it, into the same place
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        const f32x4 b = *(const f32x4 *)(bias + 8 * q + 4 * h1);
+#pragma unroll
+                        for (int t = 0; t < N; ++t) {
+                            float x[4];
+#pragma unroll
+                            for (int e = 0; e < 4; ++e) x[e] = fmaxf(acc[t][4 * q + e] + b[e], 0.f);
+                            *(uint2 *)(dst[t] + 16 * q) = make_uint2(pack2(x[0], x[1]), pack2(x[2], x[3]));
+                        }
+                    }
+                };
+                int tile = wave;
+                for (; tile + 4 < n_tile; tile += 8) tiles(tile, std::integral_constant<int, 2>{});
+                if (tile < n_tile) tiles(tile, std::integral_constant<int, 1>{});
+                lds_sync();
+                // ---- phase 2: the next image, and what the backward pass reads of this one
+                if (pass + 1 < run_end) {
+                    convert();
+                    if (pass + 2 < run_end) {
+                        fetch(pass + 2);
+                        if (pass + 3 < end) look_up(pass + 3);
+                    }
+                }
+                if (f.out && pass < f.B) {
+                    tj_bf16 *dst = f.out + (size_t)pass * OHW1 * C1;
+                    for (int v = tid1; v < OHW1 * 4; v += kHalf) *(u32x4 *)(dst + (size_t)v * 8) = *(const u32x4 *)(row1(out, v >> 2) + (v & 3) * 16);
+                }
+                lds_sync();
+            }
+            lds_sync();   // the last image's second layer
+            lds_sync();   // ... and third
+            if (pass < end) look_up(pass);
+        }
+    } else {
+        const int ct = wave - 4;
+        constexpr int T2 = 2 * kTiles2, T3 = 2 * kTiles3;
+        constexpr int D2 = 2, D3 = 2;   // reads ahead: half steps of the second layer, steps of the third
+        const int lane = tid & 63, l16 = lane & 15, q4 = lane >> 4;
+        // where the patches start in the activations of the layer below (tiles past the last patch repeat it)
+        int at2[T2], at3[T3];
+#pragma unroll
+        for (int i = 0; i < T2; ++i) {
+            const uint32_t m = min(i * 16 + l16, OHW2 - 1), oh = __umulhi(m, p.mg_ow2), ow = m - oh * a.OW2;
+            at2[i] = oh * p.pitch1 + ow * kRow1 + 16 * q4;
+        }
+#pragma unroll
+        for (int i = 0; i < T3; ++i) {
+            const uint32_t m = min(i * 16 + l16, OHW3 - 1), oh = __umulhi(m, p.mg_ow3), ow = m - oh * a.OW3;
+            at3[i] = oh * a.s3 * p.pitch2 + ow * a.s3 * kRow2 + 16 * q4;
+        }
+        for (int pass = begin; pass < end;) {
+            const int net = pass >= 2 * f.B, run_end = net ? end : min(end, 2 * f.B);
+            u32x4 w2[kSteps2], w3[kSteps3];
+            {
+                const tj_bf16 *r2 = (net ? a.W2_tg : a.W2_on) + ((size_t)(16 * ct + l16) * kUnits2 + q4) * 8;
+                const tj_bf16 *r3 = (net ? a.W3_tg : a.W3_on) + ((size_t)(16 * ct + l16) * kUnits3 + q4) * 8;
+#pragma unroll
+                for (int i = 0; i < kSteps2; ++i) w2[i] = *(const u32x4 *)(r2 + 32 * i);
+#pragma unroll
+                for (int i = 0; i < kSteps3; ++i) w3[i] = *(const u32x4 *)(r3 + 32 * i);
+            }
+            lds_sync();   // the last run is through
+            lds_sync();   // the first image and the weights of the first layer are in place
+            lds_sync();   // ... which have been read
+            lds_sync();   // the first image's first layer
+            lds_sync();   // the second image
+            for (; pass < run_end; ++pass) {
+                int tid1 = tid;
+                asm volatile("" : "+v"(tid1));
+                const int p16 = tid1 & 15, c4 = 16 * ct + 4 * ((tid1 >> 4) & 3);
+                // ---- phase 1: second layer, out1 -> out2.  A step is one tap of 32 channels, the next one's reads on their way
+                const uint8_t *const in = out1(pass);
+                f32x4 acc2[T2];
+#pragma unroll
+                for (int i = 0; i < T2; ++i) acc2[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+                u32x4 x[D2 + 1][kTiles2];
+                auto read2 = [&](int u) {   // half the tiles of step u / 2
+                    const int kh = u / 2 / K2, kw = u / 2 % K2;
+                    const int off = ((kh % S2) * p.rows1 + kh / S2) * p.pitch1 + ((kw % S2) * p.half1 + kw / S2) * kRow1;
+#pragma unroll
+                    for (int i = 0; i < kTiles2; ++i) x[u % (D2 + 1)][i] = *(const u32x4 *)(in + at2[u % 2 * kTiles2 + i] + off);
+                };
+#pragma unroll
+                for (int u = 0; u < D2; ++u) read2(u);
+#pragma unroll
+                for (int u = 0; u < 2 * kSteps2; ++u) {
+                    if (u + D2 < 2 * kSteps2) read2(u + D2);
+                    __builtin_amdgcn_sched_barrier(0);   // left alone, the compiler reads right before each product
+#pragma unroll
+                    for (int i = 0; i < kTiles2; ++i) {
+                        f32x4 &s = acc2[u % 2 * kTiles2 + i];
+                        s = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, w2[u / 2]), __builtin_bit_cast(bf16x8, x[u % (D2 + 1)][i]), s, 0, 0, 0);
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+                {   // acc[r] = channel 16 ct + 4 q4 + r of patch l16
+                    const f32x4 b = *(const f32x4 *)(bias + C1 + c4);
+#pragma unroll
+                    for (int i = 0; i < T2; ++i) {
+                        const int m = i * 16 + p16;
+                        const f32x4 s = acc2[i] + b;
+                        if (m < OHW2)
+                            *(uint2 *)(row2(m) + c4 * 2) =
+                                make_uint2(pack2(fmaxf(s[0], 0.f), fmaxf(s[1], 0.f)), pack2(fmaxf(s[2], 0.f), fmaxf(s[3], 0.f)));
+                    }
+                }
+                lds_sync();
+                // ---- phase 2: third layer, out2 -> out
+                if (f.out && pass < f.B) {
+                    tj_bf16 *dst = a.act2 + (size_t)pass * OHW2 * C2;
+                    for (int v = tid1 - kHalf; v < OHW2 * 8; v += kHalf) *(u32x4 *)(dst + (size_t)v * 8) = *(const u32x4 *)(row2(v >> 3) + (v & 7) * 16);
+                }
+                f32x4 acc3[T3];
+#pragma unroll
+                for (int i = 0; i < T3; ++i) acc3[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+                u32x4 y[D3 + 1][T3];
+                auto read3 = [&](int n) {   // a step is half a tap
+                    const int off = n / 2 / K3 * p.pitch2 + n / 2 % K3 * kRow2 + (n & 1) * 64;
+#pragma unroll
+                    for (int i = 0; i < T3; ++i) y[n % (D3 + 1)][i] = *(const u32x4 *)(out2 + at3[i] + off);
+                };
+#pragma unroll
+                for (int n = 0; n < D3; ++n) read3(n);
+#pragma unroll
+                for (int n = 0; n < kSteps3; ++n) {
+                    if (n + D3 < kSteps3) read3(n + D3);
+                    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                    for (int i = 0; i < T3; ++i)
+                        acc3[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, w3[n]), __builtin_bit_cast(bf16x8, y[n % (D3 + 1)][i]),
+                                                                          acc3[i], 0, 0, 0);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+                const f32x4 b3 = *(const f32x4 *)(bias + C1 + C2 + c4);
+#pragma unroll
+                for (int i = 0; i < T3; ++i) {
+                    const int m = i * 16 + p16;
+                    const f32x4 s = acc3[i] + b3;
+                    if (m < OHW3)
+                        *(uint2 *)(a.out + ((size_t)pass * OHW3 + m) * C3 + c4) =
+                            make_uint2(pack2(fmaxf(s[0], 0.f), fmaxf(s[1], 0.f)), pack2(fmaxf(s[2], 0.f), fmaxf(s[3], 0.f)));
+                }
+                lds_sync();
+            }
+        }
+    }
+}
+
 }  // namespace
 
 // The kernel's layer shapes; image, activations and weights beside one another in LDS; no more patches than the waves'
@@ -396,6 +722,15 @@ int tj_conv_tower(const TjConvTowerArgs &a, hipStream_t st)
     if (hipGetDevice(&dev) == hipSuccess &&
         hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && v > 0)
         n_cu = v;
+    // From four passes per block on (us per update, one image at a time : two; 3 passes 134.5 : 136.2, 4 148.9 : 145.8, 8 170.0 : 168.6,
+    // 12 267.0 : 255.8, 24 430 : 402): the first and the last image are alone.
+    PipePlan q = pipe_plan(f.H, f.W, f.OH, f.OW, a.OH2, a.OW2, a.OW3);
+    if (p.n_pass >= 4 * n_cu && (size_t)q.total <= kLdsLimit) {
+        q.n_pass = p.n_pass;
+        TJ_HIP_TRY(hipFuncSetAttribute((const void *)conv_tower_pipe, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsLimit));
+        conv_tower_pipe<<<n_cu, kThreads, q.total, st>>>(a, q);
+        return hipGetLastError() == hipSuccess ? TJ_OK : TJ_ERR_DEVICE;
+    }
     conv_tower<<<p.n_pass < n_cu ? p.n_pass : n_cu, kThreads, p.total, st>>>(a, p);
     return hipGetLastError() == hipSuccess ? TJ_OK : TJ_ERR_DEVICE;
 }

@@ -198,10 +198,12 @@ def _check(status: int, where: str) -> None:
 
 
 def _stream_ptr(stream=None) -> int:
+    """The stream's handle; of the current device's current stream without a Stream object, which costs a small call about 1 us."""
     import torch
 
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return int(s.cuda_stream)
+    if stream is not None:
+        return int(stream.cuda_stream)
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 def _require_gpu():

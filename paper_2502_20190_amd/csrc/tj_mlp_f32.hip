@@ -1061,8 +1061,9 @@ int update_plan(int L, const TjF32Layer *lay, int B, UpdatePlan &p)
 }
 
 // Groups of four rows per block: the fewest that need no second round of blocks on the chip, or the most that LDS holds.  The
-// Q-learner's second group fits where rows are narrow or the layers short enough that not all waves have partial sums
-// (us with one group : two; 4-64-64-2 at 2048 rows 37 : 31, 8192 101 : 76; 16-32-5 8192 66 : 50).
+// Q-learner's second group fits unless the network is deep and wide (us per update with one group and the partial sums that kept the second
+// one out : with two groups; 128-256-256-18 at 2048 rows 71.8 : 54.3, 8192 197 : 132, 64-128 x 6-8 at 2000 93.7 : 62.9, 300-384-384-384-33 at
+// 4096 313 : 227).
 // Acting on rows of at most kActPaired floats stays at two groups, whose blocks find place in pairs on a CU: one hides the other's
 // latency.  On wider rows the weights, read once per block, weigh more (us for 32768 rows, two groups : four; 4-64-64-3 51 : 61,
 // 128-256-256-19 121 : 134, 64-384-384-7 187 : 206, 128-512-512-19 294 : 286, 256-512-512-512-33 547 : 499).
@@ -1114,9 +1115,10 @@ template <int KIND, int NR> int launch_rows(const TjF32Rows &a, int mode, hipStr
 }  // namespace
 
 // Largest batch of a Q-learner that is updated here.  One group of four rows per block reads the weights of both networks for
-// every four transitions, and past some batch the layered kernels, whose tiles share them, are faster (us here : there;
-// 128-512-512-512-18 at 8192 rows 769 : 844, 16384 1559 : 1394; 300-500-384-500-33 757 : 773, 1515 : 1315; 128-256-256-18 at 16384
-// 358 : 370, 32768 701 : 637; seven layers of 64-128 513 : 581, 1000 : 969; with two groups 16-32-5 84 : 96, 157 : 150).
+// every four or eight transitions, and past some batch the layered kernels, whose tiles share them, are faster (us here : there;
+// 128-512-512-512-18 at 8192 rows 722 : 844, 128-256-256-18 at 16384 238 : 370, five layers of 512 at 512 rows 165 : 243 and at 4096 673 : 918,
+// six at 8192 1557 : 1833).  The lines were drawn with the slower forward pass of partial sums (512 wide at 16384 rows 1559 : 1394, 256 wide
+// at 32768 701 : 637); beyond them the present one has not been measured.
 constexpr int kQRows = 16384, kQRowsWide = 8192, kQWide = 256 + 16;   // the latter past rows of kQWide floats
 
 bool tj_f32_fits(int L, const int *in, const int *out, int passes, int max_batch)

@@ -3,9 +3,6 @@
 #pragma once
 #include "tj_mlp_rows.h"
 
-constexpr int kF32MaxWidth = 512;    // widest layer (eight 64-feature groups)
-constexpr int kF32MaxInput = 1024;   // widest observation
-constexpr int kF32MaxOut = 64;       // head outputs: one lane each
 constexpr int kF32MaxSlices = 16;    // slices of the batch in the weight gradient
 
 // One layer.  W and bias are the fp32 master parameters themselves.  WT is the weight copy that the forward pass reads,

@@ -50,40 +50,10 @@ __device__ __forceinline__ f32x4 load16(buf_rsrc r, uint32_t at, int base)
 }
 
 constexpr int kWaves = tjplan::kF32Waves, kThreads = 64 * kWaves;   // f32_rows: two waves per SIMD, 256 registers each
-constexpr size_t kLdsMax = 160 * 1024;
+constexpr size_t kLdsMax = tjplan::kF32Lds;
+typedef tjplan::F32Lds RowsLds;
 
 __host__ __device__ inline int up(int x, int a) { return (x + a - 1) / a * a; }
-
-// LDS layout of f32_rows in floats.  Activation rows are `pitch` floats apart, pitch % 64 == 16: the 16-byte pieces that a
-// quarter of a wave reads (four rows x 16 k) cover the 64 banks once.
-struct RowsLds {
-    int pitch, dzp, keep, pp, part, dz, wa, bias, small, total;
-};
-
-RowsLds rows_lds(int L, const TjF32Layer *lay, int nr, bool dqn, bool backward)
-{
-    RowsLds o;
-    int w = 0, nb = 0, waves = 0;   // waves: those with a part of some phase of the backward pass
-    for (int l = 0; l < L; ++l) {
-        if (backward && l) waves = std::max(waves, tjplan::f32_part_waves(tjplan::f32_phase(lay[l].in, lay[l].out, lay[l].in)));
-        w = std::max(w, std::max(lay[l].kp, lay[l].ldn));
-        nb += lay[l].ldn;
-    }
-    o.pitch = up(w, 64) + 16;
-    const int R = 4 * nr, NG = dqn ? 3 * nr : nr;
-    int at = 0;
-    o.keep = at; at += (backward ? L : std::min(L, 2)) * R * o.pitch;   // input rows of every layer, s; acting: two layers in turn
-    o.pp = at; at += dqn ? 2 * 2 * R * o.pitch : 0;     // s' (online), s' (target), two layers in turn
-    o.part = at; at += std::max(nr == 4 ? 0 : waves * nr * 256, tjplan::kF32Waves * NG * 64);   // the slices of a backward phase; of the head
-    // output gradients, two layers in turn; sixteen rows are read side by side, 16 bytes each: their pitch keeps them on distinct banks
-    o.dzp = o.pitch + (nr == 4 ? 4 : 0);
-    o.dz = at; at += backward ? 2 * R * o.dzp : 0;
-    o.wa = at; at += dqn ? R * o.pitch : 0;             // head weights of the actions taken
-    o.bias = at; at += nb * (dqn ? 2 : 1);
-    o.small = at; at += 64;                             // per row: loss terms, gradient
-    o.total = at;
-    return o;
-}
 
 // A layer's forward pass as the kernel reads it.  Scalar arithmetic is on every wave's critical path: what the host can work out, it does.
 struct Forward {
@@ -1060,32 +1030,15 @@ int update_plan(int L, const TjF32Layer *lay, int B, UpdatePlan &p)
     return n;
 }
 
-// Groups of four rows per block: the fewest that need no second round of blocks on the chip, or the most that LDS holds.  The
-// Q-learner's second group fits unless the network is deep and wide (us per update with one group and the partial sums that kept the second
-// one out : with two groups; 128-256-256-18 at 2048 rows 71.8 : 54.3, 8192 197 : 132, 64-128 x 6-8 at 2000 93.7 : 62.9, 300-384-384-384-33 at
-// 4096 313 : 227).
-// Acting on rows of at most kActPaired floats stays at two groups, whose blocks find place in pairs on a CU: one hides the other's
-// latency.  On wider rows the weights, read once per block, weigh more (us for 32768 rows, two groups : four; 4-64-64-3 51 : 61,
-// 128-256-256-19 121 : 134, 64-384-384-7 187 : 206, 128-512-512-19 294 : 286, 256-512-512-512-33 547 : 499).
-constexpr int kActPaired = 384 + 16;
-
 int rows_nr(const TjF32Rows &a, int mode)
 {
-    const bool dqn = mode == TJ_ROWS_DQN, back = dqn || mode == TJ_ROWS_PPO;
-    const int most = dqn ? 2 : !back && rows_lds(a.L, a.lay, 2, dqn, back).pitch <= kActPaired ? 2 : 4;
-    int best = 1;
-    for (int nr = 1; nr <= most; nr *= 2) {
-        if (rows_lds(a.L, a.lay, nr, dqn, back).total * sizeof(float) > kLdsMax) break;
-        best = nr;
-        if ((a.B + 4 * nr - 1) / (4 * nr) <= 256) break;   // one round of blocks on the chip
-    }
-    return best;
+    return tjplan::f32_groups(a.L, a.lay, a.B, mode == TJ_ROWS_DQN, mode == TJ_ROWS_DQN || mode == TJ_ROWS_PPO);
 }
 
 template <int KIND, int NR> int launch_rows(const TjF32Rows &a, int mode, hipStream_t st)
 {
     const bool dqn = KIND == TJ_ROWS_DQN, back = KIND != TJ_ROWS_ACT;
-    const size_t bytes = rows_lds(a.L, a.lay, NR, dqn, back).total * sizeof(float);
+    const RowsLds o = tjplan::f32_lds(a.L, a.lay, NR, dqn, back);
     static bool attr_set = false;   // idempotent: a race sets it twice
     if (!attr_set) {
         TJ_HIP_TRY(hipFuncSetAttribute((const void *)f32_rows<KIND, NR>, hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -1094,7 +1047,7 @@ template <int KIND, int NR> int launch_rows(const TjF32Rows &a, int mode, hipStr
     }
     RowsArgs r;
     r.a = a;
-    r.o = rows_lds(a.L, a.lay, NR, dqn, back);
+    r.o = o;
     r.bias = a.lay[0].BP; r.bias_tg = a.lay[0].BP_tg; r.head_W = a.lay[a.L - 1].W;
     r.A = a.lay[a.L - 1].out;
     r.kp = a.lay[0].kp;
@@ -1108,32 +1061,13 @@ template <int KIND, int NR> int launch_rows(const TjF32Rows &a, int mode, hipStr
     }
     const tjplan::F32Forward head = tjplan::f32_forward(a.lay[a.L - 1].in, a.lay[a.L - 1].out, true);
     r.head_slices = std::min(head.KS, head.steps);
-    f32_rows<KIND, NR><<<(a.B + 4 * NR - 1) / (4 * NR), kThreads, bytes, st>>>(r, mode);
+    f32_rows<KIND, NR><<<(a.B + 4 * NR - 1) / (4 * NR), kThreads, o.total * sizeof(float), st>>>(r, mode);
     return hipGetLastError() == hipSuccess ? TJ_OK : TJ_ERR_DEVICE;
 }
 
 }  // namespace
 
-// Largest batch of a Q-learner that is updated here.  One group of four rows per block reads the weights of both networks for
-// every four or eight transitions, and past some batch the layered kernels, whose tiles share them, are faster (us here : there;
-// 128-512-512-512-18 at 8192 rows 722 : 844, 128-256-256-18 at 16384 238 : 370, five layers of 512 at 512 rows 165 : 243 and at 4096 673 : 918,
-// six at 8192 1557 : 1833).  The lines were drawn with the slower forward pass of partial sums (512 wide at 16384 rows 1559 : 1394, 256 wide
-// at 32768 701 : 637); beyond them the present one has not been measured.
-constexpr int kQRows = 16384, kQRowsWide = 8192, kQWide = 256 + 16;   // the latter past rows of kQWide floats
-
-bool tj_f32_fits(int L, const int *in, const int *out, int passes, int max_batch)
-{
-    if (L < 1 || L > TJ_MAX_LAYERS || in[0] > kF32MaxInput || out[L - 1] > kF32MaxOut) return false;
-    TjF32Layer lay[TJ_MAX_LAYERS] = {};
-    for (int l = 0; l < L; ++l) {
-        if (l + 1 < L && out[l] > kF32MaxWidth) return false;
-        lay[l].in = in[l]; lay[l].out = out[l];
-        tj_f32_copy_shape(lay[l], l == L - 1);
-    }
-    const RowsLds o = rows_lds(L, lay, 1, passes == 3, true);
-    if (passes == 3 && max_batch > (o.pitch > kQWide ? kQRowsWide : kQRows)) return false;
-    return o.total * sizeof(float) <= kLdsMax;
-}
+bool tj_f32_fits(int L, const int *in, const int *out, int passes, int max_batch) { return tjplan::f32_fits(L, in, out, passes, max_batch); }
 
 int tj_f32_blocks(const TjF32Rows &a, int mode)
 {

@@ -76,6 +76,85 @@ TJ_HD inline unsigned f32_lane_at(unsigned row_at, unsigned last_row_at, int lan
     return (row_at < last_row_at ? row_at : last_row_at) + 64u * f + 4u * (lane & 15);
 }
 
+// LDS layout of the row kernel in floats.  Activation rows are `pitch` floats apart, pitch % 64 == 16: the 16-byte pieces that a
+// quarter of a wave reads (four rows x 16 k) cover the 64 banks once.
+constexpr size_t kF32Lds = 160 * 1024;
+struct F32Lds {
+    int pitch, dzp, keep, pp, part, dz, wa, bias, small, total;
+};
+// nr groups of four rows per block; dqn: the Q-learner's three passes; backward: an update, not acting.
+template <typename Layer> F32Lds f32_lds(int L, const Layer *lay, int nr, bool dqn, bool backward)
+{
+    F32Lds o;
+    int w = 0, nb = 0, waves = 0;   // waves: those with a part of some phase of the backward pass
+    for (int l = 0; l < L; ++l) {
+        const F32Forward p = f32_forward(lay[l].in, lay[l].out, l == L - 1);
+        if (backward && l) waves = std::max(waves, f32_part_waves(f32_phase(lay[l].in, lay[l].out, lay[l].in)));
+        w = std::max(w, std::max((16 << p.lq) * p.steps, p.pitch));
+        nb += p.pitch;
+    }
+    o.pitch = (w + 63) / 64 * 64 + 16;
+    const int R = 4 * nr, NG = dqn ? 3 * nr : nr;
+    int at = 0;
+    o.keep = at; at += (backward ? L : std::min(L, 2)) * R * o.pitch;   // input rows of every layer, s; acting: two layers in turn
+    o.pp = at; at += dqn ? 2 * 2 * R * o.pitch : 0;     // s' (online), s' (target), two layers in turn
+    o.part = at; at += std::max(nr == 4 ? 0 : waves * nr * 256, kF32Waves * NG * 64);   // the slices of a backward phase; of the head
+    // output gradients, two layers in turn; sixteen rows are read side by side, 16 bytes each: their pitch keeps them on distinct banks
+    o.dzp = o.pitch + (nr == 4 ? 4 : 0);
+    o.dz = at; at += backward ? 2 * R * o.dzp : 0;
+    o.wa = at; at += dqn ? R * o.pitch : 0;             // head weights of the actions taken
+    o.bias = at; at += nb * (dqn ? 2 : 1);
+    o.small = at; at += 64;                             // per row: loss terms, gradient
+    o.total = at;
+    return o;
+}
+
+// Groups of four rows per block: the fewest that need no second round of blocks on the chip, or the most that LDS holds.  The
+// Q-learner's second group fits unless the network is deep and wide (us per update with one group and the partial sums that kept the second
+// one out : with two groups; 128-256-256-18 at 2048 rows 71.8 : 54.3, 8192 197 : 132, 64-128 x 6-8 at 2000 93.7 : 62.9, 300-384-384-384-33 at
+// 4096 313 : 227).
+// Acting on rows of at most kF32ActPaired floats stays at two groups, whose blocks find place in pairs on a CU: one hides the other's
+// latency.  On wider rows the weights, read once per block, weigh more (us for 32768 rows, two groups : four; 4-64-64-3 51 : 61,
+// 128-256-256-19 121 : 134, 64-384-384-7 187 : 206, 128-512-512-19 294 : 286, 256-512-512-512-33 547 : 499).
+constexpr int kF32ActPaired = 384 + 16;
+template <typename Layer> int f32_groups(int L, const Layer *lay, int B, bool dqn, bool backward)
+{
+    const int most = dqn ? 2 : !backward && f32_lds(L, lay, 2, dqn, backward).pitch <= kF32ActPaired ? 2 : 4;
+    int best = 1;
+    for (int nr = 1; nr <= most; nr *= 2) {
+        if (f32_lds(L, lay, nr, dqn, backward).total * sizeof(float) > kF32Lds) break;
+        best = nr;
+        if ((B + 4 * nr - 1) / (4 * nr) <= 256) break;   // one round of blocks on the chip
+    }
+    return best;
+}
+
+// Largest batch of a Q-learner that is updated here.  One group of four rows per block reads the weights of both networks for
+// every four or eight transitions, and past some batch the layered kernels, whose tiles share them, are faster (us here : there;
+// 128-512-512-512-18 at 8192 rows 722 : 844, 128-256-256-18 at 16384 238 : 370, five layers of 512 at 512 rows 165 : 243 and at 4096 673 : 918,
+// six at 8192 1557 : 1833).  The lines were drawn with the slower forward pass of partial sums (512 wide at 16384 rows 1559 : 1394, 256 wide
+// at 32768 701 : 637); beyond them the present one has not been measured.
+constexpr int kF32QRows = 16384, kF32QRowsWide = 8192, kF32QWide = 256 + 16;   // the latter past rows of kF32QWide floats
+
+constexpr int kF32MaxWidth = 512;    // widest layer (eight 64-feature groups)
+constexpr int kF32MaxInput = 1024;   // widest observation
+constexpr int kF32MaxOut = 64;       // head outputs: one lane each
+
+// True if a learner of this shape, with updates of up to max_batch rows in `passes` forward passes (the Q-learner's three), runs in
+// these kernels.
+inline bool f32_fits(int L, const int *in, const int *out, int passes, int max_batch)
+{
+    if (L < 1 || L > TJ_MAX_LAYERS || in[0] > kF32MaxInput || out[L - 1] > kF32MaxOut) return false;
+    struct { int in, out; } lay[TJ_MAX_LAYERS];
+    for (int l = 0; l < L; ++l) {
+        if (l + 1 < L && out[l] > kF32MaxWidth) return false;
+        lay[l].in = in[l]; lay[l].out = out[l];
+    }
+    const F32Lds o = f32_lds(L, lay, 1, passes == 3, true);
+    if (passes == 3 && max_batch > (o.pitch > kF32QWide ? kF32QRowsWide : kF32QRows)) return false;
+    return o.total * sizeof(float) <= kF32Lds;
+}
+
 // ---- the weight kernel of bf16 networks
 
 constexpr int kB16MaxSlices = 16;    // slices of the batch in the bf16 weight gradient

@@ -1,4 +1,6 @@
+import ctypes
 import os
+import subprocess
 import sys
 
 import pytest
@@ -18,3 +20,12 @@ def orc():
 
     _orc.lib()
     return _orc
+
+
+@pytest.fixture(scope="session")
+def mlp_plan(tmp_path_factory):
+    """The plans of the whole-network kernels, compiled for the CPU."""
+    out = str(tmp_path_factory.mktemp("plan") / "mlp_plan.so")
+    src = os.path.join(os.path.dirname(os.path.abspath(__file__)), "mlp_plan.cpp")
+    subprocess.run(["g++", "-O2", "-std=c++17", "-Wall", "-shared", "-fPIC", src, "-o", out], check=True)
+    return ctypes.CDLL(out)

@@ -45,3 +45,12 @@ extern "C" unsigned f32_active(int pitch, int rows, int cols, int *held)
     *held = tjplan::f32_part_waves(p);
     return mask;
 }
+
+// Rows of a block of the row kernel of fp32 networks, and whether a learner of that shape runs there.
+extern "C" int f32_rows(int L, const Layer *lay, int B, int dqn, int backward) { return 4 * tjplan::f32_groups(L, lay, B, dqn, backward); }
+extern "C" int f32_fits(int L, const Layer *lay, int passes, int max_batch)
+{
+    int in[TJ_MAX_LAYERS], out[TJ_MAX_LAYERS];
+    for (int l = 0; l < L && l < TJ_MAX_LAYERS; ++l) { in[l] = lay[l].in; out[l] = lay[l].out; }
+    return tjplan::f32_fits(L, in, out, passes, max_batch);
+}

@@ -1,4 +1,6 @@
 """Shared helpers of the GPU parity tests: tolerance metrics and fixtures."""
+import ctypes
+
 import numpy as np
 
 
@@ -21,3 +23,9 @@ def top2_gap(q) -> np.ndarray:
     """Gap between the best and second-best entry of each row."""
     s = np.sort(np.asarray(q, np.float64), axis=1)
     return s[:, -1] - s[:, -2] if s.shape[1] > 1 else np.full(s.shape[0], np.inf)
+
+
+def plan_layers(*widths):
+    """Layers of a network of these widths as the plans take them: how many, and (inputs, outputs) of each."""
+    flat = [int(v) for pair in zip(widths, widths[1:]) for v in pair]
+    return len(widths) - 1, (ctypes.c_int * len(flat))(*flat)

@@ -16,6 +16,7 @@ from paper_2502_20190_amd.synth import LIN
 
 import test_gpu_learner as T
 import test_gpu_ppo as P
+from parity_util import plan_layers
 
 pytestmark = pytest.mark.gpu
 TOL = 1e-4
@@ -111,9 +112,12 @@ def test_small_networks_on_long_batches(tj, orc, D, widths, A, batches):
 @pytest.mark.parametrize("D,widths,A,batches", [
     (4, (16,), 2, (1025, 1031, 1024)), (20, (33, 64, 5), 18, (1032, 1029)), (100, (128,), 7, (1027,)), (4, (16,), 2, (16384, 16381)),
     (4, (16,), 2, (16385, 1030))])
-def test_q_learner_with_two_groups_of_rows_per_block(tj, orc, D, widths, A, batches):
+def test_q_learner_with_two_groups_of_rows_per_block(tj, orc, mlp_plan, D, widths, A, batches):
     """From 1025 rows on, narrow networks; partial groups, and both sides of the largest batch that these kernels take.  Roundings of a
     sum over 16 k rows: 16385 * 2^-24 = 1e-3 at the worst, some 128 * 2^-24 = 8e-6 where they are independent."""
+    net = plan_layers(D, *widths, A)
+    assert mlp_plan.f32_fits(*net, 3, max(batches)) == (max(batches) <= 16384)
+    assert [mlp_plan.f32_rows(*net, B, 1, 1) for B in batches] == [8 if B > 1024 else 4 for B in batches]
     layers = tuple((LIN, w, 0, 0) for w in widths) + ((LIN, A, 0, 0),)
     wl = replace(synth.WORKLOADS["c2"], obs_shape=(D,), n_actions=A, batch=max(batches), layers=layers, precision="fp32", lr=1e-3)
     g, o = T._pair(tj, orc, wl, seed=8)
@@ -145,11 +149,14 @@ def test_q_learner_at_the_edges_of_the_feature_tiles(tj, orc, D, widths, A, B):
         T._check_compute_copies(tj, g, wl)
 
 
-@pytest.mark.parametrize("D,widths,A,B", [(12, (129, 257), 18, 2101), (5, (33, 512), 2, 2049), (70, (64, 31, 96), 33, 4099)])
-def test_on_policy_learner_with_sixteen_rows_per_block(tj, orc, D, widths, A, B):
-    """From 2049 rows on: column tiles of 32 with a remainder, more tiles than waves (512 wide), contractions over fewer rows of a matrix
-    than a step and over a remainder, a last block of 1 to 5 rows.  Sums over 4099 rows: 4099 * 2^-24 = 2.4e-4 at the worst, some
-    64 * 2^-24 = 4e-6 where the roundings are independent."""
+@pytest.mark.parametrize("D,widths,A,B,rows_per_block", [
+    (12, (129, 257), 18, 2101, 16), (5, (33, 448), 2, 2049, 16), (70, (64, 31, 96), 33, 4099, 16), (5, (33, 512), 2, 2049, 8)])
+def test_on_policy_learner_with_sixteen_rows_per_block(tj, orc, mlp_plan, D, widths, A, B, rows_per_block):
+    """From 2049 rows on: column tiles of 32 with a remainder, more tiles than waves (257 and 448 wide), contractions over fewer rows of a
+    matrix than a step and over a remainder, a last block of 1 to 5 rows; and a network too wide for sixteen, which takes eight.
+    Sums over 4099 rows: 4099 * 2^-24 = 2.4e-4 at the worst, some 64 * 2^-24 = 4e-6 where the roundings are independent."""
+    net = plan_layers(D, *widths, A + 1)
+    assert mlp_plan.f32_fits(*net, 1, B) and mlp_plan.f32_rows(*net, B, 0, 1) == rows_per_block
     g, o = P._pair(tj, orc, D, widths, A, "fp32", B, seed=5, lr=1e-3)
     for step in range(2):
         rows = P._batch(orc, o, D, A, 1 + B // 8, 8, 74 + step, "fp32", n=B)

@@ -1,26 +1,10 @@
 """The plan of the whole-network kernels, compiled for the CPU: what an update writes fits what its learner holds."""
 import ctypes
-import os
-import subprocess
 
 import numpy as np
 import pytest
 
-HERE = os.path.dirname(os.path.abspath(__file__))
-
-
-@pytest.fixture(scope="module")
-def plan(tmp_path_factory):
-    out = str(tmp_path_factory.mktemp("plan") / "mlp_plan.so")
-    subprocess.run(["g++", "-O2", "-std=c++17", "-Wall", "-shared", "-fPIC", os.path.join(HERE, "mlp_plan.cpp"), "-o", out],
-                   check=True)
-    return ctypes.CDLL(out)
-
-
-def _layers(*widths):
-    flat = [v for pair in zip(widths, widths[1:]) for v in pair]
-    return len(widths) - 1, (ctypes.c_int * len(flat))(*flat)
-
+from parity_util import plan_layers
 
 def _random_nets():
     g = np.random.default_rng(0)
@@ -33,35 +17,35 @@ def _random_nets():
 
 
 @pytest.mark.parametrize("widths,max_batch", [((180, 215, 215, 3), 4177), ((187, 207, 6), 8323)] + _random_nets())
-def test_bf16_gradient_slices_of_every_smaller_batch_fit(plan, widths, max_batch):
+def test_bf16_gradient_slices_of_every_smaller_batch_fit(mlp_plan, widths, max_batch):
     held, written = ctypes.c_int(), ctypes.c_int()
-    plan.b16_slices(*_layers(*widths), max_batch, ctypes.byref(held), ctypes.byref(written))
+    mlp_plan.b16_slices(*plan_layers(*widths), max_batch, ctypes.byref(held), ctypes.byref(written))
     assert written.value == held.value, (widths, max_batch)
 
 
 SIDES = list(range(1, 70)) + [127, 128, 129, 255, 257, 511, 512]
 
 
-def test_fp32_row_kernel_loads_stay_inside_the_weight_copies(plan):
+def test_fp32_row_kernel_loads_stay_inside_the_weight_copies(mlp_plan):
     """The transposed copy of a layer has its inputs rounded up to 16 as rows and its outputs rounded up to 64 as columns."""
-    plan.f32_reach.restype = ctypes.c_long
+    mlp_plan.f32_reach.restype = ctypes.c_long
     for fin in SIDES + [1000, 1024]:
         for fout in SIDES:
             kp, ldn = (fin + 15) // 16 * 16, (fout + 63) // 64 * 64
-            assert plan.f32_reach(ldn, kp, ldn) == kp * ldn, (fin, fout)
+            assert mlp_plan.f32_reach(ldn, kp, ldn) == kp * ldn, (fin, fout)
 
 
-def test_fp32_row_kernel_loads_of_the_parameters_end_with_their_matrix(plan):
+def test_fp32_row_kernel_loads_of_the_parameters_end_with_their_matrix(mlp_plan):
     """The backward pass reads W [out][in] itself, whole groups of 64 inputs: at most 63 floats behind it."""
-    plan.f32_reach.restype = ctypes.c_long
+    mlp_plan.f32_reach.restype = ctypes.c_long
     for fin in SIDES:
         for fout in SIDES:
-            assert plan.f32_reach(fin, fout, fin) == (fout - 1) * fin + (fin + 63) // 64 * 64, (fin, fout)
+            assert mlp_plan.f32_reach(fin, fout, fin) == (fout - 1) * fin + (fin + 63) // 64 * 64, (fin, fout)
 
 
-def test_fp32_row_kernel_partial_sums_have_room_for_every_wave_that_multiplies(plan):
-    plan.f32_active.restype = ctypes.c_uint
+def test_fp32_row_kernel_partial_sums_have_room_for_every_wave_that_multiplies(mlp_plan):
+    mlp_plan.f32_active.restype = ctypes.c_uint
     held = ctypes.c_int()
     for rows in SIDES:
         for cols in SIDES:
-            assert plan.f32_active(cols, rows, cols, ctypes.byref(held)) == (1 << held.value) - 1, (rows, cols)
+            assert mlp_plan.f32_active(cols, rows, cols, ctypes.byref(held)) == (1 << held.value) - 1, (rows, cols)

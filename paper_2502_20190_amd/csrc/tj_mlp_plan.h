@@ -140,6 +140,25 @@ constexpr int kF32MaxWidth = 512;    // widest layer (eight 64-feature groups)
 constexpr int kF32MaxInput = 1024;   // widest observation
 constexpr int kF32MaxOut = 64;       // head outputs: one lane each
 
+// Q-learners with updates of few rows that run layer by layer.  Few blocks leave the weights' stream into each what it is: 12.3 us per MB of both
+// networks' forward pass, 12.5 per MB of the backward pass (5 where 32 blocks ask for the same weights in the L2), while a layer's launches
+// take 23 - 25 us (us here : there; 1024-512-18 at 8 rows 65 : 48, at 128 66 : 55, at 256 60 : 69; 512-512 x 6-18 at 32 rows 233 : 185, at 128
+// 194 : 188, at 256 192 : 220; 128-512 x 4-64 at 32 138 : 127, at 128 119 : 132; 768-384-384-384-18 at 32 91 : 91).  Only networks are asked that need
+// more LDS than kF32FewRowsLds, those that could not run here while the forward pass kept partial sums in LDS; the others lose 18 % of an
+// update at the worst (512-512-512-512-18 at 32 rows 116 : 98) and act on 8 observations in 27 us instead of 42.
+constexpr int kF32FewRows = 128;
+constexpr size_t kF32FewRowsLds = 116 * 1024;
+inline bool f32_few_rows(int L, const int *in, const int *out, size_t lds, int max_batch)
+{
+    if (max_batch > kF32FewRows || lds <= kF32FewRowsLds) return false;
+    double forward = 0, backward = 0;   // MB
+    for (int l = 0; l < L; ++l) {
+        forward += 8e-6 * in[l] * out[l];
+        if (l > 0 && l + 1 < L) backward += 4e-6 * in[l] * out[l];
+    }
+    return 18 + 12.3 * forward + (max_batch <= 64 ? 12.5 : 5) * backward > (23 + max_batch / 64.0) * L;
+}
+
 // True if a learner of this shape, with updates of up to max_batch rows in `passes` forward passes (the Q-learner's three), runs in
 // these kernels.
 inline bool f32_fits(int L, const int *in, const int *out, int passes, int max_batch)
@@ -152,7 +171,9 @@ inline bool f32_fits(int L, const int *in, const int *out, int passes, int max_b
     }
     const F32Lds o = f32_lds(L, lay, 1, passes == 3, true);
     if (passes == 3 && max_batch > (o.pitch > kF32QWide ? kF32QRowsWide : kF32QRows)) return false;
-    return o.total * sizeof(float) <= kF32Lds;
+    const size_t lds = o.total * sizeof(float);
+    if (passes == 3 && f32_few_rows(L, in, out, lds, max_batch)) return false;
+    return lds <= kF32Lds;
 }
 
 // ---- the weight kernel of bf16 networks

@@ -49,3 +49,16 @@ def test_fp32_row_kernel_partial_sums_have_room_for_every_wave_that_multiplies(m
     for rows in SIDES:
         for cols in SIDES:
             assert mlp_plan.f32_active(cols, rows, cols, ctypes.byref(held)) == (1 << held.value) - 1, (rows, cols)
+
+
+# Updates of few rows whose weight stream through one block takes longer than a launch per layer (128 rows and fewer), and networks
+# on the other side of each line: narrower, deeper for their width, longer batches, or small enough in LDS to act here
+@pytest.mark.parametrize("widths,max_batch,here", [
+    ((1024, 512, 18), 8, False), ((1024, 512, 18), 128, False), ((1024, 512, 18), 129, True), ((1024, 512, 18), 512, True),
+    ((768, 512, 18), 32, False), ((896, 512, 512, 18), 64, False), ((768, 512, 512, 512, 18), 32, False),
+    ((128, 512, 512, 512, 512, 18), 32, False), ((128, 512, 512, 512, 512, 18), 128, True),
+    ((512, 512, 512, 512, 512, 512, 512, 18), 128, False), ((512, 512, 512, 512, 512, 512, 512, 18), 256, True),
+    ((128,) + (448,) * 7 + (18,), 64, False), ((1024, 64, 18), 8, True), ((1024, 256, 18), 32, True), ((768,) + (64,) * 4 + (18,), 32, True),
+    ((512, 512, 512, 512, 18), 32, True), ((256, 512, 512, 512, 18), 32, True), ((128, 256, 256, 18), 8, True)])
+def test_fp32_q_learners_with_few_rows_run_where_an_update_is_faster(mlp_plan, widths, max_batch, here):
+    assert mlp_plan.f32_fits(*plan_layers(*widths), 3, max_batch) == here

@@ -159,6 +159,23 @@ inline bool f32_few_rows(int L, const int *in, const int *out, size_t lds, int m
     return 18 + 12.3 * forward + (max_batch <= 64 ? 12.5 : 5) * backward > (23 + max_batch / 64.0) * L;
 }
 
+// On-policy learners with long updates that run layer by layer.  Where LDS holds one group of four rows, every four transitions read the
+// weights of a forward and a backward pass (11.5 us per MB and round of blocks), past some batch for longer than the layered kernels take,
+// whose tiles share them (us here : there; 896-256 x 7-18 at 8192 rows 599 : 788, 16384 1203 : 1014, 65536 4766 : 3344; 1024-320 x 6-18 at 16384
+// 1657 : 1542; 1024-192 x 6-18 at 16384 821 : 918, 32768 1641 : 1593; 1024-128 x 6-3 at 32768 972 : 937; 896-64 x 7-18 at 65536 1410 : 1466).  Only networks
+// are asked that need more LDS than kF32LongRowsLds, as above; the others lose up to 32 % of an update (1024-256 x 5-18 at 32768 2022 : 1530) and act in
+// one launch instead of one per layer.
+constexpr int kF32LongRows = 8192;
+constexpr size_t kF32LongRowsLds = 150 * 1024;
+constexpr double kF32LongRowsRead = 38e3;   // rows x MB
+inline bool f32_long_rows(int L, const int *in, const int *out, size_t lds, int max_batch)
+{
+    if (max_batch <= kF32LongRows || lds <= kF32LongRowsLds) return false;
+    double mb = 0;
+    for (int l = 0; l < L; ++l) mb += (l > 0 ? 8e-6 : 4e-6) * in[l] * out[l];
+    return mb * max_batch > kF32LongRowsRead;
+}
+
 // True if a learner of this shape, with updates of up to max_batch rows in `passes` forward passes (the Q-learner's three), runs in
 // these kernels.
 inline bool f32_fits(int L, const int *in, const int *out, int passes, int max_batch)
@@ -172,7 +189,7 @@ inline bool f32_fits(int L, const int *in, const int *out, int passes, int max_b
     const F32Lds o = f32_lds(L, lay, 1, passes == 3, true);
     if (passes == 3 && max_batch > (o.pitch > kF32QWide ? kF32QRowsWide : kF32QRows)) return false;
     const size_t lds = o.total * sizeof(float);
-    if (passes == 3 && f32_few_rows(L, in, out, lds, max_batch)) return false;
+    if (passes == 3 ? f32_few_rows(L, in, out, lds, max_batch) : f32_long_rows(L, in, out, lds, max_batch)) return false;
     return lds <= kF32Lds;
 }
 

@@ -62,3 +62,14 @@ def test_fp32_row_kernel_partial_sums_have_room_for_every_wave_that_multiplies(m
     ((512, 512, 512, 512, 18), 32, True), ((256, 512, 512, 512, 18), 32, True), ((128, 256, 256, 18), 8, True)])
 def test_fp32_q_learners_with_few_rows_run_where_an_update_is_faster(mlp_plan, widths, max_batch, here):
     assert mlp_plan.f32_fits(*plan_layers(*widths), 3, max_batch) == here
+
+
+@pytest.mark.parametrize("widths,max_batch,here", [
+    ((896,) + (256,) * 7 + (18,), 8192, True), ((896,) + (256,) * 7 + (18,), 16384, False), ((896,) + (256,) * 7 + (18,), 65536, False),
+    ((896,) + (384,) * 7 + (18,), 16384, False), ((1024,) + (320,) * 6 + (18,), 16384, False),
+    ((1024,) + (192,) * 6 + (18,), 16384, True), ((1024,) + (192,) * 6 + (18,), 32768, False), ((1024,) + (128,) * 6 + (3,), 32768, False),
+    ((896,) + (64,) * 7 + (18,), 65536, True), ((1024,) + (256,) * 5 + (18,), 32768, True), ((512,) * 7 + (18,), 65536, True),
+    ((4, 256, 256, 3), 65536, True)])
+def test_fp32_on_policy_learners_with_long_batches_run_where_an_update_is_faster(mlp_plan, widths, max_batch, here):
+    """Networks that fill LDS with four rows; shallower ones stay, whose acting here weighs more."""
+    assert mlp_plan.f32_fits(*plan_layers(*widths), 1, max_batch) == here

@@ -201,9 +201,12 @@ def _stream_ptr(stream=None) -> int:
     """The stream's handle; of the current device's current stream without a Stream object, which costs a small call about 1 us."""
     import torch
 
-    if stream is not None:
-        return int(stream.cuda_stream)
-    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    if stream is None:
+        raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)   # not a public name
+        if raw is not None:
+            return raw(torch.cuda.current_device())
+        stream = torch.cuda.current_stream()
+    return int(stream.cuda_stream)
 
 
 def _require_gpu():

@@ -58,3 +58,20 @@ def test_synth_param_count_matches_library():
         assert b.lib().tj_learner_num_params(ctypes.byref(d)) == synth.num_params(wl.layers, wl.in_chw)
     assert synth.num_params(synth.WORKLOADS["c3"].layers, (256, 1, 1)) == 2_395_168
     assert synth.num_params(synth.WORKLOADS["c4"].layers, (4, 84, 84)) == 1_693_362
+
+
+def test_current_stream_without_torch_private_names(monkeypatch):
+    """The handle of the current stream comes from a name that torch does not promise; without it, from the Stream object."""
+    import types
+
+    import torch
+
+    from paper_2502_20190_amd import binding as b
+
+    monkeypatch.setattr(torch.cuda, "current_device", lambda: 0)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: types.SimpleNamespace(cuda_stream=0x51))
+    monkeypatch.setattr(torch._C, "_cuda_getCurrentRawStream", lambda device: 0x52 + device, raising=False)
+    assert b._stream_ptr() == 0x52
+    assert b._stream_ptr(types.SimpleNamespace(cuda_stream=0x53)) == 0x53
+    monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream")
+    assert b._stream_ptr() == 0x51

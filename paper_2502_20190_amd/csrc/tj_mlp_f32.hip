@@ -9,7 +9,7 @@
 //               and gradients of the block's rows live in LDS; only what the weight gradients need (layer inputs
 //               of s, output gradients) is written to memory.
 //   f32_update  one block per tile of a weight matrix: its gradient over the whole batch, then Adam on the
-//               tile, the transposed copy the forward pass reads, and the target network where it is due.
+//               tile, the weight copy the forward pass reads, and the target network where it is due.
 //   f32_adam    where update_plan cuts a long batch into slices: their sum, and everything behind it.
 //
 // f32_rows multiplies with v_mfma_f32_4x4x1_16b_f32: sixteen independent 4 x 4 products per instruction,
@@ -42,8 +42,6 @@ namespace {
 
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef const __attribute__((address_space(1))) uint8_t *gbytes;
-typedef const __attribute__((address_space(1))) __attribute__((aligned(4))) f32x4 *gf32x4;
 __device__ __forceinline__ f32x4 load16(buf_rsrc r, uint32_t at, int base)
 {
     return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(r, (int)at, base, 0));
@@ -225,17 +223,15 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, KIN
             mul(wa[0], c);
         }
     };
-    // ---- backward of sixteen rows (NR = 4): v_mfma_f32_16x16x4_f32, the weights its first operand (columns of the matrix as stored), the rows
-    // the second, so that a wave ends with whole sums: a tile of 32 columns, every eighth one.  Load j of a step of 32 matrix rows takes row
-    // 16 (j / 4) + 4 q + j % 4 in lane quarter q, columns 2 c, 2 c + 1; what lies past the matrix is zero.
+    // ---- backward of sixteen rows (NR = 4); its places are tjplan::f32_back16_*
     struct Back16 { const float *w; int bytes, pitch, steps, tiles; };
-    auto back16 = [&](const Phase &p) { return Back16{p.w, 4 * p.rows * p.pitch, 4 * p.pitch, (p.rows + 31) / 32, (p.cols + 31) / 32}; };
+    auto back16 = [&](const Phase &p) { return Back16{p.w, 4 * p.rows * p.pitch, 4 * p.pitch, tjplan::f32_back16_steps(p.rows), tjplan::f32_back16_tiles(p.cols)}; };
     auto load_step = [&](f32x4 (&w)[4], const Back16 &p, int tile, int s) {
         const buf_rsrc r = buf_of(p.w, p.bytes);
-        const int at = (32 * s + 4 * (int)quarter) * p.pitch + 128 * tile + 8 * (lane & 15);   // past the end in the lane's part: a scalar part must not be
+        const int at = tjplan::f32_back16_at((int)quarter, lane & 15, tile, s, p.pitch);   // past the end in the lane's part: a scalar part must not be
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
-            const f32x2 v = __builtin_bit_cast(f32x2, __builtin_amdgcn_raw_buffer_load_b64(r, at + (16 * (j / 4) + j % 4) * p.pitch, 0, 0));
+            const f32x2 v = __builtin_bit_cast(f32x2, __builtin_amdgcn_raw_buffer_load_b64(r, at + tjplan::f32_back16_row(j) * p.pitch, 0, 0));
             w[j / 2][j % 2 * 2] = v[0]; w[j / 2][j % 2 * 2 + 1] = v[1];
         }
         __builtin_amdgcn_sched_barrier(0);
@@ -563,7 +559,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, KIN
     if constexpr (NR == 4) {
         const int r = lane & 15;
         for (int l = top; l >= 1; --l) {
-            const float *const src = dzb + cur * R * o.dzp + r * o.dzp + 4 * (int)quarter;
+            const float *const src = dzb + cur * R * o.dzp + r * o.dzp + tjplan::f32_back16_dz((int)quarter, 0);
             float *const dst = dzb + (cur ^ 1) * R * o.dzp + r * o.dzp;
             const Back16 nx = back16(args.bwd[max(l - 1, 1)]);
             const int in = lay[l].in, ldz = lay[l - 1].lddz;
@@ -596,7 +592,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, KIN
                 if (tile + kWaves < bk.tiles) load_step(wa[0], bk, tile + kWaves, 0);
                 else back_first(nx, l > 1);
                 // columns c .. c + 7 of row r: element 2 i + e is register i of operand e
-                const int c = 32 * tile + 8 * (int)quarter;
+                const int c = tjplan::f32_back16_col((int)quarter, tile);
                 const float *const x = keep + (l * R + r) * P + c;
 #pragma unroll
                 for (int h = 0; h < 2; ++h) {
@@ -845,7 +841,7 @@ __device__ __forceinline__ void update_tile(const TjF32Update &a, const UpdatePl
         return;
     }
 
-    // ---- Adam, and what follows the weights: the transposed copy through LDS [k][n], features contiguous
+    // ---- Adam, and what follows the weights: the copy of the forward pass, [k / 4][n][4], through LDS [k][n]
     constexpr int TP = TN + 1;
     __syncthreads();   // the sums have been read
     if (owner) {
@@ -911,7 +907,7 @@ __global__ __launch_bounds__(kUThreads) void f32_update(const TjF32Update a, con
 
 struct F32Cast { TjF32Layer lay[TJ_MAX_LAYERS]; int online; };
 
-// Second half of an update whose gradient came in slices: their sum in slice order, Adam, the transposed copy.  A
+// Second half of an update whose gradient came in slices: their sum in slice order, Adam, the copy of the forward pass.  A
 // block owns 16 x 32 weights, a thread two of them; every load is issued before the first use.
 constexpr int kAdamN = 16, kAdamK = 32;
 

@@ -76,6 +76,20 @@ TJ_HD inline unsigned f32_lane_at(unsigned row_at, unsigned last_row_at, int lan
     return (row_at < last_row_at ? row_at : last_row_at) + 64u * f + 4u * (lane & 15);
 }
 
+// The backward pass of sixteen rows: v_mfma_f32_16x16x4_f32, the weights its first operand (columns of the matrix as stored), the rows the second,
+// so that a wave ends with whole sums: a tile of 32 columns, every eighth one.  Load j of a step of 32 matrix rows takes row
+// 16 (j / 4) + 4 q + j % 4 in lane quarter q, columns 2 c, 2 c + 1 (c = lane % 16), and multiplies them with element 16 (j / 4) + j % 4 of the lane's
+// part of the gradient; columns 8 q .. 8 q + 7 of row c are the lane's sums.  What lies past the matrix is zero.
+TJ_HD inline int f32_back16_steps(int rows) { return (rows + 31) / 32; }
+TJ_HD inline int f32_back16_tiles(int cols) { return (cols + 31) / 32; }
+TJ_HD inline int f32_back16_at(int q, int c, int tile, int step, int pitch)   // bytes to the lane's part of a step, pitch in bytes
+{
+    return (32 * step + 4 * q) * pitch + 128 * tile + 8 * c;
+}
+TJ_HD inline int f32_back16_row(int j) { return 16 * (j / 4) + j % 4; }   // load j's row from there; its element of the gradient
+TJ_HD inline int f32_back16_dz(int q, int step) { return 32 * step + 4 * q; }   // the lane's part of the gradient
+TJ_HD inline int f32_back16_col(int q, int tile) { return 32 * tile + 8 * q; }  // its first column of the result
+
 // LDS layout of the row kernel in floats.  Activation rows are `pitch` floats apart, pitch % 64 == 16: the 16-byte pieces that a
 // quarter of a wave reads (four rows x 16 k) cover the 64 banks once.
 constexpr size_t kF32Lds = 160 * 1024;

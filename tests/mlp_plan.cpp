@@ -1,5 +1,6 @@
 // The plan of the whole-network kernels as functions that a test can call.
 #include "../paper_2502_20190_amd/csrc/tj_mlp_plan.h"
+#include <vector>
 
 struct Layer { int in, out; };
 
@@ -53,4 +54,55 @@ extern "C" int f32_fits(int L, const Layer *lay, int passes, int max_batch)
     int in[TJ_MAX_LAYERS], out[TJ_MAX_LAYERS];
     for (int l = 0; l < L && l < TJ_MAX_LAYERS; ++l) { in[l] = lay[l].in; out[l] = lay[l].out; }
     return tjplan::f32_fits(L, in, out, passes, max_batch);
+}
+
+// Walks every load of the sixteen-row backward pass over a matrix [rows][cols].  Returns the columns of the gradient it multiplies, and in
+// *written the columns of the result it writes, or -1 where some weight is not multiplied exactly once, meets another row's gradient or
+// reaches another column's sum.
+extern "C" int f32_back16_reach(int rows, int cols, int *written)
+{
+    const int pitch = cols, steps = tjplan::f32_back16_steps(rows), tiles = tjplan::f32_back16_tiles(cols);
+    std::vector<int> seen((size_t)rows * cols, 0);
+    int read = 0;
+    *written = 0;
+    for (int wave = 0; wave < tjplan::kF32Waves; ++wave)
+        for (int tile = wave; tile < tiles; tile += tjplan::kF32Waves)
+            for (int lane = 0; lane < 64; ++lane) {
+                const int first = tjplan::f32_back16_col(lane >> 4, tile);
+                *written = std::max(*written, first + 8);
+                for (int step = 0; step < steps; ++step)
+                    for (int j = 0; j < 8; ++j)
+                        for (int e = 0; e < 2; ++e) {
+                            const int n = tjplan::f32_back16_dz(lane >> 4, step) + tjplan::f32_back16_row(j);
+                            read = std::max(read, n + 1);
+                            const long at = (tjplan::f32_back16_at(lane >> 4, lane & 15, tile, step, 4 * pitch) + tjplan::f32_back16_row(j) * 4l * pitch) / 4 + e;
+                            // matrix instruction: row lane % 16 of its first operand is row 4 q + i of the result, register i of quarter q; the
+                            // kernel takes register i of operand e as element 2 i + e of the quarter's eight columns
+                            const int m = lane & 15, k = 32 * tile + 8 * (m / 4) + 2 * (m % 4) + e;
+                            if (k >= cols) continue;                       // a sum that nobody reads
+                            if (n >= rows) { if (at < (long)rows * cols) return -1; continue; }   // zero, from past the end
+                            if (at != (long)n * pitch + k) return -1;
+                            ++seen[at];
+                        }
+            }
+    for (int n : seen)
+        if (n != 1) return -1;
+    return read;
+}
+
+// Floats of LDS per group of four rows that the head's slices take, and those they have.
+extern "C" int f32_head_floats(int in, int out, int *held)
+{
+    const tjplan::F32Forward p = tjplan::f32_forward(in, out, true);
+    const Layer lay = {in, out};
+    const tjplan::F32Lds o = tjplan::f32_lds(1, &lay, 1, false, true);
+    *held = o.dz - o.part;
+    return std::min(p.KS, p.steps) * 4 * 16 * p.tiles;
+}
+
+// Where the arrays of a network's rows end in LDS: floats between activation rows, between gradient rows.
+extern "C" void f32_pitches(int L, const Layer *lay, int nr, int *row, int *gradient)
+{
+    const tjplan::F32Lds o = tjplan::f32_lds(L, lay, nr, false, true);
+    *row = o.pitch; *gradient = o.dzp;
 }

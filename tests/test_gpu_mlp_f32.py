@@ -62,10 +62,12 @@ def test_on_policy_learner(tj, orc, D, widths, A, B):
 
 
 @pytest.mark.parametrize("on_policy", [False, True])
-@pytest.mark.parametrize("D,widths,B", [(4, (16, 17), 8), (20, (33, 40, 29), 33), (5, (1, 3, 2), 3)])
-def test_a_unit_switched_off_by_an_infinite_bias_leaves_the_rest_finite(tj, D, widths, B, on_policy):
+@pytest.mark.parametrize("D,widths,B", [(4, (16, 17), 8), (20, (33, 40, 29), 33), (5, (1, 3, 2), 3), (20, (33, 41, 29), 2050)])
+def test_a_unit_switched_off_by_an_infinite_bias_leaves_the_rest_finite(tj, mlp_plan, D, widths, B, on_policy):
     """Biases lie behind their weight matrix, where the last chunk of a contraction over 17, 29 .. units ends: minus infinity is a
-    unit that never fires, the same as a very large negative bias, bit for bit."""
+    unit that never fires, the same as a very large negative bias, bit for bit.  2050 rows: eight rows per block, on-policy sixteen."""
+    if B > 2048:
+        assert mlp_plan.f32_rows(*plan_layers(D, *widths, 4 if on_policy else 3), B, not on_policy, 1) == (16 if on_policy else 8)
     import torch
 
     A = 3

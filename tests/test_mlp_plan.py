@@ -26,15 +26,6 @@ def test_bf16_gradient_slices_of_every_smaller_batch_fit(mlp_plan, widths, max_b
 SIDES = list(range(1, 70)) + [127, 128, 129, 255, 257, 511, 512]
 
 
-def test_fp32_row_kernel_loads_stay_inside_the_weight_copies(mlp_plan):
-    """The transposed copy of a layer has its inputs rounded up to 16 as rows and its outputs rounded up to 64 as columns."""
-    mlp_plan.f32_reach.restype = ctypes.c_long
-    for fin in SIDES + [1000, 1024]:
-        for fout in SIDES:
-            kp, ldn = (fin + 15) // 16 * 16, (fout + 63) // 64 * 64
-            assert mlp_plan.f32_reach(ldn, kp, ldn) == kp * ldn, (fin, fout)
-
-
 def test_fp32_row_kernel_loads_of_the_parameters_end_with_their_matrix(mlp_plan):
     """The backward pass reads W [out][in] itself, whole groups of 64 inputs: at most 63 floats behind it."""
     mlp_plan.f32_reach.restype = ctypes.c_long
@@ -73,3 +64,21 @@ def test_fp32_q_learners_with_few_rows_run_where_an_update_is_faster(mlp_plan, w
 def test_fp32_on_policy_learners_with_long_batches_run_where_an_update_is_faster(mlp_plan, widths, max_batch, here):
     """Networks that fill LDS with four rows; shallower ones stay, whose acting here weighs more."""
     assert mlp_plan.f32_fits(*plan_layers(*widths), 1, max_batch) == here
+
+
+def test_fp32_sixteen_rows_multiply_every_weight_once(mlp_plan):
+    """The backward pass over W [rows][cols]: what it reads of the gradient and writes of the result stays inside their rows."""
+    written, row, gradient = ctypes.c_int(), ctypes.c_int(), ctypes.c_int()
+    for rows in SIDES:
+        for cols in SIDES:
+            read = mlp_plan.f32_back16_reach(rows, cols, ctypes.byref(written))
+            mlp_plan.f32_pitches(*plan_layers(1, cols, rows), 4, ctypes.byref(row), ctypes.byref(gradient))
+            assert rows <= read <= gradient.value and read <= (rows + 63) // 64 * 64, (rows, cols)   # zeros from `rows` on
+            assert cols <= written.value <= row.value and written.value <= (cols + 63) // 64 * 64, (rows, cols)
+
+
+def test_fp32_row_kernel_has_room_for_the_slices_of_every_head(mlp_plan):
+    held = ctypes.c_int()
+    for fin in SIDES + [1000, 1024]:
+        for fout in range(1, 65):
+            assert 0 < mlp_plan.f32_head_floats(fin, fout, ctypes.byref(held)) <= held.value, (fin, fout)

@@ -31,7 +31,7 @@ sys.path.insert(0, ROOT)
 # same counters read for a streaming kernel of known size in the same runs (adam_update: FETCH_SIZE
 # reads half the bytes, WRITE_SIZE all of them).  Valid for the sources it was taken with: the contraction
 # kernels and the learner that decides which of them a step launches.
-GEMM_SOURCES = ("tj_gemm.h", "tj_gemm.hip", "tj_gemm_plan.h", "tj_gemm_wide.hip", "tj_conv_first.hip", "tj_conv_tower.hip", "tj_conv_planes.h",
+GEMM_SOURCES = ("tj_gemm.h", "tj_gemm.hip", "tj_gemm_plan.h", "tj_gemm_wide.hip", "tj_conv_first.hip", "tj_conv_tower.hip", "tj_conv_tower_plan.h", "tj_conv_planes.h",
                 "tj_conv_wgrad.h", "tj_conv_wgrad.hip", "tj_conv.h", "tj_learner.hip")
 GEMM_TRAFFIC = {"c3": {"bytes_per_step": 729.9e6, "gemm_source_sha256_16": "c5b8b9278326a520"},
                 "c5": {"bytes_per_step": 974.1e6, "gemm_source_sha256_16": "c5b8b9278326a520"}}

@@ -14,73 +14,28 @@
 // Rows of the activations in LDS are padded by 32 bytes, to 96 and 160.  A 16-byte read serves sixteen lanes at a time, not consecutive ones
 // but rows 0 - 3 and 12 - 15 of one lane group of the fragment and rows 4 - 11 of the next one (8 channels on): rows an odd number of 16-byte
 // units apart (80, 144 bytes) meet there and run at half rate, 6.0 against 3.2 clocks per wave read in a bare loop; rows 2 mod 4 units
-// apart do not.  The second layer has stride 2, so its input keeps even and odd columns apart, which makes consecutive patches
+// apart do not.  Writes do: 34 % of the cycles in which the LDS is busy are conflicts here (profiles/c3_gemm_counters.md), no fewer than with rows of
+// 80 and 144.  By their banks, the image's pieces lie 64 bytes apart from lane to lane in conv_tower_pipe (four lanes of sixteen meet), the
+// 8-byte stores of activations meet in twos at 160 bytes (not at all at 144) and in four or five at 96 (two or three at 80).
+// The second layer has stride 2, so its input keeps even and odd columns apart, which makes consecutive patches
 // consecutive rows.  Sixteen patches mostly end one output row and begin another: the rows of the image they read (even and odd ones
 // apart as well) have a pitch that continues the sequence of columns there (tower_plan).
 // While an image is in the second layer the next one, fetched into registers a layer ahead, is converted into the image buffer.
 #include "tj_conv_planes.h"
+#include "tj_conv_tower_plan.h"
 #include <algorithm>
 #include <type_traits>
 
 namespace {
 
 using namespace tjplanes;
+using namespace tjtower;
 
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __attribute__((address_space(3))) uint8_t *lds_ptr_t;
-
-constexpr int kThreads = 512, kWaves = 8;
-constexpr int K1 = 8, C1 = 32, K2 = 4, S2 = 2, C2 = 64, K3 = 3, C3 = 64;   // kernels, strides, output channels
-constexpr int kRounds = 4;              // 4-pixel tasks per thread and image
-constexpr int kTiles2 = 3, kTiles3 = 2; // tiles of 16 patches per wave (two waves share the patches)
-constexpr int kSteps2 = K2 * K2 * C1 / 32, kSteps3 = K3 * K3 * C2 / 32;   // 32-value steps of a contraction
-constexpr int kRow1 = C1 * 2 + 32, kRow2 = C2 * 2 + 32;   // bytes between activation rows in LDS
-constexpr int kW1Pitch = (4 * K1 * K1 + 8) * 2;           // ... between the first layer's weight rows
-constexpr int kUnits2 = 4 * kSteps2, kUnits3 = 4 * kSteps3;               // 16-byte units of a weight row of the other two,
-constexpr int kGroup2 = 16 * (kUnits2 + 1) * 16, kGroup3 = 16 * (kUnits3 + 1) * 16;   // bytes of 16 such rows, a unit apart, in LDS
-constexpr size_t kLdsLimit = 160 * 1024;
-
-struct TowerPlan {
-    int w1, bias, out1, out2, total;   // byte offsets in LDS (the image is at 0)
-    int groups_img;                          // groups of 16 rows of the third layer's weights that the image buffer holds
-    int half1, rows1;                        // columns and rows per parity of the first layer's output
-    int pitch1, pitch2;                      // bytes between image rows (of one parity) of the first layer's output, of the second's
-    uint32_t mg_ow1, mg_ow2, mg_ow3;         // ceil(2^32 / OW)
-    int n_pass;
-};
-
-__host__ __device__ inline uint32_t magic(int d) { return (uint32_t)((((uint64_t)1 << 32) + d - 1) / d); }
-
-TowerPlan tower_plan(int H, int W, int OH1, int OW1, int OH2, int OW2, int OW3)
-{
-    TowerPlan p;
-    p.half1 = (OW1 + S2 - 1) / S2;
-    p.rows1 = (OH1 + S2 - 1) / S2;
-    // 16 lanes read 16 consecutive patches, which end one output row and begin the next: the step to it is the step between patches
-    // modulo the 16 units of the LDS banks (units of 16 bytes)
-    auto pitch = [](int row_bytes, int step_bytes, int OW) {
-        int u = row_bytes / 16;
-        while ((u - OW * (step_bytes / 16)) % 16) ++u;
-        return u * 16;
-    };
-    p.pitch1 = pitch(S2 * p.half1 * kRow1, kRow1, OW2);
-    p.pitch2 = pitch(OW2 * kRow2, kRow2, OW3);
-    int at = H * W * 8;
-    p.w1 = at; at += C1 * kW1Pitch;
-    p.bias = at; at += (C1 + C2 + C3) * 4;
-    p.out1 = at; at += S2 * p.rows1 * p.pitch1;
-    p.out2 = at; at += OH2 * p.pitch2;
-    auto whole = [](int bytes) { return (bytes + 1023) / 1024 * 1024; };   // a load instruction fills a KiB
-    p.groups_img = 4;
-    while (whole(p.groups_img * kGroup3) > H * W * 8) --p.groups_img;
-    p.total = std::max(at, p.out1 + std::max(whole(4 * kGroup3), 4 * kGroup2 + whole((4 - p.groups_img) * kGroup3)));
-    p.mg_ow1 = magic(OW1); p.mg_ow2 = magic(OW2); p.mg_ow3 = magic(OW3);
-    p.n_pass = 0;
-    return p;
-}
 
 // Orders LDS accesses across the block; global loads (the next image) and stores stay in flight.
 __device__ __forceinline__ void lds_sync()
@@ -358,28 +313,6 @@ void conv_tower(const TjConvTowerArgs a, const TowerPlan p)
 }
 
 // ---- many passes per block: the layers of two images side by side
-
-struct PipePlan {
-    int bias, out1, out1_bytes, out2, total; // byte offsets in LDS (the image is at 0); two outputs of the first layer, out1_bytes apart
-    int half1, rows1, pitch1, pitch2;        // as in TowerPlan
-    uint32_t mg_ow1, mg_ow2, mg_ow3;
-    int n_pass;
-};
-
-PipePlan pipe_plan(int H, int W, int OH1, int OW1, int OH2, int OW2, int OW3)
-{
-    const TowerPlan t = tower_plan(H, W, OH1, OW1, OH2, OW2, OW3);
-    PipePlan p;
-    p.half1 = t.half1; p.rows1 = t.rows1; p.pitch1 = t.pitch1; p.pitch2 = t.pitch2;
-    p.mg_ow1 = t.mg_ow1; p.mg_ow2 = t.mg_ow2; p.mg_ow3 = t.mg_ow3;
-    p.bias = H * W * 8;
-    p.out1 = p.bias + (C1 + C2 + C3) * 4;
-    p.out1_bytes = std::max(S2 * p.rows1 * p.pitch1, C1 * kW1Pitch);   // the second one takes the first layer's weights before a run
-    p.out2 = p.out1 + 2 * p.out1_bytes;
-    p.total = p.out2 + OH2 * p.pitch2;
-    p.n_pass = 0;
-    return p;
-}
 
 // The same layers, sums and results as conv_tower for blocks with several passes.  There eight waves go through the layers of one image
 // together and wait for each other behind each: LDS reads, the image's conversion and the products take turns.  Here four waves (one
@@ -722,10 +655,8 @@ int tj_conv_tower(const TjConvTowerArgs &a, hipStream_t st)
     if (hipGetDevice(&dev) == hipSuccess &&
         hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && v > 0)
         n_cu = v;
-    // From four passes per block on (us per update, one image at a time : two; 3 passes 134.5 : 136.2, 4 148.9 : 145.8, 8 170.0 : 168.6,
-    // 12 267.0 : 255.8, 24 430 : 402): the first and the last image are alone.
     PipePlan q = pipe_plan(f.H, f.W, f.OH, f.OW, a.OH2, a.OW2, a.OW3);
-    if (p.n_pass >= 4 * n_cu && (size_t)q.total <= kLdsLimit) {
+    if (two_images(q, p.n_pass, n_cu)) {
         q.n_pass = p.n_pass;
         TJ_HIP_TRY(hipFuncSetAttribute((const void *)conv_tower_pipe, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsLimit));
         conv_tower_pipe<<<n_cu, kThreads, q.total, st>>>(a, q);

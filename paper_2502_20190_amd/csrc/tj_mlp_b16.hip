@@ -31,10 +31,10 @@ typedef const __attribute__((address_space(1))) u32x4 *gu32x4;
 typedef __attribute__((address_space(3))) s16x4 *lds_s16x4;
 
 constexpr int kThreads = 512, kWaves = kThreads / 64;
-constexpr size_t kLdsMax = 160 * 1024;
+constexpr size_t kLdsMax = tjplan::kB16Lds;
 constexpr int kGroup = 4096;        // bytes of a weight group (32 rows x 64 contraction elements)
-constexpr int kPartPitch = 36;      // floats per row of the head's partial sums
-constexpr int kZPitch = 144;        // bytes per row of dL/dQ (64 columns)
+using tjplan::kPartPitch, tjplan::kZPitch;
+typedef tjplan::B16Lds RowsLds;
 
 __host__ __device__ inline int up(int x, int a) { return (x + a - 1) / a * a; }
 
@@ -46,42 +46,6 @@ __device__ __forceinline__ uint32_t pack2(float lo, float hi)
 __device__ __forceinline__ f32x4 mma(const u32x4 &p, const u32x4 &q, const f32x4 &c)
 {
     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, p), __builtin_bit_cast(bf16x8, q), c, 0, 0, 0);
-}
-
-// LDS layout of b16_rows in bytes.  Activation rows are `pitch` bytes apart, pitch % 128 == 16: the 16-byte pieces that
-// eight neighbouring lanes read fall on distinct banks.
-struct RowsLds {
-    int pitch, keep, pp, part, dz, bias, small, total, n_bias;
-};
-
-RowsLds rows_lds(int L, const int *in, const int *out, int nr, bool dqn, bool backward)
-{
-    RowsLds o;
-    int w = 0;
-    o.n_bias = 0;
-    for (int l = 0; l < L; ++l) {
-        w = std::max(w, up(in[l], 64));
-        o.n_bias += up(out[l], 32);
-    }
-    const int R = 16 * nr, ns = 4;
-    o.pitch = 2 * w + 16;
-    const int part = ns * (dqn ? 3 : 1) * R * kPartPitch * 4, half = dqn ? 2 * R * o.pitch : 0;
-    int at = 0;
-    // s' under both networks, two layers in turn; input rows of the layers, s, behind it: those of the first layer take the
-    // place of s' under the target network, where the first layer has no rows of its own
-    o.pp = at; at += 2 * half;
-    o.keep = dqn ? at - R * o.pitch : at;
-    at = o.keep + (backward ? L : std::min(L, 2)) * R * o.pitch;
-    // the head's partial sums take memory that is free by then if they fit: the half of pp that the head's input does not
-    // use, or the first layer's input (its fragments are written at the start)
-    const bool in_pp = dqn && part <= half, in_keep = !dqn && L >= 2 && (backward || (L - 1) % 2) && part <= R * o.pitch;
-    o.part = in_pp ? o.pp + ((L - 1) & 1 ? half : 0) : in_keep ? o.keep : at;
-    if (!in_pp && !in_keep) at += part;
-    o.dz = at; at += backward ? R * kZPitch : 0;
-    o.bias = at; at += o.n_bias * (dqn ? 2 : 1) * 4;
-    o.small = at; at += 3 * R * 4;
-    o.total = at;
-    return o;
 }
 
 struct Phase {
@@ -682,24 +646,9 @@ __global__ __launch_bounds__(256) void b16_cast(const TjB16Layer y, const int on
     if (e < (size_t)y.out) (online ? y.BP : y.BP_tg)[e] = b[e];
 }
 
-RowsLds lds_of(const TjB16Rows &a, int nr, bool dqn, bool back)
-{
-    int in[TJ_MAX_LAYERS], out[TJ_MAX_LAYERS];
-    for (int l = 0; l < a.L; ++l) { in[l] = a.lay[l].in; out[l] = a.lay[l].out; }
-    return rows_lds(a.L, in, out, nr, dqn, back);
-}
-
-// Rows per block: the fewest that need no second round of blocks on the chip, or the most that LDS holds.
 int rows_nr(const TjB16Rows &a, int mode)
 {
-    const bool dqn = mode == TJ_ROWS_DQN, back = dqn || mode == TJ_ROWS_PPO;
-    int best = 1;
-    for (int nr = 1; nr <= (dqn ? 2 : 4); nr *= 2) {
-        if ((size_t)lds_of(a, nr, dqn, back).total > kLdsMax) break;
-        best = nr;
-        if ((a.B + 16 * nr - 1) / (16 * nr) <= 256) break;
-    }
-    return best;
+    return tjplan::b16_groups(a.L, a.lay, a.B, mode == TJ_ROWS_DQN, mode == TJ_ROWS_DQN || mode == TJ_ROWS_PPO);
 }
 
 int grid_of(int B, int nr, bool back) { return back && nr == 1 ? (B + 31) / 32 * 2 : (B + 16 * nr - 1) / (16 * nr); }
@@ -714,7 +663,7 @@ template <int KIND, int NR> int launch_rows(const TjB16Rows &a, int mode, hipStr
     }
     RowsArgs r;
     r.a = a;
-    r.o = lds_of(a, NR, dqn, back);
+    r.o = tjplan::b16_lds(a.L, a.lay, NR, dqn, back);
     r.ms = (a.B + 31) / 32;
     for (int l = 0; l < TJ_MAX_LAYERS; ++l) {
         const TjB16Layer &y = a.lay[l < a.L ? l : 0];
@@ -727,29 +676,7 @@ template <int KIND, int NR> int launch_rows(const TjB16Rows &a, int mode, hipStr
 
 }  // namespace
 
-bool tj_b16_fits(int L, const int *in, const int *out, int passes, int max_batch)
-{
-    if (L < 1 || L > TJ_MAX_LAYERS || in[0] > kB16MaxWidth || out[L - 1] > kB16MaxOut) return false;
-    for (int l = 0; l + 1 < L; ++l)
-        if (out[l] > kB16MaxWidth) return false;
-    const bool dqn = passes == 3;
-    // The line below was measured with 33 floats per row and pass more in LDS; which networks come here follows that size still.
-    auto holds = [&](int nr) { return (size_t)rows_lds(L, in, out, nr, dqn, true).total + (dqn ? 3 : 1) * 16 * nr * 33 * sizeof(float) <= kLdsMax; };
-    if (!holds(1)) return false;
-    // Against one GEMM per layer (an update of 90 us and 820 TFLOP/s on 128-1024-1024-1024-19 at 4096 .. 32768 rows): the
-    // weights every block streams (120 GB/s per CU) and 8 us per round of blocks, then the weight gradient at 400 TFLOP/s.
-    // Wide networks on long batches are better off as GEMMs, whose tiles share the weights.
-    double params = 0, stream = 0;   // bytes of one block
-    for (int l = 0; l < L; ++l) {
-        params += (double)in[l] * out[l];
-        stream += 2.0 * in[l] * out[l] * (passes == 3 ? 2 : 1) + (l ? 2.0 * in[l] * out[l] : 0.0);
-    }
-    const int nr = holds(2) ? 2 : 1;
-    const double rounds = std::max(1.0, std::ceil(max_batch / (256.0 * 16 * nr)));
-    const double whole_us = rounds * (8 + stream / 0.12e6) + 15 + 2 * params * max_batch / 400e6;
-    const double gemms_us = 90 + 2 * params * max_batch * (passes + 2) / 820e6;
-    return whole_us <= gemms_us;
-}
+bool tj_b16_fits(int L, const int *in, const int *out, int passes, int max_batch) { return tjplan::b16_fits(L, in, out, passes, max_batch); }
 
 int tj_b16_blocks(const TjB16Rows &a, int mode)
 {

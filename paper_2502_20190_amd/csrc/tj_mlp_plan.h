@@ -2,6 +2,7 @@
 // that it can be compiled and checked on its own.  `Layer` is anything with the members in and out.
 #pragma once
 #include "../../include/tianji.h"
+#include <math.h>
 #include <stddef.h>
 #include <algorithm>
 
@@ -143,11 +144,11 @@ template <typename Layer> int f32_groups(int L, const Layer *lay, int B, bool dq
     return best;
 }
 
-// Largest batch of a Q-learner that is updated here.  One group of four rows per block reads the weights of both networks for
-// every four or eight transitions, and past some batch the layered kernels, whose tiles share them, are faster (us here : there;
-// 128-512-512-512-18 at 8192 rows 722 : 844, 128-256-256-18 at 16384 238 : 370, five layers of 512 at 512 rows 165 : 243 and at 4096 673 : 918,
-// six at 8192 1557 : 1833).  The lines were drawn with the slower forward pass of partial sums (512 wide at 16384 rows 1559 : 1394, 256 wide
-// at 32768 701 : 637); beyond them the present one has not been measured.
+// Largest batch of a Q-learner that is updated here.  One group of four rows per block reads the weights of both networks for every four
+// or eight transitions, and past some batch the layered kernels, whose tiles share them, are faster (us here : there; 128-512-512-512-18 at 8192
+// rows 729 : 844, 16384 1419 : 1397, 32768 2865 : 2696; 300-500-384-500-33 at 8192 702 : 772, 16384 1400 : 1313).  The lines are older than
+// the present forward pass, which is the faster one past them too where layers are narrower or fewer (128-384-384-384-18 at 32768 1494 : 1831,
+// 4-512-512-2 1358 : 1516, 128-256-256-18 at 65536 912 : 1233, 16-32-5 215 : 268).
 constexpr int kF32QRows = 16384, kF32QRowsWide = 8192, kF32QWide = 256 + 16;   // the latter past rows of kF32QWide floats
 
 constexpr int kF32MaxWidth = 512;    // widest layer (eight 64-feature groups)
@@ -205,6 +206,92 @@ inline bool f32_fits(int L, const int *in, const int *out, int passes, int max_b
     const size_t lds = o.total * sizeof(float);
     if (passes == 3 ? f32_few_rows(L, in, out, lds, max_batch) : f32_long_rows(L, in, out, lds, max_batch)) return false;
     return lds <= kF32Lds;
+}
+
+// ---- the row kernel of bf16 networks
+constexpr size_t kB16Lds = 160 * 1024;
+constexpr int kB16MaxWidth = 1024;   // widest layer and observation
+constexpr int kB16MaxOut = 32;       // head outputs: one block of 32 features
+constexpr int kPartPitch = 36;       // floats per row of the head's partial sums
+constexpr int kZPitch = 144;         // bytes per row of dL/dQ (64 columns)
+
+// LDS layout in bytes.  Activation rows are `pitch` bytes apart, pitch % 128 == 16: the 16-byte pieces that eight neighbouring lanes
+// read fall on distinct banks.
+struct B16Lds {
+    int pitch, keep, pp, part, dz, bias, small, total, n_bias;
+};
+// nr groups of sixteen rows per block; dqn: the Q-learner's three passes; backward: an update, not acting.
+template <typename Layer> B16Lds b16_lds(int L, const Layer *lay, int nr, bool dqn, bool backward)
+{
+    B16Lds o;
+    int w = 0;
+    o.n_bias = 0;
+    for (int l = 0; l < L; ++l) {
+        w = std::max(w, (lay[l].in + 63) / 64 * 64);
+        o.n_bias += (lay[l].out + 31) / 32 * 32;
+    }
+    const int R = 16 * nr, ns = 4;
+    o.pitch = 2 * w + 16;
+    const int part = ns * (dqn ? 3 : 1) * R * kPartPitch * 4, half = dqn ? 2 * R * o.pitch : 0;
+    int at = 0;
+    // s' under both networks, two layers in turn; input rows of the layers, s, behind it: those of the first layer take the
+    // place of s' under the target network, where the first layer has no rows of its own
+    o.pp = at; at += 2 * half;
+    o.keep = dqn ? at - R * o.pitch : at;
+    at = o.keep + (backward ? L : std::min(L, 2)) * R * o.pitch;
+    // the head's partial sums take memory that is free by then if they fit: the half of pp that the head's input does not
+    // use, or the first layer's input (its fragments are written at the start)
+    const bool in_pp = dqn && part <= half, in_keep = !dqn && L >= 2 && (backward || (L - 1) % 2) && part <= R * o.pitch;
+    o.part = in_pp ? o.pp + ((L - 1) & 1 ? half : 0) : in_keep ? o.keep : at;
+    if (!in_pp && !in_keep) at += part;
+    o.dz = at; at += backward ? R * kZPitch : 0;
+    o.bias = at; at += o.n_bias * (dqn ? 2 : 1) * 4;
+    o.small = at; at += 3 * R * 4;
+    o.total = at;
+    return o;
+}
+
+// Groups of sixteen rows per block: the fewest that need no second round of blocks on the chip, or the most that LDS holds.
+template <typename Layer> int b16_groups(int L, const Layer *lay, int B, bool dqn, bool backward)
+{
+    int best = 1;
+    for (int nr = 1; nr <= (dqn ? 2 : 4); nr *= 2) {
+        if ((size_t)b16_lds(L, lay, nr, dqn, backward).total > kB16Lds) break;
+        best = nr;
+        if ((B + 16 * nr - 1) / (16 * nr) <= 256) break;
+    }
+    return best;
+}
+
+// True if a learner of this shape, with updates of up to max_batch rows, runs in these kernels.
+inline bool b16_fits(int L, const int *in, const int *out, int passes, int max_batch)
+{
+    if (L < 1 || L > TJ_MAX_LAYERS || in[0] > kB16MaxWidth || out[L - 1] > kB16MaxOut) return false;
+    struct { int in, out; } lay[TJ_MAX_LAYERS];
+    for (int l = 0; l < L; ++l) {
+        if (l + 1 < L && out[l] > kB16MaxWidth) return false;
+        lay[l].in = in[l]; lay[l].out = out[l];
+    }
+    const bool dqn = passes == 3;
+    // The line below was measured when the kernel kept 33 floats per row and pass more in LDS.  Which networks come here follows that size
+    // still, and so does the number of groups in the estimate; the launch takes what b16_groups says.  Networks that this alone keeps out are
+    // mostly faster here (us here : layer by layer; double DQN 384-64 x 6-18 at 512 rows 23 : 155, 768-512-512-18 at 2048 58 : 81, 640-640 x 3-18 at 64
+    // 93 : 85; on-policy 128-384 x 5-18 at 32768 283 : 490, 768-512 x 5-18 at 64 80 : 122): room to move the line, with the estimate's figures.
+    auto holds = [&](int nr) { return (size_t)b16_lds(L, lay, nr, dqn, true).total + (dqn ? 3 : 1) * 16 * nr * 33 * sizeof(float) <= kB16Lds; };
+    if (!holds(1)) return false;
+    // Against one GEMM per layer (an update of 90 us and 820 TFLOP/s on 128-1024-1024-1024-19 at 4096 .. 32768 rows): the
+    // weights every block streams (120 GB/s per CU) and 8 us per round of blocks, then the weight gradient at 400 TFLOP/s.
+    // Wide networks on long batches are better off as GEMMs, whose tiles share the weights.
+    double params = 0, stream = 0;   // bytes of one block
+    for (int l = 0; l < L; ++l) {
+        params += (double)in[l] * out[l];
+        stream += 2.0 * in[l] * out[l] * (passes == 3 ? 2 : 1) + (l ? 2.0 * in[l] * out[l] : 0.0);
+    }
+    const int nr = holds(2) ? 2 : 1;
+    const double rounds = std::max(1.0, std::ceil(max_batch / (256.0 * 16 * nr)));
+    const double whole_us = rounds * (8 + stream / 0.12e6) + 15 + 2 * params * max_batch / 400e6;
+    const double gemms_us = 90 + 2 * params * max_batch * (passes + 2) / 820e6;
+    return whole_us <= gemms_us;
 }
 
 // ---- the weight kernel of bf16 networks

@@ -106,3 +106,12 @@ extern "C" void f32_pitches(int L, const Layer *lay, int nr, int *row, int *grad
     const tjplan::F32Lds o = tjplan::f32_lds(L, lay, nr, false, true);
     *row = o.pitch; *gradient = o.dzp;
 }
+
+// The same of the row kernel of bf16 networks.
+extern "C" int b16_rows(int L, const Layer *lay, int B, int dqn, int backward) { return 16 * tjplan::b16_groups(L, lay, B, dqn, backward); }
+extern "C" int b16_fits(int L, const Layer *lay, int passes, int max_batch)
+{
+    int in[TJ_MAX_LAYERS], out[TJ_MAX_LAYERS];
+    for (int l = 0; l < L && l < TJ_MAX_LAYERS; ++l) { in[l] = lay[l].in; out[l] = lay[l].out; }
+    return tjplan::b16_fits(L, in, out, passes, max_batch);
+}

@@ -16,6 +16,7 @@ from paper_2502_20190_amd.synth import LIN
 
 import test_gpu_learner as T
 import test_gpu_ppo as P
+from parity_util import plan_layers
 
 pytestmark = pytest.mark.gpu
 TOL = 2e-2
@@ -55,6 +56,19 @@ def test_on_policy_learner(tj, orc, D, widths, A, B):
     for step in range(2):
         rows = P._batch(orc, o, D, A, 1 + B // 8, 8, 70 + step, "bf16", n=B)
         P._step_both(tj, orc, g, o, rows, TOL, sync=step > 0, precision="bf16")
+
+
+# Networks whose groups of rows fill LDS to a few KB: the most that any of them takes per block
+@pytest.mark.parametrize("D,widths,A,B,rows_per_block,on_policy", [
+    (128, (160, 160, 160), 18, 4129, 32, False), (256, (64, 64), 18, 4100, 32, False), (128, (736, 736), 18, 4100, 32, True),
+    (384, (64, 64), 18, 8210, 64, True)])
+def test_rows_per_block_that_fill_lds(tj, orc, mlp_plan, D, widths, A, B, rows_per_block, on_policy):
+    net = plan_layers(D, *widths, A + on_policy)
+    assert mlp_plan.b16_fits(*net, 1 if on_policy else 3, B) and mlp_plan.b16_rows(*net, B, not on_policy, 1) == rows_per_block
+    if on_policy:
+        test_on_policy_learner(tj, orc, D, widths, A, B)
+    else:
+        test_q_learner(tj, orc, D, widths, A, B)
 
 
 @pytest.mark.parametrize("D,widths,A,max_batch,batches", [

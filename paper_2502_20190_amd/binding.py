@@ -201,12 +201,12 @@ def _stream_ptr(stream=None) -> int:
     """The stream's handle; of the current device's current stream without a Stream object (2.7 us, against 0.3)."""
     import torch
 
-    if stream is None:
-        raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)   # not a public name
-        if raw is not None:
-            return raw(torch.cuda.current_device())
-        stream = torch.cuda.current_stream()
-    return int(stream.cuda_stream)
+    if stream is not None:
+        return int(stream.cuda_stream)
+    try:
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    except AttributeError:   # not a public name
+        return int(torch.cuda.current_stream().cuda_stream)
 
 
 def _require_gpu():

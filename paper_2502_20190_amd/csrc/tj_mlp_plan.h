@@ -101,19 +101,18 @@ struct F32Lds {
 template <typename Layer> F32Lds f32_lds(int L, const Layer *lay, int nr, bool dqn, bool backward)
 {
     F32Lds o;
-    int w = 0, nb = 0, waves = 0;   // waves: those with a part of some phase of the backward pass
+    int w = 0, nb = 0, waves = 0;   // waves: those with a part of some phase of the backward pass with slices
     for (int l = 0; l < L; ++l) {
-        const F32Forward p = f32_forward(lay[l].in, lay[l].out, l == L - 1);
-        if (backward && l) waves = std::max(waves, f32_part_waves(f32_phase(lay[l].in, lay[l].out, lay[l].in)));
-        w = std::max(w, std::max((16 << p.lq) * p.steps, p.pitch));
-        nb += p.pitch;
+        if (backward && l && nr < 4) waves = std::max(waves, f32_part_waves(f32_phase(lay[l].in, lay[l].out, lay[l].in)));
+        w = std::max(w, std::max(lay[l].in, lay[l].out));   // steps of 16, 32 or 64 inputs end within whole 64 columns
+        nb += (lay[l].out + 63) / 64 * 64;
     }
     o.pitch = (w + 63) / 64 * 64 + 16;
     const int R = 4 * nr, NG = dqn ? 3 * nr : nr;
     int at = 0;
     o.keep = at; at += (backward ? L : std::min(L, 2)) * R * o.pitch;   // input rows of every layer, s; acting: two layers in turn
     o.pp = at; at += dqn ? 2 * 2 * R * o.pitch : 0;     // s' (online), s' (target), two layers in turn
-    o.part = at; at += std::max(nr == 4 ? 0 : waves * nr * 256, kF32Waves * NG * 64);   // the slices of a backward phase; of the head
+    o.part = at; at += std::max(waves * nr * 256, kF32Waves * NG * 64);   // the slices of a backward phase; of the head
     // output gradients, two layers in turn; sixteen rows are read side by side, 16 bytes each: their pitch keeps them on distinct banks
     o.dzp = o.pitch + (nr == 4 ? 4 : 0);
     o.dz = at; at += backward ? 2 * R * o.dzp : 0;

@@ -33,8 +33,8 @@ sys.path.insert(0, ROOT)
 # kernels and the learner that decides which of them a step launches.
 GEMM_SOURCES = ("tj_gemm.h", "tj_gemm.hip", "tj_gemm_plan.h", "tj_gemm_wide.hip", "tj_conv_first.hip", "tj_conv_tower.hip", "tj_conv_tower_plan.h", "tj_conv_planes.h",
                 "tj_conv_wgrad.h", "tj_conv_wgrad.hip", "tj_conv.h", "tj_learner.hip")
-GEMM_TRAFFIC = {"c3": {"bytes_per_step": 729.9e6, "gemm_source_sha256_16": "c5b8b9278326a520"},
-                "c5": {"bytes_per_step": 974.1e6, "gemm_source_sha256_16": "c5b8b9278326a520"}}
+GEMM_TRAFFIC = {"c3": {"bytes_per_step": 729.9e6, "gemm_source_sha256_16": "3a9aa74018545ac2"},
+                "c5": {"bytes_per_step": 974.7e6, "gemm_source_sha256_16": "3a9aa74018545ac2"}}
 PEAK_HBM_GBS = 8000.0
 FP32_KERNELS = {2: "f32_rows + f32_update", 3: "f32_rows + f32_update + f32_adam"}   # by launches of an update
 WIDE_KERNELS = "gemm_wide_forward + gemm_wide_pair + gemm_bf16_dlds_pair_sum (its blocks that add gradient slices included)"

@@ -1,7 +1,7 @@
 """The two-launch fp32 update against the CPU oracle at the sizes where its dispatch and its tiles change: widths one
 below, at and one above 16 and 64, the widest input, layer and head it takes and one beyond (the layered kernels), a
-single layer, batches that leave 1 to 3 rows of the last group of four, and both weight-gradient tilings, with one
-slice of the batch and with several.
+network on either side of the rule for few rows, a single layer, batches that leave 1 to 3 rows of the last group of
+four, and both weight-gradient tilings, with one slice of the batch and with several.
 
 Tolerance 1e-4 of each tensor's largest entry: a contraction here adds at most 1024 terms (rows for the gradients: at
 most 1500) in fp32, whose rounding is bounded by terms * 2^-24 of the sum of magnitudes, 9e-5 at the worst and a few
@@ -35,7 +35,8 @@ def tj():
 
 @pytest.mark.parametrize("D,widths,A,B", [
     (1, (15,), 1, 1), (17, (16, 17), 2, 3), (16, (64, 63), 5, 130), (1024, (65,), 64, 66), (4, (), 3, 33),
-    (300, (512, 512), 18, 257), (64, (128, 128, 128), 18, 1500), (20, (512,), 65, 40), (1025, (16,), 2, 9)])
+    (300, (512, 512), 18, 257), (64, (128, 128, 128), 18, 1500), (20, (512,), 65, 40), (1025, (16,), 2, 9),
+    (1024, (512,), 18, 128), (1024, (512,), 18, 129)])
 def test_q_learner(tj, orc, D, widths, A, B):
     layers = tuple((LIN, w, 0, 0) for w in widths) + ((LIN, A, 0, 0),)
     wl = replace(synth.WORKLOADS["c2"], obs_shape=(D,), n_actions=A, batch=B, layers=layers, precision="fp32",
